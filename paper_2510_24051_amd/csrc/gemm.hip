@@ -1,13 +1,14 @@
 // bf16 MFMA GEMMs  C[M, N] = A[M, K] x W[N, K]^T  with fused epilogues.
 //
-//   gemm_skinny : M <= 256 (decode batches, LM head).  HBM-bound on the weight stream: every wave owns one
+//   gemm_skinny : M <= 64 (decode batches, LM head).  HBM-bound on the weight stream: every wave owns one
 //                 32-column block of W and reads its tiles straight from global memory into MFMA B operands
 //                 (each load is 1 KiB contiguous thanks to the tiled weight layout); the activation tile is
 //                 shared by the workgroup through LDS.  K is split across gridDim.y when N alone gives too
 //                 few workgroups; partial sums go to a workspace and a second kernel applies the epilogue.
-//   gemm_large  : M > 256 (prefill).  MFMA-bound: 256x256x64 workgroup tile, 8 waves of 128x64, LDS double
-//                 buffering, swizzled A tile, W tile kept in operand order.
+//   gemm_rows   : tiles of 96 or 128 rows by 256 columns, K split where the tiles alone leave CUs idle.
+//   gemm_large  : large M (prefill).  MFMA-bound: 256x256x64 workgroup tile, 8 waves of 128x64.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "internal.h"
@@ -381,7 +382,6 @@ __global__ void splitk_epilogue_kernel(const float* __restrict__ part, int split
 #define LG_BM 256
 #define LG_BN 256
 #define LG_BK 64
-#define TILED_MIN_KTS 8  // fewest k tiles a split of the tiled kernel takes
 
 template <int MODE>
 __global__ __launch_bounds__(512) void gemm_large_kernel(const bf16_t* __restrict__ A, int lda, int M,
@@ -502,13 +502,12 @@ __global__ __launch_bounds__(512) void gemm_large_kernel(const bf16_t* __restric
 // Workgroup ids are remapped so that each XCD (id % 8) works on a contiguous range of a grouped tile order (8 row
 // tiles per group) and its L2 sees a few activation and weight panels at a time.
 // ------------------------------------------------------------------------------------------------
-// BM = 256, or 128 for products of at most 128 rows (half the accumulators and half the activation copies per wave).
-template <int MODE, bool PARTIAL, int BM>
+template <int MODE, bool PARTIAL>
 __global__ __launch_bounds__(512) void gemm_large_async_kernel(const bf16_t* __restrict__ A, int lda, int M,
                                                                const bf16_t* __restrict__ Wp, int N, int NB, int K,
                                                                EpiArgs epi, int tiles_m, int tiles_n,
                                                                int kts_per_split, float* __restrict__ part) {
-  static_assert(BM == 256 || BM == 128, "tile height");
+  constexpr int BM = LG_BM;
   constexpr int MI = BM / 64;  // 32-row accumulator blocks per wave, and activation copy instructions per wave
   __shared__ __align__(16) bf16_t As0[BM * LG_BK], As1[BM * LG_BK], As2[BM * LG_BK];  // three activation stages
   constexpr int GROUP_M = 8;
@@ -517,7 +516,7 @@ __global__ __launch_bounds__(512) void gemm_large_async_kernel(const bf16_t* __r
   const int KB = K / 16, KT = K / LG_BK;
   // split K: workgroup row blockIdx.y takes k tiles [kt0, kt1)
   // Non-temporal stores for the logits and for the partial sums of the down projection, the last product before the
-  // LM head (see gemm_skinny_kernel; LM head at 128 rows 259 -> 238 us, at 256 rows 278 -> 262 us).  The partial sums
+  // LM head (see gemm_skinny_kernel; LM head at 256 rows 278 -> 262 us).  The partial sums
   // of the QKV product are stored plainly here: at 65 to 256 rows the rotary step that sums them loses what the
   // attention kernel gains.
   constexpr bool LG_NT = MODE == EPI_STORE_F32 || (PARTIAL && MODE == EPI_RESID_OUT) || (!PARTIAL && MODE == EPI_SWIGLU);
@@ -751,6 +750,196 @@ __global__ __launch_bounds__(512) void gemm_large_async_kernel(const bf16_t* __r
 }
 
 // ------------------------------------------------------------------------------------------------
+// gemm_rows (K a multiple of 64): 65 rows up to where whole rounds of 256x256 tiles fill the chip
+//
+// Tiles of 32 * MB rows (96 or 128) by 256 columns, K in steps of 64, eight waves side by side along the columns: a
+// wave owns one 32-column block for all rows of the tile.  Against the 2 x 4 arrangement of the 256 x 256 tile no two
+// waves read the same weights, which matters because the vector memory path of a compute unit moves 64 bytes per clock
+// and its share of a step is as long as the MFMAs': 32 KiB of weights + 4 MB KiB of activations per step here, 64 KiB +
+// 4 MB KiB with every weight tile read by two waves.  The price, one LDS read per MFMA instead of one per two, is half
+// of what LDS delivers.  Registers are kept to 128 (one k step of weights, 16 MB accumulators, and for MB = 4 a single
+// set of activation operands) so that two workgroups share a compute unit and one computes while the other waits at
+// its barrier.  Measured, kernel plus epilogue, weights from HBM, against the 128-row form of the 256-column tile it
+// replaces: 28672 x 4096 at 84 rows 59 -> 52 us, at 157 rows (256-row tile) 74 -> 61, 4096 x 14336 at 333 rows 69 ->
+// 53, at 2000 rows 233 -> 189, 6144 x 4096 at 4096 rows 191 (256-row tile) -> 164.  At 8192 rows, whole rounds of both
+// tiles, the two are equal (the chip's power limit).
+// The workgroup order is that of gemm_large_async_kernel.
+// ------------------------------------------------------------------------------------------------
+template <int MODE, bool PARTIAL, int MB>
+__global__ __launch_bounds__(512, 4) void gemm_rows_kernel(const bf16_t* __restrict__ A, int lda, int M,
+                                                           const bf16_t* __restrict__ Wp, int N, int NB, int K,
+                                                           EpiArgs epi, int tiles_m, int tiles_n, int kts_per_split,
+                                                           float* __restrict__ part) {
+  static_assert(MB == 3 || MB == 4, "tile height");
+  constexpr int BM = MB * 32;
+  constexpr int PIECES = BM / 8;        // 1 KiB copy instructions per activation stage
+  constexpr int CP = (PIECES + 7) / 8;  // per wave; past the last piece a wave copies that one again (same bytes)
+  constexpr bool AHEAD = MB < 4;        // the next contraction step's activation operands are read under this one's MFMAs
+  __shared__ __align__(16) bf16_t As0[BM * LG_BK], As1[BM * LG_BK], As2[BM * LG_BK], As3[BM * LG_BK];
+  constexpr bool NT = MODE == EPI_STORE_F32 || (PARTIAL && MODE == EPI_RESID_OUT) || (!PARTIAL && MODE == EPI_SWIGLU);
+  constexpr int GROUP_M = 8;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  [[maybe_unused]] const int KB = K / 16;
+  const int KT = K / LG_BK;
+  const int kt0 = PARTIAL ? blockIdx.y * kts_per_split : 0;
+  [[maybe_unused]] const int kt1 = PARTIAL ? min(KT, kt0 + kts_per_split) : KT;
+  int pid = blockIdx.x;
+  const int ntiles = tiles_m * tiles_n;
+  if (ntiles % 8 == 0) pid = (pid & 7) * (ntiles / 8) + (pid >> 3);
+  int tm, tn;
+  {
+    const int width = GROUP_M * tiles_n;
+    const int first_m = (pid / width) * GROUP_M;
+    const int gsz = min(tiles_m - first_m, GROUP_M);
+    tm = first_m + (pid % width) % gsz;
+    tn = (pid % width) / gsz;
+  }
+  const int m0 = tm * BM, nb = tn * 8 + wave;
+
+  f32x16 acc[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+
+  {
+#if __HIP_DEVICE_COMPILE__  // (buffer descriptors: see gemm_large_async_kernel)
+    constexpr int RSRC_FLAGS = 0x00020000;
+    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(A), 0, (int)(((int64_t)(M - 1) * lda + K) * 2), RSRC_FLAGS);
+    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(Wp), 0, (int)((int64_t)NB * 32 * K * 2), RSRC_FLAGS);
+    // copy piece p of a stage covers rows p*8 .. p*8+7 of the tile: lane -> row p*8 + lane/8, stored chunk lane%8
+    int piece[CP], aoff[CP];
+#pragma unroll
+    for (int jj = 0; jj < CP; ++jj) {
+      piece[jj] = PIECES % 8 == 0 ? wave * CP + jj : min(wave * CP + jj, PIECES - 1);
+      const int r = piece[jj] * 8 + (lane >> 3);
+      const int kc = (lane & 7) ^ ((r >> 1) & 7);
+      const int gr = min(m0 + r, M - 1);  // rows past M re-read a valid row; their results are never stored
+      aoff[jj] = (int)(((int64_t)gr * lda + kc * 8) * 2);
+    }
+    // a column block past the matrix re-reads a valid one; its results are dropped
+    const int woff = (int)((packed_tile_offset(min(nb, NB - 1), 0, KB) + lane * 8) * 2);
+    u32x4 wreg[4];  // the weight operands of one k step
+    auto issue_a = [&](bf16_t* As, int kt) {
+      const int k = kt < kt1 ? kt : kt1 - 1;  // past the end: a copy nobody reads, so that the wait counts stay uniform
+#pragma unroll
+      for (int jj = 0; jj < CP; ++jj)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (__attribute__((address_space(3))) void*)(As + piece[jj] * 512),
+                                                 16, aoff[jj], k * (LG_BK * 2), 0, 0);
+    };
+    auto load_w = [&](int kt, const int s) {
+      const int k = kt < kt1 ? kt : kt1 - 1;
+      wreg[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, woff, (k * 4 + s) * 1024, 0);
+    };
+    auto load_a = [&](const bf16_t* As, int s, bf16x8 (&af)[MB]) {
+      const int kc = s * 2 + (lane >> 5);
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        const int r = i * 32 + (lane & 31);
+        af[i] = *reinterpret_cast<const bf16x8*>(As + r * LG_BK + ((kc ^ ((r >> 1) & 7)) << 3));
+      }
+    };
+    // One k step on stage Acur; the copy of k step kt + 3 goes to Afill, read last in k step kt - 1, which every wave
+    // has left.  At the barrier, before the last contraction step's MFMAs, this wave has read all of Acur and its part
+    // of the tile of k step kt + 1 has to have arrived; requested after that one were the copies of two steps (2 CP)
+    // and 4 + 4 + 3 weight loads.
+    bf16x8 af[2][MB];
+    auto step = [&](const bf16_t* Acur, const bf16_t* Anext, bf16_t* Afill, int kt) {
+      issue_a(Afill, kt + 3);
+      __builtin_amdgcn_sched_barrier(0);  // the copies go out first: the wait counts rely on the request order
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (!AHEAD) load_a(Acur, s, af[0]);
+        else if (s < 3) load_a(Acur, s + 1, af[(s + 1) & 1]);
+        if (s == 3) {
+          PIE_S_WAIT_LGKMCNT0();  // this wave's last reads of Acur have returned
+          PIE_S_WAIT_VMCNT(2 * CP + 11);
+          wg_barrier();
+          if (AHEAD) load_a(Anext, 0, af[0]);
+        }
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          Pack16 w;
+          w.u = wreg[s];
+          acc[i] = mfma32(af[AHEAD ? s & 1 : 0][i], w.h, acc[i]);
+        }
+        load_w(kt + 1, s);  // refill the register just consumed with the next k step's weights
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    issue_a(As0, kt0);
+    issue_a(As1, kt0 + 1);
+    issue_a(As2, kt0 + 2);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) load_w(kt0, s);
+    PIE_S_WAIT_VMCNT(2 * CP + 4);  // the first activation tile has arrived
+    wg_barrier();
+    if (AHEAD) load_a(As0, 0, af[0]);
+    int kt = kt0;
+    for (; kt + 4 <= kt1; kt += 4) {  // whole revolutions of the four stages, then up to three steps
+      step(As0, As1, As3, kt);
+      step(As1, As2, As0, kt + 1);
+      step(As2, As3, As1, kt + 2);
+      step(As3, As0, As2, kt + 3);
+    }
+    if (kt < kt1) step(As0, As1, As3, kt);
+    if (kt + 1 < kt1) step(As1, As2, As0, kt + 1);
+    if (kt + 2 < kt1) step(As2, As3, As1, kt + 2);
+    PIE_S_WAIT_VMCNT(0);  // the surplus copies of the last steps land before the workgroup gives up its LDS
+#endif
+  }
+  if (PARTIAL) {
+    if (nb >= NB) return;
+    const int NP = NB * 32;
+    float* P = part + (int64_t)blockIdx.y * M * NP + nb * 32 + (lane & 31);  // raw sums: part[split][m][n_packed]
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int m = m0 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+        if (m < M) {
+          if (NT) store_nt(P + (int64_t)m * NP, acc[i][v]);
+          else P[(int64_t)m * NP] = acc[i][v];
+        }
+      }
+    return;
+  }
+  const bool rows_full = m0 + BM <= M;
+  if constexpr (MODE == EPI_SWIGLU) {
+    // A gate block sits in an even wave, its up block in the wave after it, which hands its sums over through one of
+    // the stages (16 MB x 64 floats, the size of a stage; all waves have left the main loop at the first barrier).
+    const int pair = wave >> 1;
+    float* xch = reinterpret_cast<float*>(pair == 0 ? As0 : pair == 1 ? As1 : pair == 2 ? As2 : As3);
+    __syncthreads();
+    if (wave & 1) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) xch[(i * 16 + v) * 64 + lane] = acc[i][v];
+    }
+    __syncthreads();
+    if ((wave & 1) || nb >= NB) return;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      f32x16 up;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) up[v] = xch[(i * 16 + v) * 64 + lane];
+      if (rows_full) epi_tile<MODE, true, NT>(epi, acc[i], up, m0 + i * 32, nb * 32, M, NB * 32, lane);
+      else epi_tile<MODE, false, NT>(epi, acc[i], up, m0 + i * 32, nb * 32, M, NB * 32, lane);
+    }
+  } else {
+    if (nb >= NB) return;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      if (rows_full) epi_tile<MODE, true, NT>(epi, acc[i], acc[i], m0 + i * 32, nb * 32, M, N, lane);
+      else epi_tile<MODE, false, NT>(epi, acc[i], acc[i], m0 + i * 32, nb * 32, M, N, lane);
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 // dispatch
 // ------------------------------------------------------------------------------------------------
 // Raises a kernel's dynamic LDS limit once per process and device (done: one bit per device), not per launch.
@@ -860,71 +1049,105 @@ static EpiArgs offset_rows(EpiArgs e, int m0) {
   return e;
 }
 
+// Tile height and split of K for a tiled product (K a multiple of 64).
+struct TiledPlan {
+  int rows;        // tile height: 96 or 128 (gemm_rows), 256 (gemm_large_async)
+  int splits, kts; // splits of K and k steps per split
+  int full_rows;   // leading rows in whole rounds of 256-row tiles, the rest as a product of its own; 0 = one product
+  double us;
+};
+
+// The estimate every choice is made by: workgroups are spread evenly over the CUs, a workgroup's k step takes
+//   rows   one workgroup per CU   all CUs full (two workgroups of gemm_rows, one of gemm_large_async)
+//    96        0.70 us               1.25 us for both
+//   128        0.75 us               1.65 us for both
+//   256        1.35 us               1.60 us
+// the weights come from HBM at 5.4 TB/s at best (the two add up by their cubes: both matter where they are close), a
+// launch costs 3 us besides, and the partial sums of a split are written and read once at 6 TB/s (+ 3 us).  Fitted to
+// sweeps of every tile and 1..16 splits for N x K = 6144 x 4096, 4096 x 4096, 28672 x 4096, 4096 x 14336, 3072 x 2048,
+// 2048 x 2048, 16384 x 2048 and 2048 x 8192 at 84 to 8320 rows.  What it replaces: one row of tiles with as many splits
+// as CUs up to 256 rows and unsplit 256-row tiles beyond, which left most of the chip idle at a few hundred rows
+// (4096 x 14336 at 333 rows: 32 workgroups, 308 us; now 240 and 53 us).
+static TiledPlan plan_tiled(int M, int NB, int K, size_t ws_elems, int n_cus) {
+  const int tiles_n = (NB + 7) / 8, KT = K / LG_BK, NP = NB * 32;
+  const double stream_us = (double)NP * K * 2 / 5.4e6;
+  TiledPlan best{0, 1, KT, 0, 1e30};
+  auto main_us = [&](double compute) { return 3.0 + std::cbrt(compute * compute * compute + stream_us * stream_us * stream_us); };
+  auto steps_us = [&](int rows, int64_t wgs) {  // time of one k step of all workgroups
+    const int slots = rows == 256 ? n_cus : 2 * n_cus;
+    const double one = rows == 96 ? 0.70 : rows == 128 ? 0.75 : 1.35, full = rows == 96 ? 1.25 : rows == 128 ? 1.65 : 1.60;
+    const int64_t rem = wgs % slots;
+    const bool light = rows == 256 ? rem * 8 <= (int64_t)n_cus * 7 && wgs < slots : rem <= n_cus;
+    return (double)(wgs / slots) * full + (rem == 0 ? 0.0 : light ? one : full);
+  };
+  for (int rows : {96, 128, 256}) {
+    const int tiles_m = (M + rows - 1) / rows;
+    for (int splits = 1, last = 0; splits <= 16; ++splits) {
+      const int kts = (KT + splits - 1) / splits;
+      if (kts == last || (splits > 1 && kts < 4)) continue;
+      last = kts;
+      const int n = (KT + kts - 1) / kts;
+      if (n > 1 && (size_t)n * M * NP > ws_elems) break;
+      double us = main_us(kts * steps_us(rows, (int64_t)tiles_m * tiles_n * n));
+      if (n > 1) us += 3.0 + (double)n * M * NP * 8 / 6e6;
+      if (us < best.us) best = TiledPlan{rows, n, kts, 0, us};
+    }
+  }
+  // whole 256-row tiles whose remainder would open one more round of them
+  const int full = M / LG_BM, ragged = M % LG_BM;
+  if (full > 0 && ragged > 0) {
+    const double us = main_us(KT * steps_us(256, (int64_t)full * tiles_n));
+    if (us < best.us) {
+      const double rest = plan_tiled(ragged, NB, K, ws_elems, n_cus).us;
+      if (us + rest < best.us) best = TiledPlan{256, 1, KT, full * LG_BM, us + rest};
+    }
+  }
+  return best;
+}
+
+template <int MODE, bool PARTIAL>
+static hipError_t run_tiles(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, const TiledPlan& p,
+                            float* ws, hipStream_t s) {
+  const int tiles_n = (W.NB + 7) / 8, tiles_m = (M + p.rows - 1) / p.rows;
+  const dim3 grid(tiles_m * tiles_n, p.splits), block(512);
+  if (p.rows == 96)
+    gemm_rows_kernel<MODE, PARTIAL, 3><<<grid, block, 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, p.kts, ws);
+  else if (p.rows == 128)
+    gemm_rows_kernel<MODE, PARTIAL, 4><<<grid, block, 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, p.kts, ws);
+  else
+    gemm_large_async_kernel<MODE, PARTIAL><<<grid, block, 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, p.kts, ws);
+  return hipGetLastError();
+}
+
 template <int MODE>
 static hipError_t run_mode(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, float* ws,
                            size_t ws_elems, int n_cus, hipStream_t s, int* defer) {
   if (M <= 0) return hipSuccess;
   if (M <= 32) return run_skinny<1, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
   if (M <= 64) return run_skinny<2, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
-  // Very wide outputs (the LM head) give the tiled kernel at least one tile per CU even with a single row
-  // block; above 64 rows it beats streaming the weights past 4-8 row blocks per wave (measured at 128256 x 4096:
-  // 0.26 ms for up to 256 rows against 0.30 ms at 128 rows and 0.46 ms at 256 rows).
-  // the tiled kernel steps 64 contraction elements at a time and addresses both operands with 32-bit byte offsets
+  // the tiled kernels step 64 contraction elements at a time and address both operands with 32-bit byte offsets
   const bool tiled_ok = W.K % LG_BK == 0 && (int64_t)M * lda * 2 < ((int64_t)1 << 32) &&
                         (int64_t)W.NB * 32 * W.K * 2 < ((int64_t)1 << 32);
-  const bool wide = tiled_ok && (W.NB + 7) / 8 >= n_cus && M > 64;
-  if (M <= 256 && !wide && tiled_ok) {
-    // One row of 256-column tiles (128 rows high up to 128 rows, else 256) with K split so that the tiles fill the
-    // chip once; each split keeps at least TILED_MIN_KTS k tiles, or the pipeline fill and the partial sums
-    // outweigh the work.
-    const int tiles_n = (W.NB + 7) / 8, KT = W.K / LG_BK, NP = W.NB * 32;
-    int splits = std::max(1, n_cus / tiles_n);
-    int kts = (KT + splits - 1) / splits;
-    kts = std::max(kts, TILED_MIN_KTS);
-    splits = (KT + kts - 1) / kts;
-    if (splits > 1 && (size_t)splits * M * NP <= ws_elems) {
-      if (M <= 128)
-        gemm_large_async_kernel<MODE, true, 128><<<dim3(tiles_n, splits), dim3(512), 0, s>>>(
-            A, lda, M, W.data, W.N, W.NB, W.K, epi, 1, tiles_n, kts, ws);
-      else
-        gemm_large_async_kernel<MODE, true, 256><<<dim3(tiles_n, splits), dim3(512), 0, s>>>(
-            A, lda, M, W.data, W.N, W.NB, W.K, epi, 1, tiles_n, kts, ws);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      if (defer) { *defer = splits; return hipSuccess; }
-      const int cols = (MODE == EPI_SWIGLU) ? NP / 2 : W.N;
-      const int64_t total = (int64_t)M * (cols / 4);
-      splitk_epilogue_kernel<MODE><<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(ws, splits, M, W.N, NP, epi);
-      return hipGetLastError();
-    }
-  }
-  if (M <= 128 && !wide) return run_skinny<4, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
-  if constexpr (MODE != EPI_SWIGLU) {  // (eight row blocks of gate/up pairs would not fit the register file)
-    if (M <= 256 && !wide) return run_skinny<8, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
-  }
   if (tiled_ok) {
-    const int tiles_n = (W.NB + 7) / 8;
-    // A ragged last row block that would open one more round of tiles (a round = one tile per CU) costs a whole
-    // round for a fraction of a tile's work: those rows go through the weight-streaming kernel instead.
-    const int full = M / LG_BM, ragged = M % LG_BM;
-    auto rounds = [&](int tm) { return (tm * tiles_n + n_cus - 1) / n_cus; };
-    if (ragged > 0 && full > 0 && (ragged <= 128 || MODE != EPI_SWIGLU) && rounds(full + 1) > rounds(full)) {
-      const int M0 = full * LG_BM;
-      gemm_large_async_kernel<MODE, false, 256><<<dim3(full * tiles_n), dim3(512), 0, s>>>(
-          A, lda, M0, W.data, W.N, W.NB, W.K, epi, full, tiles_n, 0, nullptr);
-      hipError_t e = hipGetLastError();
+    const TiledPlan p = plan_tiled(M, W.NB, W.K, ws_elems, n_cus);
+    if (p.full_rows > 0) {
+      hipError_t e = run_tiles<MODE, false>(A, lda, p.full_rows, W, epi, p, nullptr, s);
       if (e != hipSuccess) return e;
-      return run_mode<MODE>(A + (int64_t)M0 * lda, lda, ragged, W, offset_rows<MODE>(epi, M0), ws, ws_elems, n_cus, s,
-                            nullptr);
+      return run_mode<MODE>(A + (int64_t)p.full_rows * lda, lda, M - p.full_rows, W, offset_rows<MODE>(epi, p.full_rows), ws,
+                            ws_elems, n_cus, s, nullptr);
     }
-    const int tiles_m = (M + LG_BM - 1) / LG_BM;
-    if (M <= 128)
-      gemm_large_async_kernel<MODE, false, 128><<<dim3(tiles_n), dim3(512), 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi,
-                                                                                   1, tiles_n, 0, nullptr);
-    else
-      gemm_large_async_kernel<MODE, false, 256><<<dim3(tiles_m * tiles_n), dim3(512), 0, s>>>(
-          A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, 0, nullptr);
+    if (p.splits == 1) return run_tiles<MODE, false>(A, lda, M, W, epi, p, nullptr, s);
+    hipError_t e = run_tiles<MODE, true>(A, lda, M, W, epi, p, ws, s);
+    if (e != hipSuccess) return e;
+    if (defer) { *defer = p.splits; return hipSuccess; }
+    const int NP = W.NB * 32, cols = (MODE == EPI_SWIGLU) ? NP / 2 : W.N;
+    const int64_t total = (int64_t)M * (cols / 4);
+    splitk_epilogue_kernel<MODE><<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(ws, p.splits, M, W.N, NP, epi);
     return hipGetLastError();
+  }
+  if (M <= 128) return run_skinny<4, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
+  if constexpr (MODE != EPI_SWIGLU) {  // (eight row blocks of gate/up pairs would not fit the register file)
+    if (M <= 256) return run_skinny<8, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
   }
   auto kern = gemm_large_kernel<MODE>;
   size_t smem = (size_t)4 * LG_BM * LG_BK * sizeof(bf16_t);
@@ -938,9 +1161,8 @@ static hipError_t run_mode(const bf16_t* A, int lda, int M, const PackedWeight& 
 
 hipError_t launch_gemm(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, float* splitk_ws,
                        size_t splitk_elems, int n_cus, hipStream_t s, int* deferred_splits) {
-  // Deferral is only offered where the whole product goes through one split-K launch (at most 256 rows).
-  int* defer = (deferred_splits && M <= 256) ? deferred_splits : nullptr;
-  if (deferred_splits) *deferred_splits = 0;
+  int* defer = deferred_splits;  // used where the whole product goes through one split-K launch
+  if (defer) *defer = 0;
   switch (epi.mode) {
     case EPI_STORE_BF16: return run_mode<EPI_STORE_BF16>(A, lda, M, W, epi, splitk_ws, splitk_elems, n_cus, s, defer);
     case EPI_RESID_EMBED: return run_mode<EPI_RESID_EMBED>(A, lda, M, W, epi, splitk_ws, splitk_elems, n_cus, s, defer);

@@ -282,7 +282,9 @@ pie_status pie_batch_work(const pie_batch* batch, int64_t* out);
 pie_status pie_batch_plan_info(const pie_batch* batch, int64_t* out);
 
 /* The prefill attention launches of a batch, as the planner laid them out: one entry per workgroup in launch order,
- * three values each (request, 32-token query block, kv head); request -1 marks an empty slot.  There are two
+ * three values each (request, 32-token query block, kv head); request -1 marks an empty slot.  (A block whose page
+ * list is cut into parts, because the blocks alone would not fill the chip, is one entry; its parts run on the same XCD
+ * as separate workgroups, and a merge kernel combines them.)  There are two
  * launches, listed one after the other (their sizes: pie_batch_plan_info out[6], out[7], both multiples of 8): the
  * second holds the query blocks whose rows may see only a few keys (requests with a bitmap; blocks of causal
  * requests that start within the first 64 keys) and runs with the softmax weights held as bf16 pairs.  Workgroup i

@@ -546,8 +546,13 @@ __device__ __forceinline__ void lds_copy_run(const char* src, char* dst) {
 // Workgroups are listed per XCD by the host (all query blocks of a (request, kv head) on one XCD, whose L2 then
 // serves the re-reads of its K/V); the lists are padded with empty items.
 // LO: the softmax weights as bf16 pairs (see attn_softmax); the host lists the items that need it separately.
-template <int D, int G, bool LO>
-__global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, const PrefillItem* __restrict__ items) {
+// SPLIT: blockIdx.y is the part of the item's page pairs this workgroup takes (items with fewer parts: nothing to do).
+// A launch of few query blocks over long contexts otherwise leaves most of the chip idle while each workgroup walks its
+// pairs one after the other: twelve requests of 7 tokens at 2500 tokens of context are 96 workgroups of 118 steps.
+// The parts of a block sit n_items workgroups apart, a multiple of 8, hence on one XCD.
+template <int D, int G, bool LO, bool SPLIT>
+__global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, const PrefillItem* __restrict__ items,
+                                                                 float* __restrict__ part_o, float* __restrict__ part_ml) {
   constexpr int BLK = 2 * PAGE * D;            // elements of one (page, head) block: K part then V part
   constexpr int PIECES = BLK * 2 / 1024;       // 1 KiB copy instructions per page block
   constexpr int IPW = 2 * PIECES / G;          // copy instructions per wave per pair
@@ -556,6 +561,7 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
   const int lane = threadIdx.x & 63, hg = threadIdx.x >> 6;
   const PrefillItem it = items[blockIdx.x];
   if (it.r < 0) return;  // padding of the per-XCD lists (uniform over the workgroup)
+  if (SPLIT && (int)blockIdx.y >= it.n_parts) return;
   const int hk = it.hk;
   const ReqInfo rq = a.reqs[it.r];
   const int qcol = lane & 31, g = lane >> 5, m = lane & 31;
@@ -575,14 +581,16 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
     const int pages = (rq.kv_len - rq.n_new + i_last) / PAGE + 1;
     v_end = pages < v_end ? pages : v_end;
   }
-  const int n_pairs = (v_end + 1) / 2;
+  const int first_pair = SPLIT && it.n_parts > 1 ? blockIdx.y * it.per : 0;
+  const int all_pairs = (v_end + 1) / 2;
+  const int n_pairs = SPLIT && it.n_parts > 1 ? min(all_pairs - first_pair, it.per) : all_pairs;
   if (n_pairs > 0) {
     // Page ids are workgroup-uniform: one 16-byte scalar load per pair (physical and logical id of both pages)
     // through the constant address space (scalar loads do not count as vector memory operations, so waiting for
     // them never drains the copies in flight), one pair ahead of the pair that is started.
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
     typedef const __attribute__((address_space(4))) i32x4* const_i32x4;
-    const const_i32x4 vis = (const_i32x4)(a.visit_pairs) + rq.pair0;
+    const const_i32x4 vis = (const_i32x4)(a.visit_pairs) + rq.pair0 + first_pair;
     i32x4 nx = {0, 0, 0, 0};
     auto fetch_ids = [&](int pair) { nx = vis[pair < n_pairs ? pair : n_pairs - 1]; };
     // Copies: this wave's pieces of a pair are consecutive 1 KiB pieces of one page block (of both blocks when
@@ -602,13 +610,13 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
     // their keys, which the whole workgroup knows without any per-lane arithmetic.
     const bool rows_full = !has_bitmap && it.qb * 32 + 31 < rq.n_new;
     const int first_lim = rq.kv_len - rq.n_new + it.qb * 32;
-    const int n_full = rows_full ? min(v_end / 2, (first_lim + 1) / 32) : 0;
+    const int n_full = rows_full ? min(v_end / 2, (first_lim + 1) / 32) - first_pair : 0;
     auto start_pair = [&](bf16_t* stage, int pair, Meta& md) {
       const int pc = pair < n_pairs ? pair : n_pairs - 1;
       const int pp_a = nx[0], pp_b = nx[2];  // fetched by the previous call (pairs are started in order)
       md.pl_a = nx[1];
       md.pl_b = nx[3];
-      md.has_b = pc * 2 + 1 < v_end;
+      md.has_b = (first_pair + pc) * 2 + 1 < v_end;
       fetch_ids(pair + 1);
       md.full = pair < n_full;
       if (has_bitmap && valid) { md.mw_a = mrow[md.pl_a >> 1]; md.mw_b = mrow[md.pl_b >> 1]; }
@@ -708,6 +716,22 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
   }
   const float l_tot = sum_xor32(st.l);
   if (!valid) return;
+  if (SPLIT && it.n_parts > 1) {  // (max, sum, O) of this part, for the merge kernel
+    const int64_t prow = ((int64_t)(it.slot0 + (int)blockIdx.y) * G + hg) * 32 + qcol;
+    if (g == 0) {
+      part_ml[prow * 2] = st.m;
+      part_ml[prow * 2 + 1] = l_tot;
+    }
+    float* po = part_o + prow * D + g * 4;
+#pragma unroll
+    for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x4 o4 = {st.o[b][q4 * 4], st.o[b][q4 * 4 + 1], st.o[b][q4 * 4 + 2], st.o[b][q4 * 4 + 3]};
+        *reinterpret_cast<f32x4*>(po + b * 32 + q4 * 8) = o4;
+      }
+    return;
+  }
   const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
   bf16_t* orow = a.out + (int64_t)(rq.tok0 + i_tok) * a.Hq * D + (hk * G + hg) * D;
 #pragma unroll
@@ -719,6 +743,58 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
       for (int e = 0; e < 4; ++e) o4[e] = f32_to_bf16(st.o[b][q4 * 4 + e] * inv);
       *reinterpret_cast<bf16x4*>(orow + b * 32 + q4 * 8 + g * 4) = o4;
     }
+}
+
+// Combines the parts of the query blocks that were cut (see PrefillItem): workgroup (block, head of the group, 8 (D = 128)
+// or 16 rows), D / 4 lanes per row.  Bound by reading the parts once (fp32, valid rows only): the lanes of a row first
+// share its (max, sum) pairs, one part per lane, then read eight parts at a time with independent loads (one workgroup
+// per head and one load after the other took 18 us for the 34 MB of a 333-token prompt instead of 8).
+template <int D>
+__global__ __launch_bounds__(256) void attn_prefill_merge_kernel(AttnArgs a, const PrefillItem* __restrict__ items,
+                                                                 const float* __restrict__ part_o,
+                                                                 const float* __restrict__ part_ml) {
+  constexpr int L = D / 4;  // lanes of a row: half or a quarter of a wave
+  const PrefillItem it = items[blockIdx.x];
+  const ReqInfo rq = a.reqs[it.r];
+  const int G = a.Hq / a.Hkv, hg = blockIdx.y;
+  const int rows = min(32, rq.n_new - it.qb * 32);
+  const int row = blockIdx.z * (256 / L) + threadIdx.x / L, l = threadIdx.x % L;
+  if (row >= rows) return;  // (whole rows leave, so the shuffles below stay within lanes that remain)
+  const int64_t p0 = ((int64_t)it.slot0 * G + hg) * 32 + row, step = (int64_t)G * 32;
+  float M = -INFINITY;
+  for (int p = l; p < it.n_parts; p += L) M = fmaxf(M, part_ml[(p0 + p * step) * 2]);
+#pragma unroll
+  for (int o = L / 2; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, L));
+  const float m_safe = M == -INFINITY ? 0.f : M;
+  f32x4 num = {0.f, 0.f, 0.f, 0.f};
+  float den = 0.f;
+  for (int q0 = 0; q0 < it.n_parts; q0 += L) {
+    float w = 0.f;
+    if (q0 + l < it.n_parts) {
+      const float* ml = part_ml + (p0 + (q0 + l) * step) * 2;
+      w = __builtin_amdgcn_exp2f(ml[0] - m_safe);
+      den += w * ml[1];
+    }
+    const int n = min(L, it.n_parts - q0);
+    for (int q = 0; q < n; q += 8) {
+      f32x4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        v[u] = *reinterpret_cast<const f32x4*>(part_o + (p0 + (q0 + min(q + u, n - 1)) * step) * D + l * 4);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float wu = __shfl(w, min(q + u, L - 1), L);
+        if (q + u < n) num += v[u] * wu;
+      }
+    }
+  }
+#pragma unroll
+  for (int o = L / 2; o > 0; o >>= 1) den += __shfl_xor(den, o, L);
+  const float inv = den > 0.f ? 1.0f / den : 0.f;
+  bf16x4 o4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o4[e] = f32_to_bf16(num[e] * inv);
+  *reinterpret_cast<bf16x4*>(a.out + (int64_t)(rq.tok0 + it.qb * 32 + row) * a.Hq * D + (it.hk * G + hg) * D + l * 4) = o4;
 }
 
 // Variant without LDS: every wave loads its own K/V operands from global memory (the group's waves meet in L1).
@@ -806,24 +882,42 @@ hipError_t launch_attn_merge(const AttnArgs& a, const int32_t* dec_reqs, int n_d
   return hipGetLastError();
 }
 
-template <int D, bool LO>
-static hipError_t launch_prefill_d(const AttnArgs& a, const PrefillItem* items, int n_items, hipStream_t s) {
+template <int D, bool LO, bool SPLIT>
+static hipError_t launch_prefill_d(const AttnArgs& a, const PrefillItem* items, int n_items, int max_parts, float* part_o,
+                                   float* part_ml, hipStream_t s) {
   const int G = a.Hq / a.Hkv;
-  dim3 grid(n_items), block(64 * G);
-  if (G == 1) attn_prefill_kernel<D, 1, LO><<<grid, block, 0, s>>>(a, items);
-  else if (G == 2) attn_prefill_kernel<D, 2, LO><<<grid, block, 0, s>>>(a, items);
-  else if (G == 4) attn_prefill_kernel<D, 4, LO><<<grid, block, 0, s>>>(a, items);
-  else if (G == 8) attn_prefill_kernel<D, 8, LO><<<grid, block, 0, s>>>(a, items);
+  dim3 grid(n_items, SPLIT ? max_parts : 1), block(64 * G);
+  if (G == 1) attn_prefill_kernel<D, 1, LO, SPLIT><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else if (G == 2) attn_prefill_kernel<D, 2, LO, SPLIT><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else if (G == 4) attn_prefill_kernel<D, 4, LO, SPLIT><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else if (G == 8) attn_prefill_kernel<D, 8, LO, SPLIT><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else if (SPLIT) return hipErrorInvalidValue;  // (the planner cuts blocks for the group sizes above only)
   else attn_prefill_direct_kernel<D><<<grid, block, 0, s>>>(a, items);  // other group sizes: no LDS sharing
   return hipGetLastError();
 }
 
-hipError_t launch_attn_prefill(const AttnArgs& a, const PrefillItem* items, int n_items, bool pair_weights,
-                               hipStream_t s) {
+hipError_t launch_attn_prefill(const AttnArgs& a, const PrefillItem* items, int n_items, bool pair_weights, int max_parts,
+                               float* part_o, float* part_ml, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  if (a.D == 128)
-    return pair_weights ? launch_prefill_d<128, true>(a, items, n_items, s) : launch_prefill_d<128, false>(a, items, n_items, s);
-  if (a.D == 64)
-    return pair_weights ? launch_prefill_d<64, true>(a, items, n_items, s) : launch_prefill_d<64, false>(a, items, n_items, s);
+  auto run = [&](auto d_c) {
+    constexpr int D = decltype(d_c)::value;
+    if (max_parts > 1)
+      return pair_weights ? launch_prefill_d<D, true, true>(a, items, n_items, max_parts, part_o, part_ml, s)
+                          : launch_prefill_d<D, false, true>(a, items, n_items, max_parts, part_o, part_ml, s);
+    return pair_weights ? launch_prefill_d<D, true, false>(a, items, n_items, 1, part_o, part_ml, s)
+                        : launch_prefill_d<D, false, false>(a, items, n_items, 1, part_o, part_ml, s);
+  };
+  if (a.D == 128) return run(std::integral_constant<int, 128>{});
+  if (a.D == 64) return run(std::integral_constant<int, 64>{});
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_attn_prefill_merge(const AttnArgs& a, const PrefillItem* items, int n_items, const float* part_o,
+                                     const float* part_ml, hipStream_t s) {
+  if (n_items <= 0) return hipSuccess;
+  const dim3 grid(n_items, a.Hq / a.Hkv, 32 / (256 / (a.D / 4))), block(256);
+  if (a.D == 128) attn_prefill_merge_kernel<128><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else if (a.D == 64) attn_prefill_merge_kernel<64><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }

@@ -76,7 +76,10 @@ struct DecodeCol {     // one query column of a column group: (request token, he
 // (shared prefixes), so that each K/V block is read once for all of them.
 struct DecodeSeg { int32_t cgroup, hk, n_pairs, pad; };  // a run of page pairs of one (column group, kv head) inside one wave's share
 struct DecodeWave { int32_t seg0, n_seg, n_pairs, pad; };  // a wave's share: segments [seg0, seg0 + n_seg)
-struct PrefillItem { int32_t r, qb, hk, pad; };  // query block qb (32 tokens) of request r for kv head hk; r < 0: empty slot
+// Query block qb (32 tokens) of request r for kv head hk; r < 0: empty slot.  A block whose list of visited page pairs
+// is cut into n_parts > 1 parts of `per` pairs (split over as many workgroups) leaves part p's unnormalised result in
+// partial block slot0 + p, for attn_prefill_merge_kernel.
+struct PrefillItem { int32_t r, qb, hk, n_parts, per, slot0; };
 
 struct pie_batch {
   const pie_ctx* owner = nullptr;  // the context that deserialised the batch: its pools, ranges and wave count are baked in
@@ -109,6 +112,11 @@ struct pie_batch {
   // n_pwork entries of pitems run with plain bf16 softmax weights, the following n_pwork_lo (query blocks whose rows
   // may see few keys: bitmap masks, causal blocks that start within the first 64 keys) with weights as bf16 pairs
   int32_t n_pwork = 0, n_pwork_lo = 0;
+  int32_t max_parts = 1, max_parts_lo = 1;  // most parts of a query block in each of the two launches
+  int32_t n_psplit = 0;                     // query blocks that were cut into parts
+  PrefillItem* psplit = nullptr;            // [n_psplit]
+  float* ppart_o = nullptr;   // [partial blocks, G, 32, D]
+  float* ppart_ml = nullptr;  // [partial blocks, G, 32, 2]
   float* part_o = nullptr;   // [n_dsegs * rows_cap, D]
   float* part_ml = nullptr;  // [n_dsegs * rows_cap, 2]
   int64_t work[6] = {0, 0, 0, 0, 0, 0};
@@ -240,8 +248,11 @@ hipError_t launch_attn_merge(const AttnArgs& a, const int32_t* dec_reqs, int n_d
                              const int32_t* mrefs, int rows_cap, const float* part_o, const float* part_ml,
                              hipStream_t s);
 // pair_weights: the items' softmax weights enter the PV product as bf16 pairs hi + lo (rows that may see few keys)
-hipError_t launch_attn_prefill(const AttnArgs& a, const PrefillItem* items, int n_items, bool pair_weights,
-                               hipStream_t s);
+// max_parts: most parts an item is cut into (part_o / part_ml hold their results when it is more than one)
+hipError_t launch_attn_prefill(const AttnArgs& a, const PrefillItem* items, int n_items, bool pair_weights, int max_parts,
+                               float* part_o, float* part_ml, hipStream_t s);
+hipError_t launch_attn_prefill_merge(const AttnArgs& a, const PrefillItem* items, int n_items, const float* part_o,
+                                     const float* part_ml, hipStream_t s);
 
 // rows / tile_ad: the batch's adapter tiles (32 rows each); z: [ksplits][n_tiles * 32, 3, rmax_p] fp32, where
 // ksplits (from lora_ksplits, the same for the down and the up launch of a projection group) splits the input

@@ -579,10 +579,12 @@ struct Blob {  // host image of the device allocation, written into the context'
 };
 }  // namespace
 
-static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, int32_t validate, pie_batch** out) {
+static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, int32_t validate, pie_batch** out,
+                                        bool may_split = true) {
   if (!c) return PIE_EINVAL;
   if (!b || !out) return fail(c, PIE_EINVAL, "pie_batch_create: null argument");
   *out = nullptr;
+  const pie_forward_batch* const b_given = b;
   const int R = b->n_requests, T = b->n_tokens;
   if (R <= 0 || T <= 0) return fail(c, PIE_EINVAL, "empty batch (R=%d, T=%d)", R, T);
   if (R > c->p.max_batch_requests || T > c->p.max_batch_tokens)
@@ -733,7 +735,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
       flops += visited_pages * PAGE * (int64_t)n_new * c->m.n_q_heads * D * 4;
     } else {
       const int nqb = (n_new + 31) / 32;
-      for (int qb = 0; qb < nqb; ++qb) pitems.push_back(PrefillItem{r, qb, 0, 0});
+      for (int qb = 0; qb < nqb; ++qb) pitems.push_back(PrefillItem{r, qb, 0, 1, 0, -1});
       q.pair0 = (int32_t)(visit_pairs.size() / 4);
       for (int v = 0; v < q.n_visit; v += 2) {
         const int v2 = v + 1 < q.n_visit ? v + 1 : v;
@@ -1018,10 +1020,10 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
       for (int x = 0; x < N_XCD; ++x) {
         for (const Unit& u : per_xcd[x])
           for (int32_t i = u.first + u.part; i < u.first + u.count; i += parts)
-            flat[x].push_back(PrefillItem{pitems[i].r, pitems[i].qb, u.hk, 0});
+            flat[x].push_back(PrefillItem{pitems[i].r, pitems[i].qb, u.hk, pitems[i].n_parts, pitems[i].per, -1});
         lmax = std::max(lmax, flat[x].size());
       }
-      pwork.assign(lmax * N_XCD, PrefillItem{-1, 0, 0, 0});
+      pwork.assign(lmax * N_XCD, PrefillItem{-1, 0, 0, 1, 0, -1});
       for (int x = 0; x < N_XCD; ++x)
         for (size_t i = 0; i < flat[x].size(); ++i) pwork[i * N_XCD + x] = flat[x][i];
       break;
@@ -1029,14 +1031,62 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   }
   return pwork;
   };
+  // A launch with too few query blocks to fill the chip cuts the page pairs of the long ones into parts, one workgroup
+  // each, so that all parts together are one round of resident workgroups (eight waves per compute unit, as far as LDS
+  // holds their rings).  A step takes 0.75 us with one workgroup on a compute unit and 1 us with two; the parts cost a
+  // write and a read of their fp32 results and the launch of the merge, 5 to 10 us, and the walk has about 10 us of
+  // start-up however short it is, so nothing is cut unless it shortens the longest walk by 24 steps.  Measured: twelve
+  // requests of 7 tokens over 1250 to 3750 tokens, 96 workgroups of up to 118 steps, 92 us whole, 39 + 5 us cut (parts
+  // of 64 / 48 / 32 / 24 steps: 53 / 43 / 39 / 35 us); 333 tokens over 3000, 88 workgroups, 85 us whole, 36 + 8 us cut
+  // (53 / 43 / 41 / 38).  Launches whose blocks fill the chip are never cut (8 x 1024 tokens: 237 us as before).
+  auto cut = [&](std::vector<PrefillItem>& items) {
+    if (!may_split || items.empty() || (G != 1 && G != 2 && G != 4 && G != 8)) return 1;
+    const int64_t slots = (int64_t)(c->wave_slots / 8) * std::min(8 / G, D == 128 ? 2 : 5);
+    auto pairs_of = [&](const PrefillItem& it) {  // as the kernel counts them
+      const ReqInfo& q = reqs[it.r];
+      int v = q.n_visit;
+      if (q.wpr == 0) v = std::min(v, (q.kv_len - q.n_new + std::min(it.qb * 32 + 31, q.n_new - 1)) / PAGE + 1);
+      return (v + 1) / 2;
+    };
+    int64_t total = 0;
+    int longest = 0;
+    for (const PrefillItem& it : items) {
+      total += pairs_of(it);
+      longest = std::max(longest, pairs_of(it));
+    }
+    int64_t per = std::max<int64_t>(8, (total * Hkv + slots - 1) / slots);
+    for (;; per += (per + 15) / 16) {  // the shortest parts that still are one round
+      int64_t n = 0;
+      for (const PrefillItem& it : items) n += std::max<int64_t>(1, (pairs_of(it) + per - 1) / per);
+      if (n * Hkv <= slots || per >= longest) break;
+    }
+    if (longest - per < 24) return 1;
+    int most = 1;
+    for (PrefillItem& it : items) {
+      const int n = pairs_of(it), parts = (int)std::max<int64_t>(1, (n + per - 1) / per);
+      it.per = (n + parts - 1) / parts;
+      it.n_parts = it.per > 0 ? (n + it.per - 1) / it.per : 1;  // no part is empty
+      most = std::max(most, it.n_parts);
+    }
+    return most;
+  };
   std::vector<PrefillItem> pitems_plain, pitems_pair;
   for (const PrefillItem& it : pitems) (few_keys(it) ? pitems_pair : pitems_plain).push_back(it);
+  const int max_parts = cut(pitems_plain), max_parts_lo = cut(pitems_pair);
   std::vector<PrefillItem> pwork = layout(std::move(pitems_plain));
   const size_t n_pwork_plain = pwork.size();
   {
     const std::vector<PrefillItem> lo = layout(std::move(pitems_pair));
     pwork.insert(pwork.end(), lo.begin(), lo.end());
   }
+  std::vector<PrefillItem> psplit;
+  int64_t n_pparts = 0;  // partial blocks of the cut query blocks
+  for (PrefillItem& it : pwork)
+    if (it.r >= 0 && it.n_parts > 1) {
+      it.slot0 = (int32_t)n_pparts;
+      n_pparts += it.n_parts;
+      psplit.push_back(it);
+    }
 
   pie_batch* pb = new pie_batch();
   pb->owner = c;
@@ -1048,6 +1098,9 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   pb->n_pitems = (int32_t)pitems.size();
   pb->n_pwork = (int32_t)n_pwork_plain;
   pb->n_pwork_lo = (int32_t)(pwork.size() - n_pwork_plain);
+  pb->max_parts = max_parts;
+  pb->max_parts_lo = max_parts_lo;
+  pb->n_psplit = (int32_t)psplit.size();
   pb->pwork_host = pwork;
   pb->n_dec_reqs = (int32_t)dec_reqs.size();
   pb->rows_cap = std::max(rows_cap, 1);
@@ -1090,6 +1143,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   const size_t o_mi = blob.add(mref_indptr.data(), mref_indptr.size() * 4, 4);
   const size_t o_mr = blob.add(mrefs.data(), mrefs.size() * 4, 4);
   const size_t o_pi = blob.add(pwork.data(), pwork.size() * sizeof(PrefillItem), 16);
+  const size_t o_ps = blob.add(psplit.data(), psplit.size() * sizeof(PrefillItem), 16);
   const size_t o_dr = blob.add(dec_reqs.data(), dec_reqs.size() * 4, 4);
   const size_t part_rows = (size_t)pb->n_dsegs * pb->rows_cap;
   const size_t o_po = blob.add(nullptr, 0, 0);  // metadata ends here; the partial buffers are device-only
@@ -1099,7 +1153,10 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   }
   const size_t o_pm = (o_po + part_rows * D * 4 + 255) / 256 * 256;
   const size_t o_an = (o_pm + part_rows * 2 * 4 + 255) / 256 * 256;  // rotary angle table [T, D] floats
-  const size_t total_bytes = o_an + (size_t)T * D * 4 + 256;
+  const size_t o_pp = (o_an + (size_t)T * D * 4 + 255) / 256 * 256;  // partial results of cut prefill blocks
+  const size_t pp_rows = (size_t)n_pparts * G * 32;
+  const size_t o_pq = o_pp + pp_rows * D * 4;
+  const size_t total_bytes = o_pq + pp_rows * 2 * 4 + 256;
   if (c->host_only) {  // plan only: the work lists stay on the host and are dropped, the statistics remain
     pb->n_lora_tiles = (int)lora_tile_ad.size();
     pb->used_adapters = used_adapters;
@@ -1122,6 +1179,10 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   }
   if (e != hipSuccess) {
     delete pb;
+    if (n_pparts > 0) {  // no room for the partial results: plan the batch again without cutting query blocks
+      (void)hipGetLastError();
+      return pie_batch_create_impl(c, b_given, validate, out, false);
+    }
     return fail(c, PIE_ENOMEM, "pie_batch_create: %s (%zu bytes)", hipGetErrorString(e), total_bytes);
   }
   // copy only the metadata part (everything before the partial buffers)
@@ -1150,6 +1211,8 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   pb->pitems = (PrefillItem*)(d + o_pi); pb->dec_reqs = (int32_t*)(d + o_dr);
   pb->part_o = (float*)(d + o_po); pb->part_ml = (float*)(d + o_pm);
   pb->rope_angles = (float*)(d + o_an);
+  pb->psplit = (PrefillItem*)(d + o_ps);
+  pb->ppart_o = (float*)(d + o_pp); pb->ppart_ml = (float*)(d + o_pq);
   *out = pb;
   return PIE_OK;
 }
@@ -1295,8 +1358,9 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   // which is bound by HBM reads.
   if (b->n_pitems > 0) {
     tm.begin(PIE_STAGE_ATTN_PREFILL);
-    HIP_TRY(c, launch_attn_prefill(a, b->pitems, b->n_pwork, false, s));
-    HIP_TRY(c, launch_attn_prefill(a, b->pitems + b->n_pwork, b->n_pwork_lo, true, s));
+    HIP_TRY(c, launch_attn_prefill(a, b->pitems, b->n_pwork, false, b->max_parts, b->ppart_o, b->ppart_ml, s));
+    HIP_TRY(c, launch_attn_prefill(a, b->pitems + b->n_pwork, b->n_pwork_lo, true, b->max_parts_lo, b->ppart_o, b->ppart_ml, s));
+    HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit, b->n_psplit, b->ppart_o, b->ppart_ml, s));
     tm.end(PIE_STAGE_ATTN_PREFILL);
   }
   if (b->n_dec_reqs > 0) {

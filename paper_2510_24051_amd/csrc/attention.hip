@@ -465,7 +465,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnArgs a, const D
 template <int D>
 __global__ __launch_bounds__(64) void attn_merge_kernel(AttnArgs a, const int32_t* __restrict__ dec_reqs,
                                                         const int32_t* __restrict__ mref_indptr,
-                                                        const int32_t* __restrict__ mrefs, int rows_cap,
+                                                        const int32_t* __restrict__ mrefs,
                                                         const float* __restrict__ part_o,
                                                         const float* __restrict__ part_ml) {
   const ReqInfo rq = a.reqs[dec_reqs[blockIdx.x]];
@@ -550,9 +550,18 @@ __device__ __forceinline__ void lds_copy_run(const char* src, char* dst) {
 // A launch of few query blocks over long contexts otherwise leaves most of the chip idle while each workgroup walks its
 // pairs one after the other: twelve requests of 7 tokens at 2500 tokens of context are 96 workgroups of 118 steps.
 // The parts of a block sit n_items workgroups apart, a multiple of 8, hence on one XCD.
-template <int D, int G, bool LO, bool SPLIT>
+// SHARED: decode-path requests that alias many pages (a prefix tree).  An item is a group of up to 128 query columns, 32
+// per wave, each with its own length, limit and mask row; always cut, its rows merged with the decode kernel's.  The
+// decode kernel holds 16 columns per K/V block and reads the block once per 16: 256 branches of 4 query heads on a
+// 4096-token prefix asked the caches for 1.14 GB and took 113 us; here a block is copied to LDS once per 128 columns
+// (134 MB) and the walk takes 44 us, bound by the MFMAs
+// and vector work of the pair weights (16 steps, 1.9 us for two workgroups on a compute unit).
+template <int D, int G, bool LO, bool SPLIT, bool SHARED = false>
 __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, const PrefillItem* __restrict__ items,
-                                                                 float* __restrict__ part_o, float* __restrict__ part_ml) {
+                                                                 float* __restrict__ part_o, float* __restrict__ part_ml,
+                                                                 const SharedGroup* __restrict__ sgroups = nullptr,
+                                                                 const DecodeCol* __restrict__ scols = nullptr) {
+  static_assert(!SHARED || (LO && SPLIT && G * 32 == SHARED_COLS), "shared groups: four waves, weights as pairs, cut");
   constexpr int BLK = 2 * PAGE * D;            // elements of one (page, head) block: K part then V part
   constexpr int PIECES = BLK * 2 / 1024;       // 1 KiB copy instructions per page block
   constexpr int IPW = 2 * PIECES / G;          // copy instructions per wave per pair
@@ -563,24 +572,46 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
   if (it.r < 0) return;  // padding of the per-XCD lists (uniform over the workgroup)
   if (SPLIT && (int)blockIdx.y >= it.n_parts) return;
   const int hk = it.hk;
-  const ReqInfo rq = a.reqs[it.r];
   const int qcol = lane & 31, g = lane >> 5, m = lane & 31;
-  const int i_tok = it.qb * 32 + qcol;
-  const bool valid = i_tok < rq.n_new;
-  const int i_ld = valid ? i_tok : rq.n_new - 1;
-  // requests with a bitmap are always listed in the launch with pair weights (their rows may see few keys)
-  const bool has_bitmap = LO && rq.wpr > 0;
+  ReqInfo rq{};
+  int i_tok = 0, kv_len, lim, pair0, v_end;  // the lane's row: KV length and last key visible under the causal rule
+  bool valid, has_bitmap;
+  const uint32_t* mrow;
   bf16x8 qf[D / 16];
-  load_q<D>(a.q + (int64_t)(rq.tok0 + i_ld) * a.q_stride + (hk * G + hg) * D, valid, g, qf);
+  if constexpr (SHARED) {
+    const SharedGroup sg = sgroups[it.r];
+    const int col = hg * 32 + qcol;
+    valid = col < sg.n_cols;
+    const DecodeCol cc = scols[sg.col0 + min(col, sg.n_cols - 1)];
+    kv_len = cc.kv_len;
+    lim = cc.lim;
+    has_bitmap = cc.wpr > 0;
+    mrow = a.mask_words + cc.mask_row;
+    pair0 = sg.pair0;
+    v_end = sg.n_pages;
+    load_q<D>(a.q + (int64_t)cc.tok * a.q_stride + (hk * (a.Hq / a.Hkv) + cc.hg) * D, valid, g, qf);
+  } else {
+    rq = a.reqs[it.r];
+    i_tok = it.qb * 32 + qcol;
+    valid = i_tok < rq.n_new;
+    const int i_ld = valid ? i_tok : rq.n_new - 1;
+    kv_len = rq.kv_len;
+    lim = rq.kv_len - rq.n_new + i_ld;
+    // requests with a bitmap are always listed in the launch with pair weights (their rows may see few keys)
+    has_bitmap = LO && rq.wpr > 0;
+    mrow = a.mask_words + rq.mask_off + (int64_t)i_ld * rq.wpr;
+    pair0 = rq.pair0;
+    v_end = rq.n_visit;
+    load_q<D>(a.q + (int64_t)(rq.tok0 + i_ld) * a.q_stride + (hk * G + hg) * D, valid, g, qf);
+    if (!has_bitmap) {  // inferred causal: the visit list is pages 0.. in order; stop at the block's last visible key
+      int i_last = it.qb * 32 + 31;
+      i_last = i_last < rq.n_new ? i_last : rq.n_new - 1;
+      const int pages = (rq.kv_len - rq.n_new + i_last) / PAGE + 1;
+      v_end = pages < v_end ? pages : v_end;
+    }
+  }
   AttnState<D> st;
   attn_init<D>(st);
-  int v_end = rq.n_visit;
-  if (!has_bitmap) {  // inferred causal: the visit list is pages 0.. in order; stop at the block's last visible key
-    int i_last = it.qb * 32 + 31;
-    i_last = i_last < rq.n_new ? i_last : rq.n_new - 1;
-    const int pages = (rq.kv_len - rq.n_new + i_last) / PAGE + 1;
-    v_end = pages < v_end ? pages : v_end;
-  }
   const int first_pair = SPLIT && it.n_parts > 1 ? blockIdx.y * it.per : 0;
   const int all_pairs = (v_end + 1) / 2;
   const int n_pairs = SPLIT && it.n_parts > 1 ? min(all_pairs - first_pair, it.per) : all_pairs;
@@ -590,7 +621,7 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
     // them never drains the copies in flight), one pair ahead of the pair that is started.
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
     typedef const __attribute__((address_space(4))) i32x4* const_i32x4;
-    const const_i32x4 vis = (const_i32x4)(a.visit_pairs) + rq.pair0 + first_pair;
+    const const_i32x4 vis = (const_i32x4)(a.visit_pairs) + pair0 + first_pair;
     i32x4 nx = {0, 0, 0, 0};
     auto fetch_ids = [&](int pair) { nx = vis[pair < n_pairs ? pair : n_pairs - 1]; };
     // Copies: this wave's pieces of a pair are consecutive 1 KiB pieces of one page block (of both blocks when
@@ -602,13 +633,12 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
     const char* kv_hk = reinterpret_cast<const char*>(a.kv + (int64_t)hk * BLK);
     const int64_t page_stride_b = (int64_t)a.Hkv * BLK * 2;
     const uint32_t lane_off = lane * 16;
-    const uint32_t* mrow = a.mask_words + rq.mask_off + (int64_t)i_ld * rq.wpr;
     struct Meta { int pl_a, pl_b; bool has_b, full; uint32_t mw_a, mw_b; };
     Meta m0{}, m1{}, m2{}, m3{};
     // Inferred-causal blocks of 32 real rows: the first n_full pairs lie entirely at or below the first row's
     // limit (pages are visited in logical order without gaps when there is no bitmap), so every row sees all of
     // their keys, which the whole workgroup knows without any per-lane arithmetic.
-    const bool rows_full = !has_bitmap && it.qb * 32 + 31 < rq.n_new;
+    const bool rows_full = !SHARED && !has_bitmap && it.qb * 32 + 31 < rq.n_new;
     const int first_lim = rq.kv_len - rq.n_new + it.qb * 32;
     const int n_full = rows_full ? min(v_end / 2, (first_lim + 1) / 32) - first_pair : 0;
     auto start_pair = [&](bf16_t* stage, int pair, Meta& md) {
@@ -633,15 +663,15 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
     auto bits_of = [&](uint32_t word, int pl) -> uint32_t {
       if (!valid) return 0u;
       const int j0 = pl * PAGE + g * 8;
-      int cnt = rq.kv_len - j0;
+      int cnt = kv_len - j0;
       cnt = cnt < 0 ? 0 : (cnt > 8 ? 8 : cnt);
       uint32_t bits = (1u << cnt) - 1u;
       if (has_bitmap) {
         bits &= (word >> ((pl & 1) * 16 + g * 8)) & 0xFFu;
       } else {
-        int lim = rq.kv_len - rq.n_new + i_ld - j0 + 1;
-        lim = lim < 0 ? 0 : (lim > 8 ? 8 : lim);
-        bits &= (1u << lim) - 1u;
+        int c = lim - j0 + 1;
+        c = c < 0 ? 0 : (c > 8 ? 8 : c);
+        bits &= (1u << c) - 1u;
       }
       return bits;
     };
@@ -716,7 +746,7 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
   }
   const float l_tot = sum_xor32(st.l);
   if (!valid) return;
-  if (SPLIT && it.n_parts > 1) {  // (max, sum, O) of this part, for the merge kernel
+  if (SHARED || (SPLIT && it.n_parts > 1)) {  // (max, sum, O) of this part, for the merge kernel
     const int64_t prow = ((int64_t)(it.slot0 + (int)blockIdx.y) * G + hg) * 32 + qcol;
     if (g == 0) {
       part_ml[prow * 2] = st.m;
@@ -872,12 +902,12 @@ hipError_t launch_attn_decode(const AttnArgs& a, const DecodeWave* waves, const 
 }
 
 hipError_t launch_attn_merge(const AttnArgs& a, const int32_t* dec_reqs, int n_dec_reqs, const int32_t* mref_indptr,
-                             const int32_t* mrefs, int rows_cap, const float* part_o, const float* part_ml,
+                             const int32_t* mrefs, int max_rows, const float* part_o, const float* part_ml,
                              hipStream_t s) {
   if (n_dec_reqs <= 0) return hipSuccess;
-  dim3 grid(n_dec_reqs, a.Hkv, rows_cap), block(64);
-  if (a.D == 128) attn_merge_kernel<128><<<grid, block, 0, s>>>(a, dec_reqs, mref_indptr, mrefs, rows_cap, part_o, part_ml);
-  else if (a.D == 64) attn_merge_kernel<64><<<grid, block, 0, s>>>(a, dec_reqs, mref_indptr, mrefs, rows_cap, part_o, part_ml);
+  dim3 grid(n_dec_reqs, a.Hkv, max_rows), block(64);
+  if (a.D == 128) attn_merge_kernel<128><<<grid, block, 0, s>>>(a, dec_reqs, mref_indptr, mrefs, part_o, part_ml);
+  else if (a.D == 64) attn_merge_kernel<64><<<grid, block, 0, s>>>(a, dec_reqs, mref_indptr, mrefs, part_o, part_ml);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -910,6 +940,16 @@ hipError_t launch_attn_prefill(const AttnArgs& a, const PrefillItem* items, int 
   if (a.D == 128) return run(std::integral_constant<int, 128>{});
   if (a.D == 64) return run(std::integral_constant<int, 64>{});
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_attn_shared(const AttnArgs& a, const PrefillItem* items, int n_items, int max_parts,
+                              const SharedGroup* groups, const DecodeCol* cols, float* part_o, float* part_ml, hipStream_t s) {
+  if (n_items <= 0) return hipSuccess;
+  const dim3 grid(n_items, max_parts), block(256);
+  if (a.D == 128) attn_prefill_kernel<128, 4, true, true, true><<<grid, block, 0, s>>>(a, items, part_o, part_ml, groups, cols);
+  else if (a.D == 64) attn_prefill_kernel<64, 4, true, true, true><<<grid, block, 0, s>>>(a, items, part_o, part_ml, groups, cols);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_attn_prefill_merge(const AttnArgs& a, const PrefillItem* items, int n_items, const float* part_o,

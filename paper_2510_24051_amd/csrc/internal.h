@@ -81,6 +81,11 @@ struct DecodeWave { int32_t seg0, n_seg, n_pairs, pad; };  // a wave's share: se
 // partial block slot0 + p, for attn_prefill_merge_kernel.
 struct PrefillItem { int32_t r, qb, hk, n_parts, per, slot0; };
 
+// Up to 128 query columns of decode-path requests that share many pages, walked by attn_prefill_kernel's four waves (32
+// columns each); columns [col0, col0 + n_cols) of the shared-column array, pages as pairs from pair0 of visit_pairs.
+struct SharedGroup { int32_t col0, n_cols, pair0, n_pages; };
+#define SHARED_COLS 128
+
 struct pie_batch {
   const pie_ctx* owner = nullptr;  // the context that deserialised the batch: its pools, ranges and wave count are baked in
   int32_t R = 0, T = 0;
@@ -112,13 +117,19 @@ struct pie_batch {
   // n_pwork entries of pitems run with plain bf16 softmax weights, the following n_pwork_lo (query blocks whose rows
   // may see few keys: bitmap masks, causal blocks that start within the first 64 keys) with weights as bf16 pairs
   int32_t n_pwork = 0, n_pwork_lo = 0;
+  int32_t n_sitems = 0, max_sparts = 1;     // shared groups: items (laid out per XCD), most parts of an item
+  PrefillItem* sitems = nullptr;            // [n_sitems] r = shared group
+  SharedGroup* sgroups = nullptr;
+  DecodeCol* scols = nullptr;
+  int32_t dec_rows = 1;                     // most query rows (tokens x group) of a decode-path request
+  bool dec_read_once = true;                // no page is in two column groups of the decode kernel
   int32_t max_parts = 1, max_parts_lo = 1;  // most parts of a query block in each of the two launches
   int32_t n_psplit = 0;                     // query blocks that were cut into parts
   PrefillItem* psplit = nullptr;            // [n_psplit]
   float* ppart_o = nullptr;   // [partial blocks, G, 32, D]
   float* ppart_ml = nullptr;  // [partial blocks, G, 32, 2]
-  float* part_o = nullptr;   // [n_dsegs * rows_cap, D]
-  float* part_ml = nullptr;  // [n_dsegs * rows_cap, 2]
+  float* part_o = nullptr;   // [n_dsegs * rows_cap + SHARED_COLS * (parts of all shared items), D]
+  float* part_ml = nullptr;  // [the same, 2]
   int64_t work[6] = {0, 0, 0, 0, 0, 0};
 };
 
@@ -245,8 +256,11 @@ hipError_t launch_attn_decode(const AttnArgs& a, const DecodeWave* waves, const 
                               const DecodeSeg* segs, const DecodeCol* cols, int n_waves, int rows_cap, float* part_o,
                               float* part_ml, bool read_once, hipStream_t s);
 hipError_t launch_attn_merge(const AttnArgs& a, const int32_t* dec_reqs, int n_dec_reqs, const int32_t* mref_indptr,
-                             const int32_t* mrefs, int rows_cap, const float* part_o, const float* part_ml,
+                             const int32_t* mrefs, int max_rows, const float* part_o, const float* part_ml,
                              hipStream_t s);
+// items[i].r names a shared group; the parts' results go to rows (slot0 + part) * SHARED_COLS + column of part_o / part_ml
+hipError_t launch_attn_shared(const AttnArgs& a, const PrefillItem* items, int n_items, int max_parts,
+                              const SharedGroup* groups, const DecodeCol* cols, float* part_o, float* part_ml, hipStream_t s);
 // pair_weights: the items' softmax weights enter the PV product as bf16 pairs hi + lo (rows that may see few keys)
 // max_parts: most parts an item is cut into (part_o / part_ml hold their results when it is more than one)
 hipError_t launch_attn_prefill(const AttnArgs& a, const PrefillItem* items, int n_items, bool pair_weights, int max_parts,

@@ -19,6 +19,7 @@ static char g_create_err[512] = "";
 #define PIE_STATIC_SCRATCH_BYTES (16u << 20)
 #define PIE_STATIC_DIST_ROWS 32
 #define PIE_MAX_DEVICES 64
+#define SHARED_MIN_SAVED ((int64_t)160 << 20)  // bytes of requests shared groups have to save (see pie_batch_create_impl)
 static __device__ __align__(256) unsigned char pie_static_scratch[PIE_STATIC_SCRATCH_BYTES];
 static void* g_static_scratch[PIE_MAX_DEVICES] = {nullptr};
 
@@ -782,6 +783,8 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   // stride, two slots per pair.
   struct CGroup { std::vector<int> members; int rows; std::vector<int2> pages; };  // members: decode request indices
   std::vector<CGroup> cgroups;
+  struct SGroup { std::vector<int> members; int rows, key; std::vector<int2> pages; };
+  std::vector<SGroup> sgroups_h;
   {
     std::unordered_map<int64_t, size_t> class_of;  // (rows, first physical page) -> index into classes
     std::vector<std::vector<int>> classes;
@@ -797,53 +800,102 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
       if (ins.second) classes.emplace_back();
       classes[ins.first->second].push_back((int)di);
     }
+    // Pages (of the first `common`) on which every member's table names one physical page, visited by at least one.
+    auto shared_pages = [&](const std::vector<int>& cls, size_t c0, size_t c1, const std::vector<char>* skip) {
+      int common = INT32_MAX;
+      for (size_t k = c0; k < c1; ++k) common = std::min(common, (reqs[dec_reqs[cls[k]]].kv_len + PAGE - 1) / PAGE);
+      std::vector<char> shared(common, 1), visited(common, 0);
+      const int32_t* pg0 = b->page_ids + b->page_indptr[dec_reqs[cls[c0]]];
+      for (size_t k = c0; k < c1; ++k) {
+        const ReqInfo& q = reqs[dec_reqs[cls[k]]];
+        const int32_t* pg = b->page_ids + b->page_indptr[dec_reqs[cls[k]]];
+        for (int pgi = 0; pgi < common; ++pgi) if (pg[pgi] != pg0[pgi]) shared[pgi] = 0;
+        for (int v = 0; v < q.n_visit; ++v)
+          if (visit_logical[q.visit0 + v] < common) visited[visit_logical[q.visit0 + v]] = 1;
+      }
+      for (int pgi = 0; pgi < common; ++pgi)
+        shared[pgi] = shared[pgi] && visited[pgi] && !(skip && pgi < (int)skip->size() && (*skip)[pgi]);
+      return shared;
+    };
+    // Shared groups (attn_prefill_kernel<SHARED>): up to 128 columns of one class over the pages all of them share; what
+    // they don't all share is left to the column groups below.  They take a launch of their own and fp32 parts to merge,
+    // against about 10 TB/s at which the decode kernel re-reads shared blocks out of the caches for every 16 columns:
+    // used when they save the decode kernel 160 MB of requests.  Measured (8B shape, kernels of the attention stage
+    // together, without -> with): 32 branches on 4096 tokens, 117 MB saved, 31 -> 31 us; 64, 235 MB, 50 -> 35; 128,
+    // 470 MB, 77 -> 51; 256, 940 MB, 125 -> 75; 256 branches on 1024 tokens, 235 MB, 63 -> 48.
+    std::vector<std::vector<std::vector<char>>> taken(classes.size());  // per class and 128-column chunk: pages taken
+    {
+      int64_t saved = 0;
+      for (size_t ci = 0; ci < classes.size(); ++ci) {
+        const auto& cls = classes[ci];
+        const int rows = reqs[dec_reqs[cls[0]]].n_new * G;
+        const size_t small = 16 / rows, big = SHARED_COLS / rows;
+        if (cls.size() <= small) continue;
+        for (size_t c0 = 0; c0 < cls.size(); c0 += big) {
+          const size_t c1 = std::min(cls.size(), c0 + big);
+          std::vector<char> sh;
+          if (c1 - c0 > small) sh = shared_pages(cls, c0, c1, nullptr);
+          saved += (int64_t)((c1 - c0 + small - 1) / small - 1) * std::count(sh.begin(), sh.end(), 1) * page_bytes;
+          taken[ci].push_back(std::move(sh));
+        }
+      }
+      if (!may_split || saved < SHARED_MIN_SAVED) taken.assign(classes.size(), {});
+    }
     auto single = [&](int di, const std::vector<char>* skip) {
       const ReqInfo& q = reqs[dec_reqs[di]];
       CGroup g;
       g.members.push_back(di);
       g.rows = q.n_new * G;
       for (int v = 0; v < q.n_visit; ++v)
-        if (!skip || !(*skip)[visit_logical[q.visit0 + v]])
+        if (!skip || visit_logical[q.visit0 + v] >= (int)skip->size() || !(*skip)[visit_logical[q.visit0 + v]])
           g.pages.push_back(make_int2(visit_phys[q.visit0 + v], visit_logical[q.visit0 + v]));
       if (!g.pages.empty() || !skip) cgroups.push_back(std::move(g));
     };
-    for (const auto& cls : classes) {
+    for (size_t ci = 0; ci < classes.size(); ++ci) {
+      const auto& cls = classes[ci];
       const int rows = reqs[dec_reqs[cls[0]]].n_new * G;
-      const int cap = 16 / rows;
-      for (size_t c0 = 0; c0 < cls.size(); c0 += cap) {
-        const size_t c1 = std::min(cls.size(), c0 + cap);
-        if (c1 - c0 < 2) { single(cls[c0], nullptr); continue; }
-        // logical pages on which every member's table names the same physical page, visited by at least one
-        int common = INT32_MAX;
-        for (size_t k = c0; k < c1; ++k) common = std::min(common, (reqs[dec_reqs[cls[k]]].kv_len + PAGE - 1) / PAGE);
-        std::vector<char> shared(common, 1), visited(common, 0);
-        const int32_t* pg0 = b->page_ids + b->page_indptr[dec_reqs[cls[c0]]];
-        for (size_t k = c0; k < c1; ++k) {
-          const ReqInfo& q = reqs[dec_reqs[cls[k]]];
-          const int32_t* pg = b->page_ids + b->page_indptr[dec_reqs[cls[k]]];
-          for (int pgi = 0; pgi < common; ++pgi) if (pg[pgi] != pg0[pgi]) shared[pgi] = 0;
-          for (int v = 0; v < q.n_visit; ++v)
-            if (visit_logical[q.visit0 + v] < common) visited[visit_logical[q.visit0 + v]] = 1;
+      const size_t cap = 16 / rows, big = SHARED_COLS / rows;
+      for (size_t b0 = 0; b0 < cls.size(); b0 += taken[ci].empty() ? cls.size() : big) {
+        const size_t b1 = taken[ci].empty() ? cls.size() : std::min(cls.size(), b0 + big);
+        const std::vector<char>* gone = nullptr;  // pages a shared group of these members walks
+        if (!taken[ci].empty()) {
+          const std::vector<char>& sh = taken[ci][b0 / big];
+          const int n_pg = (int)std::count(sh.begin(), sh.end(), 1);
+          if (n_pg > 0) {
+            gone = &sh;
+            SGroup g;
+            g.rows = rows;
+            g.key = b->page_ids[b->page_indptr[dec_reqs[cls[b0]]]];
+            g.members.assign(cls.begin() + b0, cls.begin() + b1);
+            const int32_t* pg0 = b->page_ids + b->page_indptr[dec_reqs[cls[b0]]];
+            for (int pgi = 0; pgi < (int)sh.size(); ++pgi) if (sh[pgi]) g.pages.push_back(make_int2(pg0[pgi], pgi));
+            sgroups_h.push_back(std::move(g));
+          }
         }
-        CGroup g;
-        g.rows = rows;
-        for (int pgi = 0; pgi < common; ++pgi) {
-          shared[pgi] = shared[pgi] && visited[pgi];
-          if (shared[pgi]) g.pages.push_back(make_int2(pg0[pgi], pgi));
-        }
-        if (g.pages.size() < 2) {  // nothing worth sharing
-          for (size_t k = c0; k < c1; ++k) single(cls[k], nullptr);
-          continue;
-        }
-        for (size_t k = c0; k < c1; ++k) g.members.push_back(cls[k]);
-        cgroups.push_back(std::move(g));
-        // what a member visits outside the shared pages (private suffix, pages beyond the shortest member)
-        std::vector<char> skip;
-        for (size_t k = c0; k < c1; ++k) {
-          const int n_pg = (reqs[dec_reqs[cls[k]]].kv_len + PAGE - 1) / PAGE;
-          skip.assign(n_pg, 0);
-          std::copy(shared.begin(), shared.end(), skip.begin());
-          single(cls[k], &skip);
+        for (size_t c0 = b0; c0 < b1; c0 += cap) {
+          const size_t c1 = std::min(b1, c0 + cap);
+          if (c1 - c0 < 2) { single(cls[c0], gone); continue; }
+          const std::vector<char> shared = shared_pages(cls, c0, c1, gone);
+          CGroup g;
+          g.rows = rows;
+          const int32_t* pg0 = b->page_ids + b->page_indptr[dec_reqs[cls[c0]]];
+          for (int pgi = 0; pgi < (int)shared.size(); ++pgi)
+            if (shared[pgi]) g.pages.push_back(make_int2(pg0[pgi], pgi));
+          if (g.pages.size() < 2) {  // nothing worth sharing
+            for (size_t k = c0; k < c1; ++k) single(cls[k], gone);
+            continue;
+          }
+          for (size_t k = c0; k < c1; ++k) g.members.push_back(cls[k]);
+          cgroups.push_back(std::move(g));
+          // what a member visits outside the shared pages (private suffix, pages beyond the shortest member)
+          std::vector<char> skip;
+          for (size_t k = c0; k < c1; ++k) {
+            const int n_pg = (reqs[dec_reqs[cls[k]]].kv_len + PAGE - 1) / PAGE;
+            skip.assign(n_pg, 0);
+            std::copy(shared.begin(), shared.end(), skip.begin());
+            if (gone) for (size_t i = 0; i < gone->size(); ++i) skip[i] = skip[i] || (*gone)[i];
+            single(cls[k], &skip);
+          }
         }
       }
     }
@@ -934,12 +986,80 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
       if (dc.tok >= T || dc.hg < 0 || dc.hg >= G || (dc.tok >= 0 && dc.wpr > 0 && dc.mask_row + dc.wpr > (int64_t)(n_mask_given + extra_words.size())))
         return fail(c, PIE_EINVAL, "internal: inconsistent decode column");
   }
-  // partial rows a (decode request, kv head) has to merge: segment * rows_cap + the request's first column
+  // Shared groups: one item per (group, kv head), the groups of one prefix and kv head on one XCD (its L2 serves all but
+  // the first read of a page), page lists cut so that all parts are one round of resident workgroups (two of four waves
+  // per compute unit).
+  std::vector<SharedGroup> sgroups;
+  std::vector<DecodeCol> scols;
+  std::vector<PrefillItem> sitems;
+  int max_sparts = 1;
+  int64_t n_sparts = 0;
+  if (!sgroups_h.empty()) {
+    const int64_t slots = c->wave_slots / 4;
+    int64_t total = 0, longest = 0;
+    for (const SGroup& g : sgroups_h) {
+      const int64_t pairs = ((int64_t)g.pages.size() + 1) / 2;
+      total += pairs * Hkv;
+      longest = std::max(longest, pairs);
+    }
+    int64_t per = std::max<int64_t>(8, (total + slots - 1) / slots);
+    for (;; per += (per + 15) / 16) {
+      int64_t n = 0;
+      for (const SGroup& g : sgroups_h) n += (((int64_t)g.pages.size() + 1) / 2 + per - 1) / per;
+      if (n * Hkv <= slots || per >= longest) break;
+    }
+    constexpr int N_XCD = 8;
+    std::vector<PrefillItem> flat[N_XCD];
+    int64_t load[N_XCD] = {0};
+    std::unordered_map<int64_t, int> home;
+    for (size_t gi = 0; gi < sgroups_h.size(); ++gi) {
+      const SGroup& g = sgroups_h[gi];
+      const int n_pg = (int)g.pages.size(), pairs = (n_pg + 1) / 2;
+      const int parts0 = (int)((pairs + per - 1) / per), plen = (pairs + parts0 - 1) / parts0, parts = (pairs + plen - 1) / plen;
+      max_sparts = std::max(max_sparts, parts);
+      sgroups.push_back(SharedGroup{(int32_t)scols.size(), (int32_t)g.members.size() * g.rows, (int32_t)(visit_pairs.size() / 4), n_pg});
+      for (int di : g.members) {
+        const ReqInfo& q = reqs[dec_reqs[di]];
+        for (int rr = 0; rr < g.rows; ++rr)
+          scols.push_back(DecodeCol{q.tok0 + rr / G, rr % G, q.kv_len, q.kv_len - q.n_new + rr / G, q.wpr, 0,
+                                    q.mask_off + (int64_t)(rr / G) * q.wpr});
+      }
+      for (int v = 0; v < n_pg; v += 2)
+        for (int e = 0; e < 2; ++e) {
+          const int2 pg = g.pages[std::min(v + e, n_pg - 1)];
+          visit_pairs.push_back(pg.x);
+          visit_pairs.push_back(pg.y);
+        }
+      kv_bytes_req += (int64_t)n_pg * page_bytes;
+      for (int hk = 0; hk < Hkv; ++hk) {
+        auto ins = home.emplace((int64_t)g.key * Hkv + hk, 0);
+        if (ins.second) ins.first->second = (int)(std::min_element(load, load + N_XCD) - load);
+        const int x = ins.first->second;
+        load[x] += pairs;
+        flat[x].push_back(PrefillItem{(int32_t)gi, 0, hk, parts, plen, (int32_t)n_sparts});
+        for (size_t mi = 0; mi < g.members.size(); ++mi)  // partial rows behind the decode kernel's, marked by the sign
+          for (int p = 0; p < parts; ++p)
+            mref_lists[(size_t)g.members[mi] * Hkv + hk].push_back(-1 - (int32_t)((n_sparts + p) * SHARED_COLS + mi * g.rows));
+        n_sparts += parts;
+      }
+    }
+    size_t lmax = 0;
+    for (const auto& f : flat) lmax = std::max(lmax, f.size());
+    sitems.assign(lmax * N_XCD, PrefillItem{-1, 0, 0, 1, 0, -1});
+    for (int x = 0; x < N_XCD; ++x)
+      for (size_t i = 0; i < flat[x].size(); ++i) sitems[i * N_XCD + x] = flat[x][i];
+  }
+  // partial rows a (decode request, kv head) has to merge: segment * rows_cap + the request's first column, or the shared
+  // groups' rows behind those
   std::vector<int32_t> mref_indptr(dec_reqs.size() * Hkv + 1, 0), mrefs;
+  const int32_t shared_row0 = (int32_t)(dsegs.size() * rows_cap);
   for (size_t i = 0; i < mref_lists.size(); ++i) {
-    for (int32_t v : mref_lists[i]) mrefs.push_back((v / 16) * rows_cap + (v % 16));
+    for (int32_t v : mref_lists[i]) mrefs.push_back(v >= 0 ? (v / 16) * rows_cap + (v % 16) : shared_row0 + (-1 - v));
     mref_indptr[i + 1] = (int32_t)mrefs.size();
   }
+  bool dec_read_once = true;  // no page is in two column groups
+  int dec_rows = 1;
+  for (int r : dec_reqs) dec_rows = std::max(dec_rows, reqs[r].n_new * G);
   // Prefill work list.  The hardware hands workgroup i to XCD i % 8, and every XCD has an L2 of its own: the
   // query blocks of one (request, kv head) read the same K/V pages, so they go to one XCD, next to each other in
   // its list (heavy blocks first), and that XCD's L2 serves all but the first read of a page.  The groups are
@@ -1098,6 +1218,9 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   pb->n_pitems = (int32_t)pitems.size();
   pb->n_pwork = (int32_t)n_pwork_plain;
   pb->n_pwork_lo = (int32_t)(pwork.size() - n_pwork_plain);
+  pb->n_sitems = (int32_t)sitems.size();
+  pb->max_sparts = max_sparts;
+  pb->dec_rows = dec_rows;
   pb->max_parts = max_parts;
   pb->max_parts_lo = max_parts_lo;
   pb->n_psplit = (int32_t)psplit.size();
@@ -1119,6 +1242,17 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
         if (st != id) { st = id; ++distinct; }
       }
     pb->work[4] = distinct * page_bytes;
+    if (++c->page_stamp_id == 0u) {
+      std::fill(c->page_stamp.begin(), c->page_stamp.end(), 0u);
+      c->page_stamp_id = 1u;
+    }
+    for (const CGroup& g : cgroups)
+      for (const int2& pg : g.pages) {
+        uint32_t& st = c->page_stamp[pg.x];
+        if (st == c->page_stamp_id) dec_read_once = false;
+        st = c->page_stamp_id;
+      }
+    pb->dec_read_once = dec_read_once;
   }
   pb->work[5] = kv_bytes_req;
   Blob blob(c);
@@ -1143,9 +1277,12 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   const size_t o_mi = blob.add(mref_indptr.data(), mref_indptr.size() * 4, 4);
   const size_t o_mr = blob.add(mrefs.data(), mrefs.size() * 4, 4);
   const size_t o_pi = blob.add(pwork.data(), pwork.size() * sizeof(PrefillItem), 16);
+  const size_t o_si = blob.add(sitems.data(), sitems.size() * sizeof(PrefillItem), 16);
+  const size_t o_sg = blob.add(sgroups.data(), sgroups.size() * sizeof(SharedGroup), 16);
+  const size_t o_sc = blob.add(scols.data(), scols.size() * sizeof(DecodeCol), 16);
   const size_t o_ps = blob.add(psplit.data(), psplit.size() * sizeof(PrefillItem), 16);
   const size_t o_dr = blob.add(dec_reqs.data(), dec_reqs.size() * 4, 4);
-  const size_t part_rows = (size_t)pb->n_dsegs * pb->rows_cap;
+  const size_t part_rows = (size_t)pb->n_dsegs * pb->rows_cap + (size_t)n_sparts * SHARED_COLS;
   const size_t o_po = blob.add(nullptr, 0, 0);  // metadata ends here; the partial buffers are device-only
   if (!blob.ok) {
     delete pb;
@@ -1179,7 +1316,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   }
   if (e != hipSuccess) {
     delete pb;
-    if (n_pparts > 0) {  // no room for the partial results: plan the batch again without cutting query blocks
+    if (n_pparts > 0 || n_sparts > 0) {  // no room for the partial results: plan the batch again without them
       (void)hipGetLastError();
       return pie_batch_create_impl(c, b_given, validate, out, false);
     }
@@ -1212,6 +1349,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   pb->part_o = (float*)(d + o_po); pb->part_ml = (float*)(d + o_pm);
   pb->rope_angles = (float*)(d + o_an);
   pb->psplit = (PrefillItem*)(d + o_ps);
+  pb->sitems = (PrefillItem*)(d + o_si); pb->sgroups = (SharedGroup*)(d + o_sg); pb->scols = (DecodeCol*)(d + o_sc);
   pb->ppart_o = (float*)(d + o_pp); pb->ppart_ml = (float*)(d + o_pq);
   *out = pb;
   return PIE_OK;
@@ -1365,11 +1503,14 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   }
   if (b->n_dec_reqs > 0) {
     tm.begin(PIE_STAGE_ATTN_DECODE);
+    const size_t shared_row0 = (size_t)b->n_dsegs * b->rows_cap;
+    HIP_TRY(c, launch_attn_shared(a, b->sitems, b->n_sitems, b->max_sparts, b->sgroups, b->scols, b->part_o + shared_row0 * D,
+                                  b->part_ml + shared_row0 * 2, s));
     HIP_TRY(c, launch_attn_decode(a, b->dwaves, b->wave_pg, b->dslots, b->dsegs, b->dcols, b->n_dwaves, b->rows_cap, b->part_o, b->part_ml,
-                                  /*read_once=*/b->work[5] <= b->work[4], s));
+                                  b->dec_read_once, s));
     tm.end(PIE_STAGE_ATTN_DECODE);
     tm.begin(PIE_STAGE_ATTN_MERGE);
-    HIP_TRY(c, launch_attn_merge(a, b->dec_reqs, b->n_dec_reqs, b->mref_indptr, b->mrefs, b->rows_cap, b->part_o, b->part_ml, s));
+    HIP_TRY(c, launch_attn_merge(a, b->dec_reqs, b->n_dec_reqs, b->mref_indptr, b->mrefs, b->dec_rows, b->part_o, b->part_ml, s));
     tm.end(PIE_STAGE_ATTN_MERGE);
   }
 

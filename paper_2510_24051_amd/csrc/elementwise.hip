@@ -163,7 +163,7 @@ hipError_t launch_splitk_resid_norm(const float* part, int splits, int NP, const
 // Rotary step + KV append.  qkv is [T, (Hq + 2 Hkv) * D] bf16.  A rotary thread handles the 8 pairs
 // (c*8 + e, D/2 + c*8 + e) of `hpt` consecutive query/key heads of one token, so the 8 angles
 // pos * theta^(-2i/D), evaluated in double (positions reach tens of thousands), are computed once for all of
-// them; a value thread copies 16 consecutive elements.  Rotated queries are written back in place; rotated
+// them; a value thread handles 16 consecutive elements of a token, or two of eight tokens.  Rotated queries are written back in place; rotated
 // keys and values go to the token's page slot.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void rope_append_kernel(bf16_t* __restrict__ qkv, int T, int Hq, int Hkv, int D,
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16_t* __restrict__ q
                                                           const int32_t* __restrict__ tok_page,
                                                           const int32_t* __restrict__ tok_slot,
                                                           const float* __restrict__ angles,
-                                                          bf16_t* __restrict__ kv_layer, int hpt,
+                                                          bf16_t* __restrict__ kv_layer, int hpt, bool by_octet,
                                                           const float* __restrict__ part, int splits, int NP) {
   // Eight consecutive values of token t from column `col` of its qkv row: read as stored, or (splits > 0) summed
   // in split order from the partials of the QKV product and rounded to bf16 like the stored row would be.
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16_t* __restrict__ q
   const int cpt = D / 16;  // work pieces per head
   const int heads = Hq + 2 * Hkv, rot = Hq + Hkv;
   const int groups = (rot + hpt - 1) / hpt;
-  const int64_t n_rot = (int64_t)T * groups * cpt, n_val = (int64_t)T * Hkv * cpt;
+  const int64_t n_rot = (int64_t)T * groups * cpt, n_val = (int64_t)((T + 7) / 8 * 8) * Hkv * cpt;
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n_rot + n_val) return;
   if (idx < n_rot) {
@@ -243,35 +243,51 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16_t* __restrict__ q
       }
     }
   } else {
+    // by_octet: eight consecutive tokens of one (head, piece) sit in neighbouring lanes; else the pieces of one token do
     idx -= n_rot;
-    const int c = (int)(idx % cpt);
-    const int hv = (int)((idx / cpt) % Hkv);
-    const int t = (int)(idx / ((int64_t)cpt * Hkv));
+    const int per8 = 8 * Hkv * cpt;
+    const int in8 = (int)(idx % per8), piece = by_octet ? in8 >> 3 : in8 % (Hkv * cpt);
+    const int t = (int)(idx / per8) * 8 + (by_octet ? in8 & 7 : in8 / (Hkv * cpt));
+    if (t >= T) return;
+    const int c = piece % cpt, hv = piece / cpt;
     const int page = tok_page[t], slot = tok_slot[t];
     bf16_t* blk = kv_layer + ((int64_t)page * Hkv + hv) * (2 * PAGE * D);
-    // The V part keeps the 8 tokens of slots 8k .. 8k+7 next to each other for every d.  When the batch fills such
-    // an octet with consecutive tokens (prefill), the thread of its first token writes all eight at once, 16 bytes
-    // per d, and the other seven have nothing to do; single tokens (decode) store their 2-byte values one by one.
+    // The V part keeps the 8 tokens of slots 8k .. 8k+7 next to each other for every d.  When the batch fills such an
+    // octet with consecutive tokens (prefill), its eight threads share the work by d: the thread of slot 8k + i gathers
+    // values 2i and 2i + 1 of the piece from all eight tokens (its neighbours read the bytes next to them) and stores 16
+    // bytes per d; single tokens (decode) store their 2-byte values one by one.  (One thread per octet, the other seven
+    // idle, left a long chain of loads at the end: 333 tokens over three split-K copies 20 -> 10 us,
+    // 8320 tokens 51 -> 49.  For batches of single tokens that order of lanes costs 1.5 us at 157 tokens.)
     const int t0 = t - (slot & 7);
     bool octet = t0 >= 0 && t0 + 7 < T;
 #pragma unroll
     for (int i = 0; i < 8; ++i) octet = octet && tok_page[t0 + i] == page && tok_slot[t0 + i] == (slot & ~7) + i;
     if (octet) {
-      if (t != t0) return;
-      Pack16 a[8], b[8];
+      const int d = c * 16 + (slot & 7) * 2, col = (rot + hv) * D + d;
+      Pack16 o0, o1;
+      if (splits > 0) {
+        float s0[8], s1[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        a[i] = load8(t0 + i, (rot + hv) * D + c * 16);
-        b[i] = load8(t0 + i, (rot + hv) * D + c * 16 + 8);
+        for (int i = 0; i < 8; ++i) { s0[i] = 0.f; s1[i] = 0.f; }
+        const int64_t stride = (int64_t)T * NP;
+        for (int k = 0; k < splits; ++k) {
+          f32x2 v[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const f32x2*>(part + k * stride + (int64_t)(t0 + i) * NP + col);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) { s0[i] += v[i][0]; s1[i] += v[i][1]; }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { o0.h[i] = f32_to_bf16(s0[i]); o1.h[i] = f32_to_bf16(s1[i]); }
+      } else {
+        uint32_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const uint32_t*>(qkv + (int64_t)(t0 + i) * NP + col);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { o0.s[i] = (uint16_t)v[i]; o1.s[i] = (uint16_t)(v[i] >> 16); }
       }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        Pack16 oa, ob;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { oa.s[i] = a[i].s[e]; ob.s[i] = b[i].s[e]; }
-        *reinterpret_cast<u32x4*>(blk + v_elem_offset(slot, c * 16 + e, D)) = oa.u;
-        *reinterpret_cast<u32x4*>(blk + v_elem_offset(slot, c * 16 + 8 + e, D)) = ob.u;
-      }
+      *reinterpret_cast<u32x4*>(blk + v_elem_offset(slot & ~7, d, D)) = o0.u;
+      *reinterpret_cast<u32x4*>(blk + v_elem_offset(slot & ~7, d + 1, D)) = o1.u;
       return;
     }
     const Pack16 a = load8(t, (rot + hv) * D + c * 16), b = load8(t, (rot + hv) * D + c * 16 + 8);
@@ -306,18 +322,18 @@ hipError_t launch_rope_table(const int32_t* pos, const double* inv_freq, int T, 
 }
 
 hipError_t launch_rope_append(bf16_t* qkv, int T, int Hq, int Hkv, int D, const int32_t* pos, const int32_t* tok_page,
-                              const int32_t* tok_slot, const float* angles, bf16_t* kv_layer, const float* part,
-                              int splits, int NP, hipStream_t s) {
+                              const int32_t* tok_slot, const float* angles, bf16_t* kv_layer, bool by_octet,
+                              const float* part, int splits, int NP, hipStream_t s) {
   if (splits > 0 && (part == nullptr || NP < (Hq + 2 * Hkv) * D)) return hipErrorInvalidValue;
   if (splits <= 0) NP = (Hq + 2 * Hkv) * D;  // row length of the stored qkv
   // few tokens: one head per thread keeps enough threads in flight; many tokens: a thread walks several heads
   // with the same 8 angles
   const int hpt = T >= 1024 ? 8 : 1;
   const int groups = (Hq + Hkv + hpt - 1) / hpt;
-  int64_t total = (int64_t)T * (groups + Hkv) * (D / 16);
+  int64_t total = ((int64_t)T * groups + (int64_t)((T + 7) / 8 * 8) * Hkv) * (D / 16);
   if (total <= 0) return hipSuccess;
   rope_append_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(qkv, T, Hq, Hkv, D, pos, tok_page,
-                                                                                   tok_slot, angles, kv_layer, hpt,
+                                                                                   tok_slot, angles, kv_layer, hpt, by_octet,
                                                                                    part, splits, NP);
   return hipGetLastError();
 }

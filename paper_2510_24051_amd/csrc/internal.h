@@ -193,10 +193,11 @@ hipError_t launch_rmsnorm_embed(const bf16_t* embeds, const int32_t* ids, const 
 hipError_t launch_rmsnorm_f32(const float* x, const bf16_t* gain, bf16_t* out, int rows, int H, float eps,
                               hipStream_t s);
 // part/splits: when splits > 0 the q, k, v values are not read from qkv but summed from the split-K partials
-// [split][T][NP] of the QKV product (then rounded to bf16 as the epilogue would have stored them).
+// [split][T][NP] of the QKV product (then rounded to bf16 as the epilogue would have stored them).  by_octet: the batch
+// holds runs of consecutive tokens of one request (lane order of the value threads; no effect on the result).
 hipError_t launch_rope_append(bf16_t* qkv, int T, int Hq, int Hkv, int D, const int32_t* pos, const int32_t* tok_page,
-                              const int32_t* tok_slot, const float* angles, bf16_t* kv_layer, const float* part,
-                              int splits, int NP, hipStream_t s);
+                              const int32_t* tok_slot, const float* angles, bf16_t* kv_layer, bool by_octet,
+                              const float* part, int splits, int NP, hipStream_t s);
 // angles [T, D]: cos (first D/2) and sin (last D/2) of pos[t] * inv_freq[i], double precision rounded to float
 hipError_t launch_rope_table(const int32_t* pos, const double* inv_freq, int T, int D, float* angles, hipStream_t s);
 // Split-K epilogue of a residual projection fused with the RMSNorm that follows it: wide[m] = residual[m] + sum of

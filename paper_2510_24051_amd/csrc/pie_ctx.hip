@@ -1483,7 +1483,7 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   }
 
   tm.begin(PIE_STAGE_ROPE_APPEND);
-  HIP_TRY(c, launch_rope_append(c->qkv, T, Hq, Hkv, D, b->pos, b->tok_page, b->tok_slot, b->rope_angles, kv_layer,
+  HIP_TRY(c, launch_rope_append(c->qkv, T, Hq, Hkv, D, b->pos, b->tok_page, b->tok_slot, b->rope_angles, kv_layer, b->n_pitems > 0,
                                 c->splitk, qkv_splits, L.wqkv.NB * 32, s));
   tm.end(PIE_STAGE_ROPE_APPEND);
 

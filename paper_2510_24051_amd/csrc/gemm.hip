@@ -97,10 +97,10 @@ __device__ __forceinline__ void epi_tile(const EpiArgs& e, const f32x16& acc, co
 #define SK_BK 128  // contraction elements per main-loop iteration (8 MFMA steps)
 #define SK_MAX_SPLITS 8
 
-// WAVES: waves per workgroup.  KS: the contraction is split KS ways INSIDE the workgroup (unsplit gate/up at widths
-// that give too few waves otherwise): waves w and w + WAVES / KS own the same column block and each takes a K-th of
+// WAVES: waves per workgroup.  KS: the contraction is split KS ways INSIDE the workgroup (where the widths give too few
+// waves otherwise): waves w and w + WAVES / KS own the same column block and each takes a K-th of
 // the contraction, with an activation tile of its own per iteration; the sums meet through LDS at the end, so twice
-// as many waves stream weights and no partial sums leave the workgroup.
+// as many waves stream weights and no more partial sums leave the workgroup.
 template <int MB, int MODE, bool PARTIAL, int NBW, int WAVES = 4, int KS = 1>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const bf16_t* __restrict__ A, int lda, int M,
                                                           const bf16_t* __restrict__ Wp, int N, int NB, int K,
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const bf16_t* _
   constexpr bool SK_NT = MODE == EPI_STORE_BF16 || MODE == EPI_STORE_F32 || (PARTIAL && MODE == EPI_RESID_OUT);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   bf16_t* As = reinterpret_cast<bf16_t*>(smem_raw);  // [2][KS][MB*32][SK_BK], 16-byte chunks swizzled by row
-  static_assert(KS == 1 || (!PARTIAL && WAVES % KS == 0), "the in-workgroup split replaces the split across workgroups");
+  static_assert(WAVES % KS == 0, "every slice gets the same number of waves");
   constexpr int BM = MB * 32;
   constexpr int NT = WAVES * 64;
   constexpr int WPS = WAVES / KS;            // waves per K slice
@@ -122,11 +122,13 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const bf16_t* _
   const int ks = wave / WPS;                 // this wave's K slice
   const int KB = K / 16;
   const int total_iters = (K + SK_BK - 1) / SK_BK;
-  // With KS > 1 the host launches one workgroup per column group over the whole contraction, whose iteration count
-  // is a multiple of KS: slice s covers iterations s * it1 .. (s + 1) * it1 and `it` below counts within the slice.
-  const int it0 = KS > 1 ? 0 : blockIdx.y * iters_per_split;
-  const int it1 = KS > 1 ? total_iters / KS : min(total_iters, it0 + iters_per_split);
-  const int slice_it0 = KS > 1 ? ks * it1 : 0;  // first global iteration of this wave's slice
+  // This workgroup covers iterations first .. of the contraction; with KS > 1 their number is a multiple of KS (the host
+  // sees to it), slice s takes the s-th part of them and `it` below counts within the slice.
+  const int first = PARTIAL || KS == 1 ? blockIdx.y * iters_per_split : 0;
+  const int last = min(total_iters, first + iters_per_split);
+  const int it0 = KS > 1 ? 0 : first;
+  const int it1 = KS > 1 ? (last - first) / KS : last;
+  const int slice_it0 = KS > 1 ? first + ks * it1 : 0;  // added to `it`: the global iteration of this wave's slice
   // a wave owns NBW adjacent 32-column blocks (SWIGLU: a gate/up pair)
   int nb0 = (blockIdx.x * WPS + wave % WPS) * NBW;
   const bool wave_active = nb0 < NB;
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const bf16_t* _
       const int c = min(tid + j * NT, A_CHUNKS - 1);
       const int sl = c / (BM * 16), cc = c % (BM * 16);
       const int r = min(cc >> 4, M - 1), kc = cc & 15;
-      const int k = min(((KS > 1 ? sl * it1 : 0) + it) * SK_BK + kc * 8, K - 8);
+      const int k = min(((KS > 1 ? first + sl * it1 : 0) + it) * SK_BK + kc * 8, K - 8);
       areg[slot][j] = *reinterpret_cast<const u32x4*>(A + (int64_t)r * lda + k);
     }
   };
@@ -173,7 +175,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const bf16_t* _
       const int c = tid + j * NT;
       const int sl = c / (BM * 16), cc = c % (BM * 16);
       const int r = cc >> 4, kc = cc & 15;
-      const bool inside = r < M && ((KS > 1 ? sl * it1 : 0) + it) * SK_BK + kc * 8 < K;
+      const bool inside = r < M && ((KS > 1 ? first + sl * it1 : 0) + it) * SK_BK + kc * 8 < K;
       if (c < A_CHUNKS)
         *reinterpret_cast<u32x4*>(As + buf * A_ELEMS + sl * A_SLICE + r * SK_BK + ((kc ^ (r & 15)) << 3)) =
             inside ? areg[slot][j] : u32x4{0, 0, 0, 0};
@@ -237,29 +239,31 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const bf16_t* _
     if (it + 1 < it1) step(std::integral_constant<int, 1>{}, it + 1);
     if (it + 2 < it1) step(std::integral_constant<int, 2>{}, it + 2);
   }
-  if constexpr (!PARTIAL && MODE == EPI_SWIGLU && NBW == 1) {
-    // One block per wave: the gate block sits in the even waves, its up block in the wave after it, which hands
-    // its sums over through LDS (the activation stages are free once the main loop has passed its last barrier).
-    float* xch = reinterpret_cast<float*>(smem_raw);  // [WPS / 2 pairs][MB][16][64]
-    if constexpr (KS > 1) {
-      // the slices' sums first: slices 1.. leave theirs behind the exchange area, slice 0 adds them in slice order
-      float* red = xch + (WPS / 2) * MB * 16 * 64;  // [KS - 1][WPS][MB][16][64]
-      if (ks > 0) {
+  if constexpr (KS > 1) {
+    // The slices' sums meet through LDS (the activation stages are free once the main loop has passed its last
+    // barrier): slices 1.. leave theirs, slice 0 adds them in slice order.
+    static_assert(NBW == 1, "one column block per wave");
+    float* red = reinterpret_cast<float*>(smem_raw) + (MODE == EPI_SWIGLU ? (WPS / 2) * MB * 16 * 64 : 0);  // [KS - 1][WPS][MB][16][64]
+    if (ks > 0) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[((((ks - 1) * WPS + wave % WPS) * MB + i) * 16 + v) * 64 + lane] = acc[0][i][v];
+    }
+    __syncthreads();
+    if (ks == 0) {
+#pragma unroll
+      for (int sl = 1; sl < KS; ++sl)
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) red[((((ks - 1) * WPS + wave % WPS) * MB + i) * 16 + v) * 64 + lane] = acc[0][i][v];
-      }
-      __syncthreads();
-      if (ks == 0) {
-#pragma unroll
-        for (int sl = 1; sl < KS; ++sl)
-#pragma unroll
-          for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[0][i][v] += red[((((sl - 1) * WPS + wave) * MB + i) * 16 + v) * 64 + lane];
-      }
+          for (int v = 0; v < 16; ++v) acc[0][i][v] += red[((((sl - 1) * WPS + wave) * MB + i) * 16 + v) * 64 + lane];
     }
+  }
+  if constexpr (!PARTIAL && MODE == EPI_SWIGLU && NBW == 1) {
+    // One block per wave: the gate block sits in the even waves, its up block in the wave after it, which hands
+    // its sums over through LDS.
+    float* xch = reinterpret_cast<float*>(smem_raw);  // [WPS / 2 pairs][MB][16][64]
     const int pair = (wave % WPS) >> 1;
     if ((wave & 1) && ks == 0) {
 #pragma unroll
@@ -279,7 +283,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const bf16_t* _
     }
     return;
   }
-  if (!wave_active) return;
+  if (!wave_active || ks > 0) return;
   if (PARTIAL) {
     // raw partial sums: part[split][m][n_packed]
     float* P = part + (int64_t)blockIdx.y * M * (NB * 32);
@@ -976,9 +980,17 @@ static hipError_t run_skinny_n(const bf16_t* A, int lda, int M, const PackedWeig
   if (MODE == EPI_STORE_BF16)
     while (splits >= 4 && splits % 2 == 0 && wg_n * (splits / 2) * 4 >= n_cus * 3) splits /= 2;
   if (splits < 1) splits = 1;
+  // At most one workgroup of four waves per CU: eight waves, each column block's share of K cut in two slices that meet
+  // through LDS, put twice as many waves on the weight stream for the same partial sums (8B shape, one row: QKV 13.8 ->
+  // 12.1 us, O 7.9 -> 7.4, down 23.7 -> 20.5).  With two row blocks, or with more workgroups, it gains nothing or loses
+  // (70B shape, 16 rows: QKV 33 -> 40 us with 320 workgroups), and below 1024 inputs the extra barriers cost more.
+  if constexpr (MB == 1 && NBW == 1 && WAVES == 4 && KS == 1 && MODE != EPI_SWIGLU)
+    if (wg_n * splits <= n_cus && total_iters >= 8 && total_iters % 2 == 0 && W.K % SK_BK == 0)
+      return run_skinny_n<MB, MODE, 1, 8, 2>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer, max_splits);
   const int NP = W.NB * 32;
   while (splits > 1 && (size_t)splits * M * NP > ws_elems) --splits;
   int ips = (total_iters + splits - 1) / splits;
+  if (KS > 1) ips = (ips + KS - 1) / KS * KS;  // (the callers see to it that total_iters is a multiple of KS)
   splits = (total_iters + ips - 1) / ips;
   size_t smem = (size_t)2 * KS * MB * 32 * SK_BK * sizeof(bf16_t);
   dim3 grid(wg_n, splits), block(WAVES * 64);
@@ -990,8 +1002,7 @@ static hipError_t run_skinny_n(const bf16_t* A, int lda, int M, const PackedWeig
     kern<<<grid, block, smem, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, ips, epi, nullptr);
     return hipGetLastError();
   }
-  if constexpr (KS > 1) return hipErrorInvalidValue;  // (the in-workgroup split is launched unsplit only)
-  auto kern = gemm_skinny_kernel<MB, MODE, true, NBW, WAVES, 1>;
+  auto kern = gemm_skinny_kernel<MB, MODE, true, NBW, WAVES, KS>;
   static uint32_t lds_set_partial = 0;
   hipError_t e = set_lds_limit_once((const void*)kern, smem, lds_set_partial);
   if (e != hipSuccess) return e;

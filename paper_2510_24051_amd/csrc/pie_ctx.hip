@@ -176,6 +176,7 @@ static pie_status pie_create_impl(const pie_model_desc* m, const pie_pool_desc* 
     chk(hipStreamSynchronize(c->stream));
   }
   for (int i = 0; i < 2 * PIE_N_STAGES && e == hipSuccess; ++i) chk(hipEventCreate(&c->ev[i]));
+  if (e == hipSuccess) chk(hipEventCreateWithFlags(&c->blob_copied, hipEventDisableTiming));
   if (e != hipSuccess) {
     pie_status st = fail(nullptr, e == hipErrorOutOfMemory ? PIE_ENOMEM : PIE_EHIP, "pie_create: %s", hipGetErrorString(e));
     pie_destroy(c);
@@ -225,6 +226,7 @@ extern "C" pie_status pie_destroy(pie_ctx* c) {
   for (auto& blk : c->blob_pool) (void)hipFree(blk.first);
   if (c->host_blob) { if (c->host_blob_pinned) (void)hipHostFree(c->host_blob); else std::free(c->host_blob); }
   for (int i = 0; i < 2 * PIE_N_STAGES; ++i) if (c->ev[i]) (void)hipEventDestroy(c->ev[i]);
+  if (c->blob_copied) (void)hipEventDestroy(c->blob_copied);
   delete c;
   return PIE_OK;
 }
@@ -642,6 +644,11 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   std::vector<PrefillItem> pitems;
   const size_t n_mask_given = b->mask_indptr ? (size_t)b->mask_indptr[R] : 0;
   std::vector<uint32_t> extra_words;  // masks synthesised for requests that touch pages with token-level masks
+  {
+    const int32_t listed = std::max(0, std::min(b->page_indptr[R], 1 << 20));  // (not checked yet)
+    visit_phys.reserve(listed);
+    visit_logical.reserve(listed);
+  }
   int rows_cap = 0;
   int64_t kv_bytes = 0, kv_bytes_dec = 0, flops = 0;
   const int64_t page_bytes = (int64_t)Hkv * 2 * PAGE * D * 2;
@@ -765,12 +772,22 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
     lora_tile_ad.resize(lora_rows.size() / 32, ad);
   }
   if (b->page_indptr[R] < 0) return fail(c, PIE_EINVAL, "bad page_indptr");
-  if (validate) {
-    std::unordered_set<int64_t> seen;
-    seen.reserve((size_t)T * 2);
-    for (int t = 0; t < T; ++t)
-      if (!seen.insert((int64_t)tok_page[t] * PAGE + tok_slot[t]).second)
+  if (validate) {  // a stamp and a slot mask per pool block, kept in the context (no clearing, no hashing)
+    if (c->write_stamp.size() != (size_t)n_pool_blocks) {
+      c->write_stamp.assign(n_pool_blocks, 0u);
+      c->write_slots.assign(n_pool_blocks, 0);
+    }
+    if (++c->write_stamp_id == 0u) {  // wrapped: start over
+      std::fill(c->write_stamp.begin(), c->write_stamp.end(), 0u);
+      c->write_stamp_id = 1u;
+    }
+    for (int t = 0; t < T; ++t) {
+      uint16_t& slots = c->write_slots[tok_page[t]];  // page ids and slots were range-checked above
+      if (c->write_stamp[tok_page[t]] != c->write_stamp_id) { c->write_stamp[tok_page[t]] = c->write_stamp_id; slots = 0; }
+      if (slots & (1u << tok_slot[t]))
         return fail(c, PIE_ECONFLICT, "token %d writes (page %d, slot %d) that another token of the batch writes", t, tok_page[t], tok_slot[t]);
+      slots |= (uint16_t)(1u << tok_slot[t]);
+    }
   }
   // Decode path.  Query columns are gathered into column groups of up to 16 columns that walk the same pages:
   // the rows of one request, or of several requests whose page tables name the same physical page at the same
@@ -846,6 +863,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
       CGroup g;
       g.members.push_back(di);
       g.rows = q.n_new * G;
+      g.pages.reserve(skip ? 8 : q.n_visit);
       for (int v = 0; v < q.n_visit; ++v)
         if (!skip || visit_logical[q.visit0 + v] >= (int)skip->size() || !(*skip)[visit_logical[q.visit0 + v]])
           g.pages.push_back(make_int2(visit_phys[q.visit0 + v], visit_logical[q.visit0 + v]));
@@ -903,8 +921,9 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   std::vector<DecodeCol> dcols(cgroups.size() * 16, DecodeCol{-1, 0, 0, 0, 0, 0, 0});
   std::vector<DecodeSeg> dsegs;
   std::vector<DecodeWave> dwaves;
-  std::vector<int2> wave_pg;
-  std::vector<std::vector<int32_t>> mref_lists(dec_reqs.size() * Hkv);
+  std::vector<int2>& wave_pg = c->plan_wave_pg;
+  struct MRef { int32_t list, row; };  // list: decode request * Hkv + kv head
+  std::vector<MRef> mref_all;
   int dslots = 2;
   int64_t kv_bytes_req = 0;  // bytes the decode kernel asks for after grouping
   {
@@ -930,13 +949,14 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
     int64_t per_wave = (total_pairs + rounds * c->wave_slots - 1) / (rounds * c->wave_slots);
     per_wave = std::min<int64_t>(std::max<int64_t>(per_wave, 2), 64);
     dslots = (int)(2 * per_wave);
-    wave_pg.reserve((size_t)((total_pairs + per_wave - 1) / per_wave + 1) * dslots);
+    // every wave but the last holds per_wave pairs, so the lists follow one another without gaps
+    wave_pg.resize((size_t)((total_pairs + per_wave - 1) / per_wave) * dslots);
+    int2* wp_out = wave_pg.data();
     int filled = 0;
     DecodeWave cur{0, 0, 0, 0};
     auto close_wave = [&]() {
       cur.n_pairs = filled;
       dwaves.push_back(cur);
-      wave_pg.resize(dwaves.size() * (size_t)dslots, make_int2(-1, 0));
       cur = DecodeWave{(int32_t)dsegs.size(), 0, 0, 0};
       filled = 0;
     };
@@ -949,14 +969,11 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
         while (p < P) {
           const int take = (int)std::min<int64_t>(per_wave - filled, P - p);
           for (size_t mi = 0; mi < g.members.size(); ++mi)  // partial rows start at segment * rows_cap (set below)
-            mref_lists[(size_t)g.members[mi] * Hkv + hk].push_back((int32_t)(dsegs.size() * 16 + mi * g.rows));
+            mref_all.push_back(MRef{g.members[mi] * Hkv + hk, (int32_t)(dsegs.size() * 16 + mi * g.rows)});
           dsegs.push_back(DecodeSeg{(int32_t)gi, hk, take, 0});
           ++cur.n_seg;
-          for (int pr = p; pr < p + take; ++pr)
-            for (int e = 0; e < 2; ++e) {
-              const int v = 2 * pr + e;
-              wave_pg.push_back(v < n_pg ? make_int2(g.pages[v].x * Hkv + hk, g.pages[v].y) : make_int2(-1, 0));
-            }
+          for (int v = 2 * p; v < 2 * (p + take); ++v)
+            *wp_out++ = v < n_pg ? make_int2(g.pages[v].x * Hkv + hk, g.pages[v].y) : make_int2(-1, 0);
           p += take;
           filled += take;
           if (filled == per_wave) close_wave();
@@ -964,8 +981,12 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
       }
     }
     if (filled > 0) close_wave();
+    std::fill(wp_out, wave_pg.data() + wave_pg.size(), make_int2(-1, 0));  // the last wave's unused slots
     // the kernel trusts this plan: check what it assumes before anything is launched from it
-    const int64_t n_blocks = (int64_t)n_pool_blocks * Hkv;
+    if (wave_pg.size() != dwaves.size() * (size_t)dslots) return fail(c, PIE_EINVAL, "internal: inconsistent decode page lists");
+    for (const CGroup& g : cgroups)  // every entry of the lists is one of these pages times a kv head
+      for (const int2& pg : g.pages)
+        if (pg.x < 0 || pg.x >= n_pool_blocks || pg.y < 0) return fail(c, PIE_EINVAL, "internal: page %d of a decode plan", pg.x);
     for (size_t w = 0; w < dwaves.size(); ++w) {
       const DecodeWave& dw = dwaves[w];
       int pairs = 0;
@@ -976,10 +997,6 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
              dsegs[sg].hk >= 0 && dsegs[sg].hk < Hkv;
       }
       ok = ok && pairs == dw.n_pairs && dw.n_pairs > 0 && 2 * dw.n_pairs <= dslots;
-      for (int j = 0; ok && j < 2 * dw.n_pairs; ++j) {
-        const int2 e = wave_pg[w * dslots + j];
-        ok = (e.x >= 0 || (j & 1)) && e.x < n_blocks && e.y >= 0;
-      }
       if (!ok) return fail(c, PIE_EINVAL, "internal: inconsistent decode plan for wave %zu", w);
     }
     for (const DecodeCol& dc : dcols)
@@ -1039,7 +1056,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
         flat[x].push_back(PrefillItem{(int32_t)gi, 0, hk, parts, plen, (int32_t)n_sparts});
         for (size_t mi = 0; mi < g.members.size(); ++mi)  // partial rows behind the decode kernel's, marked by the sign
           for (int p = 0; p < parts; ++p)
-            mref_lists[(size_t)g.members[mi] * Hkv + hk].push_back(-1 - (int32_t)((n_sparts + p) * SHARED_COLS + mi * g.rows));
+            mref_all.push_back(MRef{g.members[mi] * Hkv + hk, -1 - (int32_t)((n_sparts + p) * SHARED_COLS + mi * g.rows)});
         n_sparts += parts;
       }
     }
@@ -1051,11 +1068,14 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   }
   // partial rows a (decode request, kv head) has to merge: segment * rows_cap + the request's first column, or the shared
   // groups' rows behind those
-  std::vector<int32_t> mref_indptr(dec_reqs.size() * Hkv + 1, 0), mrefs;
+  std::vector<int32_t> mref_indptr(dec_reqs.size() * Hkv + 1, 0), mrefs(mref_all.size());
   const int32_t shared_row0 = (int32_t)(dsegs.size() * rows_cap);
-  for (size_t i = 0; i < mref_lists.size(); ++i) {
-    for (int32_t v : mref_lists[i]) mrefs.push_back(v >= 0 ? (v / 16) * rows_cap + (v % 16) : shared_row0 + (-1 - v));
-    mref_indptr[i + 1] = (int32_t)mrefs.size();
+  for (const MRef& m : mref_all) ++mref_indptr[m.list + 1];
+  for (size_t i = 1; i < mref_indptr.size(); ++i) mref_indptr[i] += mref_indptr[i - 1];
+  {
+    std::vector<int32_t> at(mref_indptr.begin(), mref_indptr.end());  // filled in the order the parts were listed
+    for (const MRef& m : mref_all)
+      mrefs[at[m.list]++] = m.row >= 0 ? (m.row / 16) * rows_cap + (m.row % 16) : shared_row0 + (-1 - m.row);
   }
   bool dec_read_once = true;  // no page is in two column groups
   int dec_rows = 1;
@@ -1255,6 +1275,13 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
     pb->dec_read_once = dec_read_once;
   }
   pb->work[5] = kv_bytes_req;
+  if (c->blob_in_flight) {  // the previous batch's copy still reads the host image
+    c->blob_in_flight = false;
+    if (hipEventSynchronize(c->blob_copied) != hipSuccess) {
+      delete pb;
+      return fail(c, PIE_EHIP, "pie_batch_create: the previous batch's copy failed");
+    }
+  }
   Blob blob(c);
   const size_t o_in = blob.add(b->in_embed_ids, (size_t)T * 4), o_out = blob.add(b->out_embed_ids, (size_t)T * 4);
   const size_t o_pos = blob.add(b->positions ? b->positions : pos_from_embeds.data(), (size_t)T * 4), o_tp = blob.add(tok_page.data(), (size_t)T * 4);
@@ -1301,6 +1328,14 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
     return PIE_OK;
   }
   hipError_t e = hipSuccess;
+  {  // a captured copy would read the host image again at every replay, long after it has changed
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      delete pb;
+      return fail(c, PIE_EHIP, "pie_batch_create: the context's stream is being captured");
+    }
+  }
   {  // the smallest kept block that is large enough, else a new one (sizes in 1 MiB steps so that blocks get reused)
     int best = -1;
     for (int i = 0; i < (int)c->blob_pool.size(); ++i)
@@ -1328,12 +1363,15 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
     e = launch_rope_table(reinterpret_cast<const int32_t*>(reinterpret_cast<unsigned char*>(pb->dev_blob) + o_pos),
                           c->inv_freq, T, D, reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(pb->dev_blob) + o_an),
                           c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  // The host image is pinned and stays untouched until the copy has read it (blob_copied), so nothing waits here: the
+  // forward call is enqueued behind the copy while the copy still runs.  Pageable images are waited for.
+  if (e == hipSuccess) e = c->host_blob_pinned ? hipEventRecord(c->blob_copied, c->stream) : hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
     (void)hipFree(pb->dev_blob);
     delete pb;
     return fail(c, PIE_EHIP, "pie_batch_create: %s", hipGetErrorString(e));
   }
+  c->blob_in_flight = c->host_blob_pinned;
   unsigned char* d = reinterpret_cast<unsigned char*>(pb->dev_blob);
   pb->in_ids = (int32_t*)(d + o_in); pb->out_ids = (int32_t*)(d + o_out); pb->pos = (int32_t*)(d + o_pos);
   pb->tok_page = (int32_t*)(d + o_tp); pb->tok_slot = (int32_t*)(d + o_ts);

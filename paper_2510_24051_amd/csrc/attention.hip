@@ -574,19 +574,20 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
   const int hk = it.hk;
   const int qcol = lane & 31, g = lane >> 5, m = lane & 31;
   ReqInfo rq{};
-  int i_tok = 0, kv_len, lim, pair0, v_end;  // the lane's row: KV length and last key visible under the causal rule
+  int i_tok = 0, i_ld = 0, pair0, v_end;
+  [[maybe_unused]] int col_kv_len = 0, col_lim = 0;  // SHARED: the lane's column, KV length and last key visible under the causal rule
+  [[maybe_unused]] const uint32_t* col_mask = nullptr;
   bool valid, has_bitmap;
-  const uint32_t* mrow;
   bf16x8 qf[D / 16];
   if constexpr (SHARED) {
     const SharedGroup sg = sgroups[it.r];
     const int col = hg * 32 + qcol;
     valid = col < sg.n_cols;
     const DecodeCol cc = scols[sg.col0 + min(col, sg.n_cols - 1)];
-    kv_len = cc.kv_len;
-    lim = cc.lim;
+    col_kv_len = cc.kv_len;
+    col_lim = cc.lim;
+    col_mask = a.mask_words + cc.mask_row;
     has_bitmap = cc.wpr > 0;
-    mrow = a.mask_words + cc.mask_row;
     pair0 = sg.pair0;
     v_end = sg.n_pages;
     load_q<D>(a.q + (int64_t)cc.tok * a.q_stride + (hk * (a.Hq / a.Hkv) + cc.hg) * D, valid, g, qf);
@@ -594,15 +595,16 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
     rq = a.reqs[it.r];
     i_tok = it.qb * 32 + qcol;
     valid = i_tok < rq.n_new;
-    const int i_ld = valid ? i_tok : rq.n_new - 1;
-    kv_len = rq.kv_len;
-    lim = rq.kv_len - rq.n_new + i_ld;
+    i_ld = valid ? i_tok : rq.n_new - 1;
     // requests with a bitmap are always listed in the launch with pair weights (their rows may see few keys)
     has_bitmap = LO && rq.wpr > 0;
-    mrow = a.mask_words + rq.mask_off + (int64_t)i_ld * rq.wpr;
     pair0 = rq.pair0;
-    v_end = rq.n_visit;
     load_q<D>(a.q + (int64_t)(rq.tok0 + i_ld) * a.q_stride + (hk * G + hg) * D, valid, g, qf);
+  }
+  AttnState<D> st;
+  attn_init<D>(st);
+  if constexpr (!SHARED) {
+    v_end = rq.n_visit;
     if (!has_bitmap) {  // inferred causal: the visit list is pages 0.. in order; stop at the block's last visible key
       int i_last = it.qb * 32 + 31;
       i_last = i_last < rq.n_new ? i_last : rq.n_new - 1;
@@ -610,8 +612,6 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
       v_end = pages < v_end ? pages : v_end;
     }
   }
-  AttnState<D> st;
-  attn_init<D>(st);
   const int first_pair = SPLIT && it.n_parts > 1 ? blockIdx.y * it.per : 0;
   const int all_pairs = (v_end + 1) / 2;
   const int n_pairs = SPLIT && it.n_parts > 1 ? min(all_pairs - first_pair, it.per) : all_pairs;
@@ -633,6 +633,7 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
     const char* kv_hk = reinterpret_cast<const char*>(a.kv + (int64_t)hk * BLK);
     const int64_t page_stride_b = (int64_t)a.Hkv * BLK * 2;
     const uint32_t lane_off = lane * 16;
+    const uint32_t* mrow = SHARED ? col_mask : a.mask_words + rq.mask_off + (int64_t)i_ld * rq.wpr;
     struct Meta { int pl_a, pl_b; bool has_b, full; uint32_t mw_a, mw_b; };
     Meta m0{}, m1{}, m2{}, m3{};
     // Inferred-causal blocks of 32 real rows: the first n_full pairs lie entirely at or below the first row's
@@ -663,15 +664,15 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
     auto bits_of = [&](uint32_t word, int pl) -> uint32_t {
       if (!valid) return 0u;
       const int j0 = pl * PAGE + g * 8;
-      int cnt = kv_len - j0;
+      int cnt = (SHARED ? col_kv_len : rq.kv_len) - j0;
       cnt = cnt < 0 ? 0 : (cnt > 8 ? 8 : cnt);
       uint32_t bits = (1u << cnt) - 1u;
       if (has_bitmap) {
         bits &= (word >> ((pl & 1) * 16 + g * 8)) & 0xFFu;
       } else {
-        int c = lim - j0 + 1;
-        c = c < 0 ? 0 : (c > 8 ? 8 : c);
-        bits &= (1u << c) - 1u;
+        int lim = (SHARED ? col_lim : rq.kv_len - rq.n_new + i_ld) - j0 + 1;
+        lim = lim < 0 ? 0 : (lim > 8 ? 8 : lim);
+        bits &= (1u << lim) - 1u;
       }
       return bits;
     };

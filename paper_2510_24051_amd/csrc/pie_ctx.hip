@@ -151,7 +151,8 @@ static pie_status pie_create_impl(const pie_model_desc* m, const pie_pool_desc* 
   c->embed_pos.assign((size_t)p->n_embeds, -1);
   c->page_mask.assign((size_t)p->n_kv_pages * F, 0xFFFFu);
   chk(dev_alloc(&c->act, T * I, false, c->stream));
-  // split-K workspace: only batches of <= 256 rows use it; 8 partial copies of the widest output
+  // split-K workspace: 8 partial copies of the widest output at up to 256 rows; larger batches use as many splits of a
+  // product as fit
   {
     size_t rows = std::min<size_t>(std::max<size_t>(T, (size_t)p->max_dist_rows), 256);
     size_t widest = std::max<size_t>((size_t)2 * I, (size_t)round_up(std::max(QD + 2 * KD, H), 32));

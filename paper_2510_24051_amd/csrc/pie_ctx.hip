@@ -1277,11 +1277,12 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   }
   pb->work[5] = kv_bytes_req;
   if (c->blob_in_flight) {  // the previous batch's copy still reads the host image
-    c->blob_in_flight = false;
-    if (hipEventSynchronize(c->blob_copied) != hipSuccess) {
+    const hipError_t we = hipEventSynchronize(c->blob_copied);
+    if (we != hipSuccess) {  // (it may still be reading: the next call waits again)
       delete pb;
-      return fail(c, PIE_EHIP, "pie_batch_create: the previous batch's copy failed");
+      return fail(c, PIE_EHIP, "pie_batch_create: waiting for the previous batch's copy: %s", hipGetErrorString(we));
     }
+    c->blob_in_flight = false;
   }
   Blob blob(c);
   const size_t o_in = blob.add(b->in_embed_ids, (size_t)T * 4), o_out = blob.add(b->out_embed_ids, (size_t)T * 4);

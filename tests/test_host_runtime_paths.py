@@ -1,0 +1,122 @@
+"""Host paths around the batch's copy to the device, without a GPU: the library is loaded against a stand-in for the HIP
+runtime (fake_hip.cpp: late copies, failures on request) in a process of its own, one per test."""
+import os
+import subprocess
+import sys
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+MODEL = SimpleNamespace(hidden=128, n_q_heads=8, n_kv_heads=2, head_dim=64, mlp_dim=256, vocab=0, page_size=16, rms_eps=1e-5,
+                        rope_theta=1e4)
+
+
+def batch_of(reqs, first_page=0):
+    """(new, prior) per request, pages in order from `first_page`."""
+    tok = np.concatenate([[0], np.cumsum([n for n, _ in reqs])]).astype(np.int32)
+    per = [(n + p + 15) // 16 for n, p in reqs]
+    T = int(tok[-1])
+    return SimpleNamespace(
+        n_requests=len(reqs), n_tokens=T, tok_indptr=tok, in_embed_ids=np.arange(T), out_embed_ids=np.arange(T)[::-1],
+        positions=np.concatenate([np.arange(p, p + n) for n, p in reqs]), page_indptr=np.concatenate([[0], np.cumsum(per)]),
+        page_ids=first_page + np.arange(sum(per)), kv_len=np.array([n + p for n, p in reqs]), mask_indptr=None, mask_words=None,
+        adapter_ids=None)
+
+
+# ---- run in the child ------------------------------------------------------------------------
+class Child:
+    def __init__(self, fake):
+        import ctypes as C
+        import types
+        self.C, self.fake = C, C.CDLL(fake, mode=C.RTLD_GLOBAL)
+        for name, ret, args in (("fake_fail_new_at", None, [C.c_long]), ("fake_malloc_limit", None, [C.c_size_t]),
+                                ("fake_largest_malloc", C.c_size_t, []), ("fake_copy_size", C.c_size_t, [C.c_int]),
+                                ("fake_copy_data", C.c_void_p, [C.c_int])):
+            getattr(self.fake, name).restype, getattr(self.fake, name).argtypes = ret, args
+        sys.modules["torch"] = types.ModuleType("torch")  # (the binding keeps it for device tensors only)
+        sys.path.insert(0, ROOT)
+        from paper_2510_24051_amd import Pie, binding
+        self.Pie, self.binding, self.lib = Pie, binding, binding.load_library()
+
+    def context(self, n_pages=1024, tokens=256, requests=64):
+        b, C, m = self.binding, self.C, MODEL
+        p = self.Pie.__new__(self.Pie)
+        p.lib, p.device, p.stream, p.model, h = self.lib, None, None, m, C.c_void_p()
+        md = b.ModelDescC(m.hidden, m.n_q_heads, m.n_kv_heads, m.head_dim, m.mlp_dim, m.vocab, m.page_size, m.rms_eps, m.rope_theta, 1)
+        pd = b.PoolDescC(n_pages, 1024, tokens, requests, 0, 0, 0, 0)
+        assert self.lib.pie_create(C.byref(md), C.byref(pd), None, C.byref(h)) == 0
+        p.ctx = h
+        return p
+
+    def copies(self):
+        return [self.C.string_at(self.fake.fake_copy_data(i), self.fake.fake_copy_size(i)) for i in range(self.fake.fake_copies_done())]
+
+    def status(self, fn):
+        try:
+            fn()
+        except self.binding.PieError as e:
+            return e.status, str(e)
+        return 0, ""
+
+
+def failed_wait(c):
+    """A wait for the previous copy that fails leaves that copy in flight: the next call waits again before it writes."""
+    ctx = c.context()
+    a, b = batch_of([(1, 40), (20, 5)]), batch_of([(1, 90), (20, 33)], first_page=100)
+    ctx.batch_create(a)
+    ctx.synchronize()
+    want = c.copies()[-1]
+    n0 = len(c.copies())
+    pa = ctx.batch_create(a)
+    assert len(c.copies()) == n0  # still queued
+    c.fake.fake_fail_event_syncs(1)
+    assert c.status(lambda: ctx.batch_create(b))[0] == -6
+    pb = ctx.batch_create(b)
+    ctx.synchronize()
+    assert c.copies()[n0] == want, "the image of a queued copy was rewritten"
+    pa.destroy(), pb.destroy()
+
+
+def late_copies(c):
+    """Batches created one after another while every copy is still queued: each device block gets its own batch's image,
+    also where the image has to grow in between."""
+    ctx = c.context(n_pages=70000, tokens=64)
+    batches = [batch_of([(1, 40 + k), (20, 5)], first_page=64 * k) for k in range(5)] + [batch_of([(1, 16 * 10000)] * 6), batch_of([(3, 7)])]
+    want = []
+    for b in batches:
+        ctx.batch_create(b)
+        ctx.synchronize()
+        want.append(c.copies()[-1])
+    assert len(want[5]) > len(want[4]) * 4
+    c2 = c.context(n_pages=70000, tokens=64)  # (an image of its own, still small)
+    n0 = len(c.copies())
+    kept = [c2.batch_create(b) for b in batches]
+    assert len(c.copies()) < n0 + len(batches)
+    c2.synchronize()
+    assert c.copies()[n0:] == want
+    del kept
+
+
+CASES = {f.__name__: f for f in (failed_wait, late_copies)}
+
+if __name__ == "__main__":
+    CASES[sys.argv[2]](Child(sys.argv[1]))
+    print("case passed")
+    sys.exit(0)
+
+
+# ---- pytest ----------------------------------------------------------------------------------
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-w", "-o", so, os.path.join(HERE, "fake_hip.cpp")], check=True)
+    return so
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_host_path(fake, case):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, case], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "case passed" in r.stdout, f"exit {r.returncode}\n{r.stdout}\n{r.stderr}"

@@ -183,6 +183,9 @@ typedef struct {
  * write-conflict check), derive the attention work lists (pages with no visible key are
  * dropped, so cost follows the mask and not the context length), and copy everything the
  * kernels need to the device.  Allocates device memory owned by the returned pie_batch.
+ * The arrays of `batch` have been read when the call returns.  The copy to the device and the batch's
+ * rotary table are enqueued on the context's stream and not waited for, so an error of theirs shows in a
+ * later call.  Refused with PIE_EHIP while that stream is being captured, without ending the capture.
  * Errors: PIE_EINVAL, PIE_ERANGE, PIE_EBATCH, PIE_ECONFLICT, PIE_ENOMEM, PIE_EHIP. */
 pie_status pie_batch_create(pie_ctx* ctx, const pie_forward_batch* batch, int32_t validate, pie_batch** out);
 pie_status pie_batch_destroy(pie_ctx* ctx, pie_batch* batch);

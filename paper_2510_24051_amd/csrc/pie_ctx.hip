@@ -1276,6 +1276,15 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
     pb->dec_read_once = dec_read_once;
   }
   pb->work[5] = kv_bytes_req;
+  if (!c->host_only) {  // a captured copy would read the host image again at every replay, long after it has changed; refused
+                        // before anything else is asked of the runtime, as a wait or an allocation would end the capture
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      delete pb;
+      return fail(c, PIE_EHIP, "pie_batch_create: the context's stream is being captured");
+    }
+  }
   if (c->blob_in_flight) {  // the previous batch's copy still reads the host image
     const hipError_t we = hipEventSynchronize(c->blob_copied);
     if (we != hipSuccess) {  // (it may still be reading: the next call waits again)
@@ -1330,14 +1339,6 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
     return PIE_OK;
   }
   hipError_t e = hipSuccess;
-  {  // a captured copy would read the host image again at every replay, long after it has changed
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      delete pb;
-      return fail(c, PIE_EHIP, "pie_batch_create: the context's stream is being captured");
-    }
-  }
   {  // the smallest kept block that is large enough, else a new one (sizes in 1 MiB steps so that blocks get reused)
     int best = -1;
     for (int i = 0; i < (int)c->blob_pool.size(); ++i)

@@ -15,7 +15,7 @@ std::vector<std::vector<char>> done;  // what each copy read, in order
 size_t n_done = 0;
 struct Event { size_t upto; };
 size_t malloc_limit = ~(size_t)0, largest_malloc = 0;
-int capturing = 0, event_syncs = 0, fail_event_syncs = 0;
+int capturing = 0, event_syncs = 0, fail_event_syncs = 0, allocations = 0;
 long news = 0, fail_new_at = 0;
 
 void drain(size_t upto) {
@@ -51,6 +51,7 @@ size_t fake_largest_malloc() { const size_t n = largest_malloc; largest_malloc =
 void fake_capturing(int on) { capturing = on; }
 void fake_fail_event_syncs(int n) { fail_event_syncs = n; }
 int fake_event_syncs() { return event_syncs; }
+int fake_allocations() { return allocations; }  // calls that allocate or free, device or pinned
 int fake_copies_done() { return (int)done.size(); }
 size_t fake_copy_size(int i) { return done[i].size(); }
 const char* fake_copy_data(int i) { return done[i].data(); }
@@ -76,15 +77,16 @@ const char* hipGetErrorString(int) { return "an error of the stand-in runtime"; 
 int hipGetLastError() { return SUCCESS; }
 int hipGetSymbolAddress(void** p, const void*) { static char array[1 << 24]; *p = array; return SUCCESS; }
 int hipMalloc(void** p, size_t n) {
+  ++allocations;
   *p = nullptr;
   if (n > largest_malloc) largest_malloc = n;
   if (n > malloc_limit) return OUT_OF_MEMORY;
   *p = malloc(n ? n : 1);
   return *p ? SUCCESS : OUT_OF_MEMORY;
 }
-int hipFree(void* p) { drain(pending.size()); free(p); return SUCCESS; }  // (waits for the device)
-int hipHostMalloc(void** p, size_t n, unsigned) { *p = malloc(n); return *p ? SUCCESS : OUT_OF_MEMORY; }
-int hipHostFree(void* p) { drain(pending.size()); free(p); return SUCCESS; }
+int hipFree(void* p) { ++allocations; drain(pending.size()); free(p); return SUCCESS; }  // (waits for the device)
+int hipHostMalloc(void** p, size_t n, unsigned) { ++allocations; *p = malloc(n); return *p ? SUCCESS : OUT_OF_MEMORY; }
+int hipHostFree(void* p) { ++allocations; drain(pending.size()); free(p); return SUCCESS; }
 int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*) { pending.push_back(Copy{d, s, n}); return SUCCESS; }
 int hipMemcpy2DAsync(void*, size_t, const void*, size_t, size_t, size_t, int, void*) { return SUCCESS; }
 int hipMemsetAsync(void*, int, size_t, void*) { return SUCCESS; }

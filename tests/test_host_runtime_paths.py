@@ -100,7 +100,26 @@ def late_copies(c):
     del kept
 
 
-CASES = {f.__name__: f for f in (failed_wait, late_copies)}
+def captured_stream(c):
+    """A call while the stream is captured is refused before the runtime is asked for anything else (a wait or an allocation
+    would end the capture), and the context goes on as before."""
+    ctx = c.context()
+    a, big = batch_of([(1, 40)]), batch_of([(1, 16000)], first_page=8)
+    pa = ctx.batch_create(a)  # its copy stays queued
+    c.fake.fake_capturing(1)
+    calls = c.fake.fake_event_syncs(), c.fake.fake_allocations()
+    for b in (a, big):
+        st, msg = c.status(lambda: ctx.batch_create(b))
+        assert st == -6 and "captured" in msg, (st, msg)
+    st, msg = c.status(lambda: ctx.batch_create(batch_of([(1, 16 * 2000)])))  # what is wrong with a batch is said first
+    assert st == -2
+    assert calls == (c.fake.fake_event_syncs(), c.fake.fake_allocations())
+    c.fake.fake_capturing(0)
+    ctx.batch_create(big).destroy()
+    pa.destroy()
+
+
+CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream)}
 
 if __name__ == "__main__":
     CASES[sys.argv[2]](Child(sys.argv[1]))

@@ -174,8 +174,8 @@ struct pie_ctx {
   hipEvent_t blob_copied = nullptr;  // recorded behind the copy of the host image; waited for before the image is rewritten
   bool blob_in_flight = false;
   std::vector<int2> plan_wave_pg;      // scratch of the batch plan, kept so that its pages stay mapped from batch to batch
-  std::vector<uint32_t> write_stamp;   // host: per pool block, the last batch that wrote a token of it, and which slots
-  std::vector<uint16_t> write_slots;   //   (write-conflict check)
+  struct WriteMark { uint32_t stamp; uint16_t slots; };
+  std::vector<WriteMark> write_marks;  // host: per pool block, the last batch that wrote a token of it, and which slots
   uint32_t write_stamp_id = 0;
   std::vector<uint32_t> page_stamp;  // host: per pool page, the last batch plan that counted it (distinct-page statistic)
   uint32_t page_stamp_id = 0;

@@ -774,20 +774,17 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   }
   if (b->page_indptr[R] < 0) return fail(c, PIE_EINVAL, "bad page_indptr");
   if (validate) {  // a stamp and a slot mask per pool block, kept in the context (no clearing, no hashing)
-    if (c->write_stamp.size() != (size_t)n_pool_blocks) {
-      c->write_stamp.assign(n_pool_blocks, 0u);
-      c->write_slots.assign(n_pool_blocks, 0);
-    }
+    if (c->write_marks.empty()) c->write_marks.assign(n_pool_blocks, pie_ctx::WriteMark{0u, 0});
     if (++c->write_stamp_id == 0u) {  // wrapped: start over
-      std::fill(c->write_stamp.begin(), c->write_stamp.end(), 0u);
+      std::fill(c->write_marks.begin(), c->write_marks.end(), pie_ctx::WriteMark{0u, 0});
       c->write_stamp_id = 1u;
     }
     for (int t = 0; t < T; ++t) {
-      uint16_t& slots = c->write_slots[tok_page[t]];  // page ids and slots were range-checked above
-      if (c->write_stamp[tok_page[t]] != c->write_stamp_id) { c->write_stamp[tok_page[t]] = c->write_stamp_id; slots = 0; }
-      if (slots & (1u << tok_slot[t]))
+      pie_ctx::WriteMark& w = c->write_marks[tok_page[t]];  // page ids and slots were range-checked above
+      if (w.stamp != c->write_stamp_id) w = pie_ctx::WriteMark{c->write_stamp_id, 0};
+      if (w.slots & (1u << tok_slot[t]))
         return fail(c, PIE_ECONFLICT, "token %d writes (page %d, slot %d) that another token of the batch writes", t, tok_page[t], tok_slot[t]);
-      slots |= (uint16_t)(1u << tok_slot[t]);
+      w.slots |= (uint16_t)(1u << tok_slot[t]);
     }
   }
   // Decode path.  Query columns are gathered into column groups of up to 16 columns that walk the same pages:

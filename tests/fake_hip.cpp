@@ -9,9 +9,20 @@
 
 namespace {
 enum { SUCCESS = 0, OUT_OF_MEMORY = 2, CAPTURE_UNSUPPORTED = 900, UNKNOWN = 999 };
+template <class T>
+struct Plain {  // the stand-in's own memory is not counted among the library's allocations
+  typedef T value_type;
+  Plain() {}
+  template <class U> Plain(const Plain<U>&) {}
+  T* allocate(size_t n) { return (T*)malloc(n * sizeof(T)); }
+  void deallocate(T* p, size_t) { free(p); }
+  bool operator==(const Plain&) const { return true; }
+  bool operator!=(const Plain&) const { return false; }
+};
 struct Copy { void* dst; const void* src; size_t n; };
-std::vector<Copy> pending;
-std::vector<std::vector<char>> done;  // what each copy read, in order
+typedef std::vector<char, Plain<char>> Bytes;
+std::vector<Copy, Plain<Copy>> pending;
+std::vector<Bytes, Plain<Bytes>> done;  // what each copy read, in order
 size_t n_done = 0;
 struct Event { size_t upto; };
 size_t malloc_limit = ~(size_t)0, largest_malloc = 0;
@@ -96,9 +107,9 @@ int hipStreamSynchronize(void*) {
   return SUCCESS;
 }
 int hipStreamIsCapturing(void*, int* status) { *status = capturing; return SUCCESS; }
-int hipEventCreate(void** e) { *e = new Event{0}; return SUCCESS; }
+int hipEventCreate(void** e) { *e = calloc(1, sizeof(Event)); return SUCCESS; }
 int hipEventCreateWithFlags(void** e, unsigned) { return hipEventCreate(e); }
-int hipEventDestroy(void* e) { delete (Event*)e; return SUCCESS; }
+int hipEventDestroy(void* e) { free(e); return SUCCESS; }
 int hipEventRecord(void* e, void*) { ((Event*)e)->upto = pending.size(); return SUCCESS; }
 int hipEventElapsedTime(float* ms, void*, void*) { *ms = 0.f; return SUCCESS; }
 int hipEventSynchronize(void* e) {

@@ -119,7 +119,34 @@ def captured_stream(c):
     pa.destroy()
 
 
-CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream)}
+def failed_allocations(c):
+    """Each C++ allocation of a first call in turn fails: the call reports it, and the next one makes the same batch."""
+    b = batch_of([(1, 40), (2, 700), (20, 5), (1, 90)])
+    first = c.context()
+    pb = first.batch_create(b)
+    want = pb.work(), pb.plan_info(), pb.prefill_work().tolist()
+    failed = 0
+    for k in range(1, 10000):
+        ctx = c.context()
+        c.fake.fake_fail_new_at(k)
+        made = []
+        st, _ = c.status(lambda: made.append(ctx.batch_create(b)))
+        hit = c.fake.fake_new_failed()
+        c.fake.fake_fail_new_at(0)
+        for pb in made:
+            pb.destroy()
+        assert (st == -5) if hit else (st == 0), (k, st, hit)
+        pb = ctx.batch_create(b)
+        assert (pb.work(), pb.plan_info(), pb.prefill_work().tolist()) == want, k
+        pb.destroy()
+        ctx.close()
+        if not hit:
+            break
+        failed += 1
+    assert 20 < failed < 5000, failed
+
+
+CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations)}
 
 if __name__ == "__main__":
     CASES[sys.argv[2]](Child(sys.argv[1]))

@@ -19,6 +19,7 @@ static char g_create_err[512] = "";
 #define PIE_STATIC_SCRATCH_BYTES (16u << 20)
 #define PIE_STATIC_DIST_ROWS 32
 #define PIE_MAX_DEVICES 64
+#define KEPT_BATCH_BLOCKS 8  // device blocks of destroyed batches a context keeps for the next ones
 #define SHARED_MIN_SAVED ((int64_t)160 << 20)  // bytes of requests shared groups have to save (see pie_batch_create_impl)
 static __device__ __align__(256) unsigned char pie_static_scratch[PIE_STATIC_SCRATCH_BYTES];
 static void* g_static_scratch[PIE_MAX_DEVICES] = {nullptr};
@@ -112,6 +113,7 @@ static pie_status pie_create_impl(const pie_model_desc* m, const pie_pool_desc* 
     *out = c;
     return PIE_OK;
   }
+  c->blob_pool.reserve(KEPT_BATCH_BLOCKS);  // (pie_batch_destroy adds to it and must not throw)
   hipError_t e = hipGetDevice(&c->device);
   if (e == hipSuccess && c->device >= 0 && c->device < PIE_MAX_DEVICES) {
     // this GPU's copy of the static scratch array (the context's device is current here)
@@ -1402,8 +1404,7 @@ extern "C" pie_status pie_batch_destroy(pie_ctx* c, pie_batch* b) {
   if (c != b->owner) return fail(c, PIE_EINVAL, "pie_batch_destroy: the batch belongs to another context");
   if (c && !c->host_only) (void)hipStreamSynchronize(c->stream);  // no kernel may still read the batch
   if (b->dev_blob) {
-    constexpr size_t POOL_BLOCKS = 8;
-    if (c && c->blob_pool.size() < POOL_BLOCKS) c->blob_pool.emplace_back(b->dev_blob, b->dev_blob_bytes);
+    if (c->blob_pool.size() < KEPT_BATCH_BLOCKS) c->blob_pool.emplace_back(b->dev_blob, b->dev_blob_bytes);
     else (void)hipFree(b->dev_blob);
   }
   delete b;

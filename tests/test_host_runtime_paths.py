@@ -146,7 +146,20 @@ def failed_allocations(c):
     assert 20 < failed < 5000, failed
 
 
-CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations)}
+def failed_allocation_in_destroy(c):
+    """pie_batch_destroy keeps device blocks for the next batch; it has no use for host memory to do so."""
+    for n in (1, 12):  # fewer and more batches than blocks are kept
+        ctx = c.context()
+        pbs = [ctx.batch_create(batch_of([(1, 40)])) for _ in range(n)]
+        for pb in pbs:
+            c.fake.fake_fail_new_at(1)
+            pb.destroy()
+            c.fake.fake_fail_new_at(0)
+        ctx.batch_create(batch_of([(1, 40)])).destroy()
+        ctx.close()
+
+
+CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy)}
 
 if __name__ == "__main__":
     CASES[sys.argv[2]](Child(sys.argv[1]))

@@ -20,7 +20,6 @@ static char g_create_err[512] = "";
 #define PIE_STATIC_DIST_ROWS 32
 #define PIE_MAX_DEVICES 64
 #define KEPT_BATCH_BLOCKS 8  // device blocks of destroyed batches a context keeps for the next ones
-#define SHARED_MIN_SAVED ((int64_t)160 << 20)  // bytes of requests shared groups have to save (see pie_batch_create_impl)
 static __device__ __align__(256) unsigned char pie_static_scratch[PIE_STATIC_SCRATCH_BYTES];
 static void* g_static_scratch[PIE_MAX_DEVICES] = {nullptr};
 
@@ -817,46 +816,71 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
       if (ins.second) classes.emplace_back();
       classes[ins.first->second].push_back((int)di);
     }
-    // Pages (of the first `common`) on which every member's table names one physical page, visited by at least one.
-    auto shared_pages = [&](const std::vector<int>& cls, size_t c0, size_t c1, const std::vector<char>* skip) {
+    // Pages (of the first `common`) on which every member's table names one physical page, with the number of column
+    // groups of `small` members that visit it; 0 elsewhere and on pages to skip.
+    std::vector<char> skipped, visited;
+    auto shared_pages = [&](const std::vector<int>& cls, size_t c0, size_t c1, size_t small, const std::vector<char>* skip) {
       int common = INT32_MAX;
       for (size_t k = c0; k < c1; ++k) common = std::min(common, (reqs[dec_reqs[cls[k]]].kv_len + PAGE - 1) / PAGE);
-      std::vector<char> shared(common, 1), visited(common, 0);
+      std::vector<char> groups(common, 0);
+      skipped.assign(common, 0);
+      if (skip) std::copy(skip->begin(), skip->begin() + std::min<size_t>(skip->size(), common), skipped.begin());
+      visited.assign(common, 0);  // by the current column group
       const int32_t* pg0 = b->page_ids + b->page_indptr[dec_reqs[cls[c0]]];
       for (size_t k = c0; k < c1; ++k) {
         const ReqInfo& q = reqs[dec_reqs[cls[k]]];
         const int32_t* pg = b->page_ids + b->page_indptr[dec_reqs[cls[k]]];
-        for (int pgi = 0; pgi < common; ++pgi) if (pg[pgi] != pg0[pgi]) shared[pgi] = 0;
-        for (int v = 0; v < q.n_visit; ++v)
-          if (visit_logical[q.visit0 + v] < common) visited[visit_logical[q.visit0 + v]] = 1;
+        char* __restrict__ off = skipped.data();
+        char* __restrict__ seen = visited.data();
+        char* __restrict__ n_groups = groups.data();
+        for (int pgi = 0; pgi < common; ++pgi) off[pgi] |= pg[pgi] != pg0[pgi];
+        const int32_t* logical = visit_logical.data() + q.visit0;
+        for (int v = 0; v < q.n_visit && logical[v] < common; ++v) seen[logical[v]] = 1;  // (ascending)
+        if ((k - c0) % small == small - 1 || k == c1 - 1)
+          for (int pgi = 0; pgi < common; ++pgi) { n_groups[pgi] += seen[pgi]; seen[pgi] = 0; }
       }
-      for (int pgi = 0; pgi < common; ++pgi)
-        shared[pgi] = shared[pgi] && visited[pgi] && !(skip && pgi < (int)skip->size() && (*skip)[pgi]);
-      return shared;
+      for (int pgi = 0; pgi < common; ++pgi) if (skipped[pgi]) groups[pgi] = 0;
+      return groups;
     };
-    // Shared groups (attn_prefill_kernel<SHARED>): up to 128 columns of one class over the pages all of them share; what
-    // they don't all share is left to the column groups below.  They take a launch of their own and fp32 parts to merge,
-    // against about 10 TB/s at which the decode kernel re-reads shared blocks out of the caches for every 16 columns:
-    // used when they save the decode kernel 160 MB of requests.  Measured (8B shape, kernels of the attention stage
-    // together, without -> with): 32 branches on 4096 tokens, 117 MB saved, 31 -> 31 us; 64, 235 MB, 50 -> 35; 128,
-    // 470 MB, 77 -> 51; 256, 940 MB, 125 -> 75; 256 branches on 1024 tokens, 235 MB, 63 -> 48.
-    std::vector<std::vector<std::vector<char>>> taken(classes.size());  // per class and 128-column chunk: pages taken
-    {
-      int64_t saved = 0;
+    // Shared groups (attn_prefill_kernel<SHARED>): up to 128 columns of one class (a chunk) over pages all of them share;
+    // the rest is left to the column groups below, and so are pages that fewer than two of the chunk's column groups visit.
+    // Weighed in microseconds:
+    //   saved    the column groups' requests for the pages taken, each group's own visits counted, at the rate at which
+    //            the decode kernel re-reads shared blocks out of the caches (6 to 10 TB/s, by how far apart the reads are)
+    //   spent    the same pages once per chunk at the rate of the wide walk, which does the work of all 128 columns whoever
+    //            sees the page; a chunk's partial rows; once, the launch and the start of the walk
+    // Measured (8B shape, whole layer, without -> with): 32 branches on 4096 tokens 139 -> 140 us; 48, 152 -> 145; 64,
+    // 168 -> 151; 256, 314 -> 267; 256 on 1024 tokens, 249 -> 243.  256 branches with bitmaps of their own over a prefix of
+    // 1024 pages, 24 pages seen by each, 285 -> 295; 40, 310 -> 314; 64, 377 -> 335; 8 of 2048 pages, 243 -> 260.
+    std::vector<std::vector<std::vector<char>>> taken(classes.size());  // per class and chunk: pages taken
+    if (may_split) {
+      const double saved_us = page_bytes / 7.5e6, spent_us = page_bytes / 4.4e6;  // one request, one page of a chunk
+      const double chunk_us = 0.3, launch_us = 16.0;
+      double gain = -launch_us;
       for (size_t ci = 0; ci < classes.size(); ++ci) {
         const auto& cls = classes[ci];
         const int rows = reqs[dec_reqs[cls[0]]].n_new * G;
         const size_t small = 16 / rows, big = SHARED_COLS / rows;
         if (cls.size() <= small) continue;
+        bool any = false;
         for (size_t c0 = 0; c0 < cls.size(); c0 += big) {
           const size_t c1 = std::min(cls.size(), c0 + big);
           std::vector<char> sh;
-          if (c1 - c0 > small) sh = shared_pages(cls, c0, c1, nullptr);
-          saved += (int64_t)((c1 - c0 + small - 1) / small - 1) * std::count(sh.begin(), sh.end(), 1) * page_bytes;
+          if (c1 - c0 > small) {
+            sh = shared_pages(cls, c0, c1, small, nullptr);
+            int64_t requests = 0, pages = 0;
+            for (char& n_groups : sh) {
+              if (n_groups >= 2) { requests += n_groups; ++pages; }
+              n_groups = n_groups >= 2;
+            }
+            const double g = requests * saved_us - pages * spent_us - chunk_us;
+            if (g > 0) { gain += g; any = true; } else sh.clear();
+          }
           taken[ci].push_back(std::move(sh));
         }
+        if (!any) taken[ci].clear();
       }
-      if (!may_split || saved < SHARED_MIN_SAVED) taken.assign(classes.size(), {});
+      if (gain <= 0) taken.assign(classes.size(), {});
     }
     auto single = [&](int di, const std::vector<char>* skip) {
       const ReqInfo& q = reqs[dec_reqs[di]];
@@ -893,7 +917,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
         for (size_t c0 = b0; c0 < b1; c0 += cap) {
           const size_t c1 = std::min(b1, c0 + cap);
           if (c1 - c0 < 2) { single(cls[c0], gone); continue; }
-          const std::vector<char> shared = shared_pages(cls, c0, c1, gone);
+          const std::vector<char> shared = shared_pages(cls, c0, c1, cap, gone);
           CGroup g;
           g.rows = rows;
           const int32_t* pg0 = b->page_ids + b->page_indptr[dec_reqs[cls[c0]]];

@@ -1,6 +1,9 @@
 """Host logic of the library without a GPU: batch deserialisation, its error codes and the attention launch plan,
 through a planner context (pie_create_planner makes no HIP call)."""
+import collections
 import copy
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 
@@ -375,3 +378,82 @@ def test_prefill_requests_over_a_shared_prefix_share_an_xcd():
         assert changes == len(set(seq)) - 1
     pb.destroy()
     ctx.close()
+
+
+def prefix_batch(families, page=16):
+    """Decode requests of one token in families (shared pages, private tokens, [pages seen by each] or None = all of them);
+    the arrays alone, as the planner needs no K/V."""
+    tables, words, ptr, kv, free = [], [], [0], [], 0
+    for n_shared, private, seen in families:
+        prefix = np.arange(free, free + n_shared)
+        free += n_shared
+        for s in seen:
+            L = n_shared * page + private
+            own = (private + page - 1) // page
+            tables.append(np.concatenate([prefix, np.arange(free, free + own)]))
+            free += own
+            kv.append(L)
+            if s is not None:
+                m = np.zeros((L + 31) // 32 * 32, np.uint8)
+                for p in s:
+                    m[p * page:(p + 1) * page] = 1
+                m[n_shared * page:L] = 1
+                words.append(np.packbits(m, bitorder="little").view(np.uint32))
+                ptr.append(ptr[-1] + len(words[-1]))
+            else:
+                ptr.append(ptr[-1])
+    R = len(tables)
+    return SimpleNamespace(
+        n_requests=R, n_tokens=R, tok_indptr=np.arange(R + 1), in_embed_ids=np.arange(R), out_embed_ids=np.full(R, -1),
+        positions=np.array(kv) - 1, page_indptr=np.concatenate([[0], np.cumsum([len(t) for t in tables])]),
+        page_ids=np.concatenate(tables), kv_len=np.array(kv), mask_indptr=np.array(ptr, np.int64),
+        mask_words=np.concatenate(words) if words else np.zeros(1, np.uint32)), free
+
+
+def requested_pages(families, columns_per_request, chunks, page=16):
+    """Pages asked for by column groups of 16 columns, or, for the families named in `chunks`, by wide groups of 128 on the
+    pages at least two of their column groups visit."""
+    total = 0
+    for f, (n_shared, private, seen) in enumerate(families):
+        small, big = 16 // columns_per_request, 128 // columns_per_request
+        sets = [set(range(n_shared)) if s is None else set(int(p) for p in s) for s in seen]
+        total += len(seen) * ((private + page - 1) // page)
+        for c0 in range(0, len(sets), big):
+            groups = [sets[k:k + small] for k in range(c0, min(c0 + big, len(sets)), small)]
+            visits = collections.Counter(p for g in groups for p in set().union(*g))
+            taken = {p for p, n in visits.items() if n >= 2} if f in chunks else set()
+            total += len(taken)
+            for g in groups:  # (a single page left to share is not shared)
+                rest = set().union(*g) - taken
+                total += len(rest) if len(rest) > 1 else sum(len(s & rest) for s in g)
+    return total
+
+
+def sparse(rng, n, pages, seen):
+    return [rng.choice(pages, size=seen, replace=False) for _ in range(n)]
+
+
+@pytest.mark.parametrize("name,families,wide", [
+    # the whole prefix, seen by all
+    ("dense tree", [(256, 40, [None] * 256)], {0}),
+    ("a few dense branches", [(256, 40, [None] * 24)], set()),
+    # every branch sees pages of its own: the column groups ask for hardly more than a wide group would
+    ("8 pages of 2048", [(2048, 40, sparse(np.random.default_rng(1), 256, 2048, 8))], set()),
+    ("10 pages of 1024", [(1024, 40, sparse(np.random.default_rng(2), 256, 1024, 10))], set()),
+    ("20 pages of 2048, half the branches", [(2048, 17, sparse(np.random.default_rng(3), 128, 2048, 20))], set()),
+    # ... and where they overlap: pages one column group visits stay with it
+    ("100 pages of 1024", [(1024, 40, sparse(np.random.default_rng(4), 256, 1024, 100))], {0}),
+    # a family that shares one page gains nothing from another family's tree
+    ("one page beside a tree", [(256, 40, [None] * 256), (1, 40, [None] * 64)], {0}),
+])
+def test_wide_groups_are_formed_where_they_save_requests(name, families, wide):
+    """The bytes asked for show which families are walked by wide groups: cost follows the masks, and wide groups are not
+    formed over a union of masks that hardly overlap."""
+    m = small_model(128, 32, 8)
+    b, n_pages = prefix_batch(families)
+    ctx = Pie.planner(m, n_pages, b.n_tokens, max_batch_tokens=b.n_tokens, max_batch_requests=b.n_requests)
+    work = ctx.batch_create(b).work()
+    page_bytes = m.n_kv_heads * 2 * 16 * m.head_dim * 2
+    assert work["kv_bytes_requested"] == requested_pages(families, 4, wide) * page_bytes
+    if not wide:
+        assert requested_pages(families, 4, wide) > requested_pages(families, 4, {0})  # (the two would differ)

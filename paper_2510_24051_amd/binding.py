@@ -93,6 +93,7 @@ def load_library():
         "pie_batch_work": [vp, vp],
         "pie_batch_plan_info": [vp, vp],
         "pie_batch_prefill_work": [vp, vp, i32, vp],
+        "pie_product_plan": [i32, i32, i32, i64, i32, vp],
         "pie_create_planner": [C.POINTER(ModelDescC), C.POINTER(PoolDescC), i32, C.POINTER(vp)],
     }
     for name, args in sigs.items():
@@ -103,6 +104,15 @@ def load_library():
     lib.pie_last_error.restype = C.c_char_p
     _lib = lib
     return lib
+
+
+def product_plan(rows: int, n_out: int, k: int, workspace_floats: int, n_cus: int = 256) -> dict:
+    """pie_product_plan: how a product would be cut into tiles."""
+    out = np.zeros(4, dtype=np.int64)
+    st = load_library().pie_product_plan(rows, n_out, k, workspace_floats, n_cus, _ptr(out))
+    if st != 0:
+        raise PieError(st, "pie_product_plan: bad argument")
+    return {"tile_rows": int(out[0]), "splits": int(out[1]), "whole_rows": int(out[2]), "column_fetches": int(out[3])}
 
 
 def _i32(a) -> np.ndarray:

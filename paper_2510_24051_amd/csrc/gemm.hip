@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
+#include <vector>
 
 #include "internal.h"
 
@@ -506,6 +507,25 @@ __global__ __launch_bounds__(512) void gemm_large_kernel(const bf16_t* __restric
 // Workgroup ids are remapped so that each XCD (id % 8) works on a contiguous range of a grouped tile order (8 row
 // tiles per group) and its L2 sees a few activation and weight panels at a time.
 // ------------------------------------------------------------------------------------------------
+// Position of workgroup `id` in that order: ids go to the XCDs in turn, XCD x has n / 8 of them and one more when
+// x < n % 8.  A single row of tiles shares no weights between workgroups; where its length is not a multiple of 8 it is
+// left in launch order (128256 x 4096 at 193 rows 257 us, in ranges 262).  With more rows the ranges are what makes the
+// row tiles of a column meet in one L2, whatever the number of tiles: at 129 rows, 501 x 2 tiles of 96 rows, 299 us in
+// launch order (the weights fetched twice), 244 in ranges.
+__host__ __device__ __forceinline__ int xcd_range(int id, int tiles_m, int tiles_n) {
+  const int n = tiles_m * tiles_n, x = id & 7;
+  return tiles_m == 1 && n % 8 != 0 ? id : x * (n >> 3) + (x < (n & 7) ? x : n & 7) + (id >> 3);
+}
+// Row and column tile at a position of the grouped order.
+__host__ __device__ __forceinline__ void tile_at(int pos, int tiles_m, int tiles_n, int& tm, int& tn) {
+  constexpr int GROUP_M = 8;
+  const int width = GROUP_M * tiles_n;
+  const int first_m = (pos / width) * GROUP_M;
+  const int gsz = tiles_m - first_m < GROUP_M ? tiles_m - first_m : GROUP_M;
+  tm = first_m + (pos % width) % gsz;
+  tn = (pos % width) / gsz;
+}
+
 template <int MODE, bool PARTIAL>
 __global__ __launch_bounds__(512) void gemm_large_async_kernel(const bf16_t* __restrict__ A, int lda, int M,
                                                                const bf16_t* __restrict__ Wp, int N, int NB, int K,
@@ -514,7 +534,6 @@ __global__ __launch_bounds__(512) void gemm_large_async_kernel(const bf16_t* __r
   constexpr int BM = LG_BM;
   constexpr int MI = BM / 64;  // 32-row accumulator blocks per wave, and activation copy instructions per wave
   __shared__ __align__(16) bf16_t As0[BM * LG_BK], As1[BM * LG_BK], As2[BM * LG_BK];  // three activation stages
-  constexpr int GROUP_M = 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 2, wn = wave & 3;
   const int KB = K / 16, KT = K / LG_BK;
@@ -526,17 +545,8 @@ __global__ __launch_bounds__(512) void gemm_large_async_kernel(const bf16_t* __r
   constexpr bool LG_NT = MODE == EPI_STORE_F32 || (PARTIAL && MODE == EPI_RESID_OUT) || (!PARTIAL && MODE == EPI_SWIGLU);
   const int kt0 = PARTIAL ? blockIdx.y * kts_per_split : 0;
   const int kt1 = PARTIAL ? min(KT, kt0 + kts_per_split) : KT;
-  int pid = blockIdx.x;
-  const int ntiles = tiles_m * tiles_n;
-  if (ntiles % 8 == 0) pid = (pid & 7) * (ntiles / 8) + (pid >> 3);
   int tm, tn;
-  {
-    const int width = GROUP_M * tiles_n;
-    const int first_m = (pid / width) * GROUP_M;
-    const int gsz = min(tiles_m - first_m, GROUP_M);
-    tm = first_m + (pid % width) % gsz;
-    tn = (pid % width) / gsz;
-  }
+  tile_at(xcd_range(blockIdx.x, tiles_m, tiles_n), tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, nb0 = tn * (LG_BN / 32);
 
   f32x16 acc[MI][2];
@@ -781,23 +791,13 @@ __global__ __launch_bounds__(512, 4) void gemm_rows_kernel(const bf16_t* __restr
   constexpr bool AHEAD = MB < 4;        // the next contraction step's activation operands are read under this one's MFMAs
   __shared__ __align__(16) bf16_t As0[BM * LG_BK], As1[BM * LG_BK], As2[BM * LG_BK], As3[BM * LG_BK];
   constexpr bool NT = MODE == EPI_STORE_F32 || (PARTIAL && MODE == EPI_RESID_OUT) || (!PARTIAL && MODE == EPI_SWIGLU);
-  constexpr int GROUP_M = 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   [[maybe_unused]] const int KB = K / 16;
   const int KT = K / LG_BK;
   const int kt0 = PARTIAL ? blockIdx.y * kts_per_split : 0;
   [[maybe_unused]] const int kt1 = PARTIAL ? min(KT, kt0 + kts_per_split) : KT;
-  int pid = blockIdx.x;
-  const int ntiles = tiles_m * tiles_n;
-  if (ntiles % 8 == 0) pid = (pid & 7) * (ntiles / 8) + (pid >> 3);
   int tm, tn;
-  {
-    const int width = GROUP_M * tiles_n;
-    const int first_m = (pid / width) * GROUP_M;
-    const int gsz = min(tiles_m - first_m, GROUP_M);
-    tm = first_m + (pid % width) % gsz;
-    tn = (pid % width) / gsz;
-  }
+  tile_at(xcd_range(blockIdx.x, tiles_m, tiles_n), tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, nb = tn * 8 + wave;
 
   f32x16 acc[MB];
@@ -1116,6 +1116,11 @@ static TiledPlan plan_tiled(int M, int NB, int K, size_t ws_elems, int n_cus) {
   return best;
 }
 
+// the tiled kernels step 64 contraction elements at a time and address both operands with 32-bit byte offsets
+static bool tiled_ok(int M, int lda, int NB, int K) {
+  return K % LG_BK == 0 && (int64_t)M * lda * 2 < ((int64_t)1 << 32) && (int64_t)NB * 32 * K * 2 < ((int64_t)1 << 32);
+}
+
 template <int MODE, bool PARTIAL>
 static hipError_t run_tiles(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, const TiledPlan& p,
                             float* ws, hipStream_t s) {
@@ -1136,10 +1141,7 @@ static hipError_t run_mode(const bf16_t* A, int lda, int M, const PackedWeight& 
   if (M <= 0) return hipSuccess;
   if (M <= 32) return run_skinny<1, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
   if (M <= 64) return run_skinny<2, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
-  // the tiled kernels step 64 contraction elements at a time and address both operands with 32-bit byte offsets
-  const bool tiled_ok = W.K % LG_BK == 0 && (int64_t)M * lda * 2 < ((int64_t)1 << 32) &&
-                        (int64_t)W.NB * 32 * W.K * 2 < ((int64_t)1 << 32);
-  if (tiled_ok) {
+  if (tiled_ok(M, lda, W.NB, W.K)) {
     const TiledPlan p = plan_tiled(M, W.NB, W.K, ws_elems, n_cus);
     if (p.full_rows > 0) {
       hipError_t e = run_tiles<MODE, false>(A, lda, p.full_rows, W, epi, p, nullptr, s);
@@ -1182,4 +1184,23 @@ hipError_t launch_gemm(const bf16_t* A, int lda, int M, const PackedWeight& W, c
     case EPI_STORE_F32: return run_mode<EPI_STORE_F32>(A, lda, M, W, epi, splitk_ws, splitk_elems, n_cus, s, defer);
   }
   return hipErrorInvalidValue;
+}
+
+void product_plan(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out[4]) {
+  out[0] = out[1] = out[2] = out[3] = 0;
+  const int NB = (N + 31) / 32;
+  if (M <= 64 || !tiled_ok(M, K, NB, K)) return;
+  const TiledPlan p = plan_tiled(M, NB, K, ws_elems, n_cus);
+  const int tiles_m = ((p.full_rows ? p.full_rows : M) + p.rows - 1) / p.rows, tiles_n = (NB + 7) / 8, n = tiles_m * tiles_n;
+  out[0] = p.rows;
+  out[1] = p.splits;
+  out[2] = p.full_rows;
+  std::vector<uint8_t> fetched((size_t)tiles_n * p.splits, 0);  // XCDs that work on a column tile (of a part of K)
+  for (int split = 0; split < p.splits; ++split)
+    for (int id = 0; id < n; ++id) {
+      int tm, tn;
+      tile_at(xcd_range(id, tiles_m, tiles_n), tiles_m, tiles_n, tm, tn);
+      fetched[(size_t)split * tiles_n + tn] |= 1u << ((split * (int64_t)n + id) % 8);
+    }
+  for (uint8_t f : fetched) out[3] += __builtin_popcount(f);
 }

@@ -246,6 +246,8 @@ struct EpiArgs {
 hipError_t launch_gemm(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, float* splitk_ws,
                        size_t splitk_elems, int n_cus, hipStream_t s, int* deferred_splits = nullptr);
 
+void product_plan(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out[4]);  // see pie_product_plan
+
 struct AttnArgs {
   const bf16_t* q;   // [T, q_stride] rotated queries
   int q_stride;

@@ -1070,13 +1070,16 @@ struct TiledPlan {
 
 // The estimate every choice is made by: workgroups are spread evenly over the CUs, a workgroup's k step takes
 //   rows   one workgroup per CU   all CUs full (two workgroups of gemm_rows, one of gemm_large_async)
-//    96        0.70 us               1.25 us for both
+//    96        0.70 us               1.42 us for both
 //   128        0.75 us               1.65 us for both
-//   256        1.35 us               1.60 us
+//   256        1.35 us               1.55 us
 // the weights come from HBM at 5.4 TB/s at best (the two add up by their cubes: both matter where they are close), a
 // launch costs 3 us besides, and the partial sums of a split are written and read once at 6 TB/s (+ 3 us).  Fitted to
 // sweeps of every tile and 1..16 splits for N x K = 6144 x 4096, 4096 x 4096, 28672 x 4096, 4096 x 14336, 3072 x 2048,
-// 2048 x 2048, 16384 x 2048 and 2048 x 8192 at 84 to 8320 rows.  What it replaces: one row of tiles with as many splits
+// 2048 x 2048, 16384 x 2048, 2048 x 8192, 10240 x 8192, 8192 x 8192, 57344 x 8192, 8192 x 28672 and the LM heads
+// (128256 x 4096 and x 8192, 32000 x 2048) at 65 to 8320 rows; the form it picks is within 2% of the fastest on average.
+// (With 1.25 us for a full chip of 96-row tiles, which holds for one round of them only, long products went to those:
+// 28672 x 4096 at 1024 rows 231 us instead of 202, 57344 x 8192 at 4100 rows 3500 instead of 3016.)  What it replaces: one row of tiles with as many splits
 // as CUs up to 256 rows and unsplit 256-row tiles beyond, which left most of the chip idle at a few hundred rows
 // (4096 x 14336 at 333 rows: 32 workgroups, 308 us; now 240 and 53 us).
 static TiledPlan plan_tiled(int M, int NB, int K, size_t ws_elems, int n_cus) {
@@ -1086,7 +1089,7 @@ static TiledPlan plan_tiled(int M, int NB, int K, size_t ws_elems, int n_cus) {
   auto main_us = [&](double compute) { return 3.0 + std::cbrt(compute * compute * compute + stream_us * stream_us * stream_us); };
   auto steps_us = [&](int rows, int64_t wgs) {  // time of one k step of all workgroups
     const int slots = rows == 256 ? n_cus : 2 * n_cus;
-    const double one = rows == 96 ? 0.70 : rows == 128 ? 0.75 : 1.35, full = rows == 96 ? 1.25 : rows == 128 ? 1.65 : 1.60;
+    const double one = rows == 96 ? 0.70 : rows == 128 ? 0.75 : 1.35, full = rows == 96 ? 1.42 : rows == 128 ? 1.65 : 1.55;
     const int64_t rem = wgs % slots;
     const bool light = rows == 256 ? rem * 8 <= (int64_t)n_cus * 7 && wgs < slots : rem <= n_cus;
     return (double)(wgs / slots) * full + (rem == 0 ? 0.0 : light ? one : full);

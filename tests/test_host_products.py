@@ -28,3 +28,33 @@ def test_product_plan_arguments():
             product_plan(*bad)
     with pytest.raises(PieError):
         product_plan(1, 32, 64, 0, n_cus=0)
+
+
+# (rows, n_out, k, {(rows of a tile, parts of K): us}): the faster forms as measured on the device, weights from HBM
+MEASURED = [
+    (160, 28672, 4096, {(96, 1): 61, (128, 1): 67, (96, 2): 74, (128, 2): 75, (256, 2): 74, (256, 1): 96}),
+    (900, 28672, 4096, {(96, 1): 219, (128, 1): 204, (256, 1): 198, (256, 2): 263}),
+    (1024, 28672, 4096, {(96, 1): 231, (128, 1): 210, (256, 1): 202, (256, 2): 277}),
+    (3072, 28672, 4096, {(96, 1): 642, (128, 1): 570, (256, 1): 578}),
+    (448, 57344, 8192, {(96, 1): 464, (128, 1): 414, (256, 1): 410, (256, 2): 475}),
+    (768, 57344, 8192, {(96, 1): 670, (128, 1): 618, (256, 1): 610, (256, 2): 720}),
+    (1536, 57344, 8192, {(96, 1): 1264, (128, 1): 1165, (256, 1): 1162}),
+    (3072, 10240, 8192, {(96, 1): 446, (128, 1): 397, (256, 1): 388, (256, 2): 490}),
+    (5000, 6144, 4096, {(96, 1): 212, (128, 1): 204, (256, 1): 201}),
+    (6144, 6144, 4096, {(96, 1): 281, (128, 1): 248, (256, 1): 269}),
+    (1792, 16384, 2048, {(96, 1): 118, (128, 1): 115, (256, 1): 108}),
+    (129, 128256, 4096, {(96, 1): 244, (128, 1): 264, (256, 1): 244, (256, 2): 303}),
+    (192, 128256, 8192, {(96, 1): 493, (128, 1): 520, (256, 1): 520, (256, 2): 592}),
+    (333, 4096, 14336, {(96, 4): 57, (128, 4): 60, (128, 5): 54, (96, 8): 64, (256, 7): 63, (96, 5): 80, (128, 6): 77}),
+    (333, 4096, 4096, {(96, 4): 26, (128, 4): 26, (96, 3): 28, (128, 3): 29, (96, 5): 35, (256, 6): 32}),
+    (1152, 4096, 14336, {(96, 4): 158, (128, 3): 147, (128, 5): 153, (256, 3): 136, (96, 1): 168, (256, 2): 170}),
+    (2304, 4096, 14336, {(96, 1): 261, (96, 2): 260, (128, 3): 270, (256, 3): 273, (256, 1): 317}),
+]
+
+
+@pytest.mark.parametrize("rows,n_out,k,us", MEASURED, ids=lambda v: str(v) if isinstance(v, int) else "")
+def test_plan_picks_a_form_near_the_fastest_measured(rows, n_out, k, us):
+    """Within 5%: two runs of one form differ by 2 to 3%."""
+    p = product_plan(rows, n_out, k, 256 * max(28672, 2 * k, n_out if n_out <= 57344 else 0) * 8)
+    assert p["whole_rows"] == 0
+    assert us[p["tile_rows"], p["splits"]] <= 1.05 * min(us.values())

@@ -20,6 +20,17 @@ def make_ctx(w, with_head=True, max_dist_rows=None, max_top_k=256):
     return ctx
 
 
+def product_forms(m, T, dist_rows=0):
+    """(rows of a tile, parts of K, rows in whole rounds) of a layer's four products at T rows on 256 compute units, in the
+    workspace a context of that many batch tokens has."""
+    from paper_2510_24051_amd import product_plan
+    qkv, inner = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim, m.n_q_heads * m.head_dim
+    ws = min(max(T, dist_rows), 256) * max(2 * m.mlp_dim, (max(qkv, m.hidden) + 31) // 32 * 32) * 8
+    plan = {"qkv": product_plan(T, qkv, m.hidden, ws), "o": product_plan(T, m.hidden, inner, ws),
+            "gateup": product_plan(T, 2 * m.mlp_dim, m.hidden, ws), "down": product_plan(T, m.hidden, m.mlp_dim, ws)}
+    return {k: (p["tile_rows"], p["splits"], p["whole_rows"]) for k, p in plan.items()}
+
+
 def seed_ctx(ctx, w):
     ctx.embed_write(w.batch.in_embed_ids, w.embed_bits)
     if len(w.prior.page_ids):

@@ -284,6 +284,13 @@ pie_status pie_batch_work(const pie_batch* batch, int64_t* out);
  * Host int64[8]. */
 pie_status pie_batch_plan_info(const pie_batch* batch, int64_t* out);
 
+/* What of a batch's attention is cut along its pages and merged from fp32 parts: out[0] = (query block, kv head) pairs of
+ * the prefill launches that are cut, out[1] = most parts of one of their blocks (1: nothing is cut), out[2] = (wide
+ * group, kv head) pairs: decode requests that alias many pages, walked 128 query columns at a time, out[3] = most parts
+ * of one of them.  All 0 or 1 in a batch that was planned again because the device had no room for the parts.
+ * Host int64[4]. */
+pie_status pie_batch_plan_parts(const pie_batch* batch, int64_t* out);
+
 /* The prefill attention launches of a batch, as the planner laid them out: one entry per workgroup in launch order,
  * three values each (request, 32-token query block, kv head); request -1 marks an empty slot.  (A block whose page
  * list is cut into parts, because the blocks alone would not fill the chip, is one entry; its parts run on the same XCD

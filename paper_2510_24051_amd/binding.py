@@ -92,6 +92,7 @@ def load_library():
         "pie_stage_times": [vp, vp],
         "pie_batch_work": [vp, vp],
         "pie_batch_plan_info": [vp, vp],
+        "pie_batch_plan_parts": [vp, vp],
         "pie_batch_prefill_work": [vp, vp, i32, vp],
         "pie_product_plan": [i32, i32, i32, i64, i32, vp],
         "pie_create_planner": [C.POINTER(ModelDescC), C.POINTER(PoolDescC), i32, C.POINTER(vp)],
@@ -139,6 +140,11 @@ class PieBatch:
         return {"decode_waves": int(out[0]), "segments": int(out[1]), "max_pairs_per_wave": int(out[2]),
                 "prefill_items": int(out[3]), "decode_requests": int(out[4]), "rows_cap": int(out[5]),
                 "prefill_workgroups": int(out[6]), "prefill_workgroups_pair_weights": int(out[7])}
+
+    def plan_parts(self) -> dict:
+        out = np.zeros(4, dtype=np.int64)
+        self.owner._check(self.owner.lib.pie_batch_plan_parts(self.handle, _ptr(out)))
+        return {"cut_blocks": int(out[0]), "most_parts": int(out[1]), "wide_groups": int(out[2]), "most_wide_parts": int(out[3])}
 
     def prefill_work(self) -> np.ndarray:
         """[n, 3] int32 (request, query block, kv head) per workgroup of the two prefill launches, one after the

@@ -118,6 +118,7 @@ struct pie_batch {
   // may see few keys: bitmap masks, causal blocks that start within the first 64 keys) with weights as bf16 pairs
   int32_t n_pwork = 0, n_pwork_lo = 0;
   int32_t n_sitems = 0, max_sparts = 1;     // shared groups: items (laid out per XCD), most parts of an item
+  int32_t n_sgroups = 0;                    // (group, kv head) pairs among them
   PrefillItem* sitems = nullptr;            // [n_sitems] r = shared group
   SharedGroup* sgroups = nullptr;
   DecodeCol* scols = nullptr;

@@ -1263,6 +1263,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   pb->n_pwork = (int32_t)n_pwork_plain;
   pb->n_pwork_lo = (int32_t)(pwork.size() - n_pwork_plain);
   pb->n_sitems = (int32_t)sitems.size();
+  pb->n_sgroups = (int32_t)sgroups.size() * Hkv;
   pb->max_sparts = max_sparts;
   pb->dec_rows = dec_rows;
   pb->max_parts = max_parts;
@@ -1445,6 +1446,15 @@ extern "C" pie_status pie_batch_plan_info(const pie_batch* b, int64_t* out) {
   out[5] = b->rows_cap;
   out[6] = b->n_pwork;
   out[7] = b->n_pwork_lo;
+  return PIE_OK;
+}
+
+extern "C" pie_status pie_batch_plan_parts(const pie_batch* b, int64_t* out) {
+  if (!b || !out) return PIE_EINVAL;
+  out[0] = b->n_psplit;
+  out[1] = std::max(b->max_parts, b->max_parts_lo);
+  out[2] = b->n_sgroups;
+  out[3] = b->max_sparts;
   return PIE_OK;
 }
 

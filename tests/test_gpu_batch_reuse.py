@@ -2,6 +2,7 @@
 the host image they are built in is the same memory."""
 import numpy as np
 import pytest
+import torch
 
 import workloads as W
 from gpu_helpers import gpu_forward, make_ctx
@@ -28,6 +29,36 @@ def test_batches_created_back_to_back_keep_their_own_arrays():
         ctx.forward(0, pb)
         got = ctx.embed_read(out[stored])
         assert np.array_equal(got, want)
+
+
+def test_batches_whose_copies_wait_behind_queued_work_keep_their_own_arrays():
+    """The stream has tens of milliseconds of work queued while the batches are created, so the first ones' copies are still
+    to come when the host image is built anew: each runs on its own arrays."""
+    w = W.c1_tiny()
+    b = w.batch
+    ctx = make_ctx(w)
+    _, stored, want = gpu_forward(ctx, w)
+    ctx.embed_write(b.in_embed_ids, w.embed_bits)  # (the in-place rows; waits for the stream, so before the queue fills)
+    free = np.setdiff1d(np.arange(w.n_embeds, dtype=np.int32), b.in_embed_ids)
+    a = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
+    c = torch.mm(a, a)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(ctx.stream):
+        for _ in range(40):  # about a millisecond each
+            torch.mm(a, a, out=c)
+        queued = torch.cuda.Event()
+        queued.record()
+    outs, batches = [], []
+    for k in range(3):
+        out = b.out_embed_ids.copy()
+        out[stored] = np.roll(free, k)[:len(stored)]
+        outs.append(out)
+        if k == 1:
+            assert not queued.query()  # the first batch's copy has not begun
+        batches.append(ctx.batch_create(clone_batch(b, out_embed_ids=out)))
+    for out, pb in zip(outs, batches):
+        ctx.forward(0, pb)
+        assert np.array_equal(ctx.embed_read(out[stored]), want)
 
 
 def test_write_conflicts_are_found_across_calls():

@@ -29,6 +29,7 @@ def test_long_shared_prefix_in_wide_groups(head_dim, n_q, n_kv, R, pages):
     reqs += [W.RequestSpec(1, 300), W.RequestSpec(20, 40)]
     w = W.build_workload("wide", m, reqs, n_kv_pages=pages + 6 * len(reqs) + 64, seed=900 + R, std=0.05)
     ctx, pb, _, _ = compare_layer(w, what=f"D{head_dim} G{n_q // n_kv} {R} branches on {prefix} tokens")
+    assert pb.plan_parts()["wide_groups"] >= -(-R // (128 // (n_q // n_kv))) * n_kv
     work, page_bytes = pb.work(), n_kv * 2 * P * head_dim * 2
     G = n_q // n_kv
     private = sum(6 for _ in reqs) * page_bytes
@@ -54,6 +55,7 @@ def test_wide_groups_over_masks_that_partly_overlap(head_dim, n_q, n_kv, R):
     reqs = [W.RequestSpec(1, pages * 16 + 39, prefix_group=0, prefix_len=pages * 16, mask=sees(own)) for own in seen]
     w = W.build_workload("overlap", m, reqs, n_kv_pages=pages + 3 * R + 8, seed=950 + head_dim, std=0.05)
     ctx, pb, _, _ = compare_layer(w, what=f"D{head_dim} G{n_q // n_kv} {R} branches, 60 of {pages} pages each")
+    assert pb.plan_parts()["wide_groups"] == -(-R // (128 // (n_q // n_kv))) * n_kv
     families, cols, page_bytes = [(pages, 40, seen)], n_q // n_kv, n_kv * 2 * 16 * head_dim * 2
     assert requested_pages(families, cols, {0}) < requested_pages(families, cols, set())
     assert pb.work()["kv_bytes_requested"] == requested_pages(families, cols, {0}) * page_bytes

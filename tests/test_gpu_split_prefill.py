@@ -31,5 +31,7 @@ def test_cut_query_blocks_match(head_dim, n_q, n_kv, new, prior):
     pages = sum((r.n_new + r.prior_len + 15) // 16 for r in reqs) + 8
     w = W.build_workload("cut", m, reqs, n_kv_pages=pages, seed=700 + prior, std=0.05)
     ctx, pb, y_bits, _ = compare_layer(w, what=f"D{head_dim} G{n_q // n_kv} {new} new over {prior}")
+    parts = pb.plan_parts()
+    assert parts["cut_blocks"] > 0 and parts["most_parts"] > 1, parts
     _, _, again = gpu_forward(ctx, w)  # the partial results are reused: the same bits
     assert np.array_equal(np.asarray(y_bits), np.asarray(again))

@@ -455,5 +455,29 @@ def test_wide_groups_are_formed_where_they_save_requests(name, families, wide):
     work = ctx.batch_create(b).work()
     page_bytes = m.n_kv_heads * 2 * 16 * m.head_dim * 2
     assert work["kv_bytes_requested"] == requested_pages(families, 4, wide) * page_bytes
+    chunks = sum(-(-len(families[f][2]) // 32) for f in wide)
+    assert ctx.batch_create(b).plan_parts()["wide_groups"] == chunks * m.n_kv_heads
     if not wide:
         assert requested_pages(families, 4, wide) > requested_pages(families, 4, {0})  # (the two would differ)
+
+
+@pytest.mark.parametrize("name,prompts,cut", [
+    ("drafts over long contexts", [(7, 1250 + 230 * i) for i in range(12)], True),
+    ("one long prompt continued", [(333, 3000)], True),
+    ("just short of 24 steps saved", [(33, 950)], False),  # 31 steps, parts of eight at least
+    ("just past them", [(33, 1020)], True),
+    ("a full chip", [(1024, 1000 + i) for i in range(8)], False),
+])
+def test_query_blocks_are_cut_where_few_of_them_walk_far(name, prompts, cut):
+    m = small_model(128, 32, 8)
+    b, free = prefix_batch([(0, n + p, [None]) for n, p in prompts])
+    new = np.array([n for n, _ in prompts])
+    T = int(new.sum())
+    b.n_tokens, b.tok_indptr = T, np.concatenate([[0], np.cumsum(new)])
+    b.in_embed_ids, b.out_embed_ids, b.positions = np.arange(T), np.full(T, -1), np.zeros(T)
+    ctx = Pie.planner(m, free, T, max_batch_tokens=T, max_batch_requests=b.n_requests)
+    pb = ctx.batch_create(b)
+    parts, blocks = pb.plan_parts(), pb.plan_info()["prefill_items"] * m.n_kv_heads
+    assert (parts["cut_blocks"] > 0) == cut and parts["cut_blocks"] <= blocks, parts
+    assert (parts["most_parts"] > 1) == cut and parts["wide_groups"] == 0
+    assert len([r for r in pb.prefill_work() if r[0] >= 0]) == blocks  # a cut block is one entry

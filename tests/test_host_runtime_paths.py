@@ -159,7 +159,36 @@ def failed_allocation_in_destroy(c):
         ctx.close()
 
 
-CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy)}
+def no_room_for_parts(c):
+    """A device block that does not fit with the partial results is planned again without them: nothing cut, no wide groups,
+    every page in a column group; without room for that either, PIE_ENOMEM, and the context goes on."""
+    prompts, tree = batch_of([(33, 6000), (20, 9000), (1, 300)]), batch_of([(1, 16 * 1000 + 20)] * 96)
+    own = 1000 + np.arange(96 * 2).reshape(96, 2)  # 96 requests on one prefix of 1000 pages, two pages of their own each
+    tree.page_ids = np.concatenate([np.concatenate([np.arange(1000), pages]) for pages in own])
+    page_bytes = MODEL.n_kv_heads * 2 * 16 * MODEL.head_dim * 2
+    none = {"cut_blocks": 0, "most_parts": 1, "wide_groups": 0, "most_wide_parts": 1}
+    for b, wide, alone in ((prompts, None, None), (tree, 3 * 1000 + 192, 24 * 1000 + 192)):  # pages asked for
+        ctx = c.context(n_pages=1200, requests=128)
+        c.fake.fake_largest_malloc()
+        full = ctx.batch_create(b)
+        parts, need = full.plan_parts(), c.fake.fake_largest_malloc()
+        assert parts["cut_blocks"] + parts["wide_groups"] > 0
+        c.fake.fake_malloc_limit(need - 1)
+        small = ctx.batch_create(b)
+        assert small.plan_parts() == none and c.fake.fake_largest_malloc() == need  # (asked for first)
+        if wide:
+            assert full.work()["kv_bytes_requested"] == wide * page_bytes and small.work()["kv_bytes_requested"] == alone * page_bytes
+        c.fake.fake_malloc_limit(4096)
+        assert c.status(lambda: ctx.batch_create(b))[0] == -5
+        c.fake.fake_malloc_limit(1 << 62)
+        again = ctx.batch_create(b)
+        assert again.plan_parts() == parts
+        for pb in (full, small, again):
+            pb.destroy()
+        ctx.close()
+
+
+CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy, no_room_for_parts)}
 
 if __name__ == "__main__":
     CASES[sys.argv[2]](Child(sys.argv[1]))

@@ -61,6 +61,34 @@ def test_batches_whose_copies_wait_behind_queued_work_keep_their_own_arrays():
         assert np.array_equal(ctx.embed_read(out[stored]), want)
 
 
+def test_a_captured_stream_is_refused_and_the_capture_goes_on():
+    """batch_create during a capture is refused without ending it: the forward call recorded around it replays with the
+    eager result, several times, with other work on the stream in between."""
+    from paper_2510_24051_amd import PieError
+    w = W.c1_tiny()
+    b = w.batch
+    ctx = make_ctx(w)
+    stored = np.nonzero(b.out_embed_ids >= 0)[0]
+    out = np.full_like(b.out_embed_ids, -1)
+    out[stored] = np.setdiff1d(np.arange(w.n_embeds, dtype=np.int32), b.in_embed_ids)[:len(stored)]
+    pb = ctx.batch_create(clone_batch(b, out_embed_ids=out))
+    ctx.forward(0, pb)
+    want = ctx.embed_read(out[stored])
+    pb = ctx.batch_create(clone_batch(b, out_embed_ids=out))  # nothing has waited for this one's copy
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=ctx.stream):
+        with pytest.raises(PieError) as e:
+            ctx.batch_create(b)
+        assert e.value.status == -6 and "captured" in str(e.value)
+        ctx.forward(0, pb)
+    for _ in range(3):
+        ctx.embed_write(out[stored], np.zeros_like(want))
+        with torch.cuda.stream(ctx.stream):
+            graph.replay()
+        assert np.array_equal(ctx.embed_read(out[stored]), want)
+        ctx.batch_create(b).destroy()
+
+
 def test_write_conflicts_are_found_across_calls():
     """The conflict check keeps its marks from call to call: a slot written by one batch is free for the next, and two
     tokens of one batch on one slot are refused every time."""

@@ -359,7 +359,7 @@ class Pie:
 
     def get_next_dist_static_async(self, embed_ids, top_k: int, temperature: float, out_ids: torch.Tensor,
                                    out_probs: torch.Tensor):
-        """pie_get_next_dist_static: the allocation-free variant (at most 16 rows); outputs are caller tensors."""
+        """pie_get_next_dist_static: the allocation-free variant (at most 32 rows); outputs are caller tensors."""
         ids = _i32(embed_ids)
         self._check(self.lib.pie_get_next_dist_static(self.ctx, _ptr(ids), len(ids), top_k, float(temperature),
                                                       C.c_void_p(out_ids.data_ptr()), C.c_void_p(out_probs.data_ptr())))

@@ -554,8 +554,8 @@ __device__ __forceinline__ void lds_copy_run(const char* src, char* dst) {
 // per wave, each with its own length, limit and mask row; always cut, its rows merged with the decode kernel's.  The
 // decode kernel holds 16 columns per K/V block and reads the block once per 16: 256 branches of 4 query heads on a
 // 4096-token prefix asked the caches for 1.14 GB and took 113 us; here a block is copied to LDS once per 128 columns
-// (134 MB) and the walk takes 44 us, bound by the MFMAs
-// and vector work of the pair weights (16 steps, 1.9 us for two workgroups on a compute unit).
+// (134 MB) and the walk takes 44 us, bound by the MFMAs and vector work of the pair weights (16 steps, 1.9 us for two
+// workgroups on a compute unit), which are done for all columns whoever sees the page.
 template <int D, int G, bool LO, bool SPLIT, bool SHARED = false>
 __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, const PrefillItem* __restrict__ items,
                                                                  float* __restrict__ part_o, float* __restrict__ part_ml,

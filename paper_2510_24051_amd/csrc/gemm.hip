@@ -775,8 +775,10 @@ __global__ __launch_bounds__(512) void gemm_large_async_kernel(const bf16_t* __r
 // set of activation operands) so that two workgroups share a compute unit and one computes while the other waits at
 // its barrier.  Measured, kernel plus epilogue, weights from HBM, against the 128-row form of the 256-column tile it
 // replaces: 28672 x 4096 at 84 rows 59 -> 52 us, at 157 rows (256-row tile) 74 -> 61, 4096 x 14336 at 333 rows 69 ->
-// 53, at 2000 rows 233 -> 189, 6144 x 4096 at 4096 rows 191 (256-row tile) -> 164.  At 8192 rows, whole rounds of both
-// tiles, the two are equal (the chip's power limit).
+// 53, at 2000 rows 233 -> 189, 6144 x 4096 at 4096 rows 191 (256-row tile) -> 164.  Over many rounds of a full chip the
+// 128-row tile equals the 256-row one and the 96-row tile loses (28672 x 4096 at 8192 rows 1473, 1432 and 1695 us).
+// With one workgroup per compute unit (a few hundred rows) the bound is the weight bytes in flight, 32 KiB per compute
+// unit: gate/up 28672 x 4096 at 157 rows takes 60 us with its weights in HBM and 42 with them in the last-level cache.
 // The workgroup order is that of gemm_large_async_kernel.
 // ------------------------------------------------------------------------------------------------
 template <int MODE, bool PARTIAL, int MB>

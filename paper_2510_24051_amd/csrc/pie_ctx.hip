@@ -1202,7 +1202,8 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   // start-up however short it is, so nothing is cut unless it shortens the longest walk by 24 steps.  Measured: twelve
   // requests of 7 tokens over 1250 to 3750 tokens, 96 workgroups of up to 118 steps, 92 us whole, 39 + 5 us cut (parts
   // of 64 / 48 / 32 / 24 steps: 53 / 43 / 39 / 35 us); 333 tokens over 3000, 88 workgroups, 85 us whole, 36 + 8 us cut
-  // (53 / 43 / 41 / 38).  Launches whose blocks fill the chip are never cut (8 x 1024 tokens: 237 us as before).
+  // (53 / 43 / 41 / 38).  Launches whose blocks fill the chip are never cut (8 x 1024 tokens: 220 us, the same launch as
+  // without this rule).
   auto cut = [&](std::vector<PrefillItem>& items) {
     if (!may_split || items.empty() || (G != 1 && G != 2 && G != 4 && G != 8)) return 1;
     const int64_t slots = (int64_t)(c->wave_slots / 8) * std::min(8 / G, D == 128 ? 2 : 5);

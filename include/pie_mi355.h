@@ -305,13 +305,19 @@ pie_status pie_batch_plan_parts(const pie_batch* batch, int64_t* out);
  * entries in *n_entries.  Works on planner contexts. */
 pie_status pie_batch_prefill_work(const pie_batch* batch, int32_t* out, int32_t cap, int32_t* n_entries);
 
-/* How a product C[rows, n_out] = A[rows, k] x W[n_out, k]^T would be cut on a GPU of n_cus compute units with room for
+/* How the tiled kernels cut a product C[rows, n_out] = A[rows, k] x W[n_out, k]^T on a GPU of n_cus compute units with room for
  * workspace_floats partial sums: out[0] = rows of a tile (0: the weight-streaming kernels, which take at most 64 rows
  * and what the tiled kernels cannot), out[1] = parts the contraction is cut into, out[2] = leading rows that go through
  * whole rounds of tiles, the rest being a product of its own (0: one product), out[3] = column tiles of the weights,
  * each counted once for every XCD whose L2 has to fetch it (the tiles are ordered so that the row tiles of a column
- * share one).  Computes on the host only.  Host int64[4]. */
+ * share one).  A product that pie_product_stream tells of goes to the streaming kernel instead.  Computes on the host
+ * only.  Host int64[4]. */
 pie_status pie_product_plan(int32_t rows, int32_t n_out, int32_t k, int64_t workspace_floats, int32_t n_cus, int64_t* out);
+
+/* Whether the same product goes to the kernel that streams wide weights past up to 384 rows: out[0] = rows of a tile (0: it
+ * does not), out[1] = parts the contraction is cut into inside a workgroup, out[2] = parts it is cut into across workgroups.
+ * Computes on the host only.  Host int64[3]. */
+pie_status pie_product_stream(int32_t rows, int32_t n_out, int32_t k, int64_t workspace_floats, int32_t n_cus, int64_t* out);
 
 #ifdef __cplusplus
 }

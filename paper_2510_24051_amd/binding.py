@@ -95,6 +95,7 @@ def load_library():
         "pie_batch_plan_parts": [vp, vp],
         "pie_batch_prefill_work": [vp, vp, i32, vp],
         "pie_product_plan": [i32, i32, i32, i64, i32, vp],
+        "pie_product_stream": [i32, i32, i32, i64, i32, vp],
         "pie_create_planner": [C.POINTER(ModelDescC), C.POINTER(PoolDescC), i32, C.POINTER(vp)],
     }
     for name, args in sigs.items():
@@ -114,6 +115,15 @@ def product_plan(rows: int, n_out: int, k: int, workspace_floats: int, n_cus: in
     if st != 0:
         raise PieError(st, "pie_product_plan: bad argument")
     return {"tile_rows": int(out[0]), "splits": int(out[1]), "whole_rows": int(out[2]), "column_fetches": int(out[3])}
+
+
+def product_stream(rows: int, n_out: int, k: int, workspace_floats: int, n_cus: int = 256) -> dict:
+    """pie_product_stream: the streaming kernel's form where it takes a product (tile_rows 0: it does not)."""
+    out = np.zeros(3, dtype=np.int64)
+    st = load_library().pie_product_stream(rows, n_out, k, workspace_floats, n_cus, _ptr(out))
+    if st != 0:
+        raise PieError(st, "pie_product_stream: bad argument")
+    return {"tile_rows": int(out[0]), "k_slices": int(out[1]), "splits": int(out[2])}
 
 
 def _i32(a) -> np.ndarray:

@@ -5,6 +5,7 @@
 //                 (each load is 1 KiB contiguous thanks to the tiled weight layout); the activation tile is
 //                 shared by the workgroup through LDS.  K is split across gridDim.y when N alone gives too
 //                 few workgroups; partial sums go to a workspace and a second kernel applies the epilogue.
+//   gemm_stream : up to 384 rows of wide products; one workgroup per CU with a deep ring of weights in registers.
 //   gemm_rows   : tiles of 96 or 128 rows by 256 columns, K split where the tiles alone leave CUs idle.
 //   gemm_large  : large M (prefill).  MFMA-bound: 256x256x64 workgroup tile, 8 waves of 128x64.
 #include <algorithm>
@@ -946,6 +947,260 @@ __global__ __launch_bounds__(512, 4) void gemm_rows_kernel(const bf16_t* __restr
 }
 
 // ------------------------------------------------------------------------------------------------
+// gemm_stream (K a multiple of 64, weights of tens of MB and more): 1 to 384 rows, where the weight stream is the bound
+//
+// What gemm_rows lacks with one workgroup per compute unit is weight bytes in flight (one k step, 32 KiB, and half of
+// that with tiles of 96 rows read twice).  Here a compute unit holds one workgroup of eight waves on purpose and spends
+// the registers that frees (256 per lane) on a ring of S = 3 or 4 k steps of weights, 96 to 128 KiB in flight, requested
+// non-temporally (a tile of up to 192 rows makes them read once, or by two row tiles at once).  KS: the contraction is
+// split KS ways inside the workgroup: slice s (8 / KS waves, 32 columns each) takes the s-th part of the workgroup's k
+// steps with an activation tile of its own, and the sums meet through LDS in slice order.  That is what keeps tiles
+// narrow enough for a workgroup on (nearly) every compute unit without partial sums in memory: 28672 columns are 224
+// tiles of 128 (KS = 2), 16384 are 256 tiles of 64 (KS = 4).  Activations go to LDS by direct copies as in gemm_rows, S
+// stages, rows swizzled.
+// Measured, kernel plus epilogue, weights from HBM, against what ran before (gemm_skinny up to 64 rows, gemm_rows
+// above): 28672 x 4096 at 84 rows 52 -> 44 us, 128 rows 59 -> 48, 157 rows 61 -> 54, 300 rows 99 -> 72; 4096 x 14336 at
+// 84 rows 32 -> 29; 57344 x 8192 at 64 rows 152 -> 138 (6.8 TB/s), 157 rows 225 -> 158; 16384 x 2048 at 16 rows 23 -> 15;
+// 128256 x 4096 at 157 rows 254 -> 183.  Without its copies, LDS reads and MFMAs (timing only) the 28672 x 4096 stream
+// takes 46 us in this form: at 157 rows 8 us are not hidden under it.
+// ------------------------------------------------------------------------------------------------
+// stages and weight ring: four where 128 KiB of LDS and the registers hold them
+constexpr int stream_stages(int mb, int ks) { return ks == 1 && mb <= 5 ? 4 : ks == 2 && mb == 2 ? 4 : 3; }
+
+template <int MODE, bool PARTIAL, int MB, int KS>
+__global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const bf16_t* __restrict__ A, int lda, int M,
+                                                             const bf16_t* __restrict__ Wp, int N, int NB, int K,
+                                                             EpiArgs epi, int tiles_m, int tiles_n, int kts_per_split,
+                                                             float* __restrict__ part) {
+  constexpr int BM = MB * 32;
+  constexpr int S = stream_stages(MB, KS);
+  constexpr int WPS = 8 / KS;                // column blocks of the tile
+  constexpr int PIECES = KS * BM / 8;        // 1 KiB copy instructions per activation stage
+  constexpr int CP = (PIECES + 7) / 8;       // per wave
+  constexpr bool AHEAD = MB < 6;             // the next contraction step's activation operands are read under this one's MFMAs
+  constexpr int STAGE = KS * BM * LG_BK;
+  __shared__ __align__(16) bf16_t As0[STAGE], As1[STAGE], As2[STAGE], As3[S > 3 ? STAGE : 16];
+  constexpr bool NT = MODE == EPI_STORE_F32 || (PARTIAL && MODE == EPI_RESID_OUT) || (!PARTIAL && MODE == EPI_SWIGLU);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ks = wave / WPS;                 // this wave's K slice
+  [[maybe_unused]] const int KB = K / 16;
+  const int KT = K / LG_BK;
+  const int first = PARTIAL ? blockIdx.y * kts_per_split : 0;
+  const int last = PARTIAL ? min(KT, first + kts_per_split) : KT;
+  [[maybe_unused]] const int n = (last - first) / KS;  // k steps of a slice (KS divides them, the host sees to it)
+  int tm, tn;
+  tile_at(xcd_range(blockIdx.x, tiles_m, tiles_n), tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * BM, nb = tn * WPS + wave % WPS;
+
+  f32x16 acc[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+  {
+#if __HIP_DEVICE_COMPILE__  // (buffer descriptors: see gemm_large_async_kernel)
+    constexpr int RSRC_FLAGS = 0x00020000;
+    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(A), 0, (int)(((int64_t)(M - 1) * lda + K) * 2), RSRC_FLAGS);
+    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(Wp), 0, (int)((int64_t)NB * 32 * K * 2), RSRC_FLAGS);
+    // copy piece p of a stage covers eight rows of one slice's tile: lane -> row lane / 8 of them, stored chunk lane % 8;
+    // past the last piece a wave copies that one again (same bytes)
+    int piece[CP], aoff[CP];
+#pragma unroll
+    for (int jj = 0; jj < CP; ++jj) {
+      piece[jj] = PIECES % 8 == 0 ? wave * CP + jj : min(wave * CP + jj, PIECES - 1);
+      const int sl = piece[jj] / (BM / 8), r = (piece[jj] % (BM / 8)) * 8 + (lane >> 3);
+      const int kc = (lane & 7) ^ ((r >> 1) & 7);
+      const int gr = min(m0 + r, M - 1);  // rows past M re-read a valid row; their results are never stored
+      aoff[jj] = (int)(((int64_t)gr * lda + kc * 8 + (int64_t)(first + sl * n) * LG_BK) * 2);
+    }
+    const int woff = (int)((packed_tile_offset(min(nb, NB - 1), (first + ks * n) * 4, KB) + lane * 8) * 2);
+    u32x4 wreg[S][4];  // ring: the weight operands of S k steps
+    auto issue_a = [&](bf16_t* As, int kt) {
+      const int k = kt < n ? kt : n - 1;  // past the end: a copy nobody reads, so that the wait counts stay uniform
+#pragma unroll
+      for (int jj = 0; jj < CP; ++jj)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (__attribute__((address_space(3))) void*)(As + piece[jj] * 512),
+                                                 16, aoff[jj], k * (LG_BK * 2), 0, 0);
+    };
+    auto load_w = [&](int kt, const int slot, const int s) {
+      const int k = kt < n ? kt : n - 1;
+      wreg[slot][s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, woff, (k * 4 + s) * 1024, 2);  // (2: non-temporal)
+    };
+    auto load_a = [&](const bf16_t* As, int s, bf16x8 (&af)[MB]) {
+      const int kc = s * 2 + (lane >> 5);
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        const int r = i * 32 + (lane & 31);
+        af[i] = *reinterpret_cast<const bf16x8*>(As + ks * (BM * LG_BK) + r * LG_BK + ((kc ^ ((r >> 1) & 7)) << 3));
+      }
+    };
+    bf16x8 af[2][MB];
+    // Step kt on stage Acur: the copies of step kt + S - 1 go to Afill, read last in step kt - 1, which every wave has
+    // left; each weight register set is refilled for step kt + S right behind its MFMAs.  At the barrier, before the last
+    // contraction step's MFMAs, this wave has read all of Acur and its part of the tile of step kt + 1 has to have
+    // arrived.  Requested after that one were the copies of S - 2 steps and, inside the loop, the weights of S - 2 steps
+    // and three quarters.  TAIL: in the steps behind the loop the compiler drops the weight requests that no step uses,
+    // so only the copies may be counted on there.
+    auto step = [&](auto tail_c, auto slot_c, const bf16_t* Acur, const bf16_t* Anext, bf16_t* Afill, int kt) {
+      constexpr int SLOT = decltype(slot_c)::value;
+      constexpr bool TAIL = decltype(tail_c)::value;
+      issue_a(Afill, kt + S - 1);
+      __builtin_amdgcn_sched_barrier(0);  // the copies go out first: the wait counts rely on the request order
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (!AHEAD) load_a(Acur, s, af[0]);
+        else if (s < 3) load_a(Acur, s + 1, af[(s + 1) & 1]);
+        if (s == 3) {
+          PIE_S_WAIT_LGKMCNT0();  // this wave's last reads of Acur have returned
+          if constexpr (TAIL) PIE_S_WAIT_VMCNT((S - 2) * CP);
+          else PIE_S_WAIT_VMCNT((S - 2) * CP + (S - 2) * 4 + 3);
+          wg_barrier();
+          if (AHEAD) load_a(Anext, 0, af[0]);
+        }
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          Pack16 w;
+          w.u = wreg[SLOT][s];
+          acc[i] = mfma32(af[AHEAD ? s & 1 : 0][i], w.h, acc[i]);
+        }
+        load_w(kt + S, SLOT, s);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // Prologue in the order of the main loop: copies of step j, weights of step j.  The loop below is entered
+    // unconditionally (every slice has at least S steps, the host sees to it): a branch around it would let the compiler
+    // move the weight requests that only the loop uses behind the wait that counts them.
+    issue_a(As0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) load_w(j, j, s);
+      __builtin_amdgcn_sched_barrier(0);
+      if (j == 0) issue_a(As1, 1);
+      if (j == 1 && S > 3) issue_a(As2, 2);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    PIE_S_WAIT_VMCNT((S - 2) * CP + S * 4);  // this wave's part of the first activation tile has arrived
+    wg_barrier();
+    if (AHEAD) load_a(As0, 0, af[0]);
+    int kt = 0;
+    using std::integral_constant;
+    if constexpr (S == 3) {
+      do {
+        step(std::false_type{}, integral_constant<int, 0>{}, As0, As1, As2, kt);
+        step(std::false_type{}, integral_constant<int, 1>{}, As1, As2, As0, kt + 1);
+        step(std::false_type{}, integral_constant<int, 2>{}, As2, As0, As1, kt + 2);
+        kt += 3;
+      } while (kt + 3 <= n);
+      if (kt < n) step(std::true_type{}, integral_constant<int, 0>{}, As0, As1, As2, kt);
+      if (kt + 1 < n) step(std::true_type{}, integral_constant<int, 1>{}, As1, As2, As0, kt + 1);
+    } else {
+      do {
+        step(std::false_type{}, integral_constant<int, 0>{}, As0, As1, As3, kt);
+        step(std::false_type{}, integral_constant<int, 1>{}, As1, As2, As0, kt + 1);
+        step(std::false_type{}, integral_constant<int, 2>{}, As2, As3, As1, kt + 2);
+        step(std::false_type{}, integral_constant<int, 3>{}, As3, As0, As2, kt + 3);
+        kt += 4;
+      } while (kt + 4 <= n);
+      if (kt < n) step(std::true_type{}, integral_constant<int, 0>{}, As0, As1, As3, kt);
+      if (kt + 1 < n) step(std::true_type{}, integral_constant<int, 1>{}, As1, As2, As0, kt + 1);
+      if (kt + 2 < n) step(std::true_type{}, integral_constant<int, 2>{}, As2, As3, As1, kt + 2);
+    }
+    PIE_S_WAIT_VMCNT(0);  // the surplus copies of the last steps land before the stages are used for anything else
+#endif
+  }
+  // 4 KiB pieces of LDS (one accumulator block of one wave) for exchanges between waves: piece p of the stages laid end
+  // to end
+  constexpr int PER_STAGE = STAGE * 2 / 4096;
+  auto lds_piece = [&](int p) {
+    const int st = p / PER_STAGE;
+    bf16_t* b = st == 0 ? As0 : st == 1 ? As1 : st == 2 ? As2 : As3;
+    return reinterpret_cast<float*>(b) + (p % PER_STAGE) * 1024;
+  };
+  __syncthreads();
+  if constexpr (KS > 1) {
+    static_assert((KS - 1) * WPS * MB <= S * PER_STAGE, "the slices' sums fit the stages");
+    if (ks > 0) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        float* d = lds_piece(((ks - 1) * WPS + wave % WPS) * MB + i);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) d[v * 64 + lane] = acc[i][v];
+      }
+    }
+    __syncthreads();
+    if (ks == 0) {
+#pragma unroll
+      for (int sl = 1; sl < KS; ++sl)
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          const float* d = lds_piece(((sl - 1) * WPS + wave) * MB + i);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][v] += d[v * 64 + lane];
+        }
+    }
+    __syncthreads();
+  }
+  if (PARTIAL) {
+    if (nb >= NB || ks > 0) return;
+    const int NP = NB * 32;
+    float* P = part + (int64_t)blockIdx.y * M * NP + nb * 32 + (lane & 31);  // raw sums: part[split][m][n_packed]
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int m = m0 + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+        if (m < M) {
+          if (NT) store_nt(P + (int64_t)m * NP, acc[i][v]);
+          else P[(int64_t)m * NP] = acc[i][v];
+        }
+      }
+    return;
+  }
+  const bool rows_full = m0 + BM <= M;
+  if constexpr (MODE == EPI_SWIGLU) {
+    // A gate block sits in an even wave, its up block in the wave after it, which hands its sums over, as many of its
+    // accumulator blocks at a time as the stages have room for from all pairs.
+    constexpr int AT_ONCE = MB < S * PER_STAGE / (WPS / 2) ? MB : S * PER_STAGE / (WPS / 2);
+    const int pair = (wave % WPS) >> 1;
+#pragma unroll
+    for (int i0 = 0; i0 < MB; i0 += AT_ONCE) {
+      if (i0 > 0) __syncthreads();
+      if ((wave & 1) && ks == 0) {
+#pragma unroll
+        for (int i = i0; i < MB && i < i0 + AT_ONCE; ++i) {
+          float* d = lds_piece(pair * AT_ONCE + i - i0);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) d[v * 64 + lane] = acc[i][v];
+        }
+      }
+      __syncthreads();
+      if (!(wave & 1) && ks == 0 && nb < NB) {
+#pragma unroll
+        for (int i = i0; i < MB && i < i0 + AT_ONCE; ++i) {
+          const float* d = lds_piece(pair * AT_ONCE + i - i0);
+          f32x16 up;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) up[v] = d[v * 64 + lane];
+          if (rows_full) epi_tile<MODE, true, NT>(epi, acc[i], up, m0 + i * 32, nb * 32, M, NB * 32, lane);
+          else epi_tile<MODE, false, NT>(epi, acc[i], up, m0 + i * 32, nb * 32, M, NB * 32, lane);
+        }
+      }
+    }
+  } else {
+    if (nb >= NB || ks > 0) return;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      if (rows_full) epi_tile<MODE, true, NT>(epi, acc[i], acc[i], m0 + i * 32, nb * 32, M, N, lane);
+      else epi_tile<MODE, false, NT>(epi, acc[i], acc[i], m0 + i * 32, nb * 32, M, N, lane);
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 // dispatch
 // ------------------------------------------------------------------------------------------------
 // Raises a kernel's dynamic LDS limit once per process and device (done: one bit per device), not per launch.
@@ -1126,6 +1381,67 @@ static bool tiled_ok(int M, int lda, int NB, int K) {
   return K % LG_BK == 0 && (int64_t)M * lda * 2 < ((int64_t)1 << 32) && (int64_t)NB * 32 * K * 2 < ((int64_t)1 << 32);
 }
 
+// The forms of gemm_stream and what a k step of a slice takes with one workgroup on every compute unit: step_us, and
+// once per workgroup (the ring's fill, the slices' sums, the epilogue) wg_us.
+struct StreamForm { int mb, ks; double step_us, wg_us; };
+static constexpr StreamForm STREAM_FORMS[] = {{2, 1, 0.57, 3.6}, {2, 2, 0.64, 4.0}, {2, 4, 0.75, 4.2}, {3, 2, 0.86, 2.7}, {3, 4, 1.07, 4.1},
+                                              {4, 1, 0.75, 3.1}, {4, 2, 0.95, 3.3}, {5, 1, 0.83, 3.6}, {5, 2, 1.09, 3.7}, {6, 1, 0.94, 2.3}};
+struct StreamPlan {
+  int form;         // index into STREAM_FORMS, -1: none fits
+  int splits, kts;  // splits of K and k steps per split, a multiple of the form's ks
+  double us;
+};
+
+// The estimate: rounds of one workgroup per compute unit, the weights at 6.36 TB/s (a twentieth more time where two row
+// tiles read them), the two added by their cubes as in plan_tiled, 3 us for a launch, the partial sums of a split written and read
+// once.  Fitted to sweeps of every form and 1..16 splits over the same products as plan_tiled's at 1 to 400 rows; the form
+// that this and plan_tiled's estimate pick together is within 2% of the fastest on average.
+static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) {
+  const int KT = K / LG_BK, NP = NB * 32;
+  const double stream_us = (double)NP * K * 2 / 6.36e6;
+  StreamPlan best{-1, 1, KT, 1e30};
+  for (int f = 0; f < (int)(sizeof(STREAM_FORMS) / sizeof(STREAM_FORMS[0])); ++f) {
+    const StreamForm& F = STREAM_FORMS[f];
+    if (KT % F.ks != 0 || (M <= 64 ? F.mb > 2 : F.mb == 2)) continue;
+    const int tiles_m = (M + F.mb * 32 - 1) / (F.mb * 32), tiles_n = (NB + 8 / F.ks - 1) / (8 / F.ks);
+    if (tiles_m > 2) continue;  // (the weights would be fetched that often)
+    const double stream = tiles_m > 1 ? 1.05 * stream_us : stream_us;
+    for (int splits = 1, last = 0; splits <= 16; ++splits) {
+      const int kts = (KT / F.ks + splits - 1) / splits * F.ks;
+      if (kts == last) continue;
+      last = kts;
+      const int n = (KT + kts - 1) / kts;
+      if ((KT - (n - 1) * kts) / F.ks < 4) continue;  // the ring is three or four steps deep, and every slice fills it
+      if (n > 1 && (size_t)n * M * NP > ws_elems) break;
+      const int64_t wgs = (int64_t)tiles_m * tiles_n * n;
+      const double compute = (kts / F.ks * F.step_us + F.wg_us) * (double)((wgs + n_cus - 1) / n_cus);
+      if (compute + 3.0 >= best.us) continue;
+      double us = 3.0 + std::cbrt(compute * compute * compute + stream * stream * stream);
+      if (n > 1) us += 2.5 + (double)n * M * NP * 8 / 5.5e6;
+      if (us < best.us) best = StreamPlan{f, n, kts, us};
+    }
+  }
+  return best;
+}
+
+// Where gemm_stream takes a product (tiled_ok holds): weights of 32 MiB and more.  Up to 64 rows gemm_skinny does as well
+// with what streams in under 8 us and with most split products (6144 x 4096 at 16 rows 15.4 us there and 16 here, 4096 x
+// 14336 24.0 and 24.5), so there it has to be an unsplit product of 48 MB and more (28672 x 4096 at 16 rows 43 -> 40 us,
+// 16384 x 2048 23 -> 15, 32000 x 2048 at 64 rows 36 -> 32) or weights of 128 MiB and more (10240 x 8192 at 33 rows 37 -> 33,
+// 8192 x 28672 79 -> 76); the widest outputs, where gemm_skinny gives a wave two column blocks, stay with it (128256 x 4096
+// at 33 rows 165 us there, 175 here).  Above 64 rows the two estimates decide, 0.8 us in favour of the tiled kernels, whose
+// smaller products are that much better than estimated.
+static bool takes_stream(int M, int NB, int K, size_t ws_elems, int n_cus, const TiledPlan* tiled, StreamPlan& p) {
+  const int64_t bytes = (int64_t)NB * 32 * K * 2;
+  if (M > 384 || bytes < (M <= 64 ? 48000000 : (int64_t)1 << 25)) return false;
+  if (M <= 64 && (NB + 3) / 4 > n_cus * (M <= 32 ? 3 : 2)) return false;
+  const bool unsplit = M <= 64 && bytes < ((int64_t)1 << 27);
+  p = plan_stream(M, NB, K, unsplit ? 0 : ws_elems, n_cus);
+  if (p.form < 0) return false;
+  if (unsplit) return ((int64_t)NB * STREAM_FORMS[p.form].ks + 7) / 8 * 4 >= n_cus * 3;
+  if (M <= 64) return true;
+  return p.us + 0.8 < tiled->us;
+}
 template <int MODE, bool PARTIAL>
 static hipError_t run_tiles(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, const TiledPlan& p,
                             float* ws, hipStream_t s) {
@@ -1140,14 +1456,67 @@ static hipError_t run_tiles(const bf16_t* A, int lda, int M, const PackedWeight&
   return hipGetLastError();
 }
 
+template <int MODE, int MB, int KS>
+static hipError_t run_stream_form(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, const StreamPlan& p,
+                                  float* ws, hipStream_t s) {
+  const int tiles_n = (W.NB + 8 / KS - 1) / (8 / KS), tiles_m = (M + MB * 32 - 1) / (MB * 32);
+  const dim3 grid(tiles_m * tiles_n, p.splits), block(512);
+  // (raw partial sums depend on the mode by how they are stored only)
+  constexpr int PART_MODE = MODE == EPI_STORE_F32 || MODE == EPI_RESID_OUT ? EPI_RESID_OUT : EPI_RESID_EMBED;
+  if (p.splits == 1) gemm_stream_kernel<MODE, false, MB, KS><<<grid, block, 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, p.kts, ws);
+  else gemm_stream_kernel<PART_MODE, true, MB, KS><<<grid, block, 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, p.kts, ws);
+  return hipGetLastError();
+}
+
+template <int MODE>
+static hipError_t run_stream(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, const StreamPlan& p, float* ws,
+                             hipStream_t s) {
+  const StreamForm& F = STREAM_FORMS[p.form];
+  switch (F.mb * 8 + F.ks) {
+    case 2 * 8 + 1: return run_stream_form<MODE, 2, 1>(A, lda, M, W, epi, p, ws, s);
+    case 2 * 8 + 2: return run_stream_form<MODE, 2, 2>(A, lda, M, W, epi, p, ws, s);
+    case 2 * 8 + 4: return run_stream_form<MODE, 2, 4>(A, lda, M, W, epi, p, ws, s);
+    case 3 * 8 + 2: return run_stream_form<MODE, 3, 2>(A, lda, M, W, epi, p, ws, s);
+    case 3 * 8 + 4: return run_stream_form<MODE, 3, 4>(A, lda, M, W, epi, p, ws, s);
+    case 4 * 8 + 1: return run_stream_form<MODE, 4, 1>(A, lda, M, W, epi, p, ws, s);
+    case 4 * 8 + 2: return run_stream_form<MODE, 4, 2>(A, lda, M, W, epi, p, ws, s);
+    case 5 * 8 + 1: return run_stream_form<MODE, 5, 1>(A, lda, M, W, epi, p, ws, s);
+    case 5 * 8 + 2: return run_stream_form<MODE, 5, 2>(A, lda, M, W, epi, p, ws, s);
+    case 6 * 8 + 1: return run_stream_form<MODE, 6, 1>(A, lda, M, W, epi, p, ws, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+// What follows a product split along K: the caller's next kernel sums the partials, or the epilogue kernel does.
+template <int MODE>
+static hipError_t finish_split(int splits, int M, const PackedWeight& W, const EpiArgs& epi, float* ws, hipStream_t s, int* defer) {
+  if (defer) { *defer = splits; return hipSuccess; }
+  const int NP = W.NB * 32, cols = (MODE == EPI_SWIGLU) ? NP / 2 : W.N;
+  const int64_t total = (int64_t)M * (cols / 4);
+  splitk_epilogue_kernel<MODE><<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(ws, splits, M, W.N, NP, epi);
+  return hipGetLastError();
+}
+
 template <int MODE>
 static hipError_t run_mode(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, float* ws,
                            size_t ws_elems, int n_cus, hipStream_t s, int* defer) {
   if (M <= 0) return hipSuccess;
-  if (M <= 32) return run_skinny<1, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
-  if (M <= 64) return run_skinny<2, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
-  if (tiled_ok(M, lda, W.NB, W.K)) {
+  const bool tiled = tiled_ok(M, lda, W.NB, W.K);
+  StreamPlan sp;
+  if (M <= 64) {
+    if (tiled && takes_stream(M, W.NB, W.K, ws_elems, n_cus, nullptr, sp)) {
+      hipError_t e = run_stream<MODE>(A, lda, M, W, epi, sp, ws, s);
+      return e != hipSuccess || sp.splits == 1 ? e : finish_split<MODE>(sp.splits, M, W, epi, ws, s, defer);
+    }
+    return M <= 32 ? run_skinny<1, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer)
+                   : run_skinny<2, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
+  }
+  if (tiled) {
     const TiledPlan p = plan_tiled(M, W.NB, W.K, ws_elems, n_cus);
+    if (takes_stream(M, W.NB, W.K, ws_elems, n_cus, &p, sp)) {
+      hipError_t e = run_stream<MODE>(A, lda, M, W, epi, sp, ws, s);
+      return e != hipSuccess || sp.splits == 1 ? e : finish_split<MODE>(sp.splits, M, W, epi, ws, s, defer);
+    }
     if (p.full_rows > 0) {
       hipError_t e = run_tiles<MODE, false>(A, lda, p.full_rows, W, epi, p, nullptr, s);
       if (e != hipSuccess) return e;
@@ -1156,12 +1525,7 @@ static hipError_t run_mode(const bf16_t* A, int lda, int M, const PackedWeight& 
     }
     if (p.splits == 1) return run_tiles<MODE, false>(A, lda, M, W, epi, p, nullptr, s);
     hipError_t e = run_tiles<MODE, true>(A, lda, M, W, epi, p, ws, s);
-    if (e != hipSuccess) return e;
-    if (defer) { *defer = p.splits; return hipSuccess; }
-    const int NP = W.NB * 32, cols = (MODE == EPI_SWIGLU) ? NP / 2 : W.N;
-    const int64_t total = (int64_t)M * (cols / 4);
-    splitk_epilogue_kernel<MODE><<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(ws, p.splits, M, W.N, NP, epi);
-    return hipGetLastError();
+    return e != hipSuccess ? e : finish_split<MODE>(p.splits, M, W, epi, ws, s, defer);
   }
   if (M <= 128) return run_skinny<4, MODE>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer);
   if constexpr (MODE != EPI_SWIGLU) {  // (eight row blocks of gate/up pairs would not fit the register file)
@@ -1208,4 +1572,17 @@ void product_plan(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out[4
       fetched[(size_t)split * tiles_n + tn] |= 1u << ((split * (int64_t)n + id) % 8);
     }
   for (uint8_t f : fetched) out[3] += __builtin_popcount(f);
+}
+
+void product_stream(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out[3]) {
+  out[0] = out[1] = out[2] = 0;
+  const int NB = (N + 31) / 32;
+  if (!tiled_ok(M, K, NB, K)) return;
+  StreamPlan p;
+  TiledPlan t{};
+  if (M > 64) t = plan_tiled(M, NB, K, ws_elems, n_cus);
+  if (!takes_stream(M, NB, K, ws_elems, n_cus, &t, p)) return;
+  out[0] = STREAM_FORMS[p.form].mb * 32;
+  out[1] = STREAM_FORMS[p.form].ks;
+  out[2] = p.splits;
 }

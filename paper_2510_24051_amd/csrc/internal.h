@@ -248,6 +248,7 @@ hipError_t launch_gemm(const bf16_t* A, int lda, int M, const PackedWeight& W, c
                        size_t splitk_elems, int n_cus, hipStream_t s, int* deferred_splits = nullptr);
 
 void product_plan(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out[4]);  // see pie_product_plan
+void product_stream(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out[3]);  // see pie_product_stream
 
 struct AttnArgs {
   const bf16_t* q;   // [T, q_stride] rotated queries

@@ -1480,6 +1480,13 @@ extern "C" pie_status pie_product_plan(int32_t rows, int32_t n_out, int32_t k, i
   });
 }
 
+extern "C" pie_status pie_product_stream(int32_t rows, int32_t n_out, int32_t k, int64_t workspace_floats, int32_t n_cus,
+                                         int64_t* out) {
+  if (rows <= 0 || n_out <= 0 || k <= 0 || k % 8 != 0 || workspace_floats < 0 || n_cus <= 0 || !out) return PIE_EINVAL;
+  product_stream(rows, n_out, k, (size_t)workspace_floats, n_cus, out);
+  return PIE_OK;
+}
+
 extern "C" pie_status pie_batch_work(const pie_batch* b, int64_t* out) {
   if (!b || !out) return PIE_EINVAL;
   for (int i = 0; i < 6; ++i) out[i] = b->work[i];

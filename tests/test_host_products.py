@@ -1,7 +1,7 @@
 """How products are cut into tiles (pie_product_plan), without a GPU."""
 import pytest
 
-from paper_2510_24051_amd import PieError, product_plan
+from paper_2510_24051_amd import PieError, product_plan, product_stream
 
 WS = 256 * 28672 * 8  # the 8B-shaped layer's workspace
 LM_HEAD = [(128256, 4096), (32000, 2048), (128256, 8192)]
@@ -58,3 +58,31 @@ def test_plan_picks_a_form_near_the_fastest_measured(rows, n_out, k, us):
     p = product_plan(rows, n_out, k, 256 * max(28672, 2 * k, n_out if n_out <= 57344 else 0) * 8)
     assert p["whole_rows"] == 0
     assert us[p["tile_rows"], p["splits"]] <= 1.05 * min(us.values())
+
+
+@pytest.mark.parametrize("rows", [1, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 256, 257, 320, 321, 384])
+@pytest.mark.parametrize("n_out,k", LM_HEAD + [(28672, 4096), (4096, 14336), (6144, 4096), (4096, 4096), (16384, 2048), (2048, 8192),
+                                               (10240, 8192), (8192, 28672), (24608, 1088), (4160, 4160)])
+@pytest.mark.parametrize("ws", [0, 3 * 4096 * 100, WS])
+def test_streamed_products_fit_their_form(rows, n_out, k, ws):
+    """At most two row tiles, parts of K that every slice of every workgroup gets at least a full ring of steps of, and room
+    for the partial sums."""
+    p = product_stream(rows, n_out, k, ws)
+    if p["tile_rows"] == 0:
+        return
+    assert p["tile_rows"] in (64, 96, 128, 160, 192) and -(-rows // p["tile_rows"]) <= 2
+    steps, parts, slices = k // 64, p["splits"], p["k_slices"]
+    assert steps % slices == 0
+    per = -(-(steps // slices) // parts)       # k steps of a slice, and what is left for the last part
+    assert -(-(steps // slices) // per) == parts and steps // slices - (parts - 1) * per >= 4
+    assert parts == 1 or parts * rows * ((n_out + 31) // 32 * 32) <= ws
+
+
+def test_what_is_not_streamed():
+    assert product_stream(385, 28672, 4096, WS)["tile_rows"] == 0         # more rows than two tiles
+    assert product_stream(100, 28672, 4096 + 32, WS)["tile_rows"] == 0    # contraction not a multiple of 64
+    assert product_stream(100, 2048, 2048, WS)["tile_rows"] == 0          # 8 MiB of weights
+    assert product_stream(16, 128256, 4096, WS)["tile_rows"] == 0         # the widest outputs at few rows
+    for bad in ((0, 32, 64, 0), (1, 0, 64, 0), (1, 32, 0, 0), (1, 32, 63, 0), (1, 32, 64, -1)):
+        with pytest.raises(PieError):
+            product_stream(*bad)

@@ -1343,7 +1343,8 @@ static TiledPlan plan_tiled(int M, int NB, int K, size_t ws_elems, int n_cus) {
   const int tiles_n = (NB + 7) / 8, KT = K / LG_BK, NP = NB * 32;
   const double stream_us = (double)NP * K * 2 / 5.4e6;
   TiledPlan best{0, 1, KT, 0, 1e30};
-  auto main_us = [&](double compute) { return 3.0 + std::cbrt(compute * compute * compute + stream_us * stream_us * stream_us); };
+  const double stream_cube = stream_us * stream_us * stream_us;
+  auto main_us = [&](double compute) { return 3.0 + std::cbrt(compute * compute * compute + stream_cube); };
   auto steps_us = [&](int rows, int64_t wgs) {  // time of one k step of all workgroups
     const int slots = rows == 256 ? n_cus : 2 * n_cus;
     const double one = rows == 96 ? 0.70 : rows == 128 ? 0.75 : 1.35, full = rows == 96 ? 1.42 : rows == 128 ? 1.65 : 1.55;
@@ -1359,9 +1360,10 @@ static TiledPlan plan_tiled(int M, int NB, int K, size_t ws_elems, int n_cus) {
       last = kts;
       const int n = (KT + kts - 1) / kts;
       if (n > 1 && (size_t)n * M * NP > ws_elems) break;
-      double us = main_us(kts * steps_us(rows, (int64_t)tiles_m * tiles_n * n));
-      if (n > 1) us += 3.0 + (double)n * M * NP * 8 / 6e6;
-      if (us < best.us) best = TiledPlan{rows, n, kts, 0, us};
+      const double compute = kts * steps_us(rows, (int64_t)tiles_m * tiles_n * n);
+      const double parts_us = n > 1 ? 3.0 + (double)n * M * NP * 8 / 6e6 : 0.0, left = best.us - 3.0 - parts_us;
+      if (left <= 0.0 || compute * compute * compute + stream_cube >= left * left * left) continue;
+      best = TiledPlan{rows, n, kts, 0, main_us(compute) + parts_us};
     }
   }
   // whole 256-row tiles whose remainder would open one more round of them
@@ -1415,10 +1417,10 @@ static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) 
       if (n > 1 && (size_t)n * M * NP > ws_elems) break;
       const int64_t wgs = (int64_t)tiles_m * tiles_n * n;
       const double compute = (kts / F.ks * F.step_us + F.wg_us) * (double)((wgs + n_cus - 1) / n_cus);
-      if (compute + 3.0 >= best.us) continue;
-      double us = 3.0 + std::cbrt(compute * compute * compute + stream * stream * stream);
-      if (n > 1) us += 2.5 + (double)n * M * NP * 8 / 5.5e6;
-      if (us < best.us) best = StreamPlan{f, n, kts, us};
+      const double rest = 3.0 + (n > 1 ? 2.5 + (double)n * M * NP * 8 / 5.5e6 : 0.0), left = best.us - rest;
+      const double cubes = compute * compute * compute + stream * stream * stream;
+      if (left <= 0.0 || cubes >= left * left * left) continue;  // (no root for what cannot win: the plan is made per launch)
+      best = StreamPlan{f, n, kts, rest + std::cbrt(cubes)};
     }
   }
   return best;

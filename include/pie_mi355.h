@@ -257,7 +257,8 @@ pie_status pie_read_tap(pie_ctx* ctx, int32_t which, void* dst, int64_t n_elemen
 
 /* Stage timing.  When enabled, pie_forward / pie_get_next_dist bracket each stage with HIP events
  * on the context's stream; pie_stage_times synchronises and returns the milliseconds of the last
- * call per stage (host float[PIE_N_STAGES]; 0 for stages that did not run). */
+ * call per stage (host float[PIE_N_STAGES]; 0 for stages that did not run).  While it is on, prefill and decode attention
+ * of a batch are launched apart. */
 enum {
   PIE_STAGE_NORM1 = 0, PIE_STAGE_QKV = 1, PIE_STAGE_ROPE_APPEND = 2, PIE_STAGE_ATTN_DECODE = 3,
   PIE_STAGE_ATTN_PREFILL = 4, PIE_STAGE_ATTN_MERGE = 5, PIE_STAGE_OPROJ = 6, PIE_STAGE_NORM2 = 7,

@@ -14,6 +14,7 @@
 //   attn_prefill : one workgroup per (request, 32-token query block, kv head), one wave per query head of
 //                  the group; K/V page blocks shared through a four-stage LDS ring filled by direct-to-LDS
 //                  loads; causal requests stop at the block's last visible page.
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -275,16 +276,16 @@ __device__ __forceinline__ uint32_t key_bits4(int kv_len, int lim, bool has_bitm
 // (for bitmap requests) the mask words of pairs requested before a boundary are loaded at the boundary.
 // NT: the K/V blocks are loaded non-temporally (batches in which no page is read twice).
 template <int D, bool NT>
-__global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnArgs a, const DecodeWave* __restrict__ waves,
-                                                             const int2* __restrict__ wave_pg, int slots,
-                                                             const DecodeSeg* __restrict__ segs,
-                                                             const DecodeCol* __restrict__ cols, int n_waves,
-                                                             int rows_cap, float* __restrict__ part_o,
-                                                             float* __restrict__ part_ml) {
+__device__ __forceinline__ void attn_decode_block(const AttnArgs& a, int block, const DecodeWave* __restrict__ waves,
+                                                  const int2* __restrict__ wave_pg, int slots,
+                                                  const DecodeSeg* __restrict__ segs,
+                                                  const DecodeCol* __restrict__ cols, int n_waves,
+                                                  int rows_cap, float* __restrict__ part_o,
+                                                  float* __restrict__ part_ml) {
   constexpr int KS = D / 32;  // K operands per page
   constexpr int DB = D / 16;  // 16-row blocks of O^T
   const int lane = threadIdx.x & 63;
-  const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const int gw = __builtin_amdgcn_readfirstlane(block * 4 + (threadIdx.x >> 6));
   if (gw >= n_waves) return;
   const int G = a.Hq / a.Hkv;
   const int qcol = lane & 15, g4 = lane >> 4;
@@ -459,6 +460,16 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnArgs a, const D
   end_segment();
 }
 
+template <int D, bool NT>
+__global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnArgs a, const DecodeWave* __restrict__ waves,
+                                                             const int2* __restrict__ wave_pg, int slots,
+                                                             const DecodeSeg* __restrict__ segs,
+                                                             const DecodeCol* __restrict__ cols, int n_waves,
+                                                             int rows_cap, float* __restrict__ part_o,
+                                                             float* __restrict__ part_ml) {
+  attn_decode_block<D, NT>(a, blockIdx.x, waves, wave_pg, slots, segs, cols, n_waves, rows_cap, part_o, part_ml);
+}
+
 // One wave per (decode-path request, kv head, query row): lanes first share the (max, sum) pairs of the row's
 // partials (one per segment in which the request has a column), then each lane combines D/64 output elements
 // over the partials with independent loads.
@@ -557,10 +568,10 @@ __device__ __forceinline__ void lds_copy_run(const char* src, char* dst) {
 // (134 MB) and the walk takes 44 us, bound by the MFMAs and vector work of the pair weights (16 steps, 1.9 us for two
 // workgroups on a compute unit), which are done for all columns whoever sees the page.
 template <int D, int G, bool LO, bool SPLIT, bool SHARED = false>
-__global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, const PrefillItem* __restrict__ items,
-                                                                 float* __restrict__ part_o, float* __restrict__ part_ml,
-                                                                 const SharedGroup* __restrict__ sgroups = nullptr,
-                                                                 const DecodeCol* __restrict__ scols = nullptr) {
+__device__ __forceinline__ void attn_prefill_block(const AttnArgs& a, const PrefillItem it, int part_index,
+                                                   float* __restrict__ part_o, float* __restrict__ part_ml,
+                                                   const SharedGroup* __restrict__ sgroups = nullptr,
+                                                   const DecodeCol* __restrict__ scols = nullptr) {
   static_assert(!SHARED || (LO && SPLIT && G * 32 == SHARED_COLS), "shared groups: four waves, weights as pairs, cut");
   constexpr int BLK = 2 * PAGE * D;            // elements of one (page, head) block: K part then V part
   constexpr int PIECES = BLK * 2 / 1024;       // 1 KiB copy instructions per page block
@@ -568,9 +579,8 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
   static_assert(IPW * G == 2 * PIECES && 2 * IPW <= 63, "group size must divide the copy instructions");
   __shared__ __align__(16) bf16_t st0[2 * BLK], st1[2 * BLK], st2[2 * BLK], st3[2 * BLK];
   const int lane = threadIdx.x & 63, hg = threadIdx.x >> 6;
-  const PrefillItem it = items[blockIdx.x];
   if (it.r < 0) return;  // padding of the per-XCD lists (uniform over the workgroup)
-  if (SPLIT && (int)blockIdx.y >= it.n_parts) return;
+  if (SPLIT && part_index >= it.n_parts) return;
   const int hk = it.hk;
   const int qcol = lane & 31, g = lane >> 5, m = lane & 31;
   ReqInfo rq{};
@@ -612,7 +622,7 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
       v_end = pages < v_end ? pages : v_end;
     }
   }
-  const int first_pair = SPLIT && it.n_parts > 1 ? blockIdx.y * it.per : 0;
+  const int first_pair = SPLIT && it.n_parts > 1 ? part_index * it.per : 0;
   const int all_pairs = (v_end + 1) / 2;
   const int n_pairs = SPLIT && it.n_parts > 1 ? min(all_pairs - first_pair, it.per) : all_pairs;
   if (n_pairs > 0) {
@@ -748,7 +758,7 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
   const float l_tot = sum_xor32(st.l);
   if (!valid) return;
   if (SHARED || (SPLIT && it.n_parts > 1)) {  // (max, sum, O) of this part, for the merge kernel
-    const int64_t prow = ((int64_t)(it.slot0 + (int)blockIdx.y) * G + hg) * 32 + qcol;
+    const int64_t prow = ((int64_t)(it.slot0 + part_index) * G + hg) * 32 + qcol;
     if (g == 0) {
       part_ml[prow * 2] = st.m;
       part_ml[prow * 2 + 1] = l_tot;
@@ -774,6 +784,53 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
       for (int e = 0; e < 4; ++e) o4[e] = f32_to_bf16(st.o[b][q4 * 4 + e] * inv);
       *reinterpret_cast<bf16x4*>(orow + b * 32 + q4 * 8 + g * 4) = o4;
     }
+}
+
+template <int D, int G, bool LO, bool SPLIT, bool SHARED = false>
+__global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, const PrefillItem* __restrict__ items,
+                                                                 float* __restrict__ part_o, float* __restrict__ part_ml,
+                                                                 const SharedGroup* __restrict__ sgroups = nullptr,
+                                                                 const DecodeCol* __restrict__ scols = nullptr) {
+  attn_prefill_block<D, G, LO, SPLIT, SHARED>(a, items[blockIdx.x], blockIdx.y, part_o, part_ml, sgroups, scols);
+}
+
+// Both attentions of a batch in one launch (groups of four query heads, decode pages read once): the prefill blocks (or the
+// tiles of shared groups) are bound by matrix and vector work, the decode waves by HBM, and each alone leaves the other's
+// resource idle.  Both have workgroups of four waves at two per compute unit.  Chunks of one workgroup per compute unit of
+// either kind alternate in dispatch order (a multiple of 8, so that prefill workgroups stay on the XCD the host listed them
+// for) until one kind has run out: a compute unit then holds one of each.  Measured, two launches against one: 2 prompts of
+// 150 tokens beside 24 decode requests (D = 64; 80 and 455 workgroups) 22 + 17 -> 26 us; 256 branches on a shared prefix
+// 41 + 20 -> 51 (in chunks of 64 60); 8 x 1024 tokens beside 128 decode requests 226 + 174 -> 375 (there the prefill blocks'
+// own copies out of L2 compete with the decode stream).
+struct DecodeWork {
+  const DecodeWave* waves;
+  const int2* wave_pg;
+  const DecodeSeg* segs;
+  const DecodeCol* cols;
+  float *part_o, *part_ml;
+  int slots, n_waves, rows_cap;
+};
+template <int D, bool SPLIT, bool SHARED>
+__global__ __launch_bounds__(256, 2) void attn_both_kernel(AttnArgs a, const PrefillItem* __restrict__ items, int n_items,
+                                                           int n_prefill, float* __restrict__ part_o, float* __restrict__ part_ml,
+                                                           const SharedGroup* __restrict__ sgroups,
+                                                           const DecodeCol* __restrict__ scols, DecodeWork d, int chunk,
+                                                           int paired) {
+  int b = blockIdx.x;
+  bool decode;
+  if (b < 2 * paired) {
+    const int q = b / (2 * chunk), r = b % (2 * chunk);
+    decode = r >= chunk;
+    b = q * chunk + (decode ? r - chunk : r);
+  } else {
+    b -= paired;
+    decode = b >= n_prefill;  // (`paired` covers all of the kind that runs out first)
+  }
+  if (decode) {
+    attn_decode_block<D, true>(a, b, d.waves, d.wave_pg, d.slots, d.segs, d.cols, d.n_waves, d.rows_cap, d.part_o, d.part_ml);
+  } else if (b < n_prefill) {
+    attn_prefill_block<D, 4, SHARED, SPLIT, SHARED>(a, items[SPLIT ? b % n_items : b], SPLIT ? b / n_items : 0, part_o, part_ml, sgroups, scols);
+  }
 }
 
 // Combines the parts of the query blocks that were cut (see PrefillItem): workgroup (block, head of the group, 8 (D = 128)
@@ -961,4 +1018,26 @@ hipError_t launch_attn_prefill_merge(const AttnArgs& a, const PrefillItem* items
   else if (a.D == 64) attn_prefill_merge_kernel<64><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
   else return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+hipError_t launch_attn_both(const AttnArgs& a, const PrefillItem* items, int n_items, int max_parts, bool shared, const SharedGroup* groups,
+                            const DecodeCol* scols, float* pre_o, float* pre_ml, const DecodeWave* waves, const int2* wave_pg,
+                            int slots, const DecodeSeg* segs, const DecodeCol* cols, int n_waves, int rows_cap, float* part_o,
+                            float* part_ml, int n_cus, hipStream_t s) {
+  if (slots < 2 || slots > 128 || (slots & 1) || n_items <= 0 || n_waves <= 0) return hipErrorInvalidValue;
+  const int n_prefill = n_items * max_parts, n_decode = (n_waves + 3) / 4;
+  const int chunk = (n_cus + 7) / 8 * 8;
+  const int paired = std::min((n_prefill + chunk - 1) / chunk, (n_decode + chunk - 1) / chunk) * chunk;
+  const int grid = 2 * paired + std::max(0, std::max(n_prefill, n_decode) - paired);
+  const DecodeWork d{waves, wave_pg, segs, cols, part_o, part_ml, slots, n_waves, rows_cap};
+  auto run = [&](auto d_c) {
+    constexpr int D = decltype(d_c)::value;
+    if (shared) attn_both_kernel<D, true, true><<<grid, 256, 0, s>>>(a, items, n_items, n_prefill, pre_o, pre_ml, groups, scols, d, chunk, paired);
+    else if (max_parts > 1) attn_both_kernel<D, true, false><<<grid, 256, 0, s>>>(a, items, n_items, n_prefill, pre_o, pre_ml, groups, scols, d, chunk, paired);
+    else attn_both_kernel<D, false, false><<<grid, 256, 0, s>>>(a, items, n_items, n_prefill, pre_o, pre_ml, groups, scols, d, chunk, paired);
+    return hipGetLastError();
+  };
+  if (a.D == 128) return run(std::integral_constant<int, 128>{});
+  if (a.D == 64) return run(std::integral_constant<int, 64>{});
+  return hipErrorInvalidValue;
 }

@@ -276,6 +276,12 @@ hipError_t launch_attn_shared(const AttnArgs& a, const PrefillItem* items, int n
 // max_parts: most parts an item is cut into (part_o / part_ml hold their results when it is more than one)
 hipError_t launch_attn_prefill(const AttnArgs& a, const PrefillItem* items, int n_items, bool pair_weights, int max_parts,
                                float* part_o, float* part_ml, hipStream_t s);
+// the blocks of launch_attn_prefill (plain weights) or of launch_attn_shared (shared) and launch_attn_decode (pages read once)
+// in one launch; four query heads per kv head
+hipError_t launch_attn_both(const AttnArgs& a, const PrefillItem* items, int n_items, int max_parts, bool shared, const SharedGroup* groups,
+                            const DecodeCol* scols, float* pre_o, float* pre_ml, const DecodeWave* waves, const int2* wave_pg,
+                            int slots, const DecodeSeg* segs, const DecodeCol* cols, int n_waves, int rows_cap, float* part_o,
+                            float* part_ml, int n_cus, hipStream_t s);
 hipError_t launch_attn_prefill_merge(const AttnArgs& a, const PrefillItem* items, int n_items, const float* part_o,
                                      const float* part_ml, hipStream_t s);
 

@@ -1581,23 +1581,34 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   a.q = c->qkv; a.q_stride = QKV; a.kv = kv_layer; a.out = c->attn; a.Hq = Hq; a.Hkv = Hkv; a.D = D;
   a.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   a.reqs = b->reqs; a.visit_phys = b->visit_phys; a.visit_logical = b->visit_logical; a.visit_pairs = b->visit_pairs; a.mask_words = b->mask_words;
-  // Prefill attention first: it is bound by arithmetic, so the write-back of the lines the rotary step left dirty
-  // (q rows and appended K/V of every prefill token) happens underneath it instead of slowing the decode kernel,
-  // which is bound by HBM reads.
+  // Where the prefill (or shared-group) workgroups and the decode waves fit one launch they share it, the one bound by
+  // arithmetic, the other by HBM (launch_attn_both); stage timing keeps them apart.  Otherwise prefill attention goes first: the
+  // write-back of the lines the rotary step left dirty (q rows and appended K/V of every prefill token) then happens
+  // underneath it instead of slowing the decode kernel.
+  const size_t shared_row0 = (size_t)b->n_dsegs * b->rows_cap;
+  float *const shared_o = b->part_o + shared_row0 * D, *const shared_ml = b->part_ml + shared_row0 * 2;
+  const bool both = !c->timing && b->n_dwaves > 0 && b->dec_read_once && (b->n_pwork > 0 ? Hq == 4 * Hkv : b->n_sitems > 0);
+  const bool both_shared = both && b->n_pwork == 0;
   if (b->n_pitems > 0) {
     tm.begin(PIE_STAGE_ATTN_PREFILL);
-    HIP_TRY(c, launch_attn_prefill(a, b->pitems, b->n_pwork, false, b->max_parts, b->ppart_o, b->ppart_ml, s));
+    if (!both || both_shared) HIP_TRY(c, launch_attn_prefill(a, b->pitems, b->n_pwork, false, b->max_parts, b->ppart_o, b->ppart_ml, s));
     HIP_TRY(c, launch_attn_prefill(a, b->pitems + b->n_pwork, b->n_pwork_lo, true, b->max_parts_lo, b->ppart_o, b->ppart_ml, s));
-    HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit, b->n_psplit, b->ppart_o, b->ppart_ml, s));
+    if (!both || both_shared) HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit, b->n_psplit, b->ppart_o, b->ppart_ml, s));
     tm.end(PIE_STAGE_ATTN_PREFILL);
   }
   if (b->n_dec_reqs > 0) {
     tm.begin(PIE_STAGE_ATTN_DECODE);
-    const size_t shared_row0 = (size_t)b->n_dsegs * b->rows_cap;
-    HIP_TRY(c, launch_attn_shared(a, b->sitems, b->n_sitems, b->max_sparts, b->sgroups, b->scols, b->part_o + shared_row0 * D,
-                                  b->part_ml + shared_row0 * 2, s));
-    HIP_TRY(c, launch_attn_decode(a, b->dwaves, b->wave_pg, b->dslots, b->dsegs, b->dcols, b->n_dwaves, b->rows_cap, b->part_o, b->part_ml,
-                                  b->dec_read_once, s));
+    if (!both_shared) HIP_TRY(c, launch_attn_shared(a, b->sitems, b->n_sitems, b->max_sparts, b->sgroups, b->scols, shared_o, shared_ml, s));
+    if (both) {
+      HIP_TRY(c, launch_attn_both(a, both_shared ? b->sitems : b->pitems, both_shared ? b->n_sitems : b->n_pwork,
+                                  both_shared ? b->max_sparts : b->max_parts, both_shared, b->sgroups, b->scols,
+                                  both_shared ? shared_o : b->ppart_o, both_shared ? shared_ml : b->ppart_ml, b->dwaves, b->wave_pg, b->dslots,
+                                  b->dsegs, b->dcols, b->n_dwaves, b->rows_cap, b->part_o, b->part_ml, c->wave_slots / 8, s));
+      if (!both_shared) HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit, b->n_psplit, b->ppart_o, b->ppart_ml, s));
+    } else {
+      HIP_TRY(c, launch_attn_decode(a, b->dwaves, b->wave_pg, b->dslots, b->dsegs, b->dcols, b->n_dwaves, b->rows_cap, b->part_o, b->part_ml,
+                                    b->dec_read_once, s));
+    }
     tm.end(PIE_STAGE_ATTN_DECODE);
     tm.begin(PIE_STAGE_ATTN_MERGE);
     HIP_TRY(c, launch_attn_merge(a, b->dec_reqs, b->n_dec_reqs, b->mref_indptr, b->mrefs, b->dec_rows, b->part_o, b->part_ml, s));

@@ -55,12 +55,11 @@ struct NormPartial {
   float* wide;          // [rows, H] fp32 destination of residual + sum
 };
 
+// id: the row's Embed, for the sources that read one.
 template <int SRC>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ xin, const int32_t* __restrict__ ids,
-                                                      const bf16_t* __restrict__ gain, bf16_t* __restrict__ out,
-                                                      int H, float eps, NormPartial np) {
+__device__ __forceinline__ void rmsnorm_row(int row, int id, const void* __restrict__ xin, const bf16_t* __restrict__ gain,
+                                            bf16_t* __restrict__ out, int H, float eps, const NormPartial& np) {
   __shared__ float red[4];
-  const int row = blockIdx.x;
   const int tid = threadIdx.x;
   constexpr int MAXV = 8;  // 8 elements per thread per pass of 2048 columns
   float vals[4][MAXV];
@@ -71,7 +70,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ x
     int c = p * 2048 + tid * 8;
     if (p < npass && c < H) {
       if (SRC == NORM_EMBED) {
-        const bf16_t* x = reinterpret_cast<const bf16_t*>(xin) + (int64_t)ids[row] * H + c;
+        const bf16_t* x = reinterpret_cast<const bf16_t*>(xin) + (int64_t)id * H + c;
         Pack16 pk;
         pk.u = *reinterpret_cast<const u32x4*>(x);
 #pragma unroll
@@ -100,7 +99,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ x
           b += *reinterpret_cast<const f32x4*>(np.resid + (int64_t)row * H + c + 4);
         } else {
           Pack16 pk;
-          pk.u = *reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(xin) + (int64_t)ids[row] * H + c);
+          pk.u = *reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(xin) + (int64_t)id * H + c);
 #pragma unroll
           for (int e = 0; e < 4; ++e) { a[e] += bf16_bits_to_f32(pk.s[e]); b[e] += bf16_bits_to_f32(pk.s[4 + e]); }
         }
@@ -137,6 +136,46 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ x
   }
 }
 
+template <int SRC>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ xin, const int32_t* __restrict__ ids,
+                                                      const bf16_t* __restrict__ gain, bf16_t* __restrict__ out,
+                                                      int H, float eps, NormPartial np) {
+  const int row = blockIdx.x;
+  const int id = SRC == NORM_EMBED || (SRC == NORM_PARTIAL && np.resid == nullptr) ? ids[row] : 0;
+  rmsnorm_row<SRC>(row, id, xin, gain, out, H, eps, np);
+}
+
+// The same over Embeds whose ids are kernel arguments: calls that take an id list from the host (distributions, reads and
+// writes of Embeds) need no copy to the device in front of their first kernel, which was a launch of its own: 4.6 us of a
+// pass that reads up to IDS_BY_VALUE output Embeds (one row through an 8B-shaped layer: 130 -> 124 us with the read).
+// Longer lists go through a device buffer.  The smaller argument block is for the usual few rows.
+template <int N>
+struct IdArgs {
+  int32_t v[N];
+};
+template <int N>
+__global__ __launch_bounds__(256) void rmsnorm_ids_kernel(const bf16_t* __restrict__ embeds, IdArgs<N> ids,
+                                                          const bf16_t* __restrict__ gain, bf16_t* __restrict__ out,
+                                                          int H, float eps) {
+  rmsnorm_row<NORM_EMBED>(blockIdx.x, ids.v[blockIdx.x], embeds, gain, out, H, eps, NormPartial{});
+}
+
+template <int N>
+static IdArgs<N> id_args(const int32_t* ids, int n) {
+  IdArgs<N> a;
+  for (int i = 0; i < n; ++i) a.v[i] = ids[i];
+  for (int i = n; i < N; ++i) a.v[i] = 0;
+  return a;
+}
+
+hipError_t launch_rmsnorm_embed_ids(const bf16_t* embeds, const int32_t* host_ids, const bf16_t* gain, bf16_t* out, int rows,
+                                    int H, float eps, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  if (rows > IDS_BY_VALUE) return hipErrorInvalidValue;
+  if (rows <= 64) rmsnorm_ids_kernel<64><<<dim3(rows), dim3(256), 0, s>>>(embeds, id_args<64>(host_ids, rows), gain, out, H, eps);
+  else rmsnorm_ids_kernel<IDS_BY_VALUE><<<dim3(rows), dim3(256), 0, s>>>(embeds, id_args<IDS_BY_VALUE>(host_ids, rows), gain, out, H, eps);
+  return hipGetLastError();
+}
 hipError_t launch_rmsnorm_embed(const bf16_t* embeds, const int32_t* ids, const bf16_t* gain, bf16_t* out, int rows,
                                 int H, float eps, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
@@ -341,16 +380,25 @@ hipError_t launch_rope_append(bf16_t* qkv, int T, int Hq, int Hkv, int D, const 
 // ---------------------------------------------------------------------------------------------
 // Pool copies for seeding and inspection.
 // ---------------------------------------------------------------------------------------------
-__global__ void embed_copy_kernel(bf16_t* __restrict__ embeds, const int32_t* __restrict__ ids, int n, int H,
-                                  bf16_t* __restrict__ buf, int to_pool) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // one 16-byte piece
-  int per_row = H / 8;
-  if (idx >= (int64_t)n * per_row) return;
-  int r = (int)(idx / per_row), c = (int)(idx % per_row) * 8;
-  bf16_t* p = embeds + (int64_t)ids[r] * H + c;
-  bf16_t* b = buf + (int64_t)r * H + c;
+__device__ __forceinline__ void embed_copy_piece(bf16_t* __restrict__ embeds, int id, int64_t idx, int H,
+                                                 bf16_t* __restrict__ buf, int to_pool) {
+  bf16_t* p = embeds + (int64_t)id * H + (int)(idx % (H / 8)) * 8;
+  bf16_t* b = buf + idx * 8;
   if (to_pool) *reinterpret_cast<u32x4*>(p) = *reinterpret_cast<const u32x4*>(b);
   else *reinterpret_cast<u32x4*>(b) = *reinterpret_cast<const u32x4*>(p);
+}
+__global__ void embed_copy_kernel(bf16_t* __restrict__ embeds, const int32_t* __restrict__ ids, int n, int H,
+                                  bf16_t* __restrict__ buf, int to_pool) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // one 16-byte piece
+  if (idx >= (int64_t)n * (H / 8)) return;
+  embed_copy_piece(embeds, ids[idx / (H / 8)], idx, H, buf, to_pool);
+}
+template <int N>
+__global__ void embed_copy_ids_kernel(bf16_t* __restrict__ embeds, IdArgs<N> ids, int n, int H, bf16_t* __restrict__ buf,
+                                      int to_pool) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= n * (H / 8)) return;
+  embed_copy_piece(embeds, ids.v[idx / (H / 8)], idx, H, buf, to_pool);
 }
 
 // embed_txt: Embed ids[r] receives row tok[r] of the embedding table, 16 bytes per thread.
@@ -377,6 +425,15 @@ hipError_t launch_embed_copy(bf16_t* embeds, const int32_t* ids, int n, int H, b
   int64_t total = (int64_t)n * (H / 8);
   if (total <= 0) return hipSuccess;
   embed_copy_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(embeds, ids, n, H, buf, to_pool);
+  return hipGetLastError();
+}
+
+hipError_t launch_embed_copy_ids(bf16_t* embeds, const int32_t* host_ids, int n, int H, bf16_t* buf, int to_pool, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  if (n > IDS_BY_VALUE) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((n * (H / 8) + 255) / 256)), block(256);
+  if (n <= 64) embed_copy_ids_kernel<64><<<grid, block, 0, s>>>(embeds, id_args<64>(host_ids, n), n, H, buf, to_pool);
+  else embed_copy_ids_kernel<IDS_BY_VALUE><<<grid, block, 0, s>>>(embeds, id_args<IDS_BY_VALUE>(host_ids, n), n, H, buf, to_pool);
   return hipGetLastError();
 }
 

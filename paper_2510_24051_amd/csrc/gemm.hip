@@ -791,7 +791,7 @@ __global__ __launch_bounds__(512, 4) void gemm_rows_kernel(const bf16_t* __restr
   constexpr int BM = MB * 32;
   constexpr int PIECES = BM / 8;        // 1 KiB copy instructions per activation stage
   constexpr int CP = (PIECES + 7) / 8;  // per wave; past the last piece a wave copies that one again (same bytes)
-  constexpr bool AHEAD = MB < 4;        // the next contraction step's activation operands are read under this one's MFMAs
+  [[maybe_unused]] constexpr bool AHEAD = MB < 4;        // the next contraction step's activation operands are read under this one's MFMAs
   __shared__ __align__(16) bf16_t As0[BM * LG_BK], As1[BM * LG_BK], As2[BM * LG_BK], As3[BM * LG_BK];
   constexpr bool NT = MODE == EPI_STORE_F32 || (PARTIAL && MODE == EPI_RESID_OUT) || (!PARTIAL && MODE == EPI_SWIGLU);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -976,8 +976,8 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const bf16_t* __res
   constexpr int S = stream_stages(MB, KS);
   constexpr int WPS = 8 / KS;                // column blocks of the tile
   constexpr int PIECES = KS * BM / 8;        // 1 KiB copy instructions per activation stage
-  constexpr int CP = (PIECES + 7) / 8;       // per wave
-  [[maybe_unused]] constexpr bool AHEAD = MB < 6;             // the next contraction step's activation operands are read under this one's MFMAs
+  [[maybe_unused]] constexpr int CP = (PIECES + 7) / 8;  // per wave
+  [[maybe_unused]] constexpr bool AHEAD = MB < 6;  // the next contraction step's activation operands are read under this one's MFMAs
   constexpr int STAGE = KS * BM * LG_BK;
   __shared__ __align__(16) bf16_t As0[STAGE], As1[STAGE], As2[STAGE], As3[S > 3 ? STAGE : 16];
   constexpr bool NT = MODE == EPI_STORE_F32 || (PARTIAL && MODE == EPI_RESID_OUT) || (!PARTIAL && MODE == EPI_SWIGLU);

@@ -197,6 +197,12 @@ hipError_t launch_pack_weight(const bf16_t* s0, int r0, const bf16_t* s1, int r1
                               int interleave, bf16_t* dst, int NB, hipStream_t s);
 hipError_t launch_rmsnorm_embed(const bf16_t* embeds, const int32_t* ids, const bf16_t* gain, bf16_t* out, int rows,
                                 int H, float eps, hipStream_t s);
+// launch_rmsnorm_embed and launch_embed_copy over at most IDS_BY_VALUE ids on the host, which travel as kernel arguments (of
+// which a launch takes 4 KiB)
+#define IDS_BY_VALUE 960
+hipError_t launch_rmsnorm_embed_ids(const bf16_t* embeds, const int32_t* host_ids, const bf16_t* gain, bf16_t* out, int rows,
+                                    int H, float eps, hipStream_t s);
+hipError_t launch_embed_copy_ids(bf16_t* embeds, const int32_t* host_ids, int n, int H, bf16_t* buf, int to_pool, hipStream_t s);
 hipError_t launch_rmsnorm_f32(const float* x, const bf16_t* gain, bf16_t* out, int rows, int H, float eps,
                               hipStream_t s);
 // part/splits: when splits > 0 the q, k, v values are not read from qkv but summed from the split-K partials

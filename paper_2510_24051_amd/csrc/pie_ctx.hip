@@ -387,10 +387,14 @@ static pie_status embed_copy(pie_ctx* c, const int32_t* ids, int32_t n, void* bu
   if (n == 0) return PIE_OK;
   for (int i = 0; i < n; ++i)
     if (ids[i] < 0 || ids[i] >= c->p.n_embeds) return fail(c, PIE_ERANGE, "embed id %d at %d outside [0, %d)", ids[i], i, c->p.n_embeds);
-  pie_status st = stage_ids(c, ids, nullptr, n);
-  if (st != PIE_OK) return st;
-  HIP_TRY(c, launch_embed_copy(c->embeds, c->ids_dev, n, c->m.hidden, (bf16_t*)buf, to_pool, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));  // ids_dev is reused by the next call
+  if (n <= IDS_BY_VALUE) {
+    HIP_TRY(c, launch_embed_copy_ids(c->embeds, ids, n, c->m.hidden, (bf16_t*)buf, to_pool, c->stream));
+  } else {
+    pie_status st = stage_ids(c, ids, nullptr, n);
+    if (st != PIE_OK) return st;
+    HIP_TRY(c, launch_embed_copy(c->embeds, c->ids_dev, n, c->m.hidden, (bf16_t*)buf, to_pool, c->stream));
+  }
+  HIP_TRY(c, hipStreamSynchronize(c->stream));  // (ids_dev is reused by the next call)
   return PIE_OK;
 }
 extern "C" pie_status pie_embed_write(pie_ctx* c, const int32_t* ids, int32_t n, const void* src) {
@@ -1716,10 +1720,11 @@ static pie_status check_dist_args(pie_ctx* c, const void* ids, int32_t n, int32_
   return PIE_OK;
 }
 
-// The kernels of get_next_dist over ids already on the device, with every intermediate buffer named by the caller
-// (the context's workspace, or the static scratch array).
+// The kernels of get_next_dist, with every intermediate buffer named by the caller (the context's workspace, or the static
+// scratch array).
 struct DistBuffers {
-  const int32_t* ids;  // [n] embed ids
+  const int32_t* ids;  // [n] embed ids on the host, or on the device
+  bool ids_on_host;    // (at most IDS_BY_VALUE of them)
   bf16_t* en;          // [n, H] normalised rows
   float* logits;       // [n, V]
   float* splitk;       // split-K partial sums of the LM head
@@ -1734,9 +1739,9 @@ static pie_status run_dist(pie_ctx* c, const DistBuffers& w, int32_t n, int32_t 
   StageTimer tm(c, PIE_STAGE_HEAD_NORM, PIE_STAGE_TOPK);
   tm.begin(PIE_STAGE_HEAD_NORM);
   if (c->g_final) {
-    HIP_TRY(c, launch_rmsnorm_embed(c->embeds, w.ids, c->g_final, w.en, n, H, c->m.rms_eps, s));
+    HIP_TRY(c, (w.ids_on_host ? launch_rmsnorm_embed_ids : launch_rmsnorm_embed)(c->embeds, w.ids, c->g_final, w.en, n, H, c->m.rms_eps, s));
   } else {
-    HIP_TRY(c, launch_embed_copy(c->embeds, w.ids, n, H, w.en, 0, s));
+    HIP_TRY(c, (w.ids_on_host ? launch_embed_copy_ids : launch_embed_copy)(c->embeds, w.ids, n, H, w.en, 0, s));
   }
   tm.end(PIE_STAGE_HEAD_NORM);
   tm.begin(PIE_STAGE_LM_HEAD);
@@ -1759,17 +1764,11 @@ extern "C" pie_status pie_get_next_dist(pie_ctx* c, const int32_t* embed_ids, in
   if (chk != PIE_OK) return chk;
   for (int i = 0; i < n; ++i)
     if (embed_ids[i] < 0 || embed_ids[i] >= c->p.n_embeds) return fail(c, PIE_ERANGE, "embed id %d at %d outside [0, %d)", embed_ids[i], i, c->p.n_embeds);
-  pie_status st = stage_ids(c, embed_ids, nullptr, n);
-  if (st != PIE_OK) return st;
-  const DistBuffers w{c->ids_dev, c->en, c->logits, c->splitk, c->splitk_elems, c->topk_cand, c->topk_stats};
+  const bool by_value = n <= IDS_BY_VALUE;
+  if (!by_value)
+    if (pie_status st = stage_ids(c, embed_ids, nullptr, n)) return st;
+  const DistBuffers w{by_value ? embed_ids : c->ids_dev, by_value, c->en, c->logits, c->splitk, c->splitk_elems, c->topk_cand, c->topk_stats};
   return run_dist(c, w, n, top_k, temperature, out_ids, out_probs);
-}
-
-// Embed ids handed to the device as kernel arguments (no host-to-device copy, nothing to stage).
-struct IdList { int32_t v[PIE_STATIC_DIST_ROWS]; };
-__global__ void ids_from_args_kernel(IdList ids, int n, int32_t* __restrict__ dst) {
-  const int i = threadIdx.x;
-  if (i < n) dst[i] = ids.v[i];
 }
 
 extern "C" pie_status pie_get_next_dist_static(pie_ctx* c, const int32_t* embed_ids, int32_t n, int32_t top_k,
@@ -1784,15 +1783,12 @@ extern "C" pie_status pie_get_next_dist_static(pie_ctx* c, const int32_t* embed_
   if (top_k <= 0 || top_k > 1024 || top_k > c->m.vocab)
     return fail(c, PIE_ERANGE, "top_k %d outside [1, min(1024, vocab %d)]", top_k, c->m.vocab);
   if (!c->static_scratch) return fail(c, PIE_EHIP, "the static scratch array of device %d was not found at pie_create", c->device);
-  IdList ids{};
-  for (int i = 0; i < n; ++i) {
+  for (int i = 0; i < n; ++i)
     if (embed_ids[i] < 0 || embed_ids[i] >= c->p.n_embeds) return fail(c, PIE_ERANGE, "embed id %d at %d outside [0, %d)", embed_ids[i], i, c->p.n_embeds);
-    ids.v[i] = embed_ids[i];
-  }
-  // carve the array: ids | normalised rows | logits | candidates | chunk statistics | split-K partials (the rest)
+  // carve the array: 256 bytes (kept free, the size limits count them) | normalised rows | logits | candidates | chunk statistics | split-K partials (the rest)
   const size_t H = (size_t)c->m.hidden, V = (size_t)c->m.vocab;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t o_ids = 0, o_en = up(o_ids + PIE_STATIC_DIST_ROWS * 4), o_lg = up(o_en + (size_t)n * H * 2);
+  const size_t o_en = 256, o_lg = up(o_en + (size_t)n * H * 2);
   const size_t o_cd = up(o_lg + (size_t)n * V * 4), o_st = up(o_cd + (size_t)n * 16 * top_k * 8);
   const size_t o_sk = up(o_st + (size_t)n * 16 * 2 * 4);
   if (o_sk > PIE_STATIC_SCRATCH_BYTES)
@@ -1801,9 +1797,8 @@ extern "C" pie_status pie_get_next_dist_static(pie_ctx* c, const int32_t* embed_
   unsigned char* base = c->static_scratch;  // the device address of this GPU's array, never the symbol itself
   // Nothing in the array has to start at zero: every kernel below writes each element it or a later kernel reads
   // (all n rows of en, logits, candidates (short chunks pad theirs), statistics and the partial sums that are used).
-  ids_from_args_kernel<<<dim3(1), dim3(64), 0, c->stream>>>(ids, n, reinterpret_cast<int32_t*>(base + o_ids));
-  HIP_TRY(c, hipGetLastError());
-  const DistBuffers w{reinterpret_cast<const int32_t*>(base + o_ids), reinterpret_cast<bf16_t*>(base + o_en),
+  static_assert(PIE_STATIC_DIST_ROWS <= IDS_BY_VALUE, "the ids travel as kernel arguments");
+  const DistBuffers w{embed_ids, true, reinterpret_cast<bf16_t*>(base + o_en),
                       reinterpret_cast<float*>(base + o_lg), reinterpret_cast<float*>(base + o_sk),
                       (PIE_STATIC_SCRATCH_BYTES - o_sk) / sizeof(float),
                       reinterpret_cast<unsigned long long*>(base + o_cd), reinterpret_cast<float*>(base + o_st)};

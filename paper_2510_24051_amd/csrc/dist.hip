@@ -14,6 +14,8 @@
 // byte would hammer a few LDS addresses with atomics; instead the top byte is found by walking the byte values
 // downward from the maximum's and counting matches in registers (a few steps for any realistic distribution).
 // The lower bytes only concern the few keys that share the selected top byte: LDS histogram with atomics.
+#include <type_traits>
+
 #include "internal.h"
 
 #define TC_THREADS 512
@@ -432,6 +434,314 @@ __global__ __launch_bounds__(TM_THREADS) void topk_merge_kernel(int n_chunks, in
   for (int i = tid; i < k; i += TM_THREADS) emit(i, top[i]);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Top-k by group maxima (vocabularies of at least 2 k groups of 16): two kernels that sort nothing until few are left
+//
+//   topk_groups : grid (rows, chunks of 8192 logits).  Reads the logits once and leaves, per group of `16 m` of them (the 16
+//                 of m neighbouring threads), the largest key and the sum of exponentials relative to it.  Bound by the
+//                 read (64 x 128256: 32.8 MB).
+//   topk_select : grid (rows).  At least k logits reach the k-th largest group maximum, so only groups whose maximum reaches
+//                 it, and in them only the logits that do, can be among the top k.  A lower bound T of that maximum that
+//                 hardly more than k groups reach comes from a histogram of the maxima between the smallest and the
+//                 largest, refined where a bin holds too many; the groups that reach T are read again (k of them, 32 KiB of
+//                 the row's 513 at k = 256), the logits that reach T (1.2 to 1.4 k of them) go to a list, and each finds its
+//                 place by the counts of a second histogram.  Composites (key, ~id) are unique, so equal logits come in the order
+//                 of their ids; a list that overflows (many equal logits) is cut by the same refinement over composites.
+// Measured against topk_chunk + topk_merge, which select each chunk's k first: 64 rows of 128256, k = 256 22 + 12 -> 9 + 14 us;
+// whole calls: 64 rows, k = 512 210 -> 194, 256 rows of the 70B shape, k = 500 626 -> 597, 26 rows of 32000, k = 50 53 -> 45,
+// 250 rows, k = 512 83 -> 58.  (Launched over and over topk_select takes 9 us: the rest is cold code.)  What is left of
+// topk_select is latency: three dependent reads of memory and a dozen barriers with one workgroup per row.
+// ------------------------------------------------------------------------------------------------
+#define TG_THREADS 512
+#define TG_CHUNK (TG_THREADS * 16)
+#define TS_THREADS 1024
+#define TS_LIST 2048
+
+__global__ __launch_bounds__(TG_THREADS) void topk_groups_kernel(const float* __restrict__ logits, int V, int m, float inv_temp,
+                                                                 uint2* __restrict__ groups) {
+  __shared__ uint32_t kred[TG_THREADS / 64];
+  __shared__ float sred[TG_THREADS / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = blockIdx.x, chunk = blockIdx.y;
+  const int n = min(TG_CHUNK, V - chunk * TG_CHUNK);
+  const float* z = logits + (int64_t)row * V + chunk * TG_CHUNK;
+  f32x4 v[4];
+  uint32_t best = 0u;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int i = tid * 4 + j * 4 * TG_THREADS;  // n and V are multiples of 4
+    v[j] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    if (i < n) v[j] = *reinterpret_cast<const f32x4*>(z + i);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (tid * 4 + j * 4 * TG_THREADS < n)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) best = max(best, order_key(v[j][e]));
+  for (int o = 1; o < m && o < 64; o <<= 1) best = max(best, (uint32_t)__shfl_xor((int)best, o));
+  const int w0 = m > 64 ? wave & ~(m / 64 - 1) : wave, w1 = m > 64 ? w0 + m / 64 : w0;  // the group's waves where it has several
+  if (m > 64) {
+    if (lane == 0) kred[wave] = best;
+    __syncthreads();
+    for (int w = w0; w < w1; ++w) best = max(best, kred[w]);
+  }
+  const float gm = best ? key_to_float(best) : -INFINITY;
+  const float c2 = inv_temp * 1.44269504088896340736f;
+  float sum = 0.f;
+  if (gm != -INFINITY) {  // (padding, and a logit of -inf among others, add 2^-inf = 0)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum += __builtin_amdgcn_exp2f((v[j][e] - gm) * c2);
+  }
+  for (int o = 1; o < m && o < 64; o <<= 1) sum += __shfl_xor(sum, o);
+  if (m > 64) {
+    if (lane == 0) sred[wave] = sum;
+    __syncthreads();
+    sum = 0.f;
+    for (int w = w0; w < w1; ++w) sum += sred[w];
+  }
+  if (tid % m == 0) groups[((int64_t)row * gridDim.y + chunk) * (TG_THREADS / m) + tid / m] = uint2{best, __float_as_uint(sum)};
+}
+
+// Where the bin of the `need`-th largest of 1024 histogram counts lies: *bin, and *above, how many lie in larger bins (bin 0
+// and everything above it when there are fewer than `need`).  Every thread returns the same.  hist must be complete (a
+// barrier behind its counts) and is cleared on return for the next count.
+__device__ __forceinline__ void cut_bin(uint32_t* hist, uint32_t need, uint32_t* wtot, uint32_t* sh, uint32_t* bin, uint32_t* above,
+                                        uint32_t* in_bin) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t c = hist[1023 - tid];  // descending bins
+  uint32_t incl = c;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t t = __shfl_up(incl, o);
+    if (lane >= o) incl += t;
+  }
+  if (lane == 63) wtot[wave] = incl;
+  __syncthreads();
+  uint32_t before = 0u;
+#pragma unroll
+  for (int w = 0; w < TS_THREADS / 64; ++w) before += w < wave ? wtot[w] : 0u;
+  const uint32_t excl = before + incl - c;
+  if ((excl < need && need <= excl + c) || (tid == 1023 && excl + c < need)) {
+    sh[0] = 1023 - tid;
+    sh[1] = excl;
+    sh[2] = c;
+  }
+  hist[1023 - tid] = 0u;
+  __syncthreads();
+  *bin = sh[0];
+  *above = sh[1];
+  *in_bin = sh[2];
+}
+
+// A place behind *counter for every lane that takes one, one LDS atomic per wave.
+__device__ __forceinline__ uint32_t wave_append(bool take, uint32_t* counter) {
+  const unsigned long long mask = __builtin_amdgcn_ballot_w64(take);
+  if (mask == 0ull) return 0u;
+  const int leader = __ffsll(mask) - 1;
+  uint32_t base = 0u;
+  if ((int)(threadIdx.x & 63) == leader) base = atomicAdd(counter, (uint32_t)__popcll(mask));
+  return (uint32_t)__builtin_amdgcn_readlane((int)base, leader) +
+         __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+template <int PER>  // groups per thread
+__global__ __launch_bounds__(TS_THREADS) void topk_select_kernel(const float* __restrict__ logits, int V, int n_groups, int m, int k,
+                                                                 float inv_temp, const uint2* __restrict__ groups,
+                                                                 int32_t* __restrict__ out_ids, float* __restrict__ out_probs) {
+  __shared__ uint32_t hist[1024];
+  __shared__ uint32_t kmax_s[TS_THREADS / 64], kmin_s[TS_THREADS / 64], wtot[TS_THREADS / 64], sh[3];
+  __shared__ float sum_s[TS_THREADS / 64];
+  __shared__ uint32_t n_list, n_sel;
+  __shared__ uint16_t sel[PER * TS_THREADS];
+  __shared__ __align__(16) unsigned long long list[TS_LIST];
+  __shared__ unsigned long long placed[TS_LIST];
+  __shared__ uint16_t first[1024];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = blockIdx.x;
+  const float* z = logits + (int64_t)row * V;
+  uint32_t key[PER];
+  float part[PER];
+  uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int g = tid + i * TS_THREADS;
+    const uint2 e = g < n_groups ? groups[(int64_t)row * n_groups + g] : uint2{0u, 0u};
+    key[i] = e.x;
+    part[i] = __uint_as_float(e.y);
+    kmax = max(kmax, e.x);
+    if (e.x != 0u) kmin = min(kmin, e.x);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
+    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
+  }
+  if (lane == 0) { kmax_s[wave] = kmax; kmin_s[wave] = kmin; }
+  hist[tid] = 0u;
+  if (tid == 0) { n_list = 0u; n_sel = 0u; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < TS_THREADS / 64; ++w) { kmax = max(kmax, kmax_s[w]); kmin = min(kmin, kmin_s[w]); }
+  const uint32_t kall = kmax;
+  const float gmax = key_to_float(kmax);
+  {
+    float s = 0.f;
+    const float c2 = inv_temp * 1.44269504088896340736f;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (part[i] != 0.f) s += part[i] * __builtin_amdgcn_exp2f((key_to_float(key[i]) - gmax) * c2);
+    s = wave_sum(s);
+    if (lane == 0) sum_s[wave] = s;
+  }
+  // T: at least k group maxima reach it, and few more.  Bins of 2^shift keys from `base` up; `above` maxima lie past the last.
+  uint32_t T = kmin, above = 0u;
+  {
+    uint32_t base = kmin, span = kmax - kmin;
+    int shift = 0;
+    while ((span >> shift) > 1023u) ++shift;
+    for (;;) {
+      const uint32_t last = (uint32_t)min((uint64_t)kmax, (uint64_t)base + (((uint64_t)1024 << shift) - 1));
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (key[i] >= base && key[i] <= last && key[i] != 0u) atomicAdd(&hist[min((key[i] - base) >> shift, 1023u)], 1u);
+      __syncthreads();
+      uint32_t bin, over, in_bin;
+      cut_bin(hist, (uint32_t)k - above, wtot, sh, &bin, &over, &in_bin);
+      T = base + (bin << shift);
+      if (shift == 0 || above + over + in_bin <= (uint32_t)(k + k / 4 + 32)) break;
+      above += over;
+      base = T;
+      kmax = (uint32_t)min((uint64_t)kmax, (uint64_t)T + (((uint64_t)1 << shift) - 1));  // the maxima past the bin are counted
+      shift = max(0, shift - 10);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const bool take = key[i] >= T && key[i] != 0u;
+    const uint32_t p = wave_append(take, &n_sel);
+    if (take) sel[p] = (uint16_t)(tid + i * TS_THREADS);
+  }
+  __syncthreads();
+  // Every 16-byte piece of the selected groups: f(id of the first logit, the four logits).
+  const int lm = __ffs(m) - 1, lp = 9 - lm;  // m and the groups per chunk are powers of two
+  static_assert(TG_THREADS == 1 << 9, "lp");
+  const int n_pieces = (int)n_sel << (2 + lm);
+  auto for_pieces = [&](auto f) {
+    for (int q = tid; q < n_pieces; q += TS_THREADS) {
+      const int g = sel[q >> (2 + lm)], idx = q & (4 * m - 1);
+      const int id = (g >> lp) * TG_CHUNK + (idx >> lm) * (4 * TG_THREADS) + (((g & ((1 << lp) - 1)) << lm) + (idx & (m - 1))) * 4;
+      if (id < V) f(id, *reinterpret_cast<const f32x4*>(z + id));
+    }
+  };
+  auto comp_of = [](float x, int id) {
+    return ((unsigned long long)order_key(x) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)id);
+  };
+  unsigned long long least = (unsigned long long)T << 32;
+  auto collect = [&]() {  // composites of at least `least`; those past the list are only counted
+    for_pieces([&](int id, const f32x4& x) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned long long c = comp_of(x[e], id + e);
+        const bool take = c >= least;
+        const uint32_t p = wave_append(take, &n_list);
+        if (take && p < TS_LIST) list[p] = c;
+      }
+    });
+    __syncthreads();
+  };
+  collect();
+  if (n_list > TS_LIST) {  // (uniform) too many: raise the bound until no more than the list holds reach it
+    unsigned long long base = least;
+    uint32_t over_all = 0u;
+    int shift = 64 - 10;  // the first bins cover every composite
+    base = 0ull;
+    for (;;) {
+      for_pieces([&](int id, const f32x4& x) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const unsigned long long c = comp_of(x[e], id + e);
+          if (c >= base && ((c - base) >> shift) < 1024ull) atomicAdd(&hist[(uint32_t)((c - base) >> shift)], 1u);
+        }
+      });
+      __syncthreads();
+      uint32_t bin, over, in_bin;
+      cut_bin(hist, (uint32_t)k - over_all, wtot, sh, &bin, &over, &in_bin);
+      base += (unsigned long long)bin << shift;
+      if (shift == 0 || over_all + over + in_bin <= TS_LIST) break;
+      over_all += over;
+      shift = max(0, shift - 10);  // the next bins subdivide the cut one
+    }
+    least = base;
+    if (tid == 0) n_list = 0u;
+    __syncthreads();
+    collect();
+  }
+  const int n = min((int)n_list, TS_LIST);
+  float sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < TS_THREADS / 64; ++w) sum += sum_s[w];
+  const float inv_sum = 1.0f / sum;
+  auto emit = [&](int slot, unsigned long long v) {
+    if (slot >= k) return;
+    out_ids[(int64_t)row * k + slot] = (int)(0xFFFFFFFFu - (uint32_t)(v & 0xFFFFFFFFull));
+    out_probs[(int64_t)row * k + slot] = expf((key_to_float((uint32_t)(v >> 32)) - gmax) * inv_temp) * inv_sum;
+  };
+  // Each composite's place is the number of larger ones.  A histogram of the list between T and the maximum, key and id as one
+  // number, says how many lie in larger bins; the rest is counted among the bin's own, a handful unless a key is common.
+  // (Counting over the whole list took 3.4 us of 18 at k = 256 and 11.5 of 30 at k = 512: every step of it moves 1 KiB out
+  // of LDS per wave.)
+  auto spot_of = [&](unsigned long long c) { return ((c - ((unsigned long long)T << 32)) >> 32 << 17) | (uint32_t)(0x1FFFFu - (0xFFFFFFFFu - (uint32_t)c)); };
+  const unsigned long long span = spot_of((unsigned long long)kall << 32 | 0xFFFFFFFFu);
+  const int shift = max(0, 54 - __clzll((long long)(span | 1ull)));
+  for (int i = tid; i < n; i += TS_THREADS) atomicAdd(&hist[(uint32_t)(spot_of(list[i]) >> shift)], 1u);
+  __syncthreads();
+  {
+    const uint32_t c = hist[1023 - tid];
+    uint32_t incl = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t t = __shfl_up(incl, o);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) wtot[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0u;
+#pragma unroll
+    for (int w = 0; w < TS_THREADS / 64; ++w) before += w < wave ? wtot[w] : 0u;
+    first[1023 - tid] = (uint16_t)(before + incl - c);
+    __syncthreads();
+  }
+  for (int i = tid; i < n; i += TS_THREADS) {
+    const unsigned long long c = list[i];
+    const uint32_t bin = (uint32_t)(spot_of(c) >> shift);
+    placed[first[bin] + atomicSub(&hist[bin], 1u) - 1u] = c;
+  }
+  __syncthreads();
+  for (int i = tid; i < n; i += TS_THREADS) {
+    const unsigned long long mine = placed[i];
+    const uint32_t bin = (uint32_t)(spot_of(mine) >> shift);
+    const int j0 = first[bin], j1 = bin ? first[bin - 1] : n;
+    int place = j0;
+    for (int j = j0; j < j1; ++j) place += placed[j] > mine ? 1 : 0;
+    emit(place, mine);
+  }
+  for (int i = n + tid; i < k; i += TS_THREADS) emit(i, 0ull);  // (fewer than k comparable logits: only with NaNs)
+}
+
+// Threads per group of topk_groups for a vocabulary of V entries, 0 where the chunk kernels take the row: as many groups as the
+// candidate buffer has room for (16 k), since that leaves the fewest logits to read again (64 rows of 128256, k = 256: 15.5 us
+// with 16 k groups, 16.2 with 8 k, 18.4 with 4 k), but of 32 logits where that still gives 2 k of them, so that few more than k
+// logits reach the k-th largest maximum (k = 512: 17.6 us, with groups of 16 20.3: their maxima span too much for one histogram).
+static int group_threads(int V, int k) {
+  const int chunks = (V + TG_CHUNK - 1) / TG_CHUNK;
+  int m = V / 32 >= 2 * k ? 2 : 1;
+  while (m < TG_THREADS && (int64_t)chunks * (TG_THREADS / m) > 16 * (int64_t)k) m <<= 1;
+  if ((int64_t)chunks * (TG_THREADS / m) > 16 * (int64_t)k || chunks > 16 || V / (16 * m) < 2 * k) return 0;
+  return m;
+}
+
 // chunks per row for a vocabulary of V entries; 0 when the combination is not supported
 int topk_chunks(int V, int k) {
   int n_chunks = (V + 8191) / 8192;
@@ -445,6 +755,21 @@ hipError_t launch_topk(const float* logits, int n, int V, int k, float inv_temp,
   if (n <= 0) return hipSuccess;
   int n_chunks = topk_chunks(V, k);
   if (n_chunks == 0 || k > 1024 || k > V || k <= 0 || (V & 3)) return hipErrorInvalidValue;
+  if (const int m = group_threads(V, k)) {
+    const int chunks = (V + TG_CHUNK - 1) / TG_CHUNK, n_groups = chunks * (TG_THREADS / m);
+    uint2* groups = reinterpret_cast<uint2*>(cand_ws);  // [n, n_groups], n_groups <= 16 k
+    topk_groups_kernel<<<dim3(n, chunks), dim3(TG_THREADS), 0, s>>>(logits, V, m, inv_temp, groups);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    auto select = [&](auto per_c) {
+      topk_select_kernel<decltype(per_c)::value><<<dim3(n), dim3(TS_THREADS), 0, s>>>(logits, V, n_groups, m, k, inv_temp, groups, out_ids, out_probs);
+    };
+    if (n_groups <= TS_THREADS) select(std::integral_constant<int, 1>{});
+    else if (n_groups <= 2 * TS_THREADS) select(std::integral_constant<int, 2>{});
+    else if (n_groups <= 4 * TS_THREADS) select(std::integral_constant<int, 4>{});
+    else return hipErrorInvalidValue;  // (groups of 16 are for vocabularies below 64 k, at most eight chunks)
+    return hipGetLastError();
+  }
   // with many rows, chunks twice as long still give every CU several workgroups
   const bool wide = n_chunks > 1 && (int64_t)n * n_chunks >= 1024;
   if (wide) n_chunks = (n_chunks + 1) / 2;

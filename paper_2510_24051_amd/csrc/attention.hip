@@ -472,37 +472,45 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnArgs a, const D
 
 // One wave per (decode-path request, kv head, query row): lanes first share the (max, sum) pairs of the row's
 // partials (one per segment in which the request has a column), then each lane combines D/64 output elements
-// over the partials with independent loads.
+// over the partials with independent loads.  A chain of latencies (list bounds, row numbers, pairs, values): each is read
+// once, the pairs of the first 64 partials stay in registers between the maximum and the weights.
 template <int D>
-__global__ __launch_bounds__(64) void attn_merge_kernel(AttnArgs a, const int32_t* __restrict__ dec_reqs,
+__global__ __launch_bounds__(64) void attn_merge_kernel(AttnArgs a, const MergeReq* __restrict__ reqs,
                                                         const int32_t* __restrict__ mref_indptr,
                                                         const int32_t* __restrict__ mrefs,
                                                         const float* __restrict__ part_o,
                                                         const float* __restrict__ part_ml) {
-  const ReqInfo rq = a.reqs[dec_reqs[blockIdx.x]];
+  const MergeReq rq = reqs[blockIdx.x];
   const int hk = blockIdx.y, row = blockIdx.z, lane = threadIdx.x;
   const int G = a.Hq / a.Hkv;
-  if (row >= rq.n_new * G) return;
   const int ref0 = mref_indptr[blockIdx.x * a.Hkv + hk];
   const int count = mref_indptr[blockIdx.x * a.Hkv + hk + 1] - ref0;
+  if (row >= rq.rows) return;
   constexpr int E = D / 64;
   float num[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) num[e] = 0.f;
-  float M = -INFINITY;
-  for (int c = lane; c < count; c += 64) M = fmaxf(M, part_ml[(int64_t)(mrefs[ref0 + c] + row) * 2]);
+  auto pair_of = [&](int c, int& prow) {  // (max, sum) of partial c of this row
+    prow = 0;
+    f32x2 ml = {-INFINITY, 0.f};
+    if (c < count) {
+      prow = mrefs[ref0 + c] + row;
+      ml = *reinterpret_cast<const f32x2*>(part_ml + (int64_t)prow * 2);
+    }
+    return ml;
+  };
+  int prow0;
+  const f32x2 ml0 = pair_of(lane, prow0);
+  float M = ml0[0];
+  for (int c = lane + 64; c < count; c += 64) M = fmaxf(M, part_ml[(int64_t)(mrefs[ref0 + c] + row) * 2]);
   M = wave_max(M);
   float den = 0.f;
   if (M != -INFINITY) {
     for (int c0 = 0; c0 < count; c0 += 64) {
-      const int c = c0 + lane;
-      float w = 0.f;
-      int64_t prow = 0;
-      if (c < count) {
-        prow = mrefs[ref0 + c] + row;
-        w = __builtin_amdgcn_exp2f(part_ml[prow * 2] - M);
-        den += w * part_ml[prow * 2 + 1];
-      }
+      int prow = prow0;
+      const f32x2 ml = c0 == 0 ? ml0 : pair_of(c0 + lane, prow);
+      const float w = __builtin_amdgcn_exp2f(ml[0] - M);  // (0 past the list)
+      den += w * ml[1];
       const int cnt = min(64, count - c0);
       // eight partial rows per round: their loads are independent and go out together
       for (int j0 = 0; j0 < cnt; j0 += 8) {
@@ -511,7 +519,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(AttnArgs a, const int32_
         for (int u = 0; u < 8; ++u) {
           const int j = min(j0 + u, cnt - 1);
           wj[u] = j0 + u < cnt ? __shfl(w, j) : 0.f;
-          const float* po = part_o + (int64_t)__shfl((int)prow, j) * D + lane * E;
+          const float* po = part_o + (int64_t)__shfl(prow, j) * D + lane * E;
 #pragma unroll
           for (int e = 0; e < E; ++e) v[u][e] = po[e];
         }
@@ -959,7 +967,7 @@ hipError_t launch_attn_decode(const AttnArgs& a, const DecodeWave* waves, const 
   return hipGetLastError();
 }
 
-hipError_t launch_attn_merge(const AttnArgs& a, const int32_t* dec_reqs, int n_dec_reqs, const int32_t* mref_indptr,
+hipError_t launch_attn_merge(const AttnArgs& a, const MergeReq* dec_reqs, int n_dec_reqs, const int32_t* mref_indptr,
                              const int32_t* mrefs, int max_rows, const float* part_o, const float* part_ml,
                              hipStream_t s) {
   if (n_dec_reqs <= 0) return hipSuccess;

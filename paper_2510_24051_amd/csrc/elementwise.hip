@@ -1,5 +1,7 @@
 // Memory-bound helper kernels: weight tiling, RMSNorm, rotary step + KV append into pages,
 // Embed / KvPage pool copies.
+#include <type_traits>
+
 #include "internal.h"
 
 // ---------------------------------------------------------------------------------------------
@@ -42,7 +44,7 @@ hipError_t launch_pack_weight(const bf16_t* s0, int r0, const bf16_t* s1, int r1
 }
 
 // ---------------------------------------------------------------------------------------------
-// RMSNorm: one workgroup per row, values kept in registers between the two passes.
+// RMSNorm: one workgroup per row, values kept in registers.
 // ---------------------------------------------------------------------------------------------
 // The row comes from an Embed (NORM_EMBED), from a wide fp32 row (NORM_F32), or is first formed as residual +
 // split-K partial sums of the projection before it (NORM_PARTIAL: partials added in split order, then the
@@ -55,94 +57,104 @@ struct NormPartial {
   float* wide;          // [rows, H] fp32 destination of residual + sum
 };
 
-// id: the row's Embed, for the sources that read one.
-template <int SRC>
+// id: the row's Embed, for the sources that read one.  A thread holds eight columns (THREADS * 8 >= H).  At decode sizes the
+// kernel is a chain of latencies, so everything that does not depend on the row's sum is requested at once: gain, residual
+// and eight partial sums at a time (one row of 256 threads that took two passes over 4096 columns and read the gain behind
+// the reduction: 4.3 us for 64 Embed rows, 6.0 with eight partial sums; now 3.6 and 5.2).
+template <int SRC, int THREADS>
 __device__ __forceinline__ void rmsnorm_row(int row, int id, const void* __restrict__ xin, const bf16_t* __restrict__ gain,
                                             bf16_t* __restrict__ out, int H, float eps, const NormPartial& np) {
-  __shared__ float red[4];
-  const int tid = threadIdx.x;
-  constexpr int MAXV = 8;  // 8 elements per thread per pass of 2048 columns
-  float vals[4][MAXV];
+  __shared__ float red[THREADS / 64];
+  const int tid = threadIdx.x, c = tid * 8;
+  float vals[8];
   float ss = 0.f;
-  const int npass = (H + 2047) / 2048;
+  Pack16 g;
+  if (c < H) {
+    g.u = *reinterpret_cast<const u32x4*>(gain + c);
+    if (SRC == NORM_EMBED) {
+      Pack16 pk;
+      pk.u = *reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(xin) + (int64_t)id * H + c);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    int c = p * 2048 + tid * 8;
-    if (p < npass && c < H) {
-      if (SRC == NORM_EMBED) {
-        const bf16_t* x = reinterpret_cast<const bf16_t*>(xin) + (int64_t)id * H + c;
-        Pack16 pk;
-        pk.u = *reinterpret_cast<const u32x4*>(x);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) vals[p][e] = bf16_bits_to_f32(pk.s[e]);
-      } else if (SRC == NORM_PARTIAL) {
-        f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-        const float* pp = np.part + (int64_t)row * np.NP + c;
-        const int64_t stride = (int64_t)np.rows * np.NP;
-        int k = 0;
-        for (; k + 8 <= np.splits; k += 8) {  // eight splits requested together, added in order
-          f32x4 va[8], vb[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            va[u] = *reinterpret_cast<const f32x4*>(pp + (k + u) * stride);
-            vb[u] = *reinterpret_cast<const f32x4*>(pp + (k + u) * stride + 4);
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u) { a += va[u]; b += vb[u]; }
-        }
-        for (; k < np.splits; ++k) {
-          a += *reinterpret_cast<const f32x4*>(pp + k * stride);
-          b += *reinterpret_cast<const f32x4*>(pp + k * stride + 4);
-        }
-        if (np.resid != nullptr) {
-          a += *reinterpret_cast<const f32x4*>(np.resid + (int64_t)row * H + c);
-          b += *reinterpret_cast<const f32x4*>(np.resid + (int64_t)row * H + c + 4);
-        } else {
-          Pack16 pk;
-          pk.u = *reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(xin) + (int64_t)id * H + c);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) { a[e] += bf16_bits_to_f32(pk.s[e]); b[e] += bf16_bits_to_f32(pk.s[4 + e]); }
-        }
-        *reinterpret_cast<f32x4*>(np.wide + (int64_t)row * H + c) = a;
-        *reinterpret_cast<f32x4*>(np.wide + (int64_t)row * H + c + 4) = b;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { vals[p][e] = a[e]; vals[p][4 + e] = b[e]; }
+      for (int e = 0; e < 8; ++e) vals[e] = bf16_bits_to_f32(pk.s[e]);
+    } else if (SRC == NORM_PARTIAL) {
+      f32x4 ra, rb;
+      Pack16 pk;
+      if (np.resid != nullptr) {
+        ra = *reinterpret_cast<const f32x4*>(np.resid + (int64_t)row * H + c);
+        rb = *reinterpret_cast<const f32x4*>(np.resid + (int64_t)row * H + c + 4);
       } else {
-        const float* x = reinterpret_cast<const float*>(xin) + (int64_t)row * H + c;
-        f32x4 a = *reinterpret_cast<const f32x4*>(x);
-        f32x4 b = *reinterpret_cast<const f32x4*>(x + 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { vals[p][e] = a[e]; vals[p][4 + e] = b[e]; }
+        pk.u = *reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(xin) + (int64_t)id * H + c);
       }
+      f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+      const float* pp = np.part + (int64_t)row * np.NP + c;
+      const int64_t stride = (int64_t)np.rows * np.NP;
+      int k = 0;
+      for (; k + 8 <= np.splits; k += 8) {  // eight splits requested together, added in order
+        f32x4 va[8], vb[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ss += vals[p][e] * vals[p][e];
+        for (int u = 0; u < 8; ++u) {
+          va[u] = *reinterpret_cast<const f32x4*>(pp + (k + u) * stride);
+          vb[u] = *reinterpret_cast<const f32x4*>(pp + (k + u) * stride + 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { a += va[u]; b += vb[u]; }
+      }
+      if (k + 4 <= np.splits) {
+        f32x4 va[4], vb[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          va[u] = *reinterpret_cast<const f32x4*>(pp + (k + u) * stride);
+          vb[u] = *reinterpret_cast<const f32x4*>(pp + (k + u) * stride + 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { a += va[u]; b += vb[u]; }
+        k += 4;
+      }
+      for (; k < np.splits; ++k) {
+        a += *reinterpret_cast<const f32x4*>(pp + k * stride);
+        b += *reinterpret_cast<const f32x4*>(pp + k * stride + 4);
+      }
+      if (np.resid == nullptr) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { ra[e] = bf16_bits_to_f32(pk.s[e]); rb[e] = bf16_bits_to_f32(pk.s[4 + e]); }
+      }
+      a += ra;
+      b += rb;
+      *reinterpret_cast<f32x4*>(np.wide + (int64_t)row * H + c) = a;
+      *reinterpret_cast<f32x4*>(np.wide + (int64_t)row * H + c + 4) = b;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { vals[e] = a[e]; vals[4 + e] = b[e]; }
+    } else {
+      const float* x = reinterpret_cast<const float*>(xin) + (int64_t)row * H + c;
+      const f32x4 a = *reinterpret_cast<const f32x4*>(x), b = *reinterpret_cast<const f32x4*>(x + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { vals[e] = a[e]; vals[4 + e] = b[e]; }
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss += vals[e] * vals[e];
   }
   ss = wave_sum(ss);
   if ((tid & 63) == 0) red[tid >> 6] = ss;
   __syncthreads();
-  float tot = red[0] + red[1] + red[2] + red[3];
-  float rstd = 1.0f / sqrtf(tot / (float)H + eps);
+  float tot = 0.f;
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    int c = p * 2048 + tid * 8;
-    if (p < npass && c < H) {
-      Pack16 g, o;
-      g.u = *reinterpret_cast<const u32x4*>(gain + c);
+  for (int w = 0; w < THREADS / 64; ++w) tot += red[w];
+  const float rstd = 1.0f / sqrtf(tot / (float)H + eps);
+  if (c < H) {
+    Pack16 o;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o.h[e] = f32_to_bf16(vals[p][e] * rstd * bf16_bits_to_f32(g.s[e]));
-      *reinterpret_cast<u32x4*>(out + (int64_t)row * H + c) = o.u;
-    }
+    for (int e = 0; e < 8; ++e) o.h[e] = f32_to_bf16(vals[e] * rstd * bf16_bits_to_f32(g.s[e]));
+    *reinterpret_cast<u32x4*>(out + (int64_t)row * H + c) = o.u;
   }
 }
 
-template <int SRC>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ xin, const int32_t* __restrict__ ids,
+template <int SRC, int THREADS>
+__global__ __launch_bounds__(THREADS) void rmsnorm_kernel(const void* __restrict__ xin, const int32_t* __restrict__ ids,
                                                       const bf16_t* __restrict__ gain, bf16_t* __restrict__ out,
                                                       int H, float eps, NormPartial np) {
   const int row = blockIdx.x;
   const int id = SRC == NORM_EMBED || (SRC == NORM_PARTIAL && np.resid == nullptr) ? ids[row] : 0;
-  rmsnorm_row<SRC>(row, id, xin, gain, out, H, eps, np);
+  rmsnorm_row<SRC, THREADS>(row, id, xin, gain, out, H, eps, np);
 }
 
 // The same over Embeds whose ids are kernel arguments: calls that take an id list from the host (distributions, reads and
@@ -153,11 +165,21 @@ template <int N>
 struct IdArgs {
   int32_t v[N];
 };
-template <int N>
-__global__ __launch_bounds__(256) void rmsnorm_ids_kernel(const bf16_t* __restrict__ embeds, IdArgs<N> ids,
+template <int N, int THREADS>
+__global__ __launch_bounds__(THREADS) void rmsnorm_ids_kernel(const bf16_t* __restrict__ embeds, IdArgs<N> ids,
                                                           const bf16_t* __restrict__ gain, bf16_t* __restrict__ out,
                                                           int H, float eps) {
-  rmsnorm_row<NORM_EMBED>(blockIdx.x, ids.v[blockIdx.x], embeds, gain, out, H, eps, NormPartial{});
+  rmsnorm_row<NORM_EMBED, THREADS>(blockIdx.x, ids.v[blockIdx.x], embeds, gain, out, H, eps, NormPartial{});
+}
+
+// Calls launch with the workgroup size a row of H columns takes.
+template <typename F>
+static hipError_t norm_threads(int H, F launch) {
+  if (H <= 2048) launch(std::integral_constant<int, 256>{});
+  else if (H <= 4096) launch(std::integral_constant<int, 512>{});
+  else if (H <= 8192) launch(std::integral_constant<int, 1024>{});
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 template <int N>
@@ -172,30 +194,38 @@ hipError_t launch_rmsnorm_embed_ids(const bf16_t* embeds, const int32_t* host_id
                                     int H, float eps, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   if (rows > IDS_BY_VALUE) return hipErrorInvalidValue;
-  if (rows <= 64) rmsnorm_ids_kernel<64><<<dim3(rows), dim3(256), 0, s>>>(embeds, id_args<64>(host_ids, rows), gain, out, H, eps);
-  else rmsnorm_ids_kernel<IDS_BY_VALUE><<<dim3(rows), dim3(256), 0, s>>>(embeds, id_args<IDS_BY_VALUE>(host_ids, rows), gain, out, H, eps);
-  return hipGetLastError();
+  return norm_threads(H, [&](auto t_c) {
+    constexpr int T = decltype(t_c)::value;
+    if (rows <= 64) rmsnorm_ids_kernel<64, T><<<dim3(rows), dim3(T), 0, s>>>(embeds, id_args<64>(host_ids, rows), gain, out, H, eps);
+    else rmsnorm_ids_kernel<IDS_BY_VALUE, T><<<dim3(rows), dim3(T), 0, s>>>(embeds, id_args<IDS_BY_VALUE>(host_ids, rows), gain, out, H, eps);
+  });
 }
 hipError_t launch_rmsnorm_embed(const bf16_t* embeds, const int32_t* ids, const bf16_t* gain, bf16_t* out, int rows,
                                 int H, float eps, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  rmsnorm_kernel<NORM_EMBED><<<dim3(rows), dim3(256), 0, s>>>(embeds, ids, gain, out, H, eps, NormPartial{});
-  return hipGetLastError();
+  return norm_threads(H, [&](auto t_c) {
+    constexpr int T = decltype(t_c)::value;
+    rmsnorm_kernel<NORM_EMBED, T><<<dim3(rows), dim3(T), 0, s>>>(embeds, ids, gain, out, H, eps, NormPartial{});
+  });
 }
 hipError_t launch_rmsnorm_f32(const float* x, const bf16_t* gain, bf16_t* out, int rows, int H, float eps,
                               hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  rmsnorm_kernel<NORM_F32><<<dim3(rows), dim3(256), 0, s>>>(x, nullptr, gain, out, H, eps, NormPartial{});
-  return hipGetLastError();
+  return norm_threads(H, [&](auto t_c) {
+    constexpr int T = decltype(t_c)::value;
+    rmsnorm_kernel<NORM_F32, T><<<dim3(rows), dim3(T), 0, s>>>(x, nullptr, gain, out, H, eps, NormPartial{});
+  });
 }
 hipError_t launch_splitk_resid_norm(const float* part, int splits, int NP, const float* resid, const bf16_t* embeds,
                                     const int32_t* ids, float* wide, const bf16_t* gain, bf16_t* out, int rows, int H,
                                     float eps, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   if (splits <= 0 || NP < H || (resid == nullptr && (embeds == nullptr || ids == nullptr))) return hipErrorInvalidValue;
-  rmsnorm_kernel<NORM_PARTIAL><<<dim3(rows), dim3(256), 0, s>>>(embeds, ids, gain, out, H, eps,
-                                                              NormPartial{part, splits, NP, rows, resid, wide});
-  return hipGetLastError();
+  return norm_threads(H, [&](auto t_c) {
+    constexpr int T = decltype(t_c)::value;
+    rmsnorm_kernel<NORM_PARTIAL, T><<<dim3(rows), dim3(T), 0, s>>>(embeds, ids, gain, out, H, eps,
+                                                                  NormPartial{part, splits, NP, rows, resid, wide});
+  });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -212,35 +242,43 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16_t* __restrict__ q
                                                           const float* __restrict__ angles,
                                                           bf16_t* __restrict__ kv_layer, int hpt, bool by_octet,
                                                           const float* __restrict__ part, int splits, int NP) {
-  // Eight consecutive values of token t from column `col` of its qkv row: read as stored, or (splits > 0) summed
-  // in split order from the partials of the QKV product and rounded to bf16 like the stored row would be.
-  auto load8 = [&](int t, int col) -> Pack16 {
-    Pack16 r;
+  // Eight consecutive values each of token t from columns `col0` and `col1` of its qkv row: read as stored, or (splits > 0)
+  // summed in split order from the partials of the QKV product and rounded to bf16 like the stored row would be.  Both
+  // pieces' loads of up to four splits go out together.
+  auto load_two = [&](int t, int col0, int col1, Pack16& r0, Pack16& r1) {
     if (splits > 0) {
-      f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-      const float* pp = part + (int64_t)t * NP + col;
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0, s3 = s0;
+      const float* pp = part + (int64_t)t * NP;
       const int64_t stride = (int64_t)T * NP;
       int k = 0;
       for (; k + 4 <= splits; k += 4) {
-        f32x4 va[4], vb[4];
+        f32x4 v0[4], v1[4], v2[4], v3[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          va[u] = *reinterpret_cast<const f32x4*>(pp + (k + u) * stride);
-          vb[u] = *reinterpret_cast<const f32x4*>(pp + (k + u) * stride + 4);
+          const float* q = pp + (k + u) * stride;
+          v0[u] = *reinterpret_cast<const f32x4*>(q + col0);
+          v1[u] = *reinterpret_cast<const f32x4*>(q + col0 + 4);
+          v2[u] = *reinterpret_cast<const f32x4*>(q + col1);
+          v3[u] = *reinterpret_cast<const f32x4*>(q + col1 + 4);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { a += va[u]; b += vb[u]; }
+        for (int u = 0; u < 4; ++u) { s0 += v0[u]; s1 += v1[u]; s2 += v2[u]; s3 += v3[u]; }
       }
       for (; k < splits; ++k) {
-        a += *reinterpret_cast<const f32x4*>(pp + k * stride);
-        b += *reinterpret_cast<const f32x4*>(pp + k * stride + 4);
+        const float* q = pp + k * stride;
+        const f32x4 v0 = *reinterpret_cast<const f32x4*>(q + col0), v1 = *reinterpret_cast<const f32x4*>(q + col0 + 4);
+        const f32x4 v2 = *reinterpret_cast<const f32x4*>(q + col1), v3 = *reinterpret_cast<const f32x4*>(q + col1 + 4);
+        s0 += v0; s1 += v1; s2 += v2; s3 += v3;
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { r.h[e] = f32_to_bf16(a[e]); r.h[4 + e] = f32_to_bf16(b[e]); }
+      for (int e = 0; e < 4; ++e) {
+        r0.h[e] = f32_to_bf16(s0[e]); r0.h[4 + e] = f32_to_bf16(s1[e]);
+        r1.h[e] = f32_to_bf16(s2[e]); r1.h[4 + e] = f32_to_bf16(s3[e]);
+      }
     } else {
-      r.u = *reinterpret_cast<const u32x4*>(qkv + (int64_t)t * NP + col);
+      r0.u = *reinterpret_cast<const u32x4*>(qkv + (int64_t)t * NP + col0);
+      r1.u = *reinterpret_cast<const u32x4*>(qkv + (int64_t)t * NP + col1);
     }
-    return r;
   };
   const int cpt = D / 16;  // work pieces per head
   const int heads = Hq + 2 * Hkv, rot = Hq + Hkv;
@@ -265,7 +303,8 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16_t* __restrict__ q
     for (int h = g * hpt; h < h1; ++h) {
       bf16_t* row = qkv + (int64_t)t * heads * D + (int64_t)h * D;
       Pack16 olo, ohi;
-      const Pack16 lo = load8(t, h * D + c * 8), hi = load8(t, h * D + D / 2 + c * 8);
+      Pack16 lo, hi;
+      load_two(t, h * D + c * 8, h * D + D / 2 + c * 8, lo, hi);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         float a = bf16_bits_to_f32(lo.s[e]), b = bf16_bits_to_f32(hi.s[e]);
@@ -298,9 +337,11 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16_t* __restrict__ q
     // idle, left a long chain of loads at the end: 333 tokens over three split-K copies 20 -> 10 us,
     // 8320 tokens 51 -> 49.  For batches of single tokens that order of lanes costs 1.5 us at 157 tokens.)
     const int t0 = t - (slot & 7);
-    bool octet = t0 >= 0 && t0 + 7 < T;
+    bool octet = by_octet && t0 >= 0 && t0 + 7 < T;
+    if (octet) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) octet = octet && tok_page[t0 + i] == page && tok_slot[t0 + i] == (slot & ~7) + i;
+      for (int i = 0; i < 8; ++i) octet = octet && tok_page[t0 + i] == page && tok_slot[t0 + i] == (slot & ~7) + i;
+    }
     if (octet) {
       const int d = c * 16 + (slot & 7) * 2, col = (rot + hv) * D + d;
       Pack16 o0, o1;
@@ -329,7 +370,8 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16_t* __restrict__ q
       *reinterpret_cast<u32x4*>(blk + v_elem_offset(slot & ~7, d + 1, D)) = o1.u;
       return;
     }
-    const Pack16 a = load8(t, (rot + hv) * D + c * 16), b = load8(t, (rot + hv) * D + c * 16 + 8);
+    Pack16 a, b;
+    load_two(t, (rot + hv) * D + c * 16, (rot + hv) * D + c * 16 + 8, a, b);
     uint16_t* dst = reinterpret_cast<uint16_t*>(blk);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -371,9 +413,11 @@ hipError_t launch_rope_append(bf16_t* qkv, int T, int Hq, int Hkv, int D, const 
   const int groups = (Hq + Hkv + hpt - 1) / hpt;
   int64_t total = ((int64_t)T * groups + (int64_t)((T + 7) / 8 * 8) * Hkv) * (D / 16);
   if (total <= 0) return hipSuccess;
-  rope_append_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(qkv, T, Hq, Hkv, D, pos, tok_page,
-                                                                                   tok_slot, angles, kv_layer, hpt, by_octet,
-                                                                                   part, splits, NP);
+  // Few threads: workgroups of one wave, so that they reach every compute unit (64 tokens of the 8B shape are 96 workgroups
+  // of four waves).
+  const int wg = total < 512 * 256 ? 64 : 256;
+  rope_append_kernel<<<dim3((unsigned)((total + wg - 1) / wg)), dim3(wg), 0, s>>>(qkv, T, Hq, Hkv, D, pos, tok_page, tok_slot,
+                                                                                    angles, kv_layer, hpt, by_octet, part, splits, NP);
   return hipGetLastError();
 }
 

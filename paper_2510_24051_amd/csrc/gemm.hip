@@ -355,29 +355,27 @@ __global__ void splitk_epilogue_kernel(const float* __restrict__ part, int split
 #pragma unroll
     for (int i = 0; i < 4; ++i) r[i] = silu_f(g[i]) * u[i];
     store_bf16x4(reinterpret_cast<bf16_t*>(e.out) + (int64_t)m * e.ldo + c, r);
+  } else if (MODE == EPI_STORE_BF16) {
+    store_bf16x4(reinterpret_cast<bf16_t*>(e.out) + (int64_t)m * e.ldo + c, total(c));
+  } else if (MODE == EPI_STORE_F32) {
+    *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(e.out) + (int64_t)m * e.ldo + c) = total(c);
   } else {
-    f32x4 x = total(c);
-    if (MODE == EPI_STORE_BF16) {
-      store_bf16x4(reinterpret_cast<bf16_t*>(e.out) + (int64_t)m * e.ldo + c, x);
-    } else if (MODE == EPI_STORE_F32) {
-      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(e.out) + (int64_t)m * e.ldo + c) = x;
-    } else if (MODE == EPI_RESID_EMBED) {
-      if (e.resid != nullptr) {
-        x += *reinterpret_cast<const f32x4*>(e.resid + (int64_t)m * e.H + c);
-      } else {
-        const bf16x4 r = *reinterpret_cast<const bf16x4*>(e.embeds + (int64_t)e.ids[m] * e.H + c);
+    // The residual (and the id of the output Embed) is requested ahead of the partial sums, not behind them.
+    f32x4 r = {0.f, 0.f, 0.f, 0.f};
+    int id = 0;
+    if (MODE == EPI_RESID_OUT || e.resid != nullptr) {
+      r = *reinterpret_cast<const f32x4*>(e.resid + (int64_t)m * e.H + c);
+      if (MODE == EPI_RESID_OUT && e.out == nullptr) id = e.ids[m];
+    } else {
+      const bf16x4 v = *reinterpret_cast<const bf16x4*>(e.embeds + (int64_t)e.ids[m] * e.H + c);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] += bf16_to_f32(r[i]);
-      }
-      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(e.out) + (int64_t)m * e.ldo + c) = x;
-    } else if (MODE == EPI_RESID_OUT) {
-      const f32x4 y = x + *reinterpret_cast<const f32x4*>(e.resid + (int64_t)m * e.H + c);
-      if (e.out != nullptr) {
-        *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(e.out) + (int64_t)m * e.ldo + c) = y;
-      } else {
-        const int id = e.ids[m];
-        if (id >= 0) store_bf16x4(e.embeds + (int64_t)id * e.H + c, y);
-      }
+      for (int i = 0; i < 4; ++i) r[i] = bf16_to_f32(v[i]);
+    }
+    const f32x4 y = total(c) + r;
+    if (MODE == EPI_RESID_EMBED || e.out != nullptr) {
+      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(e.out) + (int64_t)m * e.ldo + c) = y;
+    } else if (id >= 0) {
+      store_bf16x4(e.embeds + (int64_t)id * e.H + c, y);
     }
   }
 }
@@ -1214,6 +1212,15 @@ static hipError_t set_lds_limit_once(const void* kern, size_t bytes, uint32_t& d
   return e;
 }
 
+template <int MODE>
+static hipError_t launch_splitk_epilogue(int splits, int M, const PackedWeight& W, const EpiArgs& epi, const float* ws, hipStream_t s) {
+  const int NP = W.NB * 32, cols = (MODE == EPI_SWIGLU) ? NP / 2 : W.N;
+  const int64_t total = (int64_t)M * (cols / 4);
+  const int wg = total < 512 * 256 ? 64 : 256;  // (few threads: workgroups of one wave reach every compute unit)
+  splitk_epilogue_kernel<MODE><<<dim3((unsigned)((total + wg - 1) / wg)), dim3(wg), 0, s>>>(ws, splits, M, W.N, NP, epi);
+  return hipGetLastError();
+}
+
 template <int MB, int MODE, int NBW, int WAVES = 4, int KS = 1>
 static hipError_t run_skinny_n(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, float* ws,
                                size_t ws_elems, int n_cus, hipStream_t s, int* defer, int max_splits = SK_MAX_SPLITS) {
@@ -1267,10 +1274,7 @@ static hipError_t run_skinny_n(const bf16_t* A, int lda, int M, const PackedWeig
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (defer) { *defer = splits; return hipSuccess; }  // the caller's next kernel sums the partials
-  const int cols = (MODE == EPI_SWIGLU) ? NP / 2 : W.N;
-  int64_t total = (int64_t)M * (cols / 4);
-  splitk_epilogue_kernel<MODE><<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(ws, splits, M, W.N, NP, epi);
-  return hipGetLastError();
+  return launch_splitk_epilogue<MODE>(splits, M, W, epi, ws, s);
 }
 
 template <int MB, int MODE>
@@ -1394,8 +1398,8 @@ struct StreamPlan {
   double us;
 };
 
-// The estimate: rounds of one workgroup per compute unit, the weights at 6.36 TB/s (a twentieth more time where two row
-// tiles read them), the two added by their cubes as in plan_tiled, 3 us for a launch, the partial sums of a split written and read
+// The estimate: rounds of one workgroup per compute unit, the weights at 6.36 TB/s (with two row tiles 15% more where they
+// exceed the last-level cache, 5% less where they fit), the two added by their cubes as in plan_tiled, 3 us for a launch, the partial sums of a split written and read
 // once.  Fitted to sweeps of every form and 1..16 splits over the same products as plan_tiled's at 1 to 400 rows; the form
 // that this and plan_tiled's estimate pick together is within 2% of the fastest on average.
 static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) {
@@ -1407,7 +1411,7 @@ static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) 
     if (KT % F.ks != 0 || (M <= 64 ? F.mb > 2 : F.mb == 2)) continue;
     const int tiles_m = (M + F.mb * 32 - 1) / (F.mb * 32), tiles_n = (NB + 8 / F.ks - 1) / (8 / F.ks);
     if (tiles_m > 2) continue;  // (the weights would be fetched that often)
-    const double stream = tiles_m > 1 ? 1.05 * stream_us : stream_us;
+    const double stream = tiles_m == 1 ? stream_us : ((int64_t)NP * K * 2 <= (int64_t)1 << 28 ? 0.95 : 1.15) * stream_us;
     for (int splits = 1, last = 0; splits <= 16; ++splits) {
       const int kts = (KT / F.ks + splits - 1) / splits * F.ks;
       if (kts == last) continue;
@@ -1493,10 +1497,7 @@ static hipError_t run_stream(const bf16_t* A, int lda, int M, const PackedWeight
 template <int MODE>
 static hipError_t finish_split(int splits, int M, const PackedWeight& W, const EpiArgs& epi, float* ws, hipStream_t s, int* defer) {
   if (defer) { *defer = splits; return hipSuccess; }
-  const int NP = W.NB * 32, cols = (MODE == EPI_SWIGLU) ? NP / 2 : W.N;
-  const int64_t total = (int64_t)M * (cols / 4);
-  splitk_epilogue_kernel<MODE><<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(ws, splits, M, W.N, NP, epi);
-  return hipGetLastError();
+  return launch_splitk_epilogue<MODE>(splits, M, W, epi, ws, s);
 }
 
 template <int MODE>

@@ -74,6 +74,7 @@ struct DecodeCol {     // one query column of a column group: (request token, he
 // A column group is a set of up to 16 query columns that walk the same pages: the rows of one decode-path
 // request, or of several requests whose page tables name the same physical page at the same logical index
 // (shared prefixes), so that each K/V block is read once for all of them.
+struct MergeReq { int32_t tok0, rows; };  // a decode-path request as the merge kernel takes it: first token, query rows per kv head
 struct DecodeSeg { int32_t cgroup, hk, n_pairs, pad; };  // a run of page pairs of one (column group, kv head) inside one wave's share
 struct DecodeWave { int32_t seg0, n_seg, n_pairs, pad; };  // a wave's share: segments [seg0, seg0 + n_seg)
 // Query block qb (32 tokens) of request r for kv head hk; r < 0: empty slot.  A block whose list of visited page pairs
@@ -110,7 +111,7 @@ struct pie_batch {
   int32_t* mref_indptr = nullptr;  // [n_dec_reqs * Hkv + 1] partial rows to merge per (decode request, kv head)
   int32_t* mrefs = nullptr;        // first partial row (segment * rows_cap + first column of the request)
   PrefillItem* pitems = nullptr;
-  int32_t* dec_reqs = nullptr;  // request indices on the decode path
+  MergeReq* dec_reqs = nullptr;  // [n_dec_reqs]
   int32_t n_dsegs = 0, n_dwaves = 0, dslots = 0, n_pitems = 0, n_dec_reqs = 0, rows_cap = 0;
   std::vector<PrefillItem> pwork_host;  // host copy of the prefill launch layout (inspection)
   // workgroups of the two prefill launches, (query block, kv head) items laid out per XCD and padded: the first
@@ -272,7 +273,7 @@ struct AttnArgs {
 hipError_t launch_attn_decode(const AttnArgs& a, const DecodeWave* waves, const int2* wave_pg, int slots,
                               const DecodeSeg* segs, const DecodeCol* cols, int n_waves, int rows_cap, float* part_o,
                               float* part_ml, bool read_once, hipStream_t s);
-hipError_t launch_attn_merge(const AttnArgs& a, const int32_t* dec_reqs, int n_dec_reqs, const int32_t* mref_indptr,
+hipError_t launch_attn_merge(const AttnArgs& a, const MergeReq* dec_reqs, int n_dec_reqs, const int32_t* mref_indptr,
                              const int32_t* mrefs, int max_rows, const float* part_o, const float* part_ml,
                              hipStream_t s);
 // items[i].r names a shared group; the parts' results go to rows (slot0 + part) * SHARED_COLS + column of part_o / part_ml

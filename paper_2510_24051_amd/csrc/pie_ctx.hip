@@ -1,5 +1,6 @@
 // C ABI of libpie_mi355: context, resource pools, batch deserialisation and the per-layer launch sequence.
 #include <algorithm>
+#include <numeric>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -614,6 +615,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   pie_forward_batch in_blocks;
   if (F > 1) {
     blk_indptr.assign(R + 1, 0);
+    blk_ids.reserve((size_t)std::max(0, std::min(b->page_indptr[R], 1 << 20)) * F);  // (not checked yet)
     for (int r = 0; r < R; ++r) {
       const int p0 = b->page_indptr[r], p1 = b->page_indptr[r + 1];
       if (p1 < p0) return fail(c, PIE_EINVAL, "bad page_indptr");
@@ -735,7 +737,10 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
         if (bits) { visit_phys.push_back(b->page_ids[p0 + pg]); visit_logical.push_back(pg); }
       }
     } else {
-      for (int pg = 0; pg < n_pages; ++pg) { visit_phys.push_back(b->page_ids[p0 + pg]); visit_logical.push_back(pg); }
+      visit_phys.insert(visit_phys.end(), b->page_ids + p0, b->page_ids + p0 + n_pages);
+      const size_t at = visit_logical.size();
+      visit_logical.resize(at + n_pages);
+      std::iota(visit_logical.begin() + at, visit_logical.end(), 0);
     }
     q.n_visit = (int32_t)visit_phys.size() - q.visit0;
     const bool decode_path = n_new * G <= 16;  // query rows that fit the decode kernel's 16-column tile
@@ -980,6 +985,12 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
     // every wave but the last holds per_wave pairs, so the lists follow one another without gaps
     wave_pg.resize((size_t)((total_pairs + per_wave - 1) / per_wave) * dslots);
     int2* wp_out = wave_pg.data();
+    {
+      const size_t n_waves = (size_t)((total_pairs + per_wave - 1) / per_wave);
+      dwaves.reserve(n_waves);
+      dsegs.reserve(n_waves + cgroups.size() * Hkv);
+      mref_all.reserve(n_waves + cgroups.size() * Hkv);  // (more where groups have several members)
+    }
     int filled = 0;
     DecodeWave cur{0, 0, 0, 0};
     auto close_wave = [&]() {
@@ -993,6 +1004,13 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
       const int n_pg = (int)g.pages.size();
       const int P = (n_pg + 1) / 2;
       for (int hk = 0; hk < Hkv; ++hk) {
+        {  // the pages of all its shares, which follow one another in the lists
+          const int2* __restrict__ from = g.pages.data();
+          int2* __restrict__ to = wp_out;
+          for (int v = 0; v < n_pg; ++v) { to[v].x = from[v].x * Hkv + hk; to[v].y = from[v].y; }
+          if (n_pg % 2 != 0) to[n_pg] = make_int2(-1, 0);  // (the last pair has one page)
+          wp_out += 2 * P;
+        }
         int p = 0;
         while (p < P) {
           const int take = (int)std::min<int64_t>(per_wave - filled, P - p);
@@ -1000,8 +1018,6 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
             mref_all.push_back(MRef{g.members[mi] * Hkv + hk, (int32_t)(dsegs.size() * 16 + mi * g.rows)});
           dsegs.push_back(DecodeSeg{(int32_t)gi, hk, take, 0});
           ++cur.n_seg;
-          for (int v = 2 * p; v < 2 * (p + take); ++v)
-            *wp_out++ = v < n_pg ? make_int2(g.pages[v].x * Hkv + hk, g.pages[v].y) : make_int2(-1, 0);
           p += take;
           filled += take;
           if (filled == per_wave) close_wave();
@@ -1107,7 +1123,12 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   }
   bool dec_read_once = true;  // no page is in two column groups
   int dec_rows = 1;
-  for (int r : dec_reqs) dec_rows = std::max(dec_rows, reqs[r].n_new * G);
+  std::vector<MergeReq> merge_reqs;
+  merge_reqs.reserve(dec_reqs.size());
+  for (int r : dec_reqs) {
+    merge_reqs.push_back(MergeReq{reqs[r].tok0, reqs[r].n_new * G});
+    dec_rows = std::max(dec_rows, reqs[r].n_new * G);
+  }
   // Prefill work list.  The hardware hands workgroup i to XCD i % 8, and every XCD has an L2 of its own: the
   // query blocks of one (request, kv head) read the same K/V pages, so they go to one XCD, next to each other in
   // its list (heavy blocks first), and that XCD's L2 serves all but the first read of a page.  The groups are
@@ -1348,7 +1369,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   const size_t o_sg = blob.add(sgroups.data(), sgroups.size() * sizeof(SharedGroup), 16);
   const size_t o_sc = blob.add(scols.data(), scols.size() * sizeof(DecodeCol), 16);
   const size_t o_ps = blob.add(psplit.data(), psplit.size() * sizeof(PrefillItem), 16);
-  const size_t o_dr = blob.add(dec_reqs.data(), dec_reqs.size() * 4, 4);
+  const size_t o_dr = blob.add(merge_reqs.data(), merge_reqs.size() * sizeof(MergeReq), 8);
   const size_t part_rows = (size_t)pb->n_dsegs * pb->rows_cap + (size_t)n_sparts * SHARED_COLS;
   const size_t o_po = blob.add(nullptr, 0, 0);  // metadata ends here; the partial buffers are device-only
   if (!blob.ok) {
@@ -1415,7 +1436,7 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   pb->mask_words = (uint32_t*)(d + o_mw); pb->reqs = (ReqInfo*)(d + o_rq);
   pb->dsegs = (DecodeSeg*)(d + o_di); pb->dwaves = (DecodeWave*)(d + o_ws); pb->wave_pg = (int2*)(d + o_wp);
   pb->dcols = (DecodeCol*)(d + o_dc); pb->mref_indptr = (int32_t*)(d + o_mi); pb->mrefs = (int32_t*)(d + o_mr);
-  pb->pitems = (PrefillItem*)(d + o_pi); pb->dec_reqs = (int32_t*)(d + o_dr);
+  pb->pitems = (PrefillItem*)(d + o_pi); pb->dec_reqs = (MergeReq*)(d + o_dr);
   pb->part_o = (float*)(d + o_po); pb->part_ml = (float*)(d + o_pm);
   pb->rope_angles = (float*)(d + o_an);
   pb->psplit = (PrefillItem*)(d + o_ps);

@@ -301,7 +301,7 @@ hipError_t launch_lora_down(const bf16_t* x, int ldx, int in, int n_tiles, int n
                             int rmax_p, int ksplits, hipStream_t s);
 hipError_t launch_lora_up(void* dst, int ld, int out, int kind, int col0, int kd, int n_tiles, const int32_t* rows,
                           const int32_t* tile_ad, const LoraPair* table, int layer, int n_layers, int proj, int slot,
-                          const float* z, int rmax_p, int ksplits, hipStream_t s);
+                          const float* z, int rmax_p, int ksplits, hipStream_t s, int copies = 0, int64_t copy_elems = 0);
 hipError_t launch_swiglu_f32(const float* gu, int I, bf16_t* act, int T, hipStream_t s);
 
 int topk_chunks(int V, int k);  // chunks per row used by launch_topk (<= 16), 0 if unsupported

@@ -1586,15 +1586,15 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   tm.begin(PIE_STAGE_QKV);
   int qkv_splits = 0;
   e = EpiArgs{EPI_STORE_BF16, c->qkv, QKV, nullptr, nullptr, nullptr, 0};
-  HIP_TRY(c, launch_gemm(c->xn, H, T, L.wqkv, e, c->splitk, c->splitk_elems, c->wave_slots / 8, s,
-                         lora_qkv ? nullptr : &qkv_splits));
+  HIP_TRY(c, launch_gemm(c->xn, H, T, L.wqkv, e, c->splitk, c->splitk_elems, c->wave_slots / 8, s, &qkv_splits));
   tm.end(PIE_STAGE_QKV);
 
   if (lora_qkv) {  // q, k, v share the normalised input
     const int KD = Hkv * D;
     const int ks = lora_ksplits(LT, 3, H, RM, c->lora_z_rows);
     HIP_TRY(c, launch_lora_down(c->xn, H, H, LT, 3, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_Q, c->lora_z, RM, ks, s));
-    HIP_TRY(c, launch_lora_up(c->qkv, QKV, QKV, 3, Hq * D, KD, LT, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_Q, 0, c->lora_z, RM, ks, s));
+    const bool split = qkv_splits > 0;  // the update goes into the partial sums that the rotary step takes
+    HIP_TRY(c, launch_lora_up(split ? (void*)c->splitk : c->qkv, split ? L.wqkv.NB * 32 : QKV, QKV, split ? 4 : 3, Hq * D, KD, LT, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_Q, 0, c->lora_z, RM, ks, s, qkv_splits, (int64_t)T * L.wqkv.NB * 32));
   }
 
   tm.begin(PIE_STAGE_ROPE_APPEND);
@@ -1643,14 +1643,13 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   tm.begin(PIE_STAGE_OPROJ);
   int o_splits = 0;
   e = EpiArgs{EPI_RESID_EMBED, c->h, H, c->embeds, b->in_ids, x_in, H};
-  HIP_TRY(c, launch_gemm(c->attn, Hq * D, T, L.wo, e, c->splitk, c->splitk_elems, c->wave_slots / 8, s,
-                         lora[PIE_PROJ_O] ? nullptr : &o_splits));
+  HIP_TRY(c, launch_gemm(c->attn, Hq * D, T, L.wo, e, c->splitk, c->splitk_elems, c->wave_slots / 8, s, &o_splits));
   tm.end(PIE_STAGE_OPROJ);
 
-  if (lora[PIE_PROJ_O]) {  // h += scale * B (A attn), before the second norm reads h
+  if (lora[PIE_PROJ_O]) {  // h (or the first partial copy of it) += scale * B (A attn), before the second norm reads it
     const int ks = lora_ksplits(LT, 1, Hq * D, RM, c->lora_z_rows);
     HIP_TRY(c, launch_lora_down(c->attn, Hq * D, Hq * D, LT, 1, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_O, c->lora_z, RM, ks, s));
-    HIP_TRY(c, launch_lora_up(c->h, H, H, 1, 0, 0, LT, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_O, 0, c->lora_z, RM, ks, s));
+    HIP_TRY(c, launch_lora_up(o_splits > 0 ? c->splitk : c->h, o_splits > 0 ? L.wo.NB * 32 : H, H, 1, 0, 0, LT, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_O, 0, c->lora_z, RM, ks, s));
   }
 
   tm.begin(PIE_STAGE_NORM2);

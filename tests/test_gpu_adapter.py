@@ -7,6 +7,7 @@ import workloads as W
 from oracle import pie_oracle as O
 from helpers import clone_batch, deep_oracle_pools
 from gpu_helpers import appended_positions, assert_bf16_close, assert_close, dec
+from paper_2510_24051_amd import product_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -109,6 +110,24 @@ def test_adapter_8b_shape_decode():
                 1: W.make_adapter(m, 6600, 1, rank=16, projections=("wq", "wk", "wv", "wo"), scale=2.0)}
     ids = [i % 3 - 1 for i in range(16)]  # -1, 0, 1, ...
     compare(dw, adapters, ids, "8B shape, rank 16 on q/k/v/o")
+
+
+@pytest.mark.parametrize("rows,projections", [(153, ALL), (153, ("wv",)), (153, ("wo",)), (40, ("wq", "wk", "wo")), (3, ("wk", "wo"))])
+def test_adapter_updates_join_partial_sums(rows, projections):
+    """The qkv and output products are split along K: the updates go into their first partial copies, for several 32-row tiles
+    per adapter, rows without an adapter among them, and projections that an adapter leaves alone."""
+    m = W.ModelDesc(hidden=1024, n_q_heads=16, n_kv_heads=4, head_dim=64, mlp_dim=512, vocab=512, page_size=16, rms_eps=1e-5,
+                    rope_theta=1e4, n_layers=2)
+    reqs = {153: [(70, 19), (1, 90), (45, 0), (1, 33), (2, 64), (1, 17), (33, 5)], 40: [(1, 11 + 3 * i) for i in range(40)],
+            3: [(1, 20), (1, 1), (1, 300)]}[rows]
+    if rows > 64:
+        for n_out in (m.n_q_heads * m.head_dim + 2 * m.n_kv_heads * m.head_dim, m.hidden):
+            assert product_plan(rows, n_out, 1024, 1 << 22)["splits"] > 1
+    dw = W.build_deep_workload("ad_parts", m, [W.RequestSpec(*r) for r in reqs], n_kv_pages=256, seed=6800 + rows, std=0.02,
+                               resid_std=0.02 / np.sqrt(4.0))
+    adapters = {0: W.make_adapter(m, 6800, 0, rank=20, projections=projections, scale=0.5, std=0.05),
+                1: W.make_adapter(m, 6800, 1, rank=8, projections=("wq", "wo"), scale=1.0, std=0.05)}
+    compare(dw, adapters, [0, -1, 1, 0, -1, 1, 0] if rows == 153 else [i % 3 - 1 for i in range(rows)], f"partial sums, {rows} rows", max_rank=32)
 
 
 def test_adapter_error_codes():

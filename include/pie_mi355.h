@@ -315,7 +315,7 @@ pie_status pie_batch_prefill_work(const pie_batch* batch, int32_t* out, int32_t 
  * only.  Host int64[4]. */
 pie_status pie_product_plan(int32_t rows, int32_t n_out, int32_t k, int64_t workspace_floats, int32_t n_cus, int64_t* out);
 
-/* Whether the same product goes to the kernel that streams wide weights past up to 384 rows: out[0] = rows of a tile (0: it
+/* Whether the same product goes to the kernel that streams weights past up to 640 rows: out[0] = rows of a tile (0: it
  * does not), out[1] = parts the contraction is cut into inside a workgroup, out[2] = parts it is cut into across workgroups.
  * Computes on the host only.  Host int64[3]. */
 pie_status pie_product_stream(int32_t rows, int32_t n_out, int32_t k, int64_t workspace_floats, int32_t n_cus, int64_t* out);

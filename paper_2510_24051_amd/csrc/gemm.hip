@@ -5,7 +5,7 @@
 //                 (each load is 1 KiB contiguous thanks to the tiled weight layout); the activation tile is
 //                 shared by the workgroup through LDS.  K is split across gridDim.y when N alone gives too
 //                 few workgroups; partial sums go to a workspace and a second kernel applies the epilogue.
-//   gemm_stream : up to 384 rows of wide products; one workgroup per CU with a deep ring of weights in registers.
+//   gemm_stream : up to 640 rows where its workgroups fill the chip; one workgroup per CU with a deep ring of weights in registers.
 //   gemm_rows   : tiles of 96 or 128 rows by 256 columns, K split where the tiles alone leave CUs idle.
 //   gemm_large  : large M (prefill).  MFMA-bound: 256x256x64 workgroup tile, 8 waves of 128x64.
 #include <algorithm>
@@ -945,12 +945,12 @@ __global__ __launch_bounds__(512, 4) void gemm_rows_kernel(const bf16_t* __restr
 }
 
 // ------------------------------------------------------------------------------------------------
-// gemm_stream (K a multiple of 64, weights of tens of MB and more): 1 to 384 rows, where the weight stream is the bound
+// gemm_stream (K a multiple of 64): 1 to 640 rows, where the weight stream, or its latency, is the bound
 //
 // What gemm_rows lacks with one workgroup per compute unit is weight bytes in flight (one k step, 32 KiB, and half of
 // that with tiles of 96 rows read twice).  Here a compute unit holds one workgroup of eight waves on purpose and spends
 // the registers that frees (256 per lane) on a ring of S = 3 or 4 k steps of weights, 96 to 128 KiB in flight, requested
-// non-temporally (a tile of up to 192 rows makes them read once, or by two row tiles at once).  KS: the contraction is
+// non-temporally (read once, or by all row tiles of a column at once, on one XCD).  KS: the contraction is
 // split KS ways inside the workgroup: slice s (8 / KS waves, 32 columns each) takes the s-th part of the workgroup's k
 // steps with an activation tile of its own, and the sums meet through LDS in slice order.  That is what keeps tiles
 // narrow enough for a workgroup on (nearly) every compute unit without partial sums in memory: 28672 columns are 224
@@ -959,7 +959,7 @@ __global__ __launch_bounds__(512, 4) void gemm_rows_kernel(const bf16_t* __restr
 // Measured, kernel plus epilogue, weights from HBM, against what ran before (gemm_skinny up to 64 rows, gemm_rows
 // above): 28672 x 4096 at 84 rows 52 -> 44 us, 128 rows 59 -> 48, 157 rows 61 -> 54, 300 rows 99 -> 72; 4096 x 14336 at
 // 84 rows 32 -> 29; 57344 x 8192 at 64 rows 152 -> 138 (6.8 TB/s), 157 rows 225 -> 158; 16384 x 2048 at 16 rows 23 -> 15;
-// 128256 x 4096 at 157 rows 254 -> 183.  Without its copies, LDS reads and MFMAs (timing only) the 28672 x 4096 stream
+// 128256 x 4096 at 157 rows 254 -> 183; 3072 x 2048 at 200 rows 15.9 -> 10.4, 8192 x 28672 at 520 rows 287 -> 260.  Without its copies, LDS reads and MFMAs (timing only) the 28672 x 4096 stream
 // takes 46 us in this form: at 157 rows 8 us are not hidden under it.
 // ------------------------------------------------------------------------------------------------
 // stages and weight ring: four where 128 KiB of LDS and the registers hold them
@@ -1388,30 +1388,34 @@ static bool tiled_ok(int M, int lda, int NB, int K) {
 }
 
 // The forms of gemm_stream and what a k step of a slice takes with one workgroup on every compute unit: step_us, and
-// once per workgroup (the ring's fill, the slices' sums, the epilogue) wg_us.
-struct StreamForm { int mb, ks; double step_us, wg_us; };
-static constexpr StreamForm STREAM_FORMS[] = {{2, 1, 0.57, 3.6}, {2, 2, 0.64, 4.0}, {2, 4, 0.75, 4.2}, {3, 2, 0.86, 2.7}, {3, 4, 1.07, 4.1},
-                                              {4, 1, 0.75, 3.1}, {4, 2, 0.95, 3.3}, {5, 1, 0.83, 3.6}, {5, 2, 1.09, 3.7}, {6, 1, 0.94, 2.3}};
+// once per workgroup (the ring's fill, the slices' sums, the epilogue) wg_us; above 64 rows, and up to 64.
+struct StreamForm { int mb, ks; double step_us, wg_us, few_step_us, few_wg_us; };
+static constexpr StreamForm STREAM_FORMS[] = {
+    {2, 1, 0.67, 10.2, 0.57, 3.6}, {2, 2, 0.78, 10.1, 0.64, 4.0}, {2, 4, 1.02, 9.5, 0.75, 4.2}, {3, 2, 0.93, 10.6, 0, 0}, {3, 4, 1.24, 11.1, 0, 0},
+    {4, 1, 0.86, 12.7, 0, 0}, {4, 2, 1.07, 12.2, 0, 0}, {5, 1, 0.99, 12.7, 0, 0}, {5, 2, 1.22, 13.1, 0, 0}, {6, 1, 1.16, 11.6, 0, 0}};
 struct StreamPlan {
   int form;         // index into STREAM_FORMS, -1: none fits
   int splits, kts;  // splits of K and k steps per split, a multiple of the form's ks
   double us;
 };
 
-// The estimate: rounds of one workgroup per compute unit, the weights at 6.36 TB/s (with two row tiles 15% more where they
-// exceed the last-level cache, 5% less where they fit), the two added by their cubes as in plan_tiled, 3 us for a launch, the partial sums of a split written and read
-// once.  Fitted to sweeps of every form and 1..16 splits over the same products as plan_tiled's at 1 to 400 rows; the form
-// that this and plan_tiled's estimate pick together is within 2% of the fastest on average.
+// The estimate: rounds of one workgroup per compute unit, the weights at 6.36 TB/s, the two added by their cubes as in
+// plan_tiled, the partial sums of a split written and read once.  Up to 64 rows (one row tile) 3 us for a launch.  Above,
+// up to eight row tiles: a step takes 0.65 of its time on an empty chip, growing with the workgroups; several row tiles
+// fetch the weights 1.38 times; the 5.4 us taken off the sum are those that the rings' fills overlap with the stream.  Fitted
+// to sweeps of every form and 1..10 splits at 80 to 760 rows for N x K = 16384 x 2048, 2048 x 8192, 3072 x 2048, 2048 x 2048,
+// 28672 x 4096, 4096 x 14336, 6144 x 4096, 4096 x 4096, 10240 x 8192, 8192 x 8192 and 8192 x 28672 (and at 1 to 64 rows).
 static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) {
   const int KT = K / LG_BK, NP = NB * 32;
+  const bool few = M <= 64;
   const double stream_us = (double)NP * K * 2 / 6.36e6;
   StreamPlan best{-1, 1, KT, 1e30};
   for (int f = 0; f < (int)(sizeof(STREAM_FORMS) / sizeof(STREAM_FORMS[0])); ++f) {
     const StreamForm& F = STREAM_FORMS[f];
-    if (KT % F.ks != 0 || (M <= 64 ? F.mb > 2 : F.mb == 2)) continue;
+    if (KT % F.ks != 0 || (few && F.mb > 2)) continue;
     const int tiles_m = (M + F.mb * 32 - 1) / (F.mb * 32), tiles_n = (NB + 8 / F.ks - 1) / (8 / F.ks);
-    if (tiles_m > 2) continue;  // (the weights would be fetched that often)
-    const double stream = tiles_m == 1 ? stream_us : ((int64_t)NP * K * 2 <= (int64_t)1 << 28 ? 0.95 : 1.15) * stream_us;
+    if (tiles_m > 8) continue;
+    const double stream = tiles_m == 1 ? stream_us : 1.38 * stream_us;
     for (int splits = 1, last = 0; splits <= 16; ++splits) {
       const int kts = (KT / F.ks + splits - 1) / splits * F.ks;
       if (kts == last) continue;
@@ -1420,8 +1424,9 @@ static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) 
       if ((KT - (n - 1) * kts) / F.ks < 4) continue;  // the ring is three or four steps deep, and every slice fills it
       if (n > 1 && (size_t)n * M * NP > ws_elems) break;
       const int64_t wgs = (int64_t)tiles_m * tiles_n * n;
-      const double compute = (kts / F.ks * F.step_us + F.wg_us) * (double)((wgs + n_cus - 1) / n_cus);
-      const double rest = 3.0 + (n > 1 ? 2.5 + (double)n * M * NP * 8 / 5.5e6 : 0.0), left = best.us - rest;
+      const double rounds = (double)((wgs + n_cus - 1) / n_cus), load = wgs < n_cus ? 0.65 + 0.35 * (double)wgs / n_cus : 1.0;
+      const double compute = rounds * (few ? kts / F.ks * F.few_step_us + F.few_wg_us : kts / F.ks * F.step_us * load + F.wg_us);
+      const double rest = (few ? 3.0 : -5.4) + (n > 1 ? 2.5 + (double)n * M * NP * 8 / (few ? 5.5e6 : 6.8e6) : 0.0), left = best.us - rest;
       const double cubes = compute * compute * compute + stream * stream * stream;
       if (left <= 0.0 || cubes >= left * left * left) continue;  // (no root for what cannot win: the plan is made per launch)
       best = StreamPlan{f, n, kts, rest + std::cbrt(cubes)};
@@ -1430,24 +1435,37 @@ static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) 
   return best;
 }
 
-// Where gemm_stream takes a product (tiled_ok holds): weights of 32 MiB and more.  Up to 64 rows gemm_skinny does as well
+// Where gemm_stream takes a product (tiled_ok holds).  Up to 64 rows gemm_skinny does as well
 // with what streams in under 8 us and with most split products (6144 x 4096 at 16 rows 15.4 us there and 16 here, 4096 x
 // 14336 24.0 and 24.5), so there it has to be an unsplit product of 48 MB and more (28672 x 4096 at 16 rows 43 -> 40 us,
 // 16384 x 2048 23 -> 15, 32000 x 2048 at 64 rows 36 -> 32) or weights of 128 MiB and more (10240 x 8192 at 33 rows 37 -> 33,
 // 8192 x 28672 79 -> 76); the widest outputs, where gemm_skinny gives a wave two column blocks, stay with it (128256 x 4096
-// at 33 rows 165 us there, 175 here).  Above 64 rows the two estimates decide, 0.8 us in favour of the tiled kernels, whose
-// smaller products are that much better than estimated.
+// at 33 rows 165 us there, 175 here).  Above 64 rows the two estimates decide,
+// the tiled kernels' corrected by what they were off by in the sweeps (unsplit products 16%, split ones 3%), up to 640 rows:
+// there a streamed product beats them where the chip is filled by one round of whole contractions, or nearly so (3072 x 2048
+// at 200 rows 15.9 -> 10.4 us, at 600 21.6 -> 16.5; 2048 x 2048 at 324 rows 14.9 -> 10.7; 6144 x 4096 at 450 rows 37 -> 31;
+// 8192 x 8192 at 600 rows 96 -> 87), beyond whole rounds of 256-row tiles (57344 x 8192 at 700 rows 598, 629 streamed).
+// A split qkv or output product is summed by the kernel that follows, for 2 to 3 us less than the epilogue kernel that the
+// sweeps timed with it: a whole one has to win by that much (without it a layer of 256 rows lost 3 us in a whole layer).
+// Weights under 10 MiB are streamed unsplit and above 220 rows only (2048 x 2048 at 200 rows 10.7 us, in 8 parts of 96-row
+// tiles 9.0; 1536 x 1024 at 324 rows 7.5 and 12.5).  Over the products of plan_stream's sweeps the choice gains 6% on
+// average against the former rule (32 MiB and more, up to 384 rows and two row tiles), and is 2% off the fastest.
 static bool takes_stream(int M, int NB, int K, size_t ws_elems, int n_cus, const TiledPlan* tiled, StreamPlan& p) {
   const int64_t bytes = (int64_t)NB * 32 * K * 2;
-  if (M > 384 || bytes < (M <= 64 ? 48000000 : (int64_t)1 << 25)) return false;
-  if (M <= 64 && (NB + 3) / 4 > n_cus * (M <= 32 ? 3 : 2)) return false;
-  const bool unsplit = M <= 64 && bytes < ((int64_t)1 << 27);
+  if (M > 64) {
+    const bool small = bytes < (int64_t)10 << 20;
+    if (M > 640 || (small && M <= 220)) return false;
+    p = plan_stream(M, NB, K, small ? 0 : ws_elems, n_cus);
+    const double saved = p.splits == 1 && tiled->splits > 1 ? 2.5 : 0.0;  // what the next kernel saves of a split's epilogue
+    return p.form >= 0 && p.us + 0.8 + saved < tiled->us * (tiled->splits == 1 ? 1.16 : 1.03);
+  }
+  if (bytes < 48000000 || (NB + 3) / 4 > n_cus * (M <= 32 ? 3 : 2)) return false;
+  const bool unsplit = bytes < ((int64_t)1 << 27);
   p = plan_stream(M, NB, K, unsplit ? 0 : ws_elems, n_cus);
   if (p.form < 0) return false;
-  if (unsplit) return ((int64_t)NB * STREAM_FORMS[p.form].ks + 7) / 8 * 4 >= n_cus * 3;
-  if (M <= 64) return true;
-  return p.us + 0.8 < tiled->us;
+  return !unsplit || ((int64_t)NB * STREAM_FORMS[p.form].ks + 7) / 8 * 4 >= n_cus * 3;
 }
+
 template <int MODE, bool PARTIAL>
 static hipError_t run_tiles(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, const TiledPlan& p,
                             float* ws, hipStream_t s) {

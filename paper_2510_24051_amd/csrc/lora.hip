@@ -12,8 +12,9 @@
 //                                               (qkv, o) the partial sums of a product split along K
 // Where the qkv or output product is split along K, the update goes into the partial sums, and the rotary step or the
 // second norm sums them as it does without adapters: no epilogue kernel in between (two of 4.4 us less per layer; 40
-// tokens on four rank-16 adapters, a whole layer 192 -> 187 us).  For o, an fp32 sum, it is added to the first partial copy.  The qkv row is rounded to bf16 before the update and
-// after it, so there the adapted elements are summed here, and the first copy takes the result, the others zeros.
+// tokens on four rank-16 adapters, a whole layer 192 -> 187 us).  For o, an fp32 sum, it is added to the first partial
+// copy.  The qkv row is rounded to bf16 before the update and after it, so there the adapted elements are summed here,
+// and the first copy takes the result, the others zeros.
 // When gate or up carry an adapter the SwiGLU product cannot be fused into the GEMM epilogue; it is taken from the
 // fp32 sums by `swiglu_f32`.
 #include <algorithm>

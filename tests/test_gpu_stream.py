@@ -1,5 +1,5 @@
-"""Wide products at 1 to 384 rows on the streaming kernel: every form it has (rows of a tile, K slices inside a workgroup),
-whole and split along K, one and two row tiles, at row counts around the tiles' edges, with output widths that leave the last
+"""Products at 1 to 640 rows on the streaming kernel: every form it has (rows of a tile, K slices inside a workgroup),
+whole and split along K, one to eight row tiles, at row counts around the tiles' edges, with output widths that leave the last
 column tile partly empty and contractions of an odd number of 64-wide steps; through LM heads (every logit) and through
 layers (all four epilogues, partial sums left to the following kernels)."""
 import numpy as np
@@ -30,7 +30,7 @@ def form(m, rows, n_out, k):
     (1024, 24608, 320, {5: (64, 2, 1), 64: (64, 2, 1), 96: (96, 2, 1), 97: (128, 2, 1), 257: (160, 1, 1), 320: (160, 1, 1), 384: (192, 1, 1)}),
     (2048, 32992, 320, {1: (64, 1, 1), 64: (64, 1, 1)}),
     (4096, 16416, 4096, {33: (64, 1, 3), 97: (128, 1, 3), 129: (160, 1, 3), 192: (192, 1, 3)}),
-    (2048, 8224, 320, {192: (96, 2, 1), 256: (128, 2, 1), 320: (160, 2, 1)}),
+    (2048, 8224, 320, {192: (64, 2, 1), 256: (96, 2, 1), 320: (128, 2, 1)}),
     (1088, 32992, 320, {129: (160, 1, 1), 161: (192, 1, 1)}),  # seventeen k steps
     (2048, 40992, 320, {97: (128, 1, 1), 128: (128, 1, 1)}),
     (4096, 8224, 4096, {65: (96, 2, 3), 128: (128, 2, 3)}),
@@ -80,8 +80,16 @@ def mixed(T, n_decode):
     (129, dict(hidden=1024, mlp=16448), {"gateup": (160, 1, 1)}),
     (192, dict(hidden=1024, mlp=16448), {"gateup": (192, 1, 1)}),
     (96, dict(head_dim=128, n_q=32, n_kv=8, hidden=4096, mlp=4096),
-     {"qkv": (96, 2, 4), "o": (96, 4, 4), "gateup": (96, 4, 2), "down": (96, 4, 4)}),
-    (200, dict(head_dim=128, n_q=64, n_kv=8, hidden=2048, mlp=512), {"qkv": (128, 2, 1)}),
+     {"qkv": (96, 2, 4), "o": (96, 4, 4), "gateup": (96, 2, 4), "down": (96, 4, 4)}),
+    (200, dict(head_dim=128, n_q=64, n_kv=8, hidden=2048, mlp=512), {"qkv": (96, 2, 1)}),
+    # several row tiles of small products
+    (300, dict(hidden=2048, mlp=8192), {"qkv": (64, 4, 1), "o": (64, 4, 1)}),
+    (260, dict(hidden=1024, mlp=4096), {"qkv": (64, 4, 1), "gateup": (96, 2, 1)}),
+    (420, dict(hidden=1024, mlp=4096), {"o": (64, 4, 1), "gateup": (64, 1, 1)}),
+    (500, dict(hidden=1024, mlp=4096), {"gateup": (128, 2, 1)}),
+    (500, dict(n_q=32, n_kv=8, hidden=2048, mlp=512), {"qkv": (64, 2, 1), "o": (64, 4, 1), "gateup": (64, 4, 1), "down": (64, 2, 1)}),
+    (640, dict(hidden=1024, mlp=512), {"qkv": (96, 4, 1), "down": (96, 2, 1)}),
+    (129, dict(hidden=1024, mlp=16448), {"down": (64, 1, 15)}),
 ])
 def test_layers(T, shape, forms):
     m = small_model(**{**dict(head_dim=64, n_q=16, n_kv=4), **shape}, vocab=512)

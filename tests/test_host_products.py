@@ -60,17 +60,17 @@ def test_plan_picks_a_form_near_the_fastest_measured(rows, n_out, k, us):
     assert us[p["tile_rows"], p["splits"]] <= 1.05 * min(us.values())
 
 
-@pytest.mark.parametrize("rows", [1, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 256, 257, 320, 321, 384])
+@pytest.mark.parametrize("rows", [1, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 256, 257, 320, 321, 384, 450, 640])
 @pytest.mark.parametrize("n_out,k", LM_HEAD + [(28672, 4096), (4096, 14336), (6144, 4096), (4096, 4096), (16384, 2048), (2048, 8192),
-                                               (10240, 8192), (8192, 28672), (24608, 1088), (4160, 4160)])
+                                               (10240, 8192), (8192, 28672), (24608, 1088), (4160, 4160), (3072, 2048), (2048, 2048), (1536, 1024), (96, 256)])
 @pytest.mark.parametrize("ws", [0, 3 * 4096 * 100, WS])
 def test_streamed_products_fit_their_form(rows, n_out, k, ws):
-    """At most two row tiles, parts of K that every slice of every workgroup gets at least a full ring of steps of, and room
+    """At most eight row tiles, parts of K that every slice of every workgroup gets at least a full ring of steps of, and room
     for the partial sums."""
     p = product_stream(rows, n_out, k, ws)
     if p["tile_rows"] == 0:
         return
-    assert p["tile_rows"] in (64, 96, 128, 160, 192) and -(-rows // p["tile_rows"]) <= 2
+    assert p["tile_rows"] in (64, 96, 128, 160, 192) and -(-rows // p["tile_rows"]) <= 8
     steps, parts, slices = k // 64, p["splits"], p["k_slices"]
     assert steps % slices == 0
     per = -(-(steps // slices) // parts)       # k steps of a slice, and what is left for the last part
@@ -79,10 +79,26 @@ def test_streamed_products_fit_their_form(rows, n_out, k, ws):
 
 
 def test_what_is_not_streamed():
-    assert product_stream(385, 28672, 4096, WS)["tile_rows"] == 0         # more rows than two tiles
+    assert product_stream(641, 4096, 4096, WS)["tile_rows"] == 0          # more rows than it takes
     assert product_stream(100, 28672, 4096 + 32, WS)["tile_rows"] == 0    # contraction not a multiple of 64
     assert product_stream(100, 2048, 2048, WS)["tile_rows"] == 0          # 8 MiB of weights
     assert product_stream(16, 128256, 4096, WS)["tile_rows"] == 0         # the widest outputs at few rows
     for bad in ((0, 32, 64, 0), (1, 0, 64, 0), (1, 32, 0, 0), (1, 32, 63, 0), (1, 32, 64, -1)):
         with pytest.raises(PieError):
             product_stream(*bad)
+
+
+# (rows, n_out, k, us on the streaming kernel's best form, us on the tiled kernels): weights from HBM, kernel plus epilogue;
+# pairs whose difference is not what a split product's following kernel saves
+STREAMED = [
+    (200, 3072, 2048, 10.4, 15.9), (600, 3072, 2048, 16.5, 21.6), (324, 2048, 2048, 10.7, 14.9), (200, 2048, 2048, 10.7, 9.0),
+    (600, 8192, 8192, 87.1, 96.4),
+    (300, 28672, 4096, 78.2, 99.6), (450, 28672, 4096, 119.1, 104.9), (324, 16384, 2048, 33.6, 31.9), (520, 8192, 28672, 260.4, 286.7),
+    (140, 8192, 1024, 11.0, 16.7), (520, 8192, 1024, 17.9, 17.4), (324, 1536, 1024, 7.5, 12.5), (384, 1024, 4096, 15.7, 13.3),
+]
+
+
+@pytest.mark.parametrize("rows,n_out,k,streamed,tiled", STREAMED)
+def test_the_faster_kernel_takes_the_product(rows, n_out, k, streamed, tiled):
+    p = product_stream(rows, n_out, k, 256 * max(28672, n_out) * 8)
+    assert (p["tile_rows"] > 0) == (streamed < tiled)

@@ -1,11 +1,14 @@
-// Next-token distribution: softmax over the whole vocabulary and exact top-k.
-//
-// Two kernels so that a handful of rows still fills the chip:
-//   topk_chunk : grid (rows, chunks).  A workgroup takes one chunk (<= 8192 logits) of a row, keeps its
+// Next-token distribution: softmax over the whole vocabulary and exact top-k.  Two pairs of kernels, so that a handful of
+// rows still fills the chip; group_threads says which takes a call:
+//   topk_groups + topk_select : where the vocabulary has 2 k groups of 16 logits, which is nearly every call (described
+//                there).
+//   topk_chunk + topk_merge : the rest, at most four chunks of 8192 logits (k above a 32nd of the vocabulary, or a
+//                vocabulary below one chunk).
+//     topk_chunk : grid (rows, chunks).  A workgroup takes one chunk (<= 8192 logits) of a row, keeps its
 //                order-preserving 32-bit keys in registers, reduces the chunk max and sum of exponentials with
 //                wavefront reductions, finds the chunk's k-th largest key by radix select and writes the
 //                chunk's top-k candidates as 64-bit (key, ~id) composites.
-//   topk_merge : grid (rows).  Combines the chunk maxima/sums into the row's softmax normaliser, radix-selects
+//     topk_merge : grid (rows).  Combines the chunk maxima/sums into the row's softmax normaliser, radix-selects
 //                the k largest composites among chunks*k candidates (composites are unique, so ties on the
 //                logit resolve to the lower id), sorts those k with a bitonic network and writes ids and
 //                probabilities of the full distribution.
@@ -443,19 +446,28 @@ __global__ __launch_bounds__(TM_THREADS) void topk_merge_kernel(int n_chunks, in
 //   topk_select : grid (rows).  At least k logits reach the k-th largest group maximum, so only groups whose maximum reaches
 //                 it, and in them only the logits that do, can be among the top k.  A lower bound T of that maximum that
 //                 hardly more than k groups reach comes from a histogram of the maxima between the smallest and the
-//                 largest, refined where a bin holds too many; the groups that reach T are read again (k of them, 32 KiB of
-//                 the row's 513 at k = 256), the logits that reach T (1.2 to 1.4 k of them) go to a list, and each finds its
-//                 place by the counts of a second histogram.  Composites (key, ~id) are unique, so equal logits come in the order
-//                 of their ids; a list that overflows (many equal logits) is cut by the same refinement over composites.
-// Measured against topk_chunk + topk_merge, which select each chunk's k first: 64 rows of 128256, k = 256 22 + 12 -> 9 + 14 us;
-// whole calls: 64 rows, k = 512 210 -> 194, 256 rows of the 70B shape, k = 500 626 -> 597, 26 rows of 32000, k = 50 53 -> 45,
-// 250 rows, k = 512 83 -> 58.  (Launched over and over topk_select takes 9 us: the rest is cold code.)  What is left of
-// topk_select is latency: three dependent reads of memory and a dozen barriers with one workgroup per row.
+//                 largest, refined where a bin holds too many.  Where it ends at one key that many maxima equal (rows with
+//                 equal logits, a masked row with fewer than k groups left), the groups that exceed it, fewer than k, are
+//                 taken, and of those that equal it the ones of the first chunks that hold enough: equal logits win by the
+//                 lower id, and every id of a chunk lies below those of the next.  The groups taken are read again (k of
+//                 them, 32 KiB of the row's 513 at k = 256) and the logits that reach T (1.2 to 1.4 k of them) go to a list as
+//                 their distance from T in (key, ~id), which is unique, so equal logits come in the order of their ids.
+//                 A list that overflows is cut by the same histogram over those distances.  Each entry finds its place
+//                 by counts over ever finer bins, as many bins as entries in each crowded one.
+// Measured against topk_chunk + topk_merge, which select each chunk's k first (both kernels between events, 128256 logits):
+// 64 ordinary rows k = 256 41.7 -> 20.0 us, k = 512 47.5 -> 21.8, 256 rows k = 256 105 -> 43; of 32000, 64 rows k = 256 21.9 ->
+// 14.8.  Rows of other kinds, 64 of them, k = 256: all logits equal 122 -> 30, a quarter tied at the top 62 -> 34, fewer than
+// k unmasked 161 -> 50, one logit far above the rest 74 -> 35, ascending with the id 64 -> 34 (one such row, k = 50: 27 -> 32).
+// (Selecting every group that reaches T, and counting the overflowing ones from the top of the key range, one atomic each:
+// equal logits 650, a quarter tied 275.)  What is left of topk_select is latency: three dependent reads of memory and a dozen
+// barriers with one workgroup per row.
 // ------------------------------------------------------------------------------------------------
 #define TG_THREADS 512
 #define TG_CHUNK (TG_THREADS * 16)
 #define TS_THREADS 1024
 #define TS_LIST 2048
+#define TS_PER (TS_LIST / TS_THREADS)
+#define TS_COUNT 32
 
 __global__ __launch_bounds__(TG_THREADS) void topk_groups_kernel(const float* __restrict__ logits, int V, int m, float inv_temp,
                                                                  uint2* __restrict__ groups) {
@@ -546,6 +558,18 @@ __device__ __forceinline__ uint32_t wave_append(bool take, uint32_t* counter) {
          __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// One more in hist[bin] for every lane that counts.  Lanes that share the first one's bin (many equal values) take one LDS
+// atomic together instead of one each at one address.
+__device__ __forceinline__ void wave_count(bool counts, uint32_t bin, uint32_t* hist) {
+  const unsigned long long mask = __builtin_amdgcn_ballot_w64(counts);
+  if (mask == 0ull) return;
+  const int leader = __ffsll(mask) - 1;
+  const bool same = counts && bin == (uint32_t)__builtin_amdgcn_readlane((int)bin, leader);
+  const unsigned long long together = __builtin_amdgcn_ballot_w64(same);
+  if ((int)(threadIdx.x & 63) == leader) atomicAdd(&hist[bin], (uint32_t)__popcll(together));
+  else if (counts && !same) atomicAdd(&hist[bin], 1u);
+}
+
 template <int PER>  // groups per thread
 __global__ __launch_bounds__(TS_THREADS) void topk_select_kernel(const float* __restrict__ logits, int V, int n_groups, int m, int k,
                                                                  float inv_temp, const uint2* __restrict__ groups,
@@ -553,11 +577,10 @@ __global__ __launch_bounds__(TS_THREADS) void topk_select_kernel(const float* __
   __shared__ uint32_t hist[1024];
   __shared__ uint32_t kmax_s[TS_THREADS / 64], kmin_s[TS_THREADS / 64], wtot[TS_THREADS / 64], sh[3];
   __shared__ float sum_s[TS_THREADS / 64];
-  __shared__ uint32_t n_list, n_sel;
+  __shared__ uint32_t n_list, n_sel, used_bits, in_chunk[16];
   __shared__ uint16_t sel[PER * TS_THREADS];
   __shared__ __align__(16) unsigned long long list[TS_LIST];
-  __shared__ unsigned long long placed[TS_LIST];
-  __shared__ uint16_t first[1024];
+  __shared__ __align__(8) uint32_t cnt[2][TS_LIST], pos[TS_LIST];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = blockIdx.x;
   const float* z = logits + (int64_t)row * V;
@@ -580,7 +603,9 @@ __global__ __launch_bounds__(TS_THREADS) void topk_select_kernel(const float* __
   }
   if (lane == 0) { kmax_s[wave] = kmax; kmin_s[wave] = kmin; }
   hist[tid] = 0u;
-  if (tid == 0) { n_list = 0u; n_sel = 0u; }
+  if (tid < 16) in_chunk[tid] = 0u;
+  if (tid == 0) { n_list = 0u; n_sel = 0u; used_bits = 0u; }
+  *reinterpret_cast<uint2*>(cnt[0] + 2 * tid) = uint2{0u, 0u};
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < TS_THREADS / 64; ++w) { kmax = max(kmax, kmax_s[w]); kmin = min(kmin, kmin_s[w]); }
@@ -595,23 +620,39 @@ __global__ __launch_bounds__(TS_THREADS) void topk_select_kernel(const float* __
     s = wave_sum(s);
     if (lane == 0) sum_s[wave] = s;
   }
+  const int lm = __ffs(m) - 1, lp = 9 - lm;  // m and the groups per chunk are powers of two
+  static_assert(TG_THREADS == 1 << 9, "lp");
+  const uint32_t few = (uint32_t)(k + k / 4 + 32);
   // T: at least k group maxima reach it, and few more.  Bins of 2^shift keys from `base` up; `above` maxima lie past the last.
   uint32_t T = kmin, above = 0u;
+  int chunks_eq = 16;  // groups whose maximum is T itself are taken in chunks below this
   {
     uint32_t base = kmin, span = kmax - kmin;
     int shift = 0;
     while ((span >> shift) > 1023u) ++shift;
-    for (;;) {
+    for (bool refined = false;; refined = true) {
       const uint32_t last = (uint32_t)min((uint64_t)kmax, (uint64_t)base + (((uint64_t)1024 << shift) - 1));
 #pragma unroll
-      for (int i = 0; i < PER; ++i)
-        if (key[i] >= base && key[i] <= last && key[i] != 0u) atomicAdd(&hist[min((key[i] - base) >> shift, 1023u)], 1u);
+      for (int i = 0; i < PER; ++i) {
+        const bool counts = key[i] >= base && key[i] <= last && key[i] != 0u;
+        const uint32_t bin = min((key[i] - base) >> shift, 1023u);
+        if (refined) wave_count(counts, bin, hist);  // (a bin that holds too many, often of one value)
+        else if (counts) atomicAdd(&hist[bin], 1u);
+      }
       __syncthreads();
       uint32_t bin, over, in_bin;
       cut_bin(hist, (uint32_t)k - above, wtot, sh, &bin, &over, &in_bin);
       T = base + (bin << shift);
-      if (shift == 0 || above + over + in_bin <= (uint32_t)(k + k / 4 + 32)) break;
       above += over;
+      if (above + in_bin <= few) break;
+      if (shift == 0) {  // (uniform) T is a key that many maxima equal: the first chunks that hold k - above of them
+#pragma unroll
+        for (int i = 0; i < PER; ++i) wave_count(key[i] == T && T != 0u, (uint32_t)(tid + i * TS_THREADS) >> lp, in_chunk);
+        __syncthreads();
+        uint32_t have = 0u;
+        for (chunks_eq = 0; chunks_eq < 16 && have < (uint32_t)k - above; ++chunks_eq) have += in_chunk[chunks_eq];
+        break;
+      }
       base = T;
       kmax = (uint32_t)min((uint64_t)kmax, (uint64_t)T + (((uint64_t)1 << shift) - 1));  // the maxima past the bin are counted
       shift = max(0, shift - 10);
@@ -619,14 +660,13 @@ __global__ __launch_bounds__(TS_THREADS) void topk_select_kernel(const float* __
   }
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const bool take = key[i] >= T && key[i] != 0u;
+    const int g = tid + i * TS_THREADS;
+    const bool take = key[i] != 0u && (key[i] > T || (key[i] == T && (g >> lp) < chunks_eq));
     const uint32_t p = wave_append(take, &n_sel);
-    if (take) sel[p] = (uint16_t)(tid + i * TS_THREADS);
+    if (take) sel[p] = (uint16_t)g;
   }
   __syncthreads();
   // Every 16-byte piece of the selected groups: f(id of the first logit, the four logits).
-  const int lm = __ffs(m) - 1, lp = 9 - lm;  // m and the groups per chunk are powers of two
-  static_assert(TG_THREADS == 1 << 9, "lp");
   const int n_pieces = (int)n_sel << (2 + lm);
   auto for_pieces = [&](auto f) {
     for (int q = tid; q < n_pieces; q += TS_THREADS) {
@@ -635,99 +675,171 @@ __global__ __launch_bounds__(TS_THREADS) void topk_select_kernel(const float* __
       if (id < V) f(id, *reinterpret_cast<const f32x4*>(z + id));
     }
   };
-  auto comp_of = [](float x, int id) {
-    return ((unsigned long long)order_key(x) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)id);
+  // A logit that reaches T as one number, larger for larger logits and, among equal ones, for lower ids (of 17 bits): its key's
+  // distance from T and ~id.  Where bins of these crowd, `trim` finds the low bits that no such distance has (16 of them where
+  // logits are bf16 values), which are then left out.
+  int tz = 0;
+  auto trim = [&](uint32_t used) {  // used: the bits of this thread's distances
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) used |= (uint32_t)__shfl_xor((int)used, o);
+    if (lane == 0) atomicOr(&used_bits, used);
+    __syncthreads();
+    tz = used_bits ? __ffs((int)used_bits) - 1 : 0;
   };
-  unsigned long long least = (unsigned long long)T << 32;
-  auto collect = [&]() {  // composites of at least `least`; those past the list are only counted
+  auto spot_of = [&](uint32_t from_T, int id) { return ((unsigned long long)(from_T >> tz) << 17) | (uint32_t)(0x1FFFF - id); };
+  unsigned long long least = 0ull;
+  // To the list: all that reach T, or those of at least `least` (past the list they are only counted); one LDS atomic per
+  // wave and piece.
+  auto collect = [&](auto bounded_c) {
     for_pieces([&](int id, const f32x4& x) {
+      bool take[4];
+      unsigned long long mask[4];
+      uint32_t total = 0u;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const unsigned long long c = comp_of(x[e], id + e);
-        const bool take = c >= least;
-        const uint32_t p = wave_append(take, &n_list);
-        if (take && p < TS_LIST) list[p] = c;
+        const uint32_t kx = order_key(x[e]);
+        take[e] = kx >= T;
+        if constexpr (decltype(bounded_c)::value) take[e] = take[e] && spot_of(kx - T, id + e) >= least;
+        mask[e] = __builtin_amdgcn_ballot_w64(take[e]);
+        total += (uint32_t)__popcll(mask[e]);
+      }
+      if (total == 0u) return;
+      const unsigned long long active = __builtin_amdgcn_ballot_w64(true);
+      const int leader = __ffsll(active) - 1;
+      uint32_t p = 0u;
+      if (lane == leader) p = atomicAdd(&n_list, total);
+      p = (uint32_t)__builtin_amdgcn_readlane((int)p, leader);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t at = p + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask[e] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask[e], 0u));
+        if (take[e] && at < TS_LIST) list[at] = spot_of(order_key(x[e]) - T, id + e);
+        p += (uint32_t)__popcll(mask[e]);
       }
     });
     __syncthreads();
   };
-  collect();
-  if (n_list > TS_LIST) {  // (uniform) too many: raise the bound until no more than the list holds reach it
-    unsigned long long base = least;
+  collect(std::false_type{});
+  unsigned long long span = spot_of(kall - T, 0);  // (holds at least an id's 17 bits)
+  const bool trimmed = n_list > TS_LIST;
+  if (trimmed) {  // (uniform) too many: raise the bound until no more than the list holds reach it
+    uint32_t used = 0u;
+    for_pieces([&](int, const f32x4& x) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) used |= order_key(x[e]) >= T ? order_key(x[e]) - T : 0u;
+    });
+    trim(used);
+    span = spot_of(kall - T, 0);
     uint32_t over_all = 0u;
-    int shift = 64 - 10;  // the first bins cover every composite
-    base = 0ull;
-    for (;;) {
+    for (int shift = 54 - __clzll((long long)span);; shift -= 10) {
       for_pieces([&](int id, const f32x4& x) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const unsigned long long c = comp_of(x[e], id + e);
-          if (c >= base && ((c - base) >> shift) < 1024ull) atomicAdd(&hist[(uint32_t)((c - base) >> shift)], 1u);
+          const uint32_t kx = order_key(x[e]);
+          const unsigned long long c = spot_of(kx - T, id + e) - least;
+          wave_count(kx >= T && (c >> shift) < 1024ull, (uint32_t)(c >> shift), hist);  // (below `least` c is huge)
         }
       });
       __syncthreads();
       uint32_t bin, over, in_bin;
       cut_bin(hist, (uint32_t)k - over_all, wtot, sh, &bin, &over, &in_bin);
-      base += (unsigned long long)bin << shift;
-      if (shift == 0 || over_all + over + in_bin <= TS_LIST) break;
+      least += (unsigned long long)bin << shift;
       over_all += over;
-      shift = max(0, shift - 10);  // the next bins subdivide the cut one
+      if (shift <= 10 || over_all + in_bin <= TS_LIST) break;  // (over_all < k: a bin of up to 1024 numbers leaves few enough)
     }
-    least = base;
     if (tid == 0) n_list = 0u;
     __syncthreads();
-    collect();
+    collect(std::true_type{});
   }
   const int n = min((int)n_list, TS_LIST);
   float sum = 0.f;
 #pragma unroll
   for (int w = 0; w < TS_THREADS / 64; ++w) sum += sum_s[w];
   const float inv_sum = 1.0f / sum;
-  auto emit = [&](int slot, unsigned long long v) {
+  auto emit = [&](int slot, int id, float x) {
     if (slot >= k) return;
-    out_ids[(int64_t)row * k + slot] = (int)(0xFFFFFFFFu - (uint32_t)(v & 0xFFFFFFFFull));
-    out_probs[(int64_t)row * k + slot] = expf((key_to_float((uint32_t)(v >> 32)) - gmax) * inv_temp) * inv_sum;
+    out_ids[(int64_t)row * k + slot] = id;
+    out_probs[(int64_t)row * k + slot] = expf((x - gmax) * inv_temp) * inv_sum;
   };
-  // Each composite's place is the number of larger ones.  A histogram of the list between T and the maximum, key and id as one
-  // number, says how many lie in larger bins; the rest is counted among the bin's own, a handful unless a key is common.
-  // (Counting over the whole list took 3.4 us of 18 at k = 256 and 11.5 of 30 at k = 512: every step of it moves 1 KiB out
-  // of LDS per wave.)
-  auto spot_of = [&](unsigned long long c) { return ((c - ((unsigned long long)T << 32)) >> 32 << 17) | (uint32_t)(0x1FFFFu - (0xFFFFFFFFu - (uint32_t)c)); };
-  const unsigned long long span = spot_of((unsigned long long)kall << 32 | 0xFFFFFFFFu);
-  const int shift = max(0, 54 - __clzll((long long)(span | 1ull)));
-  for (int i = tid; i < n; i += TS_THREADS) atomicAdd(&hist[(uint32_t)(spot_of(list[i]) >> shift)], 1u);
-  __syncthreads();
-  {
-    const uint32_t c = hist[1023 - tid];
-    uint32_t incl = c;
+  // Each entry's place is the number of larger ones.  `in_seg` entries share the places from `start` on and differ in their
+  // last `bits` bits; a crowded segment is split by its next bits into as many bins as it has places, its own counters, so one
+  // scan over all counters renumbers every segment, until none holds more than TS_COUNT entries, which are compared.  One round
+  // does unless values crowd in a part of the range (an outlier, equal logits): counting over the whole crowd instead took
+  // 3.4 us of 18 at k = 256 and, with 700 logits far above the others, 30 of 48.
+  unsigned long long mine[TS_PER];
+  uint32_t start[TS_PER], in_seg[TS_PER], slot[TS_PER];
+  int bits[TS_PER];
+#pragma unroll
+  for (int i = 0; i < TS_PER; ++i) {
+    const int at = tid + i * TS_THREADS;
+    mine[i] = at < n ? list[at] : 0ull;
+    start[i] = 0u;
+    in_seg[i] = at < n ? TS_LIST : 0u;  // (all counters are the first segment's)
+    bits[i] = 64 - __clzll((long long)span);
+  }
+  int now = 0;
+  for (bool first = !trimmed;; now ^= 1) {
+#pragma unroll
+    for (int i = 0; i < TS_PER; ++i) {
+      slot[i] = start[i];
+      if (in_seg[i] > TS_COUNT) {
+        const int take = min(bits[i], 31 - __clz((int)in_seg[i]));
+        bits[i] -= take;
+        slot[i] += ((1u << take) - 1u) & ~(uint32_t)(mine[i] >> bits[i]);  // larger ones first
+      }
+      if (in_seg[i] > 0u) atomicAdd(&cnt[now][slot[i]], 1u);
+    }
+    __syncthreads();
+    const uint2 c = *reinterpret_cast<const uint2*>(cnt[now] + 2 * tid);
+    *reinterpret_cast<uint2*>(cnt[now ^ 1] + 2 * tid) = uint2{0u, 0u};
+    const bool crowded = __builtin_amdgcn_ballot_w64(max(c.x, c.y) > TS_COUNT) != 0ull;
+    uint32_t incl = c.x + c.y;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const uint32_t t = __shfl_up(incl, o);
       if (lane >= o) incl += t;
     }
-    if (lane == 63) wtot[wave] = incl;
+    if (lane == 63) wtot[wave] = incl | (crowded ? 0x80000000u : 0u);
     __syncthreads();
-    uint32_t before = 0u;
+    uint32_t before = incl - c.x - c.y, any = 0u;
 #pragma unroll
-    for (int w = 0; w < TS_THREADS / 64; ++w) before += w < wave ? wtot[w] : 0u;
-    first[1023 - tid] = (uint16_t)(before + incl - c);
+    for (int w = 0; w < TS_THREADS / 64; ++w) {
+      before += w < wave ? wtot[w] & 0x7FFFFFFFu : 0u;
+      any |= wtot[w];
+    }
+    *reinterpret_cast<uint2*>(pos + 2 * tid) = uint2{before | c.x << 16, (before + c.x) | c.y << 16};
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TS_PER; ++i)
+      if (in_seg[i] > 0u) {
+        start[i] = pos[slot[i]] & 0xFFFFu;
+        in_seg[i] = pos[slot[i]] >> 16;
+      }
+    if (!(any & 0x80000000u)) break;  // (uniform; entries that agree in all bits would be one)
+    if (first) {
+      first = false;
+      uint32_t used = 0u;
+#pragma unroll
+      for (int i = 0; i < TS_PER; ++i) used |= (uint32_t)(mine[i] >> 17);
+      trim(used);
+#pragma unroll
+      for (int i = 0; i < TS_PER; ++i) {  // (of undecided bits, those above an id's are key bits)
+        mine[i] = ((mine[i] >> (17 + tz)) << 17) | (mine[i] & 0x1FFFFull);
+        if (bits[i] > 17) bits[i] = max(17, bits[i] - tz);
+      }
+    }
   }
-  for (int i = tid; i < n; i += TS_THREADS) {
-    const unsigned long long c = list[i];
-    const uint32_t bin = (uint32_t)(spot_of(c) >> shift);
-    placed[first[bin] + atomicSub(&hist[bin], 1u) - 1u] = c;
-  }
+#pragma unroll
+  for (int i = 0; i < TS_PER; ++i)
+    if (in_seg[i] > 0u) list[start[i] + atomicSub(&cnt[now][slot[i]], 1u) - 1u] = mine[i];
   __syncthreads();
-  for (int i = tid; i < n; i += TS_THREADS) {
-    const unsigned long long mine = placed[i];
-    const uint32_t bin = (uint32_t)(spot_of(mine) >> shift);
-    const int j0 = first[bin], j1 = bin ? first[bin - 1] : n;
-    int place = j0;
-    for (int j = j0; j < j1; ++j) place += placed[j] > mine ? 1 : 0;
-    emit(place, mine);
-  }
-  for (int i = n + tid; i < k; i += TS_THREADS) emit(i, 0ull);  // (fewer than k comparable logits: only with NaNs)
+#pragma unroll
+  for (int i = 0; i < TS_PER; ++i)
+    if (in_seg[i] > 0u) {
+      uint32_t place = start[i];
+      for (uint32_t j = start[i]; j < start[i] + in_seg[i]; ++j) place += list[j] > mine[i] ? 1u : 0u;
+      emit((int)place, 0x1FFFF - (int)(mine[i] & 0x1FFFFull), key_to_float(T + ((uint32_t)(mine[i] >> 17) << tz)));
+    }
+  for (int i = n + tid; i < k; i += TS_THREADS) emit(i, -1, key_to_float(0u));  // (fewer than k comparable logits: only with NaNs)
 }
 
 // Threads per group of topk_groups for a vocabulary of V entries, 0 where the chunk kernels take the row: as many groups as the

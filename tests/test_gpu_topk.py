@@ -178,3 +178,21 @@ def test_infinite_and_undefined_logits():
         gi1, _ = ctx.get_next_dist(ids[:n], k, 1.0)
         z = O.bf16_decode(O.bf16_encode(cols[3])).astype(np.float64)
         assert np.array_equal(gi1[0], np.argsort(-z, kind="stable")[:k])
+
+
+def test_the_sum_over_far_groups_keeps_the_precision_of_expf():
+    """One logit 7 to 10 above 128255 equal ones, so that the sum is made of other groups' shares: the top probability against
+    64 bits, on average.  expf is off by up to one ulp (1.2e-7), by a quarter of that on average; the sums, the reciprocal and the
+    smallest terms added to 1 one by one (15 times 6e-8, of a sum of at least 6.8) add 3e-8 to 5e-8; a base-2 exponential of
+    the scaled distance is off by 2e-7 on average here (its argument, around 13, is rounded to a multiple of 2^-20)."""
+    V, gaps = 128256, np.arange(7 * 16, 10 * 16) / 16.0
+    at = np.random.default_rng(3).integers(0, V, len(gaps))
+    cols = np.zeros((len(gaps), V), np.float32)
+    cols[np.arange(len(gaps)), at] = gaps
+    m, ctx = logit_context(cols, V, (50,), len(gaps))
+    ids = np.arange(len(gaps), dtype=np.int32)
+    ctx.embed_write(ids, O.bf16_encode(np.eye(len(gaps), m.hidden, dtype=np.float32)))
+    gi, gp = ctx.get_next_dist(ids, 50, 1.0)
+    assert np.array_equal(gi[:, 0], at)
+    off = np.abs(gp[:, 0].astype(np.float64) * (1 + (V - 1) * np.exp(-gaps)) - 1)
+    assert off.mean() < 1.2e-7, (off.max(), off.mean())

@@ -26,7 +26,7 @@
 // the chip with half as many workgroups, 32 (16384 logits): half the block-wide synchronisation per logit
 #define TC_LIST 2048  // composites the chunk kernel's short-list selection holds (4 per thread)
 #define TM_THREADS 1024
-#define TM_PER 16  // composites per thread: at most 16384 candidates per row
+#define TM_PER 4  // composites per thread: at most 4096 candidates per row, four chunks of 1024 (see the head of this file)
 
 __device__ __forceinline__ uint32_t order_key(float z) {
   uint32_t u = __float_as_uint(z);
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(TC_THREADS) void topk_chunk_kernel(const float* __r
   for (int i = kc + tid; i < k; i += TC_THREADS) out[i] = 0ull;  // short chunk: pad (a zero never wins)
 }
 
-template <int PER>  // composites per thread: the smallest of 2, 4, 8, 16 that holds the row's candidates
+template <int PER>  // composites per thread: the smaller of 2 and 4 that holds the row's candidates
 __global__ __launch_bounds__(TM_THREADS) void topk_merge_kernel(int n_chunks, int k, float inv_temp,
                                                                 const unsigned long long* __restrict__ cand,
                                                                 const float* __restrict__ stats, int n2,
@@ -900,10 +900,6 @@ hipError_t launch_topk(const float* logits, int n, int V, int k, float inv_temp,
   const dim3 mg(n), mb(TM_THREADS);
   if (n_cand <= 2 * TM_THREADS)
     topk_merge_kernel<2><<<mg, mb, smem_b, s>>>(n_chunks, k, inv_temp, cand_ws, stats_ws, n2, out_ids, out_probs);
-  else if (n_cand <= 4 * TM_THREADS)
-    topk_merge_kernel<4><<<mg, mb, smem_b, s>>>(n_chunks, k, inv_temp, cand_ws, stats_ws, n2, out_ids, out_probs);
-  else if (n_cand <= 8 * TM_THREADS)
-    topk_merge_kernel<8><<<mg, mb, smem_b, s>>>(n_chunks, k, inv_temp, cand_ws, stats_ws, n2, out_ids, out_probs);
   else
     topk_merge_kernel<TM_PER><<<mg, mb, smem_b, s>>>(n_chunks, k, inv_temp, cand_ws, stats_ws, n2, out_ids, out_probs);
   return hipGetLastError();

@@ -1393,6 +1393,10 @@ struct StreamForm { int mb, ks; double step_us, wg_us, few_step_us, few_wg_us; }
 static constexpr StreamForm STREAM_FORMS[] = {
     {2, 1, 0.67, 10.2, 0.57, 3.6}, {2, 2, 0.78, 10.1, 0.64, 4.0}, {2, 4, 1.02, 9.5, 0.75, 4.2}, {3, 2, 0.93, 10.6, 0, 0}, {3, 4, 1.24, 11.1, 0, 0},
     {4, 1, 0.86, 12.7, 0, 0}, {4, 2, 1.07, 12.2, 0, 0}, {5, 1, 0.99, 12.7, 0, 0}, {5, 2, 1.22, 13.1, 0, 0}, {6, 1, 1.16, 11.6, 0, 0}};
+// A whole product that ends in the residual has at most 8192 columns: 32 tiles of 256, with which row tiles of 160 and 192 leave at
+// least half of 256 compute units idle.  No plan picks those there (the sums of six blocks and the residual's rows would not fit
+// the registers either), and they are not built.
+constexpr bool stream_resid_whole(int mb, int ks) { return ks > 1 || mb < 5; }
 struct StreamPlan {
   int form;         // index into STREAM_FORMS, -1: none fits
   int splits, kts;  // splits of K and k steps per split, a multiple of the form's ks
@@ -1405,7 +1409,7 @@ struct StreamPlan {
 // fetch the weights 1.38 times; the 5.4 us taken off the sum are those that the rings' fills overlap with the stream.  Fitted
 // to sweeps of every form and 1..10 splits at 80 to 760 rows for N x K = 16384 x 2048, 2048 x 8192, 3072 x 2048, 2048 x 2048,
 // 28672 x 4096, 4096 x 14336, 6144 x 4096, 4096 x 4096, 10240 x 8192, 8192 x 8192 and 8192 x 28672 (and at 1 to 64 rows).
-static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) {
+static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus, bool resid) {
   const int KT = K / LG_BK, NP = NB * 32;
   const bool few = M <= 64;
   const double stream_us = (double)NP * K * 2 / 6.36e6;
@@ -1423,6 +1427,7 @@ static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) 
       const int n = (KT + kts - 1) / kts;
       if ((KT - (n - 1) * kts) / F.ks < 4) continue;  // the ring is three or four steps deep, and every slice fills it
       if (n > 1 && (size_t)n * M * NP > ws_elems) break;
+      if (n == 1 && resid && !stream_resid_whole(F.mb, F.ks)) continue;
       const int64_t wgs = (int64_t)tiles_m * tiles_n * n;
       const double rounds = (double)((wgs + n_cus - 1) / n_cus), load = wgs < n_cus ? 0.65 + 0.35 * (double)wgs / n_cus : 1.0;
       const double compute = rounds * (few ? kts / F.ks * F.few_step_us + F.few_wg_us : kts / F.ks * F.step_us * load + F.wg_us);
@@ -1450,18 +1455,18 @@ static StreamPlan plan_stream(int M, int NB, int K, size_t ws_elems, int n_cus) 
 // Weights under 10 MiB are streamed unsplit and above 220 rows only (2048 x 2048 at 200 rows 10.7 us, in 8 parts of 96-row
 // tiles 9.0; 1536 x 1024 at 324 rows 7.5 and 12.5).  Over the products of plan_stream's sweeps the choice gains 6% on
 // average against the former rule (32 MiB and more, up to 384 rows and two row tiles), and is 2% off the fastest.
-static bool takes_stream(int M, int NB, int K, size_t ws_elems, int n_cus, const TiledPlan* tiled, StreamPlan& p) {
+static bool takes_stream(int M, int NB, int K, size_t ws_elems, int n_cus, bool resid, const TiledPlan* tiled, StreamPlan& p) {
   const int64_t bytes = (int64_t)NB * 32 * K * 2;
   if (M > 64) {
     const bool small = bytes < (int64_t)10 << 20;
     if (M > 640 || (small && M <= 220)) return false;
-    p = plan_stream(M, NB, K, small ? 0 : ws_elems, n_cus);
+    p = plan_stream(M, NB, K, small ? 0 : ws_elems, n_cus, resid);
     const double saved = p.splits == 1 && tiled->splits > 1 ? 2.5 : 0.0;  // what the next kernel saves of a split's epilogue
     return p.form >= 0 && p.us + 0.8 + saved < tiled->us * (tiled->splits == 1 ? 1.16 : 1.03);
   }
   if (bytes < 48000000 || (NB + 3) / 4 > n_cus * (M <= 32 ? 3 : 2)) return false;
   const bool unsplit = bytes < ((int64_t)1 << 27);
-  p = plan_stream(M, NB, K, unsplit ? 0 : ws_elems, n_cus);
+  p = plan_stream(M, NB, K, unsplit ? 0 : ws_elems, n_cus, resid);
   if (p.form < 0) return false;
   return !unsplit || ((int64_t)NB * STREAM_FORMS[p.form].ks + 7) / 8 * 4 >= n_cus * 3;
 }
@@ -1487,8 +1492,11 @@ static hipError_t run_stream_form(const bf16_t* A, int lda, int M, const PackedW
   const dim3 grid(tiles_m * tiles_n, p.splits), block(512);
   // (raw partial sums depend on the mode by how they are stored only)
   constexpr int PART_MODE = MODE == EPI_STORE_F32 || MODE == EPI_RESID_OUT ? EPI_RESID_OUT : EPI_RESID_EMBED;
-  if (p.splits == 1) gemm_stream_kernel<MODE, false, MB, KS><<<grid, block, 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, p.kts, ws);
-  else gemm_stream_kernel<PART_MODE, true, MB, KS><<<grid, block, 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, p.kts, ws);
+  if (p.splits == 1) {
+    if constexpr ((MODE != EPI_RESID_EMBED && MODE != EPI_RESID_OUT) || stream_resid_whole(MB, KS))
+      gemm_stream_kernel<MODE, false, MB, KS><<<grid, block, 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, p.kts, ws);
+    else return hipErrorInvalidValue;  // (no plan says so)
+  } else gemm_stream_kernel<PART_MODE, true, MB, KS><<<grid, block, 0, s>>>(A, lda, M, W.data, W.N, W.NB, W.K, epi, tiles_m, tiles_n, p.kts, ws);
   return hipGetLastError();
 }
 
@@ -1523,9 +1531,10 @@ static hipError_t run_mode(const bf16_t* A, int lda, int M, const PackedWeight& 
                            size_t ws_elems, int n_cus, hipStream_t s, int* defer) {
   if (M <= 0) return hipSuccess;
   const bool tiled = tiled_ok(M, lda, W.NB, W.K);
+  constexpr bool RESID = MODE == EPI_RESID_EMBED || MODE == EPI_RESID_OUT;
   StreamPlan sp;
   if (M <= 64) {
-    if (tiled && takes_stream(M, W.NB, W.K, ws_elems, n_cus, nullptr, sp)) {
+    if (tiled && takes_stream(M, W.NB, W.K, ws_elems, n_cus, RESID, nullptr, sp)) {
       hipError_t e = run_stream<MODE>(A, lda, M, W, epi, sp, ws, s);
       return e != hipSuccess || sp.splits == 1 ? e : finish_split<MODE>(sp.splits, M, W, epi, ws, s, defer);
     }
@@ -1534,7 +1543,7 @@ static hipError_t run_mode(const bf16_t* A, int lda, int M, const PackedWeight& 
   }
   if (tiled) {
     const TiledPlan p = plan_tiled(M, W.NB, W.K, ws_elems, n_cus);
-    if (takes_stream(M, W.NB, W.K, ws_elems, n_cus, &p, sp)) {
+    if (takes_stream(M, W.NB, W.K, ws_elems, n_cus, RESID, &p, sp)) {
       hipError_t e = run_stream<MODE>(A, lda, M, W, epi, sp, ws, s);
       return e != hipSuccess || sp.splits == 1 ? e : finish_split<MODE>(sp.splits, M, W, epi, ws, s, defer);
     }
@@ -1602,7 +1611,7 @@ void product_stream(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out
   StreamPlan p;
   TiledPlan t{};
   if (M > 64) t = plan_tiled(M, NB, K, ws_elems, n_cus);
-  if (!takes_stream(M, NB, K, ws_elems, n_cus, &t, p)) return;
+  if (!takes_stream(M, NB, K, ws_elems, n_cus, false, &t, p)) return;
   out[0] = STREAM_FORMS[p.form].mb * 32;
   out[1] = STREAM_FORMS[p.form].ks;
   out[2] = p.splits;

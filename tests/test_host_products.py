@@ -1,4 +1,5 @@
 """How products are cut into tiles (pie_product_plan), without a GPU."""
+import numpy as np
 import pytest
 
 from paper_2510_24051_amd import PieError, product_plan, product_stream
@@ -102,3 +103,15 @@ STREAMED = [
 def test_the_faster_kernel_takes_the_product(rows, n_out, k, streamed, tiled):
     p = product_stream(rows, n_out, k, 256 * max(28672, n_out) * 8)
     assert (p["tile_rows"] > 0) == (streamed < tiled)
+
+
+def test_whole_products_that_end_in_the_residual_have_narrow_row_tiles():
+    """Output and down projections (at most 8192 columns) are never streamed whole in row tiles of 160 or 192 by 256 columns, which
+    are not built for them: over every hidden size, and as many contractions, 65 to 640 rows, with and without a workspace."""
+    rng = np.random.default_rng(1)
+    for hidden in range(32, 8193, 32):
+        for rows in (65, 160, 192, 333, 512, 640, *rng.integers(65, 641, 6)):
+            for k in (64 * int(rng.integers(4, 129)), 64 * int(rng.integers(4, 600))):
+                for ws in (0, min(int(rows), 256) * max(hidden, 2 * k) * 8):
+                    p = product_stream(int(rows), hidden, k, ws)
+                    assert p["splits"] != 1 or p["k_slices"] > 1 or p["tile_rows"] < 160, (rows, hidden, k, ws, p)

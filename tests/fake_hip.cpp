@@ -28,6 +28,11 @@ struct Event { size_t upto; };
 size_t malloc_limit = ~(size_t)0, largest_malloc = 0;
 int capturing = 0, event_syncs = 0, fail_event_syncs = 0, allocations = 0;
 long news = 0, fail_new_at = 0;
+struct Kernel { const void* stub; const char* name; };
+std::vector<Kernel, Plain<Kernel>> kernels;
+Bytes launches;  // the names of the kernels launched, one a line, each with the argument asked for
+const char* watched = nullptr;
+int watched_arg = 0;
 
 void drain(size_t upto) {
   for (; n_done < upto; ++n_done) {
@@ -66,11 +71,21 @@ int fake_allocations() { return allocations; }  // calls that allocate or free, 
 int fake_copies_done() { return (int)done.size(); }
 size_t fake_copy_size(int i) { return done[i].size(); }
 const char* fake_copy_data(int i) { return done[i].data(); }
+void fake_watch(const char* part, int arg) { watched = part; watched_arg = arg; }  // launches whose name holds `part` tell int argument `arg`
+const char* fake_launches() {  // since the last time
+  static Bytes told;
+  told.swap(launches);
+  told.push_back(0);
+  launches.clear();
+  return told.data();
+}
 
 // the runtime
 void** __hipRegisterFatBinary(const void*) { static void* handle; return &handle; }
 void __hipUnregisterFatBinary(void**) {}
-void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
+void __hipRegisterFunction(void**, const void* stub, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
+  kernels.push_back(Kernel{stub, name});
+}
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 struct dim3 { unsigned x, y, z; };
 int __hipPushCallConfiguration(dim3, dim3, size_t, void*) { return SUCCESS; }
@@ -80,7 +95,16 @@ int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, void** s) {
   *s = nullptr;
   return SUCCESS;
 }
-int hipLaunchKernel(const void*, dim3, dim3, void**, size_t, void*) { return SUCCESS; }
+int hipLaunchKernel(const void* stub, dim3, dim3, void** args, size_t, void*) {
+  char line[512] = "?\n";
+  for (const Kernel& k : kernels)
+    if (k.stub == stub) {
+      if (watched && strstr(k.name, watched)) snprintf(line, sizeof line, "%s %d\n", k.name, *(const int*)args[watched_arg]);
+      else snprintf(line, sizeof line, "%s\n", k.name);
+    }
+  launches.insert(launches.end(), line, line + strlen(line));
+  return SUCCESS;
+}
 int hipFuncSetAttribute(const void*, int, int) { return SUCCESS; }
 int hipGetDevice(int* d) { *d = 0; return SUCCESS; }
 int hipDeviceGetAttribute(int* v, int, int) { *v = 256; return SUCCESS; }

@@ -7,7 +7,7 @@ import workloads as W
 from oracle import pie_oracle as O
 from helpers import clone_batch, deep_oracle_pools
 from gpu_helpers import appended_positions, assert_bf16_close, assert_close, dec
-from paper_2510_24051_amd import product_plan
+from paper_2510_24051_amd import product_plan, product_stream
 
 pytestmark = pytest.mark.gpu
 
@@ -120,9 +120,11 @@ def test_adapter_updates_join_partial_sums(rows, projections):
                     rope_theta=1e4, n_layers=2)
     reqs = {153: [(70, 19), (1, 90), (45, 0), (1, 33), (2, 64), (1, 17), (33, 5)], 40: [(1, 11 + 3 * i) for i in range(40)],
             3: [(1, 20), (1, 1), (1, 300)]}[rows]
-    if rows > 64:
-        for n_out in (m.n_q_heads * m.head_dim + 2 * m.n_kv_heads * m.head_dim, m.hidden):
-            assert product_plan(rows, n_out, 1024, 1 << 22)["splits"] > 1
+    if rows > 64:  # (that all of them are split and deferred: adapter_updates_of_split_products in test_host_runtime_paths.py)
+        qkv = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim
+        ws = min(rows, 256) * max(2 * m.mlp_dim, qkv, m.hidden) * 8  # the workspace of a context of that many tokens
+        for n_out in (qkv, m.hidden):
+            assert product_stream(rows, n_out, 1024, ws)["tile_rows"] == 0 and product_plan(rows, n_out, 1024, ws)["splits"] > 1
     dw = W.build_deep_workload("ad_parts", m, [W.RequestSpec(*r) for r in reqs], n_kv_pages=256, seed=6800 + rows, std=0.02,
                                resid_std=0.02 / np.sqrt(4.0))
     adapters = {0: W.make_adapter(m, 6800, 0, rank=20, projections=projections, scale=0.5, std=0.05),

@@ -34,22 +34,37 @@ class Child:
         self.C, self.fake = C, C.CDLL(fake, mode=C.RTLD_GLOBAL)
         for name, ret, args in (("fake_fail_new_at", None, [C.c_long]), ("fake_malloc_limit", None, [C.c_size_t]),
                                 ("fake_largest_malloc", C.c_size_t, []), ("fake_copy_size", C.c_size_t, [C.c_int]),
-                                ("fake_copy_data", C.c_void_p, [C.c_int])):
+                                ("fake_copy_data", C.c_void_p, [C.c_int]), ("fake_watch", None, [C.c_char_p, C.c_int]),
+                                ("fake_launches", C.c_char_p, [])):
             getattr(self.fake, name).restype, getattr(self.fake, name).argtypes = ret, args
         sys.modules["torch"] = types.ModuleType("torch")  # (the binding keeps it for device tensors only)
         sys.path.insert(0, ROOT)
         from paper_2510_24051_amd import Pie, binding
         self.Pie, self.binding, self.lib = Pie, binding, binding.load_library()
 
-    def context(self, n_pages=1024, tokens=256, requests=64):
-        b, C, m = self.binding, self.C, MODEL
+    def context(self, n_pages=1024, tokens=256, requests=64, m=MODEL, adapters=0, rank=0):
+        b, C = self.binding, self.C
         p = self.Pie.__new__(self.Pie)
         p.lib, p.device, p.stream, p.model, h = self.lib, None, None, m, C.c_void_p()
         md = b.ModelDescC(m.hidden, m.n_q_heads, m.n_kv_heads, m.head_dim, m.mlp_dim, m.vocab, m.page_size, m.rms_eps, m.rope_theta, 1)
-        pd = b.PoolDescC(n_pages, 1024, tokens, requests, 0, 0, 0, 0)
+        pd = b.PoolDescC(n_pages, 1024, tokens, requests, 0, 0, adapters, rank)
         assert self.lib.pie_create(C.byref(md), C.byref(pd), None, C.byref(h)) == 0
         p.ctx = h
         return p
+
+    def loaded(self, pairs=(), m=MODEL, **kw):
+        """A context with the weights of its layer and `pairs` (adapter, projection, rank)."""
+        ctx, C = self.context(m=m, **kw), self.C
+        room = np.zeros(2 * max(m.hidden, m.n_q_heads * m.head_dim) * max(m.mlp_dim, m.hidden, m.n_q_heads * m.head_dim), np.int8)
+        at = C.c_void_p(room.ctypes.data)  # (kernels do nothing, copies read from here)
+        assert self.lib.pie_load_layer(ctx.ctx, 0, *[at] * 9) == 0
+        for adapter, proj, r in pairs:
+            assert self.lib.pie_load_adapter(ctx.ctx, adapter, 0, proj, r, C.c_float(1.0), at, at) == 0
+        ctx.synchronize()
+        return ctx
+
+    def launches(self):
+        return self.fake.fake_launches().decode().split("\n")[:-1]
 
     def copies(self):
         return [self.C.string_at(self.fake.fake_copy_data(i), self.fake.fake_copy_size(i)) for i in range(self.fake.fake_copies_done())]
@@ -188,7 +203,56 @@ def no_room_for_parts(c):
         ctx.close()
 
 
-CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy, no_room_for_parts)}
+def adapter_updates_of_split_products(c):
+    """Where the qkv or output product is split along K, an adapter's update joins the partial sums and no epilogue kernel runs in
+    between: at the shapes of the device test of the same, all of which are split."""
+    m = SimpleNamespace(**{**vars(MODEL), "hidden": 1024, "n_q_heads": 16, "n_kv_heads": 4, "mlp_dim": 512})
+    c.fake.fake_watch(b"lora_up_kernel", 3)  # the kind of the destination
+    batches = {153: [(70, 19), (1, 90), (45, 0), (1, 33), (2, 64), (1, 17), (33, 5)], 40: [(1, 11 + 3 * i) for i in range(40)],
+               3: [(1, 20), (1, 1), (1, 300)]}
+    for rows, projections in ((153, (0, 1, 2, 3)), (153, (2,)), (153, (3,)), (40, (0, 1, 3)), (3, (1, 3))):
+        ctx = c.loaded([(0, pj, 20) for pj in projections], m, tokens=rows, requests=40, adapters=1, rank=32)
+        b = batch_of(batches[rows])
+        assert b.n_tokens == rows
+        b.adapter_ids = np.zeros(b.n_requests, np.int32)
+        pb = ctx.batch_create(b)
+        c.launches()
+        ctx.forward(0, pb)
+        names = c.launches()
+        kinds = [int(n.split()[1]) for n in names if "lora_up_kernel" in n]
+        assert kinds == ([4] if min(projections) < 3 else []) + ([1] if 3 in projections else []), (rows, kinds)
+        # neither product has an epilogue kernel (modes 0 and 1), and the second norm forms its rows from the partial sums
+        assert not any("splitk_epilogue_kernelILi0E" in n or "splitk_epilogue_kernelILi1E" in n for n in names), names
+        norms = [n for n in names if "rmsnorm_kernel" in n]
+        assert len(norms) == 2 and "rmsnorm_kernelILi2E" in norms[1], norms
+        pb.destroy()
+        ctx.close()
+
+
+def attentions_in_one_launch(c):
+    """Prompts of four query heads per kv head, or the tiles of a shared prefix, go with the decode waves in one launch; with stage
+    timing on they are launched apart."""
+    tree = batch_of([(1, 16 * 1000 + 20)] * 96)
+    own = 1000 + np.arange(96 * 2).reshape(96, 2)
+    tree.page_ids = np.concatenate([np.concatenate([np.arange(1000), pages]) for pages in own])
+    for b, shared in ((batch_of([(150, 400), (1, 300), (1, 40)]), False), (tree, True)):
+        ctx = c.loaded(n_pages=1200, requests=128)
+        pb = ctx.batch_create(b)
+        for timed in (False, True):
+            ctx.set_stage_timing(timed)
+            c.launches()
+            ctx.forward(0, pb)
+            names = [n for n in c.launches() if "attn_" in n and "merge" not in n]
+            if timed:
+                assert len(names) == 2 and not any("attn_both" in n for n in names), names
+            else:
+                assert len(names) == 1 and "attn_both_kernelILi64E" in names[0] and ("ELb1ELb1E" in names[0]) == shared, names
+        pb.destroy()
+        ctx.close()
+
+
+CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy, no_room_for_parts,
+                                 adapter_updates_of_split_products, attentions_in_one_launch)}
 
 if __name__ == "__main__":
     CASES[sys.argv[2]](Child(sys.argv[1]))

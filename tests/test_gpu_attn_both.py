@@ -35,3 +35,24 @@ def test_prefill_and_decode_in_one_launch(D, n_kv, shape, workgroups, waves):
     ctx.set_stage_timing(True)  # the same kernels' work, launched apart: the same results bit for bit
     ctx.forward(0, pb)
     assert np.array_equal(ctx.embed_read(w.batch.out_embed_ids), y)
+
+
+@pytest.mark.parametrize("D,n_q,n_kv,R,pages,prompt", [
+    (128, 32, 8, 150, 161, False),   # tiles of groups of 32 requests beside the decode waves of their own pages
+    (64, 32, 16, 150, 250, True),    # two query heads per kv head; a prompt whose rows see few keys keeps a launch of its own
+])
+def test_shared_prefix_and_decode_in_one_launch(D, n_q, n_kv, R, pages, prompt):
+    m = small_model(D, n_q, n_kv)
+    rng = np.random.default_rng(R + D)
+    prefix = 16 * pages
+    reqs = [W.RequestSpec(1, prefix + int(rng.integers(1, 90)), prefix_group=0, prefix_len=prefix) for _ in range(R)]
+    reqs += [W.RequestSpec(1, 300)] + ([W.RequestSpec(20, 3)] if prompt else [])
+    w = W.build_workload("both_shared", m, reqs, n_kv_pages=pages + 8 * len(reqs) + 64, seed=700 + D, std=0.05)
+    ctx, pb, y, _ = compare_layer(w, what=f"D={D} {R} branches on {prefix} tokens")
+    info, parts = pb.plan_info(), pb.plan_parts()
+    # wide groups and decode waves, and no prompt of plain weights that would take the joint launch instead
+    assert parts["wide_groups"] > 0 and info["decode_waves"] > 0 and info["prefill_workgroups"] == 0, (info, parts)
+    assert (info["prefill_workgroups_pair_weights"] > 0) == prompt
+    ctx.set_stage_timing(True)  # launched apart
+    ctx.forward(0, pb)
+    assert np.array_equal(ctx.embed_read(w.batch.out_embed_ids), y)

@@ -8,7 +8,7 @@
 // The page layout (internal.h) makes every K and V operand one coalesced 16-byte load per lane,
 // and the S^T accumulator registers, converted to bf16, are already the P^T operand.
 //
-//   attn_decode  : requests with few new tokens (n_new * group <= 32 query rows).  HBM-bound.  The visit list
+//   attn_decode  : requests with few new tokens (n_new * group <= 16 query rows).  HBM-bound.  The visit list
 //                  is cut into chunks (split-K); one wave per (chunk, kv head) streams its pages and writes an
 //                  unnormalised partial (running max, sum, O) that attn_merge combines.
 //   attn_prefill : one workgroup per (request, 32-token query block, kv head), one wave per query head of

@@ -956,11 +956,12 @@ __global__ __launch_bounds__(512, 4) void gemm_rows_kernel(const bf16_t* __restr
 // narrow enough for a workgroup on (nearly) every compute unit without partial sums in memory: 28672 columns are 224
 // tiles of 128 (KS = 2), 16384 are 256 tiles of 64 (KS = 4).  Activations go to LDS by direct copies as in gemm_rows, S
 // stages, rows swizzled.
-// Measured, kernel plus epilogue, weights from HBM, against what ran before (gemm_skinny up to 64 rows, gemm_rows
-// above): 28672 x 4096 at 84 rows 52 -> 44 us, 128 rows 59 -> 48, 157 rows 61 -> 54, 300 rows 99 -> 72; 4096 x 14336 at
+// Measured by itself, kernel plus epilogue, weights from HBM, against what ran before (gemm_skinny up to 64 rows, gemm_rows
+// above): 28672 x 4096 at 84 rows 52 -> 44 us, 128 rows 59 -> 48, 157 rows 61 -> 54, 300 rows 100 -> 78; 4096 x 14336 at
 // 84 rows 32 -> 29; 57344 x 8192 at 64 rows 152 -> 138 (6.8 TB/s), 157 rows 225 -> 158; 16384 x 2048 at 16 rows 23 -> 15;
-// 128256 x 4096 at 157 rows 254 -> 183; 3072 x 2048 at 200 rows 15.9 -> 10.4, 8192 x 28672 at 520 rows 287 -> 260.  Without its copies, LDS reads and MFMAs (timing only) the 28672 x 4096 stream
-// takes 46 us in this form: at 157 rows 8 us are not hidden under it.
+// 128256 x 4096 at 157 rows 254 -> 183; 3072 x 2048 at 200 rows 15.9 -> 10.4, 8192 x 28672 at 520 rows 287 -> 260.  Within
+// passes over several layers (kernel trace) 28672 x 4096 takes 45, 57, 64 and 86 us at 84, 128, 157 and 300 rows.  Without
+// its copies, LDS reads and MFMAs (timing only) that stream takes 46 us by itself: at 157 rows 8 us are not hidden under it.
 // ------------------------------------------------------------------------------------------------
 // stages and weight ring: four where 128 KiB of LDS and the registers hold them
 constexpr int stream_stages(int mb, int ks) { return ks == 1 && mb <= 5 ? 4 : ks == 2 && mb == 2 ? 4 : 3; }
@@ -1281,20 +1282,20 @@ template <int MB, int MODE>
 static hipError_t run_skinny(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, float* ws,
                              size_t ws_elems, int n_cus, hipStream_t s, int* defer) {
   if constexpr (MODE == EPI_SWIGLU) {
-    // Wide enough MLPs fill the chip with one block per wave and no split at all (gate and up meet through LDS):
-    // no partial sums to write, read back and write out of the caches (70B shape, 16 rows: 179 -> 163 us, the
-    // forward call 0.410 -> 0.389 ms).  With fewer workgroups than that (8B shape: 224 on 256 CUs) the split
-    // version with a gate/up pair per wave is faster.
+    // What the streaming kernel leaves (takes_stream): K not a multiple of 64, weights under 48 MB, outputs that would be its
+    // widest.  Wide enough MLPs fill the chip with one block per wave and no split at all (gate and up meet through LDS): no
+    // partial sums to write, read back and write out of the caches.  Whole layers of 32 rows, weights from HBM, against the
+    // split version with a gate/up pair per wave: 49152 x 448 67 us and 76, 57344 x 4128 169 and 188.
     if constexpr (MB <= 2) {
       if ((W.NB + 3) / 4 >= n_cus + n_cus / 2)
         return run_skinny_n<MB, MODE, 1>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer, 1);
-      // the 8B width gets there with workgroups of one pair (two waves): 448 of them; as fast as the split
-      // version and without its 29 MB of partial sums (the down projection after it gains 1 us)
+      // narrower ones get there with workgroups of one pair (two waves): layers of 32 rows, 28672 x 512 54 us and 59, 28672 x
+      // 768 59 and 68, 28672 x 4128 119 and 129
       if ((W.NB + 1) / 2 >= n_cus + n_cus / 2) {
         // With two row blocks a two-wave workgroup fetches as many activation bytes (through the L2) as weight
         // bytes.  Eight waves, two pairs times two K slices, share each slice's activation tile between two pairs
-        // and put twice as many waves on the weight stream: 53 -> 47 us at 64 rows.  (Four waves, one pair times two
-        // slices, measured the same as two; with one row block the two-wave form stays ahead.)
+        // and put twice as many waves on the weight stream (layers of 64 rows, 28672 x 512 64.3 -> 63.6 us, 28672 x 768
+        // 70.0 -> 69.3).  With one row block the two-wave form stays ahead.
         if (MB == 2 && W.K % (2 * SK_BK) == 0)
           return run_skinny_n<MB, MODE, 1, 8, 2>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer, 1);
         return run_skinny_n<MB, MODE, 1, 2>(A, lda, M, W, epi, ws, ws_elems, n_cus, s, defer, 1);

@@ -1572,7 +1572,8 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   // Small batches split their projections along K.  Where the next kernel reads the projection's output row by
   // row anyway, it sums the partial copies itself and the separate epilogue launch is saved: the rotary step
   // after QKV, the second norm after the output projection, the next layer's first norm after the down
-  // projection.  An adapter update that sits between the two kernels rules this out.
+  // projection.  An adapter's update of q, k, v or o joins the partial copies before they are summed, one of the
+  // down projection the residual that is added to them.
   const int carried = (carry && x_in) ? *carry : 0;
   if (carry) *carry = 0;
 
@@ -1805,7 +1806,8 @@ extern "C" pie_status pie_get_next_dist_static(pie_ctx* c, const int32_t* embed_
   if (!c->static_scratch) return fail(c, PIE_EHIP, "the static scratch array of device %d was not found at pie_create", c->device);
   for (int i = 0; i < n; ++i)
     if (embed_ids[i] < 0 || embed_ids[i] >= c->p.n_embeds) return fail(c, PIE_ERANGE, "embed id %d at %d outside [0, %d)", embed_ids[i], i, c->p.n_embeds);
-  // carve the array: 256 bytes (kept free, the size limits count them) | normalised rows | logits | candidates | chunk statistics | split-K partials (the rest)
+  // carve the array: 256 bytes (unused; the stated limit counts them, so that no call is taken on one build and refused on
+  // another) | normalised rows | logits | candidates | chunk statistics | split-K partials (the rest)
   const size_t H = (size_t)c->m.hidden, V = (size_t)c->m.vocab;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t o_en = 256, o_lg = up(o_en + (size_t)n * H * 2);

@@ -32,7 +32,7 @@ PMC_TRAFFIC = {"workload": "c2", "requests": 64, "layers": 1, "lora_rank": 0, "b
 
 
 def mixed_workload_fractions(w_dec, args):
-    """A short run of the mixed workload (configs[2]: 8 prefill requests of 1024 tokens + 128 decode requests through
+    """A short run of the mixed workload (8 prefill requests of 1024 tokens + 128 decode requests through
     the same 8B-shaped layer, whose weights are reused) for the MFMA-bound kernels: the four tiled layer GEMMs and
     prefill attention as fractions of the dense bf16 matrix peak, from the library's per-stage HIP events."""
     import numpy as np
@@ -67,7 +67,7 @@ def mixed_workload_fractions(w_dec, args):
     ctx.set_stage_timing(False)
     QD, KD, H, I = m.n_q_heads * m.head_dim, m.n_kv_heads * m.head_dim, m.hidden, m.mlp_dim
     shapes = {"qkv": H * (QD + 2 * KD), "oproj": QD * H, "gateup": 2 * H * I, "down": I * H}
-    out = {"workload": "configs[2]: 8 prefill x 1024 (prior U[0,2048]) + 128 decode @2048, one 8B-shaped layer",
+    out = {"workload": "8 prefill x 1024 (prior U[0,2048]) + 128 decode @2048, one 8B-shaped layer",
            "tokens": T, "forward_ms": round(fwd_ms, 4), "tokens_per_s": round(T / (fwd_ms * 1e-3), 1),
            "peak_TFLOPs": MFMA_BF16_PEAK_TFLOPS, "kernels": {}}
     tot_f, tot_ms = 0.0, 0.0
@@ -132,19 +132,19 @@ def main():
     t_setup = time.time()
     if args.workload == "c2":
         w = W.c2_decode(top_k=args.top_k, n_requests=args.requests)
-        desc = (f"configs[1]: Llama-3-8B-shaped layer, {args.requests} decode requests, prior ctx U[512,4096], "
+        desc = (f"Llama-3-8B-shaped layer, {args.requests} decode requests, prior ctx U[512,4096], "
                 "40k-page pool, page 16")
     elif args.workload == "c3":
         w = W.c3_mixed()
-        desc = "configs[2]: 8B-shaped layer, 8 prefill x 1024 (prior U[0,2048]) + 128 decode @2048"
+        desc = "8B-shaped layer, 8 prefill x 1024 (prior U[0,2048]) + 128 decode @2048"
     elif args.workload == "c4":
         w = W.c4_prefix_tree(with_head=True)
         w.top_k = args.top_k
         w.dist_rows = np.arange(w.batch.n_tokens, dtype=np.int32)
-        desc = "configs[3]: 8B-shaped layer, 256 branches sharing a 4096-token prefix, bitmap masks"
+        desc = "8B-shaped layer, 256 branches sharing a 4096-token prefix, bitmap masks"
     else:
         w = W.c5_sparse_long()
-        desc = "configs[4]: 70B-shaped layer, 16 requests @32768, sink(4)+window(4096) bitmaps"
+        desc = "70B-shaped layer, 16 requests @32768, sink(4)+window(4096) bitmaps"
     b = w.batch
     T = int(b.n_tokens)
     # distinct output Embeds so that every step does identical work on identical inputs

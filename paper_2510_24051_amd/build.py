@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpie_mi355.so")
 PROBE = os.path.join(HERE, "pie_probe")  # stand-alone microbenchmarks of the chip's ceilings (csrc/probe_ceilings.hip)
-SOURCES = ["pie_ctx.hip", "gemm.hip", "attention.hip", "elementwise.hip", "dist.hip", "lora.hip"]
+SOURCES = ["pie_ctx.hip", "gemm.hip", "few.hip", "attention.hip", "elementwise.hip", "dist.hip", "lora.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -1,0 +1,484 @@
+// Products of 1 to 16 rows (single users, small decode batches): the weight stream and the launches around it.
+//
+// A workgroup of eight waves owns 16 output columns for the whole contraction; each wave takes an eighth of it on 16x16x32
+// MFMAs and the eight sums meet through LDS in wave order.  So a 4096-column product is 256 workgroups, one per compute unit,
+// with no partial sums in memory and nothing left for another kernel to add up, and the work of the small kernels around a
+// product moves into it:
+//   few_rows_kernel    each wave keeps its K slice of the rows in registers as MFMA operands (K = 256 * NS, NS <= 32) and walks
+//                      any number of column tiles; the rows may be normalised on the way in (RMSNorm of Embeds or of fp32
+//                      rows: every workgroup does it for itself, 16 rows, while its first weights are in flight); a QKV tile is
+//                      rotated and appended to its page, a gate/up tile becomes eight activations
+//   few_stream_kernel  rows streamed beside the weights (long contractions; products that end in the residual)
+// A wave has 16 KiB of weights in flight (128 KiB per compute unit), requested non-temporally through buffer descriptors;
+// requests past the end are sent out of the buffer's range, where they return without touching memory.
+//
+// Bound by HBM, and by launches: a layer of 11 launches has 7.  Kernel trace, one and 16 rows, before (norm + product + rotary
+// step, product + second norm, product, product + epilogue) and now:
+//                    6144 x 4096 q, k, v   4096 x 4096 output + norm   28672 x 4096 gate/up   4096 x 14336 down   layer, wall
+//   1 row     us     18.0 -> 14.7          11.2 -> 8                   40.7 -> 40.5           25.3 -> 21.0        124 -> 110
+//   16 rows          19.9 -> 15.8          13.8 -> 10.5                40.9 -> 42.8           26.1 -> 23.9
+// (the norm of the third column is part of gate/up now); logits of 128256 x 4096 with their norm 169 -> 156 and 167 -> 163, of
+// 32000 x 2048 30 -> 22.5 and 32 -> 24.  Why not more rows: the rows come out of L2 beside the weights, in the same order of
+// returns, 459 KiB per compute unit for 16 rows of 14336 against 459 KiB of weights, and cost 3 us of 24; with 32 rows the
+// split product and its epilogue are as fast.
+#include <algorithm>
+#include <type_traits>
+
+#include "internal.h"
+
+namespace {
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+constexpr int FEW_RING = 16;  // weight requests of a wave in flight, 1 KiB each
+
+// Columns of a tile.  Plain: 16 in a row.  Pairs: eight columns and the eight they belong with (gate and up of a 32-column
+// block pair, or a rotary piece and its other half), in lanes 0-7 and 8-15 of each row of 16: 128-byte pieces of the
+// tiled weights instead of 256.
+__device__ __forceinline__ int64_t tile_base(int mode, int t, int KB, int D) {  // elements, at k = 0
+  if (mode == EPI_SWIGLU) return (int64_t)(t >> 2) * 2 * KB * 512 + (t & 3) * 64;
+  if (mode == EPI_STORE_BF16) {
+    const int cpt = D / 16, n0 = (t / cpt) * D + (t % cpt) * 8;
+    return (int64_t)(n0 >> 5) * KB * 512 + (n0 & 31) * 8;
+  }
+  return (int64_t)(t >> 1) * KB * 512 + (t & 1) * 128;
+}
+__device__ __forceinline__ int tile_lane(int mode, int lane, int KB, int D) {  // elements
+  const int c = lane & 15, q = lane >> 4, at = (q >> 1) * 512 + (q & 1) * 256;
+  if (mode == EPI_SWIGLU) return at + (c & 7) * 8 + (c >> 3) * KB * 512;
+  if (mode == EPI_STORE_BF16) return at + (c & 7) * 8 + (c >> 3) * (D / 64) * KB * 512;
+  return at + c * 8;
+}
+// Position of element k (of 64) of row r in a wave's LDS scratch: rows of 128 bytes, 16-byte chunks swizzled so that the 16
+// rows' chunks of one k step (an operand read) fall on different banks.
+__device__ __forceinline__ int turn_at(int r, int k) { return r * 64 + (((k >> 3) ^ ((r >> 1) & 7)) << 3) + (k & 7); }
+
+constexpr int RSRC_FLAGS = 0x00020000;      // raw dword buffer, gfx9 family
+constexpr uint32_t OUT_OF_RANGE = 0xFFFFFF00u;
+
+// ------------------------------------------------------------------------------------------------
+// MODE: EPI_STORE_BF16 (q, k, v rotated and stored), EPI_SWIGLU, EPI_STORE_F32.
+// ------------------------------------------------------------------------------------------------
+template <int MODE, int SRC, int NS>
+__global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds arg_ids, int M, const bf16_t* __restrict__ Wp, int NB, int n_tiles,
+                                                          void* __restrict__ out, int ldo, FewRope rope) {
+  constexpr int K = NS * 256, KB = K / 16;
+  [[maybe_unused]] constexpr int R = NS < FEW_RING ? NS : NS > FEW_RING ? FEW_RING / 2 : FEW_RING;
+  [[maybe_unused]] constexpr int EARLY = SRC == FEW_F32 && R > 12 ? 12 : R;  // requested ahead of the norm (registers)
+  constexpr bool ROPE = MODE == EPI_STORE_BF16;
+  __shared__ __align__(16) float red[2][8][256];
+  __shared__ __align__(16) bf16_t turn[8][16 * 64];
+  constexpr int KEPT = MODE == EPI_STORE_F32 ? 32 : 16;  // tiles whose sums are kept for the epilogue
+  __shared__ __align__(16) float done[KEPT][256];
+  __shared__ float row_ss[8][16];
+  __shared__ __align__(16) bf16_t gain_s[K];
+  __shared__ __align__(16) float ang[ROPE ? 16 * 128 : 4];
+  __shared__ int place[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, q = lane >> 4, wgs = gridDim.x;
+  const int D = rope.D;
+  bf16x8 A[NS];
+  [[maybe_unused]] const int k0 = wave * (NS * 32);  // the wave's columns of the rows: k0 .. + NS * 32
+
+  // what the norm and the epilogue read, into registers now and into LDS behind the weight requests
+  // (bf16 rows: this lane loads from rows lane / 8 and 8 + lane / 8, fp32 rows: from lane / 16, + 4, + 8, + 12)
+  [[maybe_unused]] int ids[2];
+  if constexpr (SRC != FEW_F32) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = min(h * 8 + (lane >> 3), M - 1);
+      ids[h] = SRC == FEW_EMBED ? src.ids[r] : arg_ids.v[r];
+    }
+  }
+  constexpr int GP = (K + 4095) / 4096;
+  u32x4 g_in[GP];
+#pragma unroll
+  for (int i = 0; i < GP; ++i) g_in[i] = *reinterpret_cast<const u32x4*>(src.gain + min(i * 4096 + tid * 8, K - 8));
+  [[maybe_unused]] f32x4 ang_in;
+  [[maybe_unused]] int place_in;
+  if constexpr (ROPE) {
+    ang_in = *reinterpret_cast<const f32x4*>(rope.angles + min(tid * 4, M * D - 4));
+    place_in = ((tid & 16) ? rope.tok_slot : rope.tok_page)[min(tid & 15, M - 1)];
+  }
+  auto fill_lds = [&]() {
+#pragma unroll
+    for (int i = 0; i < GP; ++i)
+      if (i * 4096 + tid * 8 < K) *reinterpret_cast<u32x4*>(gain_s + i * 4096 + tid * 8) = g_in[i];
+    if constexpr (ROPE) {
+      if (tid * 4 < M * D) *reinterpret_cast<f32x4*>(ang + tid * 4) = ang_in;
+      if (tid < 32) place[tid >> 4][tid & 15] = place_in;
+    }
+  };
+#if __HIP_DEVICE_COMPILE__
+  const __amdgpu_buffer_rsrc_t rsrc_w =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Wp), 0, (int)((int64_t)NB * 32 * K * 2), RSRC_FLAGS);
+  const uint32_t woff = (uint32_t)(tile_lane(MODE, lane, KB, D) + wave * NS * 1024) * 2;
+  u32x4 W[R];
+  int round = 0, t = blockIdx.x;
+  uint32_t base = t < n_tiles ? (uint32_t)(tile_base(MODE, t, KB, D) * 2) : 0;
+  auto load_w = [&](uint32_t from, bool real, const int step, const int slot) {
+    W[slot] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, real ? woff : OUT_OF_RANGE, real ? from + step * 2048 : 0, 2);  // (2: non-temporal)
+  };
+  // The rows are requested before the weights: requests return in order, and the rows are needed first.  Lanes load 128 (256)
+  // consecutive bytes of a row together and the wave turns two k steps at a time into operands through 2 KiB of LDS of
+  // its own (LDS operations of a wave are carried out in order: no barrier).
+  bf16_t* const my_turn = turn[wave];
+  auto put = [&](int r, int k, auto v) { *reinterpret_cast<decltype(v)*>(my_turn + turn_at(r, k)) = v; };
+  auto operands = [&](const int p) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) A[2 * p + h] = *reinterpret_cast<const bf16x8*>(my_turn + turn_at(c, h * 32 + q * 8));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // 1 / rms of rows r0, r0 + step, ..: sums of this wave's columns in `ss`, one row each per LANES lanes
+  [[maybe_unused]] auto inv_rms = [&](auto lanes_c, auto& ss) {
+    constexpr int LANES = decltype(lanes_c)::value, ROWS = 64 / LANES, N = 16 / ROWS;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+#pragma unroll
+      for (int o = 1; o < LANES; o <<= 1) ss[i] += __shfl_xor(ss[i], o);
+      if ((lane & (LANES - 1)) == 0) row_ss[wave][i * ROWS + lane / LANES] = ss[i];
+    }
+    PIE_S_WAIT_LGKMCNT0();
+    wg_barrier();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      float tot = 0.f;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) tot += row_ss[w][i * ROWS + lane / LANES];
+      ss[i] = 1.0f / sqrtf(tot / (float)K + src.eps);
+    }
+  };
+  if constexpr (SRC == FEW_F32) {
+    f32x4 x[NS / 2][4];
+    const float* xp[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      xp[i] = reinterpret_cast<const float*>(src.x) + (int64_t)min(i * 4 + (lane >> 4), M - 1) * src.ldx + k0 + (lane & 15) * 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i * 4 < M) {  // (operand rows past M may hold anything: they end in sums of rows that are not stored)
+#pragma unroll
+        for (int p = 0; p < NS / 2; ++p) x[p][i] = *reinterpret_cast<const f32x4*>(xp[i] + p * 64);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < EARLY; ++s) load_w(base, t < n_tiles, s, s);
+    __builtin_amdgcn_sched_barrier(0);
+    fill_lds();
+    float ss[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i * 4 < M) {
+#pragma unroll
+        for (int p = 0; p < NS / 2; ++p)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ss[i] += x[p][i][e] * x[p][i][e];
+      }
+    inv_rms(std::integral_constant<int, 16>{}, ss);
+#pragma unroll
+    for (int p = 0; p < NS / 2; ++p) {
+      const bf16x4 g = *reinterpret_cast<const bf16x4*>(gain_s + k0 + p * 64 + (lane & 15) * 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(x[p][i][e] * ss[i] * bf16_to_f32(g[e]));
+        put(i * 4 + (lane >> 4), (lane & 15) * 4, o);
+      }
+      operands(p);
+    }
+  } else {
+    Pack16 x[NS / 2][2];
+#pragma unroll
+    for (int p = 0; p < NS / 2; ++p)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        x[p][h].u = *reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(src.x) + (int64_t)ids[h] * src.ldx + k0 + (lane & 7) * 8 + p * 64);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < EARLY; ++s) load_w(base, t < n_tiles, s, s);
+    __builtin_amdgcn_sched_barrier(0);
+    fill_lds();
+    float ss[2] = {0.f, 0.f};
+#pragma unroll
+    for (int p = 0; p < NS / 2; ++p)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float v = bf16_bits_to_f32(x[p][h].s[e]);
+          ss[h] += v * v;
+        }
+        asm("" : "+v"(x[p][h].u));  // (widened again below, not kept widened: twice the registers)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    inv_rms(std::integral_constant<int, 8>{}, ss);
+#pragma unroll
+    for (int p = 0; p < NS / 2; ++p) {
+      Pack16 g;
+      g.u = *reinterpret_cast<const u32x4*>(gain_s + k0 + p * 64 + (lane & 7) * 8);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        Pack16 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o.h[e] = f32_to_bf16(bf16_bits_to_f32(x[p][h].s[e]) * ss[h] * bf16_bits_to_f32(g.s[e]));
+        put(h * 8 + (lane >> 3), (lane & 7) * 8, o.u);
+      }
+      operands(p);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = EARLY; s < R; ++s) load_w(base, t < n_tiles, s, s);
+
+  while (t < n_tiles) {
+    const int t_next = t + wgs;
+    const bool more = t_next < n_tiles;
+    const uint32_t base_next = more ? (uint32_t)(tile_base(MODE, t_next, KB, D) * 2) : 0;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      Pack16 w;
+      w.u = W[s % R];
+      acc = mfma16(A[s], w.h, acc);
+      if (s + R < NS) load_w(base, true, s + R, s % R);
+      else load_w(base_next, more, s + R - NS, s % R);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    float* mine = red[round & 1][wave];
+    *reinterpret_cast<f32x4*>(mine + lane * 4) = acc;
+    PIE_S_WAIT_LGKMCNT0();
+    wg_barrier();
+    // One wave after the other adds a tile's sums up while the others go on with the next tile.  (red is written again two tiles
+    // on, behind another barrier.)  What follows, the stores above all, waits for the last tile: a store holds up what its wave
+    // requests behind it until memory has taken it (128256 x 4096 at 16 rows: 168 us with every tile stored when it was done).
+    if (wave == (round & 7)) {
+      const float* sums = &red[round & 1][0][lane * 4];
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < 8; ++w) v += *reinterpret_cast<const f32x4*>(sums + w * 256);
+      *reinterpret_cast<f32x4*>(&done[round % KEPT][lane * 4]) = v;
+    }
+    if (!more || round % KEPT == KEPT - 1) {
+      PIE_S_WAIT_LGKMCNT0();
+      wg_barrier();
+      for (int r = round / KEPT * KEPT + wave; r <= round; r += 8) {
+        const int tr = blockIdx.x + r * wgs;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(&done[r % KEPT][lane * 4]);  // rows q * 4 .. + 3 of column c
+        if constexpr (MODE == EPI_STORE_F32) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (q * 4 + i < M) store_nt(reinterpret_cast<float*>(out) + (int64_t)(q * 4 + i) * ldo + tr * 16 + c, v[i]);
+        } else if constexpr (MODE == EPI_SWIGLU) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float up = __shfl_xor(v[i], 8);
+            if (q * 4 + i < M && c < 8)
+              reinterpret_cast<bf16_t*>(out)[(int64_t)(q * 4 + i) * ldo + tr * 8 + c] = f32_to_bf16(v[i] / (1.0f + __expf(-v[i])) * up);
+          }
+        } else {
+          const int cpt = D / 16, h = tr / cpt, f = (tr % cpt) * 8 + (c & 7), d = f + (c >> 3) * (D / 2);
+          const int hk = h - rope.Hq, hv = hk - rope.Hkv;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int m = q * 4 + i;
+            const float own = bf16_to_f32(f32_to_bf16(v[i])), other = __shfl_xor(own, 8);  // (rounded like a stored row)
+            if (m >= M) continue;
+            bf16_t* page = rope.kv_layer + ((int64_t)place[0][m] * rope.Hkv + (hv >= 0 ? hv : hk)) * (2 * PAGE * D);
+            if (hv >= 0) {
+              page[v_elem_offset(place[1][m], d, D)] = f32_to_bf16(own);
+            } else {
+              const float fc = ang[m * D + f], fs = ang[m * D + D / 2 + f];
+              const bf16_t o = f32_to_bf16(c < 8 ? own * fc - other * fs : own * fc + other * fs);
+              if (hk < 0) reinterpret_cast<bf16_t*>(out)[(int64_t)m * ldo + h * D + d] = o;
+              else page[k_elem_offset(place[1][m], d)] = o;
+            }
+          }
+        }
+      }
+    }
+    base = base_next;
+    t = t_next;
+    ++round;
+  }
+#endif
+}
+
+// Workgroup ids go to the XCDs in turn; here the tiles go to them in ranges, so that the two tiles of a 32-column block, whose
+// weights alternate in pieces of 256 bytes, are read through one L2 (4096 x 4096 at one row 7.9 us, 9.9 in launch order;
+// the pair tiles above are as fast or faster in launch order).
+__device__ __forceinline__ int xcd_order(int wgs, int wg) { return wgs % 8 == 0 ? (wg & 7) * (wgs >> 3) + (wg >> 3) : wg; }
+
+// ------------------------------------------------------------------------------------------------
+// NC: 16-column tiles of a workgroup, next to each other.  MODE: EPI_RESID_EMBED, EPI_RESID_OUT.  Any K that is a multiple of
+// 32; wave w takes k steps [w n / 8, (w + 1) n / 8) of the n = K / 32.
+// ------------------------------------------------------------------------------------------------
+template <int MODE, int NC>
+__global__ __launch_bounds__(512, 2) void few_stream_kernel(const bf16_t* __restrict__ A, int lda, int M, const bf16_t* __restrict__ Wp,
+                                                            int NB, int K, EpiArgs epi) {
+  constexpr int P = FEW_RING / 2 / NC;  // pairs of k steps in flight
+  __shared__ __align__(16) float red[8][NC][256];
+  __shared__ __align__(16) bf16_t turn[8][16 * 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  [[maybe_unused]] const int c = lane & 15, q = lane >> 4;
+  const int KB = K / 16, wg = xcd_order(gridDim.x, blockIdx.x);
+  // the element of the tile(s) this thread finishes, and its residual
+  const int em = (tid >> 4) & 15, ej = NC == 1 ? 0 : tid >> 8, en = (wg * NC + ej) * 16 + (tid & 15), er = min(em, M - 1);
+  const bool by_id = MODE == EPI_RESID_EMBED ? epi.resid == nullptr : epi.out == nullptr;
+  const int id = by_id ? epi.ids[er] : 0;
+  float resid = 0.f;
+#if __HIP_DEVICE_COMPILE__
+  const __amdgpu_buffer_rsrc_t rsrc_w =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Wp), 0, (int)((int64_t)NB * 32 * K * 2), RSRC_FLAGS);
+  const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, (int)(((int64_t)(M - 1) * lda + K) * 2), RSRC_FLAGS);
+  const int steps = K / 32, s0 = wave * steps / 8, n = (wave + 1) * steps / 8 - s0;
+  const uint32_t woff = (uint32_t)(tile_lane(MODE, lane, KB, 0) * 2);
+  uint32_t aoff[2];  // rows lane / 8 and 8 + lane / 8, 128 bytes (two k steps) of a row by eight lanes
+#pragma unroll
+  for (int h = 0; h < 2; ++h) aoff[h] = h * 8 < M ? (uint32_t)((min(h * 8 + (lane >> 3), M - 1) * lda + (lane & 7) * 8) * 2) : OUT_OF_RANGE;
+  const uint32_t wbase = (uint32_t)(tile_base(MODE, wg * NC, KB, 0) * 2) + s0 * 2048, abase = s0 * 64;
+  u32x4 W[P][2][NC], X[P][2];
+  auto load_x = [&](int p, const int slot) {
+    const bool real = 2 * p < n;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      X[slot][h] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, real ? aoff[h] : OUT_OF_RANGE, real ? abase + p * 128 : 0, 0);
+  };
+  auto load_w = [&](int p, const int slot) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int s = 2 * p + h;
+#pragma unroll
+      for (int j = 0; j < NC; ++j)
+        W[slot][h][j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, s < n ? woff + j * 256 : OUT_OF_RANGE, s < n ? wbase + s * 2048 : 0, 2);
+    }
+  };
+  f32x4 acc[NC];
+#pragma unroll
+  for (int j = 0; j < NC; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    load_x(p, p);
+    load_w(p, p);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (MODE == EPI_RESID_EMBED && by_id) resid = bf16_to_f32(epi.embeds[(int64_t)id * epi.H + en]);
+  else resid = epi.resid[(int64_t)er * epi.H + en];
+  __builtin_amdgcn_sched_barrier(0);
+  bf16_t* const my_turn = turn[wave];
+  for (int b = 0; 2 * b < n; b += P) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) *reinterpret_cast<u32x4*>(my_turn + turn_at(h * 8 + (lane >> 3), (lane & 7) * 8)) = X[p][h];
+      load_x(b + p + P, p);
+      __builtin_amdgcn_sched_barrier(0);
+      bf16x8 x[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) x[h] = *reinterpret_cast<const bf16x8*>(my_turn + turn_at(c, h * 32 + q * 8));
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (2 * (b + p) + h < n) {  // (uniform)
+#pragma unroll
+          for (int j = 0; j < NC; ++j) {
+            Pack16 w;
+            w.u = W[p][h][j];
+            acc[j] = mfma16(x[h], w.h, acc[j]);
+          }
+        }
+      load_w(b + p + P, p);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NC; ++j) *reinterpret_cast<f32x4*>(&red[wave][j][lane * 4]) = acc[j];
+#endif
+  PIE_S_WAIT_LGKMCNT0();
+  wg_barrier();
+  if (tid >= 256 * NC || em >= M) return;
+  const float* sums = &red[0][ej][((em >> 2) * 16 + (tid & 15)) * 4 + (em & 3)];
+  float v = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) v += sums[w * (NC * 256)];
+  v += resid;
+  if (MODE == EPI_RESID_EMBED || !by_id) reinterpret_cast<float*>(epi.out)[(int64_t)em * epi.ldo + en] = v;
+  else if (id >= 0) epi.embeds[(int64_t)id * epi.H + en] = f32_to_bf16(v);
+}
+
+bool fits(const PackedWeight& W) { return (int64_t)W.NB * 32 * W.K * 2 < ((int64_t)1 << 32) - (1 << 20); }
+
+// Workgroups for n tiles with one workgroup per compute unit: as many rounds as it takes, evenly.
+int even_wgs(int n, int n_cus) {
+  const int rounds = (n + n_cus - 1) / n_cus, wgs = (n + rounds - 1) / rounds;
+  return std::min((wgs + 7) / 8 * 8, n_cus);
+}
+
+template <int MODE, int SRC>
+hipError_t run_rows(const FewSource& given, int M, const PackedWeight& W, int n_tiles, void* out, int ldo, const FewRope& rope, int n_cus,
+                    hipStream_t s) {
+  FewIds ids{};
+  FewSource src = given;
+  if (SRC == FEW_EMBED_ARGS) {  // (a host array)
+    for (int i = 0; i < M; ++i) ids.v[i] = src.ids[i];
+    src.ids = nullptr;
+  }
+  const dim3 grid(even_wgs(n_tiles, n_cus)), block(512);
+  auto run = [&](auto ns_c) {
+    few_rows_kernel<MODE, SRC, decltype(ns_c)::value><<<grid, block, 0, s>>>(src, ids, M, W.data, W.NB, n_tiles, out, ldo, rope);
+    return hipGetLastError();
+  };
+  if (W.K == 8 * 256) return run(std::integral_constant<int, 8>{});
+  if (W.K == 16 * 256) return run(std::integral_constant<int, 16>{});
+  if constexpr (MODE == EPI_STORE_BF16 && SRC == FEW_EMBED)
+    if (W.K == 32 * 256) return run(std::integral_constant<int, 32>{});
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// Rows of 8192 leave registers for half a ring of weights only: as good as the kernels it replaces where the rotary step and a
+// norm of Embeds go with it (10240 x 8192: 36.7 us at one row for 2.7 + 29.3 + 4.8, 37.5 at 16 for 3.8 + 30.5 + 5.1).
+bool few_rows_ok(int M, const PackedWeight& W, int mode, int source) {
+  if (M < 1 || M > FEW_ROWS || !fits(W)) return false;
+  return W.K == 8 * 256 || W.K == 16 * 256 || (W.K == 32 * 256 && mode == EPI_STORE_BF16 && source == FEW_EMBED);
+}
+
+hipError_t launch_few_qkv(const FewSource& src, int M, const PackedWeight& W, bf16_t* qkv, const FewRope& rope, int n_cus, hipStream_t s) {
+  const int heads = rope.Hq + 2 * rope.Hkv;
+  if (!few_rows_ok(M, W, EPI_STORE_BF16, src.kind) || (rope.D != 64 && rope.D != 128) || W.N != heads * rope.D) return hipErrorInvalidValue;
+  const int tiles = heads * (rope.D / 16);
+  if (src.kind == FEW_EMBED) return run_rows<EPI_STORE_BF16, FEW_EMBED>(src, M, W, tiles, qkv, W.N, rope, n_cus, s);
+  if (src.kind == FEW_F32) return run_rows<EPI_STORE_BF16, FEW_F32>(src, M, W, tiles, qkv, W.N, rope, n_cus, s);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_few_swiglu(const FewSource& src, int M, const PackedWeight& W, bf16_t* act, int n_cus, hipStream_t s) {
+  if (!few_rows_ok(M, W, EPI_SWIGLU, src.kind) || W.N % 64 != 0 || src.kind != FEW_F32) return hipErrorInvalidValue;
+  return run_rows<EPI_SWIGLU, FEW_F32>(src, M, W, W.N / 16, act, W.N / 2, FewRope{}, n_cus, s);
+}
+
+hipError_t launch_few_f32(const FewSource& src, int M, const PackedWeight& W, float* out, int n_cus, hipStream_t s) {
+  if (!few_rows_ok(M, W, EPI_STORE_F32, src.kind) || W.N % 32 != 0 || src.kind != FEW_EMBED_ARGS) return hipErrorInvalidValue;
+  return run_rows<EPI_STORE_F32, FEW_EMBED_ARGS>(src, M, W, W.N / 16, out, W.N, FewRope{}, n_cus, s);
+}
+
+bool few_resid_ok(int M, int lda, const PackedWeight& W) {
+  return M >= 1 && M <= FEW_ROWS && W.K % 32 == 0 && W.N % 32 == 0 && fits(W) && (int64_t)M * lda * 2 < ((int64_t)1 << 31);
+}
+
+hipError_t launch_few_resid(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, int n_cus, hipStream_t s) {
+  if (!few_resid_ok(M, lda, W) || (epi.mode != EPI_RESID_EMBED && epi.mode != EPI_RESID_OUT)) return hipErrorInvalidValue;
+  const int tiles = W.N / 16;
+  const bool two = tiles > n_cus;  // (an even number of tiles: two next to each other are a whole 32-column block)
+  const dim3 grid(two ? tiles / 2 : tiles), block(512);
+  if (epi.mode == EPI_RESID_EMBED) {
+    if (two) few_stream_kernel<EPI_RESID_EMBED, 2><<<grid, block, 0, s>>>(A, lda, M, W.data, W.NB, W.K, epi);
+    else few_stream_kernel<EPI_RESID_EMBED, 1><<<grid, block, 0, s>>>(A, lda, M, W.data, W.NB, W.K, epi);
+  } else {
+    if (two) few_stream_kernel<EPI_RESID_OUT, 2><<<grid, block, 0, s>>>(A, lda, M, W.data, W.NB, W.K, epi);
+    else few_stream_kernel<EPI_RESID_OUT, 1><<<grid, block, 0, s>>>(A, lda, M, W.data, W.NB, W.K, epi);
+  }
+  return hipGetLastError();
+}

@@ -254,6 +254,33 @@ struct EpiArgs {
 hipError_t launch_gemm(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, float* splitk_ws,
                        size_t splitk_elems, int n_cus, hipStream_t s, int* deferred_splits = nullptr);
 
+// Products of up to FEW_ROWS rows with the small kernels around them taken in (few.hip).  The rows are normalised on the way in
+// (RMSNorm times gain, rounded to bf16 as the norm kernels do): Embeds whose ids are on the device or on the host (which
+// travel as kernel arguments), or fp32 rows.
+#define FEW_ROWS 16
+enum FewSourceKind { FEW_EMBED = 0, FEW_EMBED_ARGS = 1, FEW_F32 = 2 };
+struct FewIds { int32_t v[FEW_ROWS]; };
+struct FewSource {
+  int kind;
+  const void* x;  // the Embed pool, or fp32 [M, ldx]
+  int ldx;
+  const int32_t* ids;
+  const bf16_t* gain;
+  float eps;
+};
+struct FewRope {  // q, k, v of a product are rotated (v not) and stored: q in its row, k and v in their token's page slot
+  const float* angles;
+  const int32_t *tok_page, *tok_slot;
+  bf16_t* kv_layer;
+  int Hq, Hkv, D;
+};
+bool few_rows_ok(int M, const PackedWeight& W, int mode, int source);  // what the next three take
+hipError_t launch_few_qkv(const FewSource& src, int M, const PackedWeight& W, bf16_t* qkv, const FewRope& rope, int n_cus, hipStream_t s);
+hipError_t launch_few_swiglu(const FewSource& src, int M, const PackedWeight& W, bf16_t* act, int n_cus, hipStream_t s);
+hipError_t launch_few_f32(const FewSource& src, int M, const PackedWeight& W, float* out, int n_cus, hipStream_t s);
+bool few_resid_ok(int M, int lda, const PackedWeight& W);
+hipError_t launch_few_resid(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, int n_cus, hipStream_t s);
+
 void product_plan(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out[4]);  // see pie_product_plan
 void product_stream(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out[3]);  // see pie_product_stream
 

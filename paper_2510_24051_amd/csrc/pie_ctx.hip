@@ -1577,8 +1577,16 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   const int carried = (carry && x_in) ? *carry : 0;
   if (carry) *carry = 0;
 
+  // Up to FEW_ROWS tokens: the norms, the rotary step and the epilogues are part of the products (few.hip), where nothing else
+  // reads what lies between them (an adapter's pair reads the normalised rows and joins the sums before the next step).
+  const int n_cus = c->wave_slots / 8;
+  const int wide_or_embed = x_in ? FEW_F32 : FEW_EMBED;
+  const bool few_qkv = !lora_qkv && carried == 0 && few_rows_ok(T, L.wqkv, EPI_STORE_BF16, wide_or_embed);
+  const bool few_gu = !lora[PIE_PROJ_GATE] && !lora[PIE_PROJ_UP] && few_rows_ok(T, L.wgu, EPI_SWIGLU, FEW_F32);
+
   tm.begin(PIE_STAGE_NORM1);
-  if (x_in && carried > 0)
+  if (few_qkv) {}
+  else if (x_in && carried > 0)
     HIP_TRY(c, launch_splitk_resid_norm(c->splitk, carried, L.wdown.NB * 32, c->h, nullptr, nullptr, x_in, L.g1, c->xn, T, H, m.rms_eps, s));
   else if (x_in) HIP_TRY(c, launch_rmsnorm_f32(x_in, L.g1, c->xn, T, H, m.rms_eps, s));
   else HIP_TRY(c, launch_rmsnorm_embed(c->embeds, b->in_ids, L.g1, c->xn, T, H, m.rms_eps, s));
@@ -1587,7 +1595,12 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   tm.begin(PIE_STAGE_QKV);
   int qkv_splits = 0;
   e = EpiArgs{EPI_STORE_BF16, c->qkv, QKV, nullptr, nullptr, nullptr, 0};
-  HIP_TRY(c, launch_gemm(c->xn, H, T, L.wqkv, e, c->splitk, c->splitk_elems, c->wave_slots / 8, s, &qkv_splits));
+  if (few_qkv) {
+    const FewSource src{wide_or_embed, x_in ? (const void*)x_in : c->embeds, H, b->in_ids, L.g1, m.rms_eps};
+    HIP_TRY(c, launch_few_qkv(src, T, L.wqkv, c->qkv, FewRope{b->rope_angles, b->tok_page, b->tok_slot, kv_layer, Hq, Hkv, D}, n_cus, s));
+  } else {
+    HIP_TRY(c, launch_gemm(c->xn, H, T, L.wqkv, e, c->splitk, c->splitk_elems, n_cus, s, &qkv_splits));
+  }
   tm.end(PIE_STAGE_QKV);
 
   if (lora_qkv) {  // q, k, v share the normalised input
@@ -1599,8 +1612,9 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   }
 
   tm.begin(PIE_STAGE_ROPE_APPEND);
-  HIP_TRY(c, launch_rope_append(c->qkv, T, Hq, Hkv, D, b->pos, b->tok_page, b->tok_slot, b->rope_angles, kv_layer, b->n_pitems > 0,
-                                c->splitk, qkv_splits, L.wqkv.NB * 32, s));
+  if (!few_qkv)
+    HIP_TRY(c, launch_rope_append(c->qkv, T, Hq, Hkv, D, b->pos, b->tok_page, b->tok_slot, b->rope_angles, kv_layer, b->n_pitems > 0,
+                                  c->splitk, qkv_splits, L.wqkv.NB * 32, s));
   tm.end(PIE_STAGE_ROPE_APPEND);
 
   AttnArgs a{};
@@ -1644,7 +1658,8 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   tm.begin(PIE_STAGE_OPROJ);
   int o_splits = 0;
   e = EpiArgs{EPI_RESID_EMBED, c->h, H, c->embeds, b->in_ids, x_in, H};
-  HIP_TRY(c, launch_gemm(c->attn, Hq * D, T, L.wo, e, c->splitk, c->splitk_elems, c->wave_slots / 8, s, &o_splits));
+  if (!lora[PIE_PROJ_O] && few_resid_ok(T, Hq * D, L.wo)) HIP_TRY(c, launch_few_resid(c->attn, Hq * D, T, L.wo, e, n_cus, s));
+  else HIP_TRY(c, launch_gemm(c->attn, Hq * D, T, L.wo, e, c->splitk, c->splitk_elems, n_cus, s, &o_splits));
   tm.end(PIE_STAGE_OPROJ);
 
   if (lora[PIE_PROJ_O]) {  // h (or the first partial copy of it) += scale * B (A attn), before the second norm reads it
@@ -1654,7 +1669,8 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   }
 
   tm.begin(PIE_STAGE_NORM2);
-  if (o_splits > 0)
+  if (few_gu) {}
+  else if (o_splits > 0)
     HIP_TRY(c, launch_splitk_resid_norm(c->splitk, o_splits, L.wo.NB * 32, x_in, c->embeds, b->in_ids, c->h, L.g2, c->xn, T, H, m.rms_eps, s));
   else HIP_TRY(c, launch_rmsnorm_f32(c->h, L.g2, c->xn, T, H, m.rms_eps, s));
   tm.end(PIE_STAGE_NORM2);
@@ -1669,6 +1685,8 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
     HIP_TRY(c, launch_lora_up(c->gu32, 2 * I, I, 2, 0, 0, LT, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_GATE, 0, c->lora_z, RM, ks, s));
     HIP_TRY(c, launch_lora_up(c->gu32, 2 * I, I, 2, 32, 0, LT, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_UP, 1, c->lora_z, RM, ks, s));
     HIP_TRY(c, launch_swiglu_f32(c->gu32, I, c->act, T, s));
+  } else if (few_gu) {
+    HIP_TRY(c, launch_few_swiglu(FewSource{FEW_F32, c->h, H, nullptr, L.g2, m.rms_eps}, T, L.wgu, c->act, n_cus, s));
   } else {
     e = EpiArgs{EPI_SWIGLU, c->act, I, nullptr, nullptr, nullptr, 0};
     HIP_TRY(c, launch_gemm(c->xn, H, T, L.wgu, e, c->splitk, c->splitk_elems, c->wave_slots / 8, s));
@@ -1683,8 +1701,8 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
 
   tm.begin(PIE_STAGE_DOWN);
   e = EpiArgs{EPI_RESID_OUT, y_out, y_out ? H : 0, c->embeds, b->out_ids, c->h, H};
-  HIP_TRY(c, launch_gemm(c->act, I, T, L.wdown, e, c->splitk, c->splitk_elems, c->wave_slots / 8, s,
-                         (carry && y_out) ? carry : nullptr));
+  if (few_resid_ok(T, I, L.wdown)) HIP_TRY(c, launch_few_resid(c->act, I, T, L.wdown, e, n_cus, s));
+  else HIP_TRY(c, launch_gemm(c->act, I, T, L.wdown, e, c->splitk, c->splitk_elems, n_cus, s, (carry && y_out) ? carry : nullptr));
   tm.end(PIE_STAGE_DOWN);
   c->last_T = T;
   return PIE_OK;
@@ -1759,7 +1777,9 @@ static pie_status run_dist(pie_ctx* c, const DistBuffers& w, int32_t n, int32_t 
   hipStream_t s = c->stream;
   StageTimer tm(c, PIE_STAGE_HEAD_NORM, PIE_STAGE_TOPK);
   tm.begin(PIE_STAGE_HEAD_NORM);
-  if (c->g_final) {
+  const bool few = c->g_final && w.ids_on_host && few_rows_ok(n, c->wlm, EPI_STORE_F32, FEW_EMBED_ARGS);
+  if (few) {
+  } else if (c->g_final) {
     HIP_TRY(c, (w.ids_on_host ? launch_rmsnorm_embed_ids : launch_rmsnorm_embed)(c->embeds, w.ids, c->g_final, w.en, n, H, c->m.rms_eps, s));
   } else {
     HIP_TRY(c, (w.ids_on_host ? launch_embed_copy_ids : launch_embed_copy)(c->embeds, w.ids, n, H, w.en, 0, s));
@@ -1767,7 +1787,8 @@ static pie_status run_dist(pie_ctx* c, const DistBuffers& w, int32_t n, int32_t 
   tm.end(PIE_STAGE_HEAD_NORM);
   tm.begin(PIE_STAGE_LM_HEAD);
   EpiArgs e{EPI_STORE_F32, w.logits, V, nullptr, nullptr, nullptr, 0};
-  HIP_TRY(c, launch_gemm(w.en, H, n, c->wlm, e, w.splitk, w.splitk_elems, c->wave_slots / 8, s));
+  if (few) HIP_TRY(c, launch_few_f32(FewSource{FEW_EMBED_ARGS, c->embeds, H, w.ids, c->g_final, c->m.rms_eps}, n, c->wlm, w.logits, c->wave_slots / 8, s));
+  else HIP_TRY(c, launch_gemm(w.en, H, n, c->wlm, e, w.splitk, w.splitk_elems, c->wave_slots / 8, s));
   tm.end(PIE_STAGE_LM_HEAD);
   tm.begin(PIE_STAGE_TOPK);
   HIP_TRY(c, launch_topk(w.logits, n, V, top_k, 1.0f / temperature, out_ids, out_probs, w.cand, w.stats, s));

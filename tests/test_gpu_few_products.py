@@ -1,0 +1,73 @@
+"""Layers of 1 to 16 tokens, whose products take in the norms, the rotary step and the epilogues: rows around the edges, both
+head sizes, contractions that divide unevenly over the waves, column tiles in one and in several rounds, prompts beside decode
+requests, several layers (wide residual in, wide residual out), pages of 32 tokens."""
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_helpers import make_ctx
+from helpers import check_topk
+from oracle import pie_oracle as O
+from paper_2510_24051_amd import TAP_LOGITS
+from test_gpu_model import compare_deep
+from test_gpu_parity import compare_layer, small_model
+
+pytestmark = pytest.mark.gpu
+
+# hidden 2048 and 4096: everything is taken in; others: the output and down projections (alone)
+SHAPES = [
+    dict(head_dim=64, n_q=8, n_kv=2, hidden=2048, mlp=96),
+    dict(head_dim=128, n_q=8, n_kv=2, hidden=4096, mlp=4128),
+    dict(head_dim=64, n_q=12, n_kv=3, hidden=4096, mlp=8224),
+    dict(head_dim=64, n_q=4, n_kv=2, hidden=96, mlp=160),
+    dict(head_dim=128, n_q=4, n_kv=4, hidden=8192, mlp=288),   # q, k, v only
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"H{s['hidden']}-I{s['mlp']}-D{s['head_dim']}")
+@pytest.mark.parametrize("T", [1, 2, 15, 16, 17])
+def test_layer(shape, T):
+    m = small_model(vocab=512, **shape)
+    reqs = [W.RequestSpec(1, 3 + 9 * i) for i in range(T if T < 4 else T - 6)] + ([] if T < 4 else [W.RequestSpec(6, 21)])
+    w = W.build_workload("few", m, reqs, n_kv_pages=T * 12 + 8, seed=1100 + T + m.hidden, std=0.02, resid_std=0.005)
+    compare_layer(w, what=f"T={T} H{m.hidden} I{m.mlp_dim}")
+
+
+@pytest.mark.parametrize("hidden", [2048, 4096])
+@pytest.mark.parametrize("T", [1, 16])
+def test_layers_in_a_row(hidden, T):
+    m = small_model(64, 16, 4, hidden=hidden, mlp=1024, vocab=512)
+    m.n_layers = 3
+    dw = W.build_deep_workload("few", m, [W.RequestSpec(1, 5 + 7 * i) for i in range(T)], n_kv_pages=T * 8 + 8, seed=1200 + T, std=0.02, resid_std=0.003)
+    compare_deep(dw, f"few T={T}")
+
+
+def test_more_tiles_than_sums_are_kept_for():
+    """33088 gate/up pairs: seventeen column tiles for most of 256 workgroups, which keep the sums of sixteen."""
+    m = small_model(64, 4, 2, hidden=2048, mlp=33088, vocab=512)
+    w = W.build_workload("few", m, [W.RequestSpec(1, 9), W.RequestSpec(2, 30)], n_kv_pages=8, seed=1300, std=0.02, resid_std=0.003)
+    compare_layer(w, what="I33088")
+
+
+@pytest.mark.parametrize("hidden,vocab", [(2048, 96), (2048, 4128), (2048, 131072), (4096, 8224)])
+def test_logits(hidden, vocab):
+    m = small_model(64, 4, 2, hidden=hidden, mlp=64, vocab=vocab)
+    rng = np.random.default_rng(vocab)
+    w = W.build_workload("few", m, [W.RequestSpec(1, 3)], n_kv_pages=4, seed=1400 + vocab, std=0.02, n_embeds=24)
+    bits = O.bf16_encode(rng.standard_normal((24, hidden)).astype(np.float32))
+    emb = O.EmbedPool(24, hidden)
+    emb.write(np.arange(24, dtype=np.int32), bits)
+    w_lm = O.bf16_decode(w.head.w_lm)
+    ctx = make_ctx(w, max_dist_rows=17, max_top_k=16)
+    ctx.embed_write(np.arange(24, dtype=np.int32), bits)
+    for n in (1, 3, 16, 17):
+        ids = rng.permutation(24)[:n].astype(np.int32)
+        z = O.logits_from_embeds(m, w.head, emb, ids, True)
+        gi, gp = ctx.get_next_dist(ids, 16, 1.0)
+        zg = ctx.read_tap(TAP_LOGITS, n)
+        # fp32 sums against 64 bits: 1e-5; besides, a normalised input that rounds the other way moves a row's logits by up to
+        # one bf16 ulp of it (2^-7 of the largest, about 4.5) times a weight, and a row may hold two such inputs
+        d = np.abs(zg - z)
+        assert d.max() < 2 * 4.5 / 128 * np.abs(w_lm).max() and d.mean() < 1e-4, (n, d.max(), d.mean())
+        oi, op = O.top_k_dist(zg.astype(np.float64), 16, 1.0)
+        check_topk(gi, gp, zg.astype(np.float64), oi, op)

@@ -575,12 +575,19 @@ __device__ __forceinline__ void lds_copy_run(const char* src, char* dst) {
 // 4096-token prefix asked the caches for 1.14 GB and took 113 us; here a block is copied to LDS once per 128 columns
 // (134 MB) and the walk takes 44 us, bound by the MFMAs and vector work of the pair weights (16 steps, 1.9 us for two
 // workgroups on a compute unit), which are done for all columns whoever sees the page.
-template <int D, int G, bool LO, bool SPLIT, bool SHARED = false>
+// PACKED: blocks of few tokens (drafts to be checked), n_new * group <= 32 G columns, causal.  The G waves (one or two) take
+// 32 columns each, column = token * group + head, instead of one head each with most of its 32 columns empty: the walk of
+// K/V is the same, with a fraction of the MFMAs and exponentials and a wave per SIMD at most.  Bound by the chain of one step
+// (copy, scores, softmax, PV) times the walks a compute unit's LDS has room for, so it pays where packing lets more workgroups in:
+// groups of eight (6 requests of 6 tokens over 1000 to 3000, D = 128: 38 -> 18.5 us; 12 of 8 over 500 to 1500 46 -> 21) and
+// D = 64 (8 of 8 over 1500 to 4500, groups of four: 21 -> 12; 20 of 16 over 300 to 900, whole blocks: 23.5 -> 18).
+template <int D, int G, bool LO, bool SPLIT, bool SHARED = false, bool PACKED = false>
 __device__ __forceinline__ void attn_prefill_block(const AttnArgs& a, const PrefillItem it, int part_index,
                                                    float* __restrict__ part_o, float* __restrict__ part_ml,
                                                    const SharedGroup* __restrict__ sgroups = nullptr,
                                                    const DecodeCol* __restrict__ scols = nullptr) {
   static_assert(!SHARED || (LO && SPLIT && G * 32 == SHARED_COLS), "shared groups: four waves, weights as pairs, cut");
+  static_assert(!PACKED || (!LO && !SHARED), "packed columns: causal blocks, plain weights");
   constexpr int BLK = 2 * PAGE * D;            // elements of one (page, head) block: K part then V part
   constexpr int PIECES = BLK * 2 / 1024;       // 1 KiB copy instructions per page block
   constexpr int IPW = 2 * PIECES / G;          // copy instructions per wave per pair
@@ -591,6 +598,8 @@ __device__ __forceinline__ void attn_prefill_block(const AttnArgs& a, const Pref
   if (SPLIT && part_index >= it.n_parts) return;
   const int hk = it.hk;
   const int qcol = lane & 31, g = lane >> 5, m = lane & 31;
+  const int heads = PACKED ? a.Hq / a.Hkv : G;             // query heads of the kv head, and this lane's
+  const int head = PACKED ? (hg * 32 + qcol) % heads : hg;
   ReqInfo rq{};
   int i_tok = 0, i_ld = 0, pair0, v_end;
   [[maybe_unused]] int col_kv_len = 0, col_lim = 0;  // SHARED: the lane's column, KV length and last key visible under the causal rule
@@ -611,13 +620,13 @@ __device__ __forceinline__ void attn_prefill_block(const AttnArgs& a, const Pref
     load_q<D>(a.q + (int64_t)cc.tok * a.q_stride + (hk * (a.Hq / a.Hkv) + cc.hg) * D, valid, g, qf);
   } else {
     rq = a.reqs[it.r];
-    i_tok = it.qb * 32 + qcol;
+    i_tok = PACKED ? (hg * 32 + qcol) / heads : it.qb * 32 + qcol;
     valid = i_tok < rq.n_new;
     i_ld = valid ? i_tok : rq.n_new - 1;
     // requests with a bitmap are always listed in the launch with pair weights (their rows may see few keys)
     has_bitmap = LO && rq.wpr > 0;
     pair0 = rq.pair0;
-    load_q<D>(a.q + (int64_t)(rq.tok0 + i_ld) * a.q_stride + (hk * G + hg) * D, valid, g, qf);
+    load_q<D>(a.q + (int64_t)(rq.tok0 + i_ld) * a.q_stride + (hk * heads + head) * D, valid, g, qf);
   }
   AttnState<D> st;
   attn_init<D>(st);
@@ -657,7 +666,8 @@ __device__ __forceinline__ void attn_prefill_block(const AttnArgs& a, const Pref
     // Inferred-causal blocks of 32 real rows: the first n_full pairs lie entirely at or below the first row's
     // limit (pages are visited in logical order without gaps when there is no bitmap), so every row sees all of
     // their keys, which the whole workgroup knows without any per-lane arithmetic.
-    const bool rows_full = !SHARED && !has_bitmap && it.qb * 32 + 31 < rq.n_new;
+    // (packed columns past the last have zero queries and are dropped)
+    const bool rows_full = PACKED || (!SHARED && !has_bitmap && it.qb * 32 + 31 < rq.n_new);
     const int first_lim = rq.kv_len - rq.n_new + it.qb * 32;
     const int n_full = rows_full ? min(v_end / 2, (first_lim + 1) / 32) - first_pair : 0;
     auto start_pair = [&](bf16_t* stage, int pair, Meta& md) {
@@ -766,7 +776,8 @@ __device__ __forceinline__ void attn_prefill_block(const AttnArgs& a, const Pref
   const float l_tot = sum_xor32(st.l);
   if (!valid) return;
   if (SHARED || (SPLIT && it.n_parts > 1)) {  // (max, sum, O) of this part, for the merge kernel
-    const int64_t prow = ((int64_t)(it.slot0 + part_index) * G + hg) * 32 + qcol;
+    const int64_t prow = PACKED ? (int64_t)(it.slot0 + part_index) * heads * 32 + hg * 32 + qcol
+                                : ((int64_t)(it.slot0 + part_index) * G + hg) * 32 + qcol;
     if (g == 0) {
       part_ml[prow * 2] = st.m;
       part_ml[prow * 2 + 1] = l_tot;
@@ -782,7 +793,7 @@ __device__ __forceinline__ void attn_prefill_block(const AttnArgs& a, const Pref
     return;
   }
   const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  bf16_t* orow = a.out + (int64_t)(rq.tok0 + i_tok) * a.Hq * D + (hk * G + hg) * D;
+  bf16_t* orow = a.out + (int64_t)(rq.tok0 + i_tok) * a.Hq * D + (hk * heads + head) * D;
 #pragma unroll
   for (int b = 0; b < D / 32; ++b)
 #pragma unroll
@@ -800,6 +811,12 @@ __global__ __launch_bounds__(64 * G, 2) void attn_prefill_kernel(AttnArgs a, con
                                                                  const SharedGroup* __restrict__ sgroups = nullptr,
                                                                  const DecodeCol* __restrict__ scols = nullptr) {
   attn_prefill_block<D, G, LO, SPLIT, SHARED>(a, items[blockIdx.x], blockIdx.y, part_o, part_ml, sgroups, scols);
+}
+
+template <int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void attn_packed_kernel(AttnArgs a, const PrefillItem* __restrict__ items,
+                                                                    float* __restrict__ part_o, float* __restrict__ part_ml) {
+  attn_prefill_block<D, WAVES, false, true, false, true>(a, items[blockIdx.x], blockIdx.y, part_o, part_ml);
 }
 
 // Both attentions of a batch in one launch (groups of four query heads, decode pages read once): the prefill blocks (or the
@@ -848,7 +865,7 @@ __global__ __launch_bounds__(256, 2) void attn_both_kernel(AttnArgs a, const Pre
 template <int D>
 __global__ __launch_bounds__(256) void attn_prefill_merge_kernel(AttnArgs a, const PrefillItem* __restrict__ items,
                                                                  const float* __restrict__ part_o,
-                                                                 const float* __restrict__ part_ml) {
+                                                                 const float* __restrict__ part_ml, bool packed) {
   constexpr int L = D / 4;  // lanes of a row: half or a quarter of a wave
   const PrefillItem it = items[blockIdx.x];
   const ReqInfo rq = a.reqs[it.r];
@@ -856,7 +873,7 @@ __global__ __launch_bounds__(256) void attn_prefill_merge_kernel(AttnArgs a, con
   const int rows = min(32, rq.n_new - it.qb * 32);
   const int row = blockIdx.z * (256 / L) + threadIdx.x / L, l = threadIdx.x % L;
   if (row >= rows) return;  // (whole rows leave, so the shuffles below stay within lanes that remain)
-  const int64_t p0 = ((int64_t)it.slot0 * G + hg) * 32 + row, step = (int64_t)G * 32;
+  const int64_t p0 = (int64_t)it.slot0 * G * 32 + (packed ? row * G + hg : hg * 32 + row), step = (int64_t)G * 32;
   float M = -INFINITY;
   for (int p = l; p < it.n_parts; p += L) M = fmaxf(M, part_ml[(p0 + p * step) * 2]);
 #pragma unroll
@@ -1018,12 +1035,24 @@ hipError_t launch_attn_shared(const AttnArgs& a, const PrefillItem* items, int n
   return hipGetLastError();
 }
 
+hipError_t launch_attn_packed(const AttnArgs& a, const PrefillItem* items, int n_items, int max_parts, int waves, float* part_o,
+                              float* part_ml, hipStream_t s) {
+  if (n_items <= 0) return hipSuccess;
+  const dim3 grid(n_items, max_parts), block(64 * waves);
+  if (a.D == 128 && waves == 1) attn_packed_kernel<128, 1><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else if (a.D == 128 && waves == 2) attn_packed_kernel<128, 2><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else if (a.D == 64 && waves == 1) attn_packed_kernel<64, 1><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else if (a.D == 64 && waves == 2) attn_packed_kernel<64, 2><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 hipError_t launch_attn_prefill_merge(const AttnArgs& a, const PrefillItem* items, int n_items, const float* part_o,
-                                     const float* part_ml, hipStream_t s) {
+                                     const float* part_ml, bool packed, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   const dim3 grid(n_items, a.Hq / a.Hkv, 32 / (256 / (a.D / 4))), block(256);
-  if (a.D == 128) attn_prefill_merge_kernel<128><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
-  else if (a.D == 64) attn_prefill_merge_kernel<64><<<grid, block, 0, s>>>(a, items, part_o, part_ml);
+  if (a.D == 128) attn_prefill_merge_kernel<128><<<grid, block, 0, s>>>(a, items, part_o, part_ml, packed);
+  else if (a.D == 64) attn_prefill_merge_kernel<64><<<grid, block, 0, s>>>(a, items, part_o, part_ml, packed);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -126,7 +126,9 @@ struct pie_batch {
   int32_t dec_rows = 1;                     // most query rows (tokens x group) of a decode-path request
   bool dec_read_once = true;                // no page is in two column groups of the decode kernel
   int32_t max_parts = 1, max_parts_lo = 1;  // most parts of a query block in each of the two launches
-  int32_t n_psplit = 0;                     // query blocks that were cut into parts
+  int32_t n_psplit = 0;                     // query blocks that were cut into parts, those of the plain launch first
+  int32_t n_psplit_plain = 0;
+  int32_t pack_waves = 0;                   // waves of a block of the plain launch where its columns are packed, else 0
   PrefillItem* psplit = nullptr;            // [n_psplit]
   float* ppart_o = nullptr;   // [partial blocks, G, 32, D]
   float* ppart_ml = nullptr;  // [partial blocks, G, 32, 2]
@@ -316,8 +318,12 @@ hipError_t launch_attn_both(const AttnArgs& a, const PrefillItem* items, int n_i
                             const DecodeCol* scols, float* pre_o, float* pre_ml, const DecodeWave* waves, const int2* wave_pg,
                             int slots, const DecodeSeg* segs, const DecodeCol* cols, int n_waves, int rows_cap, float* part_o,
                             float* part_ml, int n_cus, hipStream_t s);
+// causal blocks of few tokens, waves (1 or 2) of 32 columns (token, head) each, plain weights; cut or not
+hipError_t launch_attn_packed(const AttnArgs& a, const PrefillItem* items, int n_items, int max_parts, int waves, float* part_o,
+                              float* part_ml, hipStream_t s);
+// packed: the parts were left by launch_attn_packed
 hipError_t launch_attn_prefill_merge(const AttnArgs& a, const PrefillItem* items, int n_items, const float* part_o,
-                                     const float* part_ml, hipStream_t s);
+                                     const float* part_ml, bool packed, hipStream_t s);
 
 // rows / tile_ad: the batch's adapter tiles (32 rows each); z: [ksplits][n_tiles * 32, 3, rmax_p] fp32, where
 // ksplits (from lora_ksplits, the same for the down and the up launch of a projection group) splits the input

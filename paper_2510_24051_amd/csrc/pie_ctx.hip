@@ -1229,9 +1229,9 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   // of 64 / 48 / 32 / 24 steps: 53 / 43 / 39 / 35 us); 333 tokens over 3000, 88 workgroups, 85 us whole, 36 + 8 us cut
   // (53 / 43 / 41 / 38).  Launches whose blocks fill the chip are never cut (8 x 1024 tokens: 220 us, the same launch as
   // without this rule).
-  auto cut = [&](std::vector<PrefillItem>& items) {
+  auto cut = [&](std::vector<PrefillItem>& items, int waves) {
     if (!may_split || items.empty() || (G != 1 && G != 2 && G != 4 && G != 8)) return 1;
-    const int64_t slots = (int64_t)(c->wave_slots / 8) * std::min(8 / G, D == 128 ? 2 : 5);
+    const int64_t slots = (int64_t)(c->wave_slots / 8) * std::min(8 / waves, D == 128 ? 2 : 5);
     auto pairs_of = [&](const PrefillItem& it) {  // as the kernel counts them
       const ReqInfo& q = reqs[it.r];
       int v = q.n_visit;
@@ -1262,7 +1262,16 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   };
   std::vector<PrefillItem> pitems_plain, pitems_pair;
   for (const PrefillItem& it : pitems) (few_keys(it) ? pitems_pair : pitems_plain).push_back(it);
-  const int max_parts = cut(pitems_plain), max_parts_lo = cut(pitems_pair);
+  // Where every block of the plain launch has few tokens its columns are packed into one or two waves (attn_packed_kernel).  Not
+  // beside decode waves, whose launch the four-wave blocks share, and not four heads of 128: two workgroups fit a compute unit
+  // either way, and one wave alone issues what four share (12 requests of 7 tokens over 2500: 37 us, packed 41).
+  int pack_waves = 0;
+  if (dwaves.empty() && ((D == 64 && (G == 2 || G == 4)) || G == 8)) {
+    int cols = 0;
+    for (const PrefillItem& it : pitems_plain) cols = std::max(cols, reqs[it.r].n_new * G);
+    if (cols > 0 && cols <= 64 && (cols + 31) / 32 < G) pack_waves = (cols + 31) / 32;
+  }
+  const int max_parts = cut(pitems_plain, pack_waves > 0 ? pack_waves : G), max_parts_lo = cut(pitems_pair, G);
   std::vector<PrefillItem> pwork = layout(std::move(pitems_plain));
   const size_t n_pwork_plain = pwork.size();
   {
@@ -1271,12 +1280,16 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   }
   std::vector<PrefillItem> psplit;
   int64_t n_pparts = 0;  // partial blocks of the cut query blocks
-  for (PrefillItem& it : pwork)
+  int n_psplit_plain = 0;
+  for (size_t i = 0; i < pwork.size(); ++i) {
+    PrefillItem& it = pwork[i];
     if (it.r >= 0 && it.n_parts > 1) {
       it.slot0 = (int32_t)n_pparts;
       n_pparts += it.n_parts;
       psplit.push_back(it);
+      n_psplit_plain += i < n_pwork_plain;
     }
+  }
 
   pie_batch* pb = new pie_batch();
   pb->owner = c;
@@ -1295,6 +1308,8 @@ static pie_status pie_batch_create_impl(pie_ctx* c, const pie_forward_batch* b, 
   pb->max_parts = max_parts;
   pb->max_parts_lo = max_parts_lo;
   pb->n_psplit = (int32_t)psplit.size();
+  pb->n_psplit_plain = n_psplit_plain;
+  pb->pack_waves = pack_waves;
   pb->pwork_host = pwork;
   pb->n_dec_reqs = (int32_t)dec_reqs.size();
   pb->rows_cap = std::max(rows_cap, 1);
@@ -1631,9 +1646,15 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   const bool both_shared = both && b->n_pwork == 0;
   if (b->n_pitems > 0) {
     tm.begin(PIE_STAGE_ATTN_PREFILL);
-    if (!both || both_shared) HIP_TRY(c, launch_attn_prefill(a, b->pitems, b->n_pwork, false, b->max_parts, b->ppart_o, b->ppart_ml, s));
+    if (b->pack_waves > 0) HIP_TRY(c, launch_attn_packed(a, b->pitems, b->n_pwork, b->max_parts, b->pack_waves, b->ppart_o, b->ppart_ml, s));
+    else if (!both || both_shared) HIP_TRY(c, launch_attn_prefill(a, b->pitems, b->n_pwork, false, b->max_parts, b->ppart_o, b->ppart_ml, s));
     HIP_TRY(c, launch_attn_prefill(a, b->pitems + b->n_pwork, b->n_pwork_lo, true, b->max_parts_lo, b->ppart_o, b->ppart_ml, s));
-    if (!both || both_shared) HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit, b->n_psplit, b->ppart_o, b->ppart_ml, s));
+    if (b->pack_waves > 0) {
+      HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit, b->n_psplit_plain, b->ppart_o, b->ppart_ml, true, s));
+      HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit + b->n_psplit_plain, b->n_psplit - b->n_psplit_plain, b->ppart_o, b->ppart_ml, false, s));
+    } else if (!both || both_shared) {
+      HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit, b->n_psplit, b->ppart_o, b->ppart_ml, false, s));
+    }
     tm.end(PIE_STAGE_ATTN_PREFILL);
   }
   if (b->n_dec_reqs > 0) {
@@ -1644,7 +1665,7 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
                                   both_shared ? b->max_sparts : b->max_parts, both_shared, b->sgroups, b->scols,
                                   both_shared ? shared_o : b->ppart_o, both_shared ? shared_ml : b->ppart_ml, b->dwaves, b->wave_pg, b->dslots,
                                   b->dsegs, b->dcols, b->n_dwaves, b->rows_cap, b->part_o, b->part_ml, c->wave_slots / 8, s));
-      if (!both_shared) HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit, b->n_psplit, b->ppart_o, b->ppart_ml, s));
+      if (!both_shared) HIP_TRY(c, launch_attn_prefill_merge(a, b->psplit, b->n_psplit, b->ppart_o, b->ppart_ml, false, s));
     } else {
       HIP_TRY(c, launch_attn_decode(a, b->dwaves, b->wave_pg, b->dslots, b->dsegs, b->dcols, b->n_dwaves, b->rows_cap, b->part_o, b->part_ml,
                                     b->dec_read_once, s));

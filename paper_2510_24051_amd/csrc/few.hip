@@ -1,10 +1,11 @@
-// Products of 1 to 16 rows (single users, small decode batches): the weight stream and the launches around it.
+// Products of 1 to 32 rows (single users, small decode batches): the weight stream and the launches around it.
 //
 // A workgroup of eight waves owns 16 output columns for the whole contraction; each wave takes an eighth of it on 16x16x32
 // MFMAs and the eight sums meet through LDS in wave order.  So a 4096-column product is 256 workgroups, one per compute unit,
 // with no partial sums in memory and nothing left for another kernel to add up, and the work of the small kernels around a
 // product moves into it:
-//   few_rows_kernel    each wave keeps its K slice of the rows in registers as MFMA operands (K = 256 * NS, NS <= 32) and walks
+//   few_rows_kernel    each wave keeps its K slice of the rows in registers as MFMA operands (K = 256 * NS, NS <= 32; MB blocks
+//                      of 16 rows, two of them for q, k, v and logits of Embeds up to K = 4096) and walks
 //                      any number of column tiles; the rows may be normalised on the way in (RMSNorm of Embeds or of fp32
 //                      rows: every workgroup does it for itself, 16 rows, while its first weights are in flight); a QKV tile is
 //                      rotated and appended to its page, a gate/up tile becomes eight activations
@@ -18,9 +19,10 @@
 //   1 row     us     18.0 -> 14.7          11.2 -> 8                   40.7 -> 40.5           25.3 -> 21.0        124 -> 110
 //   16 rows          19.9 -> 15.8          13.8 -> 10.5                40.9 -> 42.8           26.1 -> 23.9
 // (the norm of the third column is part of gate/up now); logits of 128256 x 4096 with their norm 169 -> 156 and 167 -> 163, of
-// 32000 x 2048 30 -> 22.5 and 32 -> 24.  Why not more rows: the rows come out of L2 beside the weights, in the same order of
-// returns, 459 KiB per compute unit for 16 rows of 14336 against 459 KiB of weights, and cost 3 us of 24; with 32 rows the
-// split product and its epilogue are as fast.
+// 32000 x 2048 30 -> 22.5 and 32 -> 24.  With 32 rows, norm and rotary step included: q, k, v 22.9 -> 21.3 (17 rows 20.1 and
+// 20.2), 3072 x 2048 14.7 -> 10.8; logits of 128256 x 4096 179 -> 174, of 32000 x 2048 33.9 -> 27.4.  Why not more rows, and 16
+// where rows are streamed: they come out of L2 beside the weights, in the same order of returns, 459 KiB per compute unit for 16
+// rows of 14336 against 459 KiB of weights, and cost 3 us of 24; with 32 rows the split product and its epilogue are as fast.
 #include <algorithm>
 #include <type_traits>
 
@@ -61,33 +63,34 @@ constexpr uint32_t OUT_OF_RANGE = 0xFFFFFF00u;
 // ------------------------------------------------------------------------------------------------
 // MODE: EPI_STORE_BF16 (q, k, v rotated and stored), EPI_SWIGLU, EPI_STORE_F32.
 // ------------------------------------------------------------------------------------------------
-template <int MODE, int SRC, int NS>
+template <int MODE, int SRC, int NS, int MB>
 __global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds arg_ids, int M, const bf16_t* __restrict__ Wp, int NB, int n_tiles,
                                                           void* __restrict__ out, int ldo, FewRope rope) {
   constexpr int K = NS * 256, KB = K / 16;
   [[maybe_unused]] constexpr int R = NS < FEW_RING ? NS : NS > FEW_RING ? FEW_RING / 2 : FEW_RING;
-  [[maybe_unused]] constexpr int EARLY = SRC == FEW_F32 && R > 12 ? 12 : R;  // requested ahead of the norm (registers)
+  [[maybe_unused]] constexpr int EARLY = SRC == FEW_F32 && R > 12 ? 12 : MB == 2 && NS == 16 ? 4 : R;  // requested ahead of the norm (as registers allow)
   constexpr bool ROPE = MODE == EPI_STORE_BF16;
-  __shared__ __align__(16) float red[2][8][256];
-  __shared__ __align__(16) bf16_t turn[8][16 * 64];
-  constexpr int KEPT = MODE == EPI_STORE_F32 ? 32 : 16;  // tiles whose sums are kept for the epilogue
-  __shared__ __align__(16) float done[KEPT][256];
-  __shared__ float row_ss[8][16];
+  __shared__ __align__(16) float red[2][8][MB * 256];
+  __shared__ __align__(16) bf16_t turn[8][MB * 16 * 64];
+  constexpr int KEPT = (MODE == EPI_STORE_F32 ? 32 : 16) / MB;  // tiles whose sums are kept for the epilogue
+  __shared__ __align__(16) float done[KEPT][MB * 256];
+  __shared__ float row_ss[8][16 * MB];
   __shared__ __align__(16) bf16_t gain_s[K];
-  __shared__ __align__(16) float ang[ROPE ? 16 * 128 : 4];
-  __shared__ int place[2][16];
+  __shared__ __align__(16) float ang[ROPE ? MB * 16 * 128 : 4];
+  __shared__ int place[2][16 * MB];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, q = lane >> 4, wgs = gridDim.x;
   const int D = rope.D;
-  bf16x8 A[NS];
+  static_assert(MB == 1 || SRC != FEW_F32, "fp32 rows: 16");
+  bf16x8 A[MB][NS];
   [[maybe_unused]] const int k0 = wave * (NS * 32);  // the wave's columns of the rows: k0 .. + NS * 32
 
   // what the norm and the epilogue read, into registers now and into LDS behind the weight requests
-  // (bf16 rows: this lane loads from rows lane / 8 and 8 + lane / 8, fp32 rows: from lane / 16, + 4, + 8, + 12)
-  [[maybe_unused]] int ids[2];
+  // (bf16 rows: this lane loads from rows lane / 8, 8 + lane / 8 and so on, fp32 rows: from lane / 16, + 4, + 8, + 12)
+  [[maybe_unused]] int ids[2 * MB];
   if constexpr (SRC != FEW_F32) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < 2 * MB; ++h) {
       const int r = min(h * 8 + (lane >> 3), M - 1);
       ids[h] = SRC == FEW_EMBED ? src.ids[r] : arg_ids.v[r];
     }
@@ -96,19 +99,22 @@ __global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds 
   u32x4 g_in[GP];
 #pragma unroll
   for (int i = 0; i < GP; ++i) g_in[i] = *reinterpret_cast<const u32x4*>(src.gain + min(i * 4096 + tid * 8, K - 8));
-  [[maybe_unused]] f32x4 ang_in;
+  [[maybe_unused]] f32x4 ang_in[MB];
   [[maybe_unused]] int place_in;
   if constexpr (ROPE) {
-    ang_in = *reinterpret_cast<const f32x4*>(rope.angles + min(tid * 4, M * D - 4));
-    place_in = ((tid & 16) ? rope.tok_slot : rope.tok_page)[min(tid & 15, M - 1)];
+#pragma unroll
+    for (int b = 0; b < MB; ++b) ang_in[b] = *reinterpret_cast<const f32x4*>(rope.angles + min(b * 2048 + tid * 4, M * D - 4));
+    place_in = ((tid & (16 * MB)) ? rope.tok_slot : rope.tok_page)[min(tid & (16 * MB - 1), M - 1)];
   }
   auto fill_lds = [&]() {
 #pragma unroll
     for (int i = 0; i < GP; ++i)
       if (i * 4096 + tid * 8 < K) *reinterpret_cast<u32x4*>(gain_s + i * 4096 + tid * 8) = g_in[i];
     if constexpr (ROPE) {
-      if (tid * 4 < M * D) *reinterpret_cast<f32x4*>(ang + tid * 4) = ang_in;
-      if (tid < 32) place[tid >> 4][tid & 15] = place_in;
+#pragma unroll
+      for (int b = 0; b < MB; ++b)
+        if (b * 2048 + tid * 4 < M * D) *reinterpret_cast<f32x4*>(ang + b * 2048 + tid * 4) = ang_in[b];
+      if (tid < 32 * MB) place[tid / (16 * MB)][tid & (16 * MB - 1)] = place_in;
     }
   };
 #if __HIP_DEVICE_COMPILE__
@@ -128,12 +134,14 @@ __global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds 
   auto put = [&](int r, int k, auto v) { *reinterpret_cast<decltype(v)*>(my_turn + turn_at(r, k)) = v; };
   auto operands = [&](const int p) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) A[2 * p + h] = *reinterpret_cast<const bf16x8*>(my_turn + turn_at(c, h * 32 + q * 8));
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) A[b][2 * p + h] = *reinterpret_cast<const bf16x8*>(my_turn + turn_at(b * 16 + c, h * 32 + q * 8));
     __builtin_amdgcn_sched_barrier(0);
   };
   // 1 / rms of rows r0, r0 + step, ..: sums of this wave's columns in `ss`, one row each per LANES lanes
   [[maybe_unused]] auto inv_rms = [&](auto lanes_c, auto& ss) {
-    constexpr int LANES = decltype(lanes_c)::value, ROWS = 64 / LANES, N = 16 / ROWS;
+    constexpr int LANES = decltype(lanes_c)::value, ROWS = 64 / LANES, N = 16 * MB / ROWS;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
 #pragma unroll
@@ -190,22 +198,24 @@ __global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds 
       operands(p);
     }
   } else {
-    Pack16 x[NS / 2][2];
+    Pack16 x[NS / 2][2 * MB];
 #pragma unroll
     for (int p = 0; p < NS / 2; ++p)
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < 2 * MB; ++h)
         x[p][h].u = *reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(src.x) + (int64_t)ids[h] * src.ldx + k0 + (lane & 7) * 8 + p * 64);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < EARLY; ++s) load_w(base, t < n_tiles, s, s);
     __builtin_amdgcn_sched_barrier(0);
     fill_lds();
-    float ss[2] = {0.f, 0.f};
+    float ss[2 * MB];
+#pragma unroll
+    for (int h = 0; h < 2 * MB; ++h) ss[h] = 0.f;
 #pragma unroll
     for (int p = 0; p < NS / 2; ++p)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < 2 * MB; ++h) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float v = bf16_bits_to_f32(x[p][h].s[e]);
@@ -220,7 +230,7 @@ __global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds 
       Pack16 g;
       g.u = *reinterpret_cast<const u32x4*>(gain_s + k0 + p * 64 + (lane & 7) * 8);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < 2 * MB; ++h) {
         Pack16 o;
 #pragma unroll
         for (int e = 0; e < 8; ++e) o.h[e] = f32_to_bf16(bf16_bits_to_f32(x[p][h].s[e]) * ss[h] * bf16_bits_to_f32(g.s[e]));
@@ -237,53 +247,60 @@ __global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds 
     const int t_next = t + wgs;
     const bool more = t_next < n_tiles;
     const uint32_t base_next = more ? (uint32_t)(tile_base(MODE, t_next, KB, D) * 2) : 0;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[MB];
+#pragma unroll
+    for (int b = 0; b < MB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       Pack16 w;
       w.u = W[s % R];
-      acc = mfma16(A[s], w.h, acc);
+#pragma unroll
+      for (int b = 0; b < MB; ++b) acc[b] = mfma16(A[b][s], w.h, acc[b]);
       if (s + R < NS) load_w(base, true, s + R, s % R);
       else load_w(base_next, more, s + R - NS, s % R);
       __builtin_amdgcn_sched_barrier(0);
     }
     float* mine = red[round & 1][wave];
-    *reinterpret_cast<f32x4*>(mine + lane * 4) = acc;
+#pragma unroll
+    for (int b = 0; b < MB; ++b) *reinterpret_cast<f32x4*>(mine + b * 256 + lane * 4) = acc[b];
     PIE_S_WAIT_LGKMCNT0();
     wg_barrier();
     // One wave after the other adds a tile's sums up while the others go on with the next tile.  (red is written again two tiles
     // on, behind another barrier.)  What follows, the stores above all, waits for the last tile: a store holds up what its wave
     // requests behind it until memory has taken it (128256 x 4096 at 16 rows: 168 us with every tile stored when it was done).
     if (wave == (round & 7)) {
-      const float* sums = &red[round & 1][0][lane * 4];
-      f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int w = 0; w < 8; ++w) v += *reinterpret_cast<const f32x4*>(sums + w * 256);
-      *reinterpret_cast<f32x4*>(&done[round % KEPT][lane * 4]) = v;
+      for (int b = 0; b < MB; ++b) {
+        const float* sums = &red[round & 1][0][b * 256 + lane * 4];
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v += *reinterpret_cast<const f32x4*>(sums + w * (MB * 256));
+        *reinterpret_cast<f32x4*>(&done[round % KEPT][b * 256 + lane * 4]) = v;
+      }
     }
     if (!more || round % KEPT == KEPT - 1) {
       PIE_S_WAIT_LGKMCNT0();
       wg_barrier();
-      for (int r = round / KEPT * KEPT + wave; r <= round; r += 8) {
-        const int tr = blockIdx.x + r * wgs;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(&done[r % KEPT][lane * 4]);  // rows q * 4 .. + 3 of column c
+      for (int u = round / KEPT * KEPT * MB + wave; u < (round + 1) * MB; u += 8) {
+        const int r = u / MB, m0 = u % MB * 16 + q * 4, tr = blockIdx.x + r * wgs;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(&done[r % KEPT][u % MB * 256 + lane * 4]);  // rows m0 .. + 3 of column c
         if constexpr (MODE == EPI_STORE_F32) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (q * 4 + i < M) store_nt(reinterpret_cast<float*>(out) + (int64_t)(q * 4 + i) * ldo + tr * 16 + c, v[i]);
+            if (m0 + i < M) store_nt(reinterpret_cast<float*>(out) + (int64_t)(m0 + i) * ldo + tr * 16 + c, v[i]);
         } else if constexpr (MODE == EPI_SWIGLU) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const float up = __shfl_xor(v[i], 8);
-            if (q * 4 + i < M && c < 8)
-              reinterpret_cast<bf16_t*>(out)[(int64_t)(q * 4 + i) * ldo + tr * 8 + c] = f32_to_bf16(v[i] / (1.0f + __expf(-v[i])) * up);
+            if (m0 + i < M && c < 8)
+              reinterpret_cast<bf16_t*>(out)[(int64_t)(m0 + i) * ldo + tr * 8 + c] = f32_to_bf16(v[i] / (1.0f + __expf(-v[i])) * up);
           }
         } else {
           const int cpt = D / 16, h = tr / cpt, f = (tr % cpt) * 8 + (c & 7), d = f + (c >> 3) * (D / 2);
           const int hk = h - rope.Hq, hv = hk - rope.Hkv;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int m = q * 4 + i;
+            const int m = m0 + i;
             const float own = bf16_to_f32(f32_to_bf16(v[i])), other = __shfl_xor(own, 8);  // (rounded like a stored row)
             if (m >= M) continue;
             bf16_t* page = rope.kv_layer + ((int64_t)place[0][m] * rope.Hkv + (hv >= 0 ? hv : hk)) * (2 * PAGE * D);
@@ -426,7 +443,13 @@ hipError_t run_rows(const FewSource& given, int M, const PackedWeight& W, int n_
   }
   const dim3 grid(even_wgs(n_tiles, n_cus)), block(512);
   auto run = [&](auto ns_c) {
-    few_rows_kernel<MODE, SRC, decltype(ns_c)::value><<<grid, block, 0, s>>>(src, ids, M, W.data, W.NB, n_tiles, out, ldo, rope);
+    constexpr int NS = decltype(ns_c)::value;
+    if constexpr (SRC != FEW_F32 && NS <= 16)
+      if (M > 16) {
+        few_rows_kernel<MODE, SRC, NS, 2><<<grid, block, 0, s>>>(src, ids, M, W.data, W.NB, n_tiles, out, ldo, rope);
+        return hipGetLastError();
+      }
+    few_rows_kernel<MODE, SRC, NS, 1><<<grid, block, 0, s>>>(src, ids, M, W.data, W.NB, n_tiles, out, ldo, rope);
     return hipGetLastError();
   };
   if (W.K == 8 * 256) return run(std::integral_constant<int, 8>{});
@@ -441,7 +464,7 @@ hipError_t run_rows(const FewSource& given, int M, const PackedWeight& W, int n_
 // Rows of 8192 leave registers for half a ring of weights only: as good as the kernels it replaces where the rotary step and a
 // norm of Embeds go with it (10240 x 8192: 36.7 us at one row for 2.7 + 29.3 + 4.8, 37.5 at 16 for 3.8 + 30.5 + 5.1).
 bool few_rows_ok(int M, const PackedWeight& W, int mode, int source) {
-  if (M < 1 || M > FEW_ROWS || !fits(W)) return false;
+  if (M < 1 || M > (source == FEW_F32 || W.K > 16 * 256 ? 16 : FEW_ROWS) || !fits(W)) return false;
   return W.K == 8 * 256 || W.K == 16 * 256 || (W.K == 32 * 256 && mode == EPI_STORE_BF16 && source == FEW_EMBED);
 }
 
@@ -465,7 +488,7 @@ hipError_t launch_few_f32(const FewSource& src, int M, const PackedWeight& W, fl
 }
 
 bool few_resid_ok(int M, int lda, const PackedWeight& W) {
-  return M >= 1 && M <= FEW_ROWS && W.K % 32 == 0 && W.N % 32 == 0 && fits(W) && (int64_t)M * lda * 2 < ((int64_t)1 << 31);
+  return M >= 1 && M <= 16 && W.K % 32 == 0 && W.N % 32 == 0 && fits(W) && (int64_t)M * lda * 2 < ((int64_t)1 << 31);
 }
 
 hipError_t launch_few_resid(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, int n_cus, hipStream_t s) {

@@ -1,4 +1,4 @@
-"""Layers of 1 to 16 tokens, whose products take in the norms, the rotary step and the epilogues: rows around the edges, both
+"""Layers of 1 to 32 tokens, whose products take in the norms, the rotary step and the epilogues: rows around the edges, both
 head sizes, contractions that divide unevenly over the waves, column tiles in one and in several rounds, prompts beside decode
 requests, several layers (wide residual in, wide residual out), pages of 32 tokens."""
 import numpy as np
@@ -25,7 +25,7 @@ SHAPES = [
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"H{s['hidden']}-I{s['mlp']}-D{s['head_dim']}")
-@pytest.mark.parametrize("T", [1, 2, 15, 16, 17])
+@pytest.mark.parametrize("T", [1, 2, 15, 16, 17, 32, 33])
 def test_layer(shape, T):
     m = small_model(vocab=512, **shape)
     reqs = [W.RequestSpec(1, 3 + 9 * i) for i in range(T if T < 4 else T - 6)] + ([] if T < 4 else [W.RequestSpec(6, 21)])
@@ -53,15 +53,15 @@ def test_more_tiles_than_sums_are_kept_for():
 def test_logits(hidden, vocab):
     m = small_model(64, 4, 2, hidden=hidden, mlp=64, vocab=vocab)
     rng = np.random.default_rng(vocab)
-    w = W.build_workload("few", m, [W.RequestSpec(1, 3)], n_kv_pages=4, seed=1400 + vocab, std=0.02, n_embeds=24)
-    bits = O.bf16_encode(rng.standard_normal((24, hidden)).astype(np.float32))
-    emb = O.EmbedPool(24, hidden)
-    emb.write(np.arange(24, dtype=np.int32), bits)
+    w = W.build_workload("few", m, [W.RequestSpec(1, 3)], n_kv_pages=4, seed=1400 + vocab, std=0.02, n_embeds=40)
+    bits = O.bf16_encode(rng.standard_normal((40, hidden)).astype(np.float32))
+    emb = O.EmbedPool(40, hidden)
+    emb.write(np.arange(40, dtype=np.int32), bits)
     w_lm = O.bf16_decode(w.head.w_lm)
-    ctx = make_ctx(w, max_dist_rows=17, max_top_k=16)
-    ctx.embed_write(np.arange(24, dtype=np.int32), bits)
-    for n in (1, 3, 16, 17):
-        ids = rng.permutation(24)[:n].astype(np.int32)
+    ctx = make_ctx(w, max_dist_rows=33, max_top_k=16)
+    ctx.embed_write(np.arange(40, dtype=np.int32), bits)
+    for n in (1, 3, 16, 17, 32, 33):
+        ids = rng.permutation(40)[:n].astype(np.int32)
         z = O.logits_from_embeds(m, w.head, emb, ids, True)
         gi, gp = ctx.get_next_dist(ids, 16, 1.0)
         zg = ctx.read_tap(TAP_LOGITS, n)

@@ -1597,7 +1597,9 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   const int n_cus = c->wave_slots / 8;
   const int wide_or_embed = x_in ? FEW_F32 : FEW_EMBED;
   const bool few_qkv = !lora_qkv && carried == 0 && few_rows_ok(T, L.wqkv, EPI_STORE_BF16, wide_or_embed);
-  const bool few_gu = !lora[PIE_PROJ_GATE] && !lora[PIE_PROJ_UP] && few_rows_ok(T, L.wgu, EPI_SWIGLU, FEW_F32);
+  const bool few_o = !lora[PIE_PROJ_O] && few_resid_ok(T, Hq * D, L.wo);
+  // (reads the rows of c->h, which the general output product may leave as partial sums for the second norm to sum)
+  const bool few_gu = few_o && !lora[PIE_PROJ_GATE] && !lora[PIE_PROJ_UP] && few_rows_ok(T, L.wgu, EPI_SWIGLU, FEW_F32);
 
   tm.begin(PIE_STAGE_NORM1);
   if (few_qkv) {}
@@ -1679,7 +1681,7 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   tm.begin(PIE_STAGE_OPROJ);
   int o_splits = 0;
   e = EpiArgs{EPI_RESID_EMBED, c->h, H, c->embeds, b->in_ids, x_in, H};
-  if (!lora[PIE_PROJ_O] && few_resid_ok(T, Hq * D, L.wo)) HIP_TRY(c, launch_few_resid(c->attn, Hq * D, T, L.wo, e, n_cus, s));
+  if (few_o) HIP_TRY(c, launch_few_resid(c->attn, Hq * D, T, L.wo, e, n_cus, s));
   else HIP_TRY(c, launch_gemm(c->attn, Hq * D, T, L.wo, e, c->splitk, c->splitk_elems, n_cus, s, &o_splits));
   tm.end(PIE_STAGE_OPROJ);
 

@@ -155,3 +155,17 @@ def test_adapter_error_codes():
     ctx.embed_txt(dw.token_ids, b.positions, b.in_embed_ids)
     assert status_of(lambda: ctx.batch_create(clone_batch(b, adapter_ids=np.full(b.n_requests, 1, np.int32)))) == -2
     assert status_of(lambda: ctx.batch_create(clone_batch(b, adapter_ids=np.full(b.n_requests, -2, np.int32)))) == -2
+
+
+@pytest.mark.parametrize("hidden,tokens", [(1024, 2), (2048, 33), (3072, 5), (4096, 40)])
+def test_adapter_contraction_split_over_workgroups(hidden, tokens):
+    """x A summed in one to four partial copies (one for each 1024 of the input dimension while there are few tiles), two blocks
+    of rank columns with the second half empty, and qkv sums in more and in fewer copies than are requested ahead."""
+    m = W.ModelDesc(hidden=hidden, n_q_heads=hidden // 64, n_kv_heads=hidden // 512, head_dim=64, mlp_dim=512, vocab=512,
+                    page_size=16, rms_eps=1e-5, rope_theta=1e4, n_layers=1)
+    dw = W.build_deep_workload("ad_split", m, [W.RequestSpec(1, 3 + 5 * i, in_place=True) for i in range(tokens)], n_kv_pages=600,
+                               seed=6900 + tokens, std=0.02, resid_std=0.02 / 8.0)
+    projections = ("wq", "wk", "wv", "wo")
+    adapters = {0: W.make_adapter(m, 6900, 0, rank=33, projections=projections, scale=0.5, std=0.05),
+                1: W.make_adapter(m, 6900, 1, rank=16, projections=projections, scale=1.0, std=0.05)}
+    compare(dw, adapters, [i % 2 for i in range(tokens)], f"split contraction, hidden {hidden}", max_rank=33)

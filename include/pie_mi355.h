@@ -258,7 +258,8 @@ pie_status pie_read_tap(pie_ctx* ctx, int32_t which, void* dst, int64_t n_elemen
 /* Stage timing.  When enabled, pie_forward / pie_get_next_dist bracket each stage with HIP events
  * on the context's stream; pie_stage_times synchronises and returns the milliseconds of the last
  * call per stage (host float[PIE_N_STAGES]; 0 for stages that did not run).  While it is on, prefill and decode attention
- * of a batch are launched apart. */
+ * of a batch are launched apart.  With up to 32 rows the norms and the rotary step may be part of the products: their time
+ * is in the product's stage then, and their own stages hold next to nothing. */
 enum {
   PIE_STAGE_NORM1 = 0, PIE_STAGE_QKV = 1, PIE_STAGE_ROPE_APPEND = 2, PIE_STAGE_ATTN_DECODE = 3,
   PIE_STAGE_ATTN_PREFILL = 4, PIE_STAGE_ATTN_MERGE = 5, PIE_STAGE_OPROJ = 6, PIE_STAGE_NORM2 = 7,
@@ -311,8 +312,9 @@ pie_status pie_batch_prefill_work(const pie_batch* batch, int32_t* out, int32_t 
  * and what the tiled kernels cannot), out[1] = parts the contraction is cut into, out[2] = leading rows that go through
  * whole rounds of tiles, the rest being a product of its own (0: one product), out[3] = column tiles of the weights,
  * each counted once for every XCD whose L2 has to fetch it (the tiles are ordered so that the row tiles of a column
- * share one).  A product that pie_product_stream tells of goes to the streaming kernel instead.  Computes on the host
- * only.  Host int64[4]. */
+ * share one).  A product that pie_product_stream tells of goes to the streaming kernel instead.  The products of a layer of
+ * up to 16 tokens, and q, k, v and logits of up to 32 rows, may be taken by kernels of their own before either is asked.
+ * Computes on the host only.  Host int64[4]. */
 pie_status pie_product_plan(int32_t rows, int32_t n_out, int32_t k, int64_t workspace_floats, int32_t n_cus, int64_t* out);
 
 /* Whether the same product goes to the kernel that streams weights past up to 640 rows: out[0] = rows of a tile (0: it

@@ -1,5 +1,7 @@
 // bf16 MFMA GEMMs  C[M, N] = A[M, K] x W[N, K]^T  with fused epilogues.
 //
+// (Products of 1 to 16 rows, logits and q, k, v of 17 to 32 as well, that also norm, rotate or finish their rows: few.hip,
+// where its conditions hold.)
 //   gemm_skinny : M <= 64 (decode batches, LM head).  HBM-bound on the weight stream: every wave owns one
 //                 32-column block of W and reads its tiles straight from global memory into MFMA B operands
 //                 (each load is 1 KiB contiguous thanks to the tiled weight layout); the activation tile is

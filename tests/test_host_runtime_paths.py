@@ -229,6 +229,24 @@ def adapter_updates_of_split_products(c):
         ctx.close()
 
 
+def few_rows_with_an_adapter_on_o(c):
+    """A few tokens at a width where the norms go into the products: with an adapter on the output projection that product leaves
+    partial sums, so the second norm has to run; without one the products do everything."""
+    m = SimpleNamespace(**{**vars(MODEL), "hidden": 2048, "n_q_heads": 32, "n_kv_heads": 8, "mlp_dim": 1024})
+    for projections, norms in (((), 0), ((6,), 0), ((3,), 1), ((0, 3), 2)):
+        ctx = c.loaded([(0, pj, 16) for pj in projections], m, tokens=16, adapters=1, rank=16)
+        b = batch_of([(1, 20), (1, 1), (2, 300)])
+        b.adapter_ids = np.zeros(b.n_requests, np.int32) if projections else None
+        pb = ctx.batch_create(b)
+        c.launches()
+        ctx.forward(0, pb)
+        names = c.launches()
+        assert sum("rmsnorm_kernel" in n for n in names) == norms, (projections, names)
+        assert any("rmsnorm_kernelILi2E" in n for n in names) == (3 in projections), (projections, names)
+        pb.destroy()
+        ctx.close()
+
+
 def attentions_in_one_launch(c):
     """Prompts of four query heads per kv head, or the tiles of a shared prefix, go with the decode waves in one launch; with stage
     timing on they are launched apart."""
@@ -252,7 +270,7 @@ def attentions_in_one_launch(c):
 
 
 CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy, no_room_for_parts,
-                                 adapter_updates_of_split_products, attentions_in_one_launch)}
+                                 adapter_updates_of_split_products, few_rows_with_an_adapter_on_o, attentions_in_one_launch)}
 
 if __name__ == "__main__":
     CASES[sys.argv[2]](Child(sys.argv[1]))

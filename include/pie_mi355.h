@@ -259,7 +259,7 @@ pie_status pie_read_tap(pie_ctx* ctx, int32_t which, void* dst, int64_t n_elemen
  * on the context's stream; pie_stage_times synchronises and returns the milliseconds of the last
  * call per stage (host float[PIE_N_STAGES]; 0 for stages that did not run).  While it is on, prefill and decode attention
  * of a batch are launched apart.  With up to 32 rows the norms and the rotary step may be part of the products: their time
- * is in the product's stage then, and their own stages hold only what two events take (4 to 5 us). */
+ * is in the product's stage then, and their own stages did not run. */
 enum {
   PIE_STAGE_NORM1 = 0, PIE_STAGE_QKV = 1, PIE_STAGE_ROPE_APPEND = 2, PIE_STAGE_ATTN_DECODE = 3,
   PIE_STAGE_ATTN_PREFILL = 4, PIE_STAGE_ATTN_MERGE = 5, PIE_STAGE_OPROJ = 6, PIE_STAGE_NORM2 = 7,

@@ -1601,13 +1601,15 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   // (reads the rows of c->h, which the general output product may leave as partial sums for the second norm to sum)
   const bool few_gu = few_o && !lora[PIE_PROJ_GATE] && !lora[PIE_PROJ_UP] && few_rows_ok(T, L.wgu, EPI_SWIGLU, FEW_F32);
 
-  tm.begin(PIE_STAGE_NORM1);
-  if (few_qkv) {}
-  else if (x_in && carried > 0)
-    HIP_TRY(c, launch_splitk_resid_norm(c->splitk, carried, L.wdown.NB * 32, c->h, nullptr, nullptr, x_in, L.g1, c->xn, T, H, m.rms_eps, s));
-  else if (x_in) HIP_TRY(c, launch_rmsnorm_f32(x_in, L.g1, c->xn, T, H, m.rms_eps, s));
-  else HIP_TRY(c, launch_rmsnorm_embed(c->embeds, b->in_ids, L.g1, c->xn, T, H, m.rms_eps, s));
-  tm.end(PIE_STAGE_NORM1);
+  // (a stage that a product takes in is not bracketed: it reports 0)
+  if (!few_qkv) {
+    tm.begin(PIE_STAGE_NORM1);
+    if (x_in && carried > 0)
+      HIP_TRY(c, launch_splitk_resid_norm(c->splitk, carried, L.wdown.NB * 32, c->h, nullptr, nullptr, x_in, L.g1, c->xn, T, H, m.rms_eps, s));
+    else if (x_in) HIP_TRY(c, launch_rmsnorm_f32(x_in, L.g1, c->xn, T, H, m.rms_eps, s));
+    else HIP_TRY(c, launch_rmsnorm_embed(c->embeds, b->in_ids, L.g1, c->xn, T, H, m.rms_eps, s));
+    tm.end(PIE_STAGE_NORM1);
+  }
 
   tm.begin(PIE_STAGE_QKV);
   int qkv_splits = 0;
@@ -1628,11 +1630,12 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
     HIP_TRY(c, launch_lora_up(split ? (void*)c->splitk : c->qkv, split ? L.wqkv.NB * 32 : QKV, QKV, split ? 4 : 3, Hq * D, KD, LT, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_Q, 0, c->lora_z, RM, ks, s, qkv_splits, (int64_t)T * L.wqkv.NB * 32));
   }
 
-  tm.begin(PIE_STAGE_ROPE_APPEND);
-  if (!few_qkv)
+  if (!few_qkv) {
+    tm.begin(PIE_STAGE_ROPE_APPEND);
     HIP_TRY(c, launch_rope_append(c->qkv, T, Hq, Hkv, D, b->pos, b->tok_page, b->tok_slot, b->rope_angles, kv_layer, b->n_pitems > 0,
                                   c->splitk, qkv_splits, L.wqkv.NB * 32, s));
-  tm.end(PIE_STAGE_ROPE_APPEND);
+    tm.end(PIE_STAGE_ROPE_APPEND);
+  }
 
   AttnArgs a{};
   a.q = c->qkv; a.q_stride = QKV; a.kv = kv_layer; a.out = c->attn; a.Hq = Hq; a.Hkv = Hkv; a.D = D;
@@ -1691,12 +1694,13 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
     HIP_TRY(c, launch_lora_up(o_splits > 0 ? c->splitk : c->h, o_splits > 0 ? L.wo.NB * 32 : H, H, 1, 0, 0, LT, b->lora_rows, b->lora_tile_ad, c->lora_dev, layer, NL, PIE_PROJ_O, 0, c->lora_z, RM, ks, s));
   }
 
-  tm.begin(PIE_STAGE_NORM2);
-  if (few_gu) {}
-  else if (o_splits > 0)
-    HIP_TRY(c, launch_splitk_resid_norm(c->splitk, o_splits, L.wo.NB * 32, x_in, c->embeds, b->in_ids, c->h, L.g2, c->xn, T, H, m.rms_eps, s));
-  else HIP_TRY(c, launch_rmsnorm_f32(c->h, L.g2, c->xn, T, H, m.rms_eps, s));
-  tm.end(PIE_STAGE_NORM2);
+  if (!few_gu) {
+    tm.begin(PIE_STAGE_NORM2);
+    if (o_splits > 0)
+      HIP_TRY(c, launch_splitk_resid_norm(c->splitk, o_splits, L.wo.NB * 32, x_in, c->embeds, b->in_ids, c->h, L.g2, c->xn, T, H, m.rms_eps, s));
+    else HIP_TRY(c, launch_rmsnorm_f32(c->h, L.g2, c->xn, T, H, m.rms_eps, s));
+    tm.end(PIE_STAGE_NORM2);
+  }
 
   tm.begin(PIE_STAGE_GATEUP);
   if (lora[PIE_PROJ_GATE] || lora[PIE_PROJ_UP]) {
@@ -1799,15 +1803,14 @@ static pie_status run_dist(pie_ctx* c, const DistBuffers& w, int32_t n, int32_t 
   const int H = c->m.hidden, V = c->m.vocab;
   hipStream_t s = c->stream;
   StageTimer tm(c, PIE_STAGE_HEAD_NORM, PIE_STAGE_TOPK);
-  tm.begin(PIE_STAGE_HEAD_NORM);
   const bool few = c->g_final && w.ids_on_host && few_rows_ok(n, c->wlm, EPI_STORE_F32, FEW_EMBED_ARGS);
-  if (few) {
-  } else if (c->g_final) {
-    HIP_TRY(c, (w.ids_on_host ? launch_rmsnorm_embed_ids : launch_rmsnorm_embed)(c->embeds, w.ids, c->g_final, w.en, n, H, c->m.rms_eps, s));
-  } else {
-    HIP_TRY(c, (w.ids_on_host ? launch_embed_copy_ids : launch_embed_copy)(c->embeds, w.ids, n, H, w.en, 0, s));
+  if (!few) {
+    tm.begin(PIE_STAGE_HEAD_NORM);
+    if (c->g_final)
+      HIP_TRY(c, (w.ids_on_host ? launch_rmsnorm_embed_ids : launch_rmsnorm_embed)(c->embeds, w.ids, c->g_final, w.en, n, H, c->m.rms_eps, s));
+    else HIP_TRY(c, (w.ids_on_host ? launch_embed_copy_ids : launch_embed_copy)(c->embeds, w.ids, n, H, w.en, 0, s));
+    tm.end(PIE_STAGE_HEAD_NORM);
   }
-  tm.end(PIE_STAGE_HEAD_NORM);
   tm.begin(PIE_STAGE_LM_HEAD);
   EpiArgs e{EPI_STORE_F32, w.logits, V, nullptr, nullptr, nullptr, 0};
   if (few) HIP_TRY(c, launch_few_f32(FewSource{FEW_EMBED_ARGS, c->embeds, H, w.ids, c->g_final, c->m.rms_eps}, n, c->wlm, w.logits, c->wave_slots / 8, s));

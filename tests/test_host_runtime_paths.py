@@ -42,12 +42,12 @@ class Child:
         from paper_2510_24051_amd import Pie, binding
         self.Pie, self.binding, self.lib = Pie, binding, binding.load_library()
 
-    def context(self, n_pages=1024, tokens=256, requests=64, m=MODEL, adapters=0, rank=0):
+    def context(self, n_pages=1024, tokens=256, requests=64, m=MODEL, adapters=0, rank=0, dist=(0, 0)):
         b, C = self.binding, self.C
         p = self.Pie.__new__(self.Pie)
         p.lib, p.device, p.stream, p.model, h = self.lib, None, None, m, C.c_void_p()
         md = b.ModelDescC(m.hidden, m.n_q_heads, m.n_kv_heads, m.head_dim, m.mlp_dim, m.vocab, m.page_size, m.rms_eps, m.rope_theta, 1)
-        pd = b.PoolDescC(n_pages, 1024, tokens, requests, 0, 0, adapters, rank)
+        pd = b.PoolDescC(n_pages, 1024, tokens, requests, dist[1], dist[0], adapters, rank)
         assert self.lib.pie_create(C.byref(md), C.byref(pd), None, C.byref(h)) == 0
         p.ctx = h
         return p
@@ -58,9 +58,12 @@ class Child:
         room = np.zeros(2 * max(m.hidden, m.n_q_heads * m.head_dim) * max(m.mlp_dim, m.hidden, m.n_q_heads * m.head_dim), np.int8)
         at = C.c_void_p(room.ctypes.data)  # (kernels do nothing, copies read from here)
         assert self.lib.pie_load_layer(ctx.ctx, 0, *[at] * 9) == 0
+        if m.vocab:
+            head = np.zeros(m.vocab * m.hidden, np.int16)
+            assert self.lib.pie_load_head(ctx.ctx, at, C.c_void_p(head.ctypes.data)) == 0
         for adapter, proj, r in pairs:
             assert self.lib.pie_load_adapter(ctx.ctx, adapter, 0, proj, r, C.c_float(1.0), at, at) == 0
-        ctx.synchronize()
+        ctx.synchronize()  # (the copies are carried out here)
         return ctx
 
     def launches(self):
@@ -247,6 +250,29 @@ def few_rows_with_an_adapter_on_o(c):
         ctx.close()
 
 
+def stages_that_do_not_run(c):
+    """A stage whose work a product has taken in reports 0, also when the call before it ran that stage."""
+    m = SimpleNamespace(**{**vars(MODEL), "hidden": 2048, "n_q_heads": 32, "n_kv_heads": 8, "mlp_dim": 1024, "vocab": 512})
+    ctx = c.loaded(m=m, tokens=40, dist=(40, 8))
+    ctx.set_stage_timing(True)
+    taken_in = {"norm1", "rope_append", "norm2"}
+    for tokens, without in ((40, set()), (3, taken_in), (40, set()), (20, taken_in - {"norm2"})):
+        pb = ctx.batch_create(batch_of([(1, 20 + i) for i in range(tokens)]))
+        ctx.forward(0, pb)
+        times = ctx.stage_times()
+        ran = {"norm1", "qkv", "rope_append", "attn_decode", "attn_merge", "oproj", "norm2", "gateup", "down"} - without
+        assert {k for k, v in times.items() if v > 0} - {"head_norm", "lm_head", "topk"} == ran, (tokens, times)
+        pb.destroy()
+    room = np.zeros(40 * 8, np.int32)
+    out = c.C.c_void_p(room.ctypes.data)
+    for rows, ran in ((40, True), (3, False)):
+        ids = np.arange(rows, dtype=np.int32)
+        assert c.lib.pie_get_next_dist(ctx.ctx, ids.ctypes.data_as(c.C.c_void_p), rows, 8, c.C.c_float(1.0), out, out) == 0
+        times = ctx.stage_times()
+        assert (times["head_norm"] > 0) == ran and times["lm_head"] > 0 and times["topk"] > 0, (rows, times)
+    ctx.close()
+
+
 def attentions_in_one_launch(c):
     """Prompts of four query heads per kv head, or the tiles of a shared prefix, go with the decode waves in one launch; with stage
     timing on they are launched apart."""
@@ -270,7 +296,8 @@ def attentions_in_one_launch(c):
 
 
 CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy, no_room_for_parts,
-                                 adapter_updates_of_split_products, few_rows_with_an_adapter_on_o, attentions_in_one_launch)}
+                                 adapter_updates_of_split_products, few_rows_with_an_adapter_on_o, stages_that_do_not_run,
+                                 attentions_in_one_launch)}
 
 if __name__ == "__main__":
     CASES[sys.argv[2]](Child(sys.argv[1]))

@@ -53,6 +53,11 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// The activation of every SwiGLU, so that a token's does not depend on the rows beside it or on an adapter.  (Divided, rounded
+// correctly.  A reciprocal times z, good to one unit in the last place, took 3433 us for a layer of 8320 tokens against 3450
+// and the same for 84 to 333: not worth the error.)
+__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
+
 // max(a, b, c) in one instruction.  (fmaxf chains compile to v_max_f32 pairs preceded by a canonicalising
 // v_max_f32 x, x per input, because the inputs might be signalling NaNs; MFMA results never are.)
 __device__ __forceinline__ float max3(float a, float b, float c) {

@@ -293,7 +293,7 @@ __global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds 
           for (int i = 0; i < 4; ++i) {
             const float up = __shfl_xor(v[i], 8);
             if (m0 + i < M && c < 8)
-              reinterpret_cast<bf16_t*>(out)[(int64_t)(m0 + i) * ldo + tr * 8 + c] = f32_to_bf16(v[i] / (1.0f + __expf(-v[i])) * up);
+              reinterpret_cast<bf16_t*>(out)[(int64_t)(m0 + i) * ldo + tr * 8 + c] = f32_to_bf16(silu_f(v[i]) * up);
           }
         } else {
           const int cpt = D / 16, h = tr / cpt, f = (tr % cpt) * 8 + (c & 7), d = f + (c >> 3) * (D / 2);

@@ -20,11 +20,6 @@
 // ------------------------------------------------------------------------------------------------
 // epilogue on one 32x32 accumulator tile (rows m0.., columns n0..), see mfma32 for the lane layout
 // ------------------------------------------------------------------------------------------------
-// (A reciprocal, good to one unit in the last place, instead of a correctly rounded division: what it goes into is rounded to
-// bf16, 2^16 times coarser, and the division's ten instructions were a third of the SwiGLU epilogues: 8320 x 28672 x 4096
-// 1486 -> 1464 us, 324 x 16384 x 2048 31.6 -> 30.2.)
-__device__ __forceinline__ float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
-
 // Loads are batched ahead of the stores (ids, then residual values, then all stores) so that a tile costs
 // three dependent memory round trips instead of one per element.
 // FULL: all 32 rows of the tile exist (the caller's uniform test), so no per-row predicates are needed; with them

@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void swiglu_f32_kernel(const float* __restrict
   const float* row = gu + t * 2 * I;
   const int c = (i >> 5) * 64 + (i & 31);
   const float g = row[c], u = row[c + 32];
-  act[idx] = f32_to_bf16(g / (1.0f + __expf(-g)) * u);
+  act[idx] = f32_to_bf16(silu_f(g) * u);
 }
 
 }  // namespace

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds 
                                                           void* __restrict__ out, int ldo, FewRope rope) {
   constexpr int K = NS * 256, KB = K / 16;
   [[maybe_unused]] constexpr int R = NS < FEW_RING ? NS : NS > FEW_RING ? FEW_RING / 2 : FEW_RING;
-  [[maybe_unused]] constexpr int EARLY = SRC == FEW_F32 && R > 12 ? 12 : MB == 2 && NS == 16 ? 4 : R;  // requested ahead of the norm (as registers allow)
+  [[maybe_unused]] constexpr int EARLY = SRC == FEW_F32 && R > 12 ? 12 : MB == 2 && NS == 16 ? 3 : R;  // requested ahead of the norm (as registers allow: no spills)
   constexpr bool ROPE = MODE == EPI_STORE_BF16;
   __shared__ __align__(16) float red[2][8][MB * 256];
   __shared__ __align__(16) bf16_t turn[8][MB * 16 * 64];

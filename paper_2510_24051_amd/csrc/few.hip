@@ -4,16 +4,17 @@
 // MFMAs and the eight sums meet through LDS in wave order.  So a 4096-column product is 256 workgroups, one per compute unit,
 // with no partial sums in memory and nothing left for another kernel to add up, and the work of the small kernels around a
 // product moves into it:
-//   few_rows_kernel    each wave keeps its K slice of the rows in registers as MFMA operands (K = 256 * NS, NS <= 32; MB blocks
-//                      of 16 rows, two of them for q, k, v and logits of Embeds up to K = 4096) and walks
-//                      any number of column tiles; the rows may be normalised on the way in (RMSNorm of Embeds or of fp32
+//   few_rows_kernel    each wave keeps its K slice of the rows in registers as MFMA operands (K = 256 * NS; MB blocks of 16 rows,
+//                      two of them for q, k, v and logits of Embeds) and walks any number of column tiles; the rows may be normalised on the way in (RMSNorm of Embeds or of fp32
 //                      rows: every workgroup does it for itself, 16 rows, while its first weights are in flight); a QKV tile is
 //                      rotated and appended to its page, a gate/up tile becomes eight activations
 //   few_stream_kernel  rows streamed beside the weights (long contractions; products that end in the residual)
-// A wave has 16 KiB of weights in flight (128 KiB per compute unit), requested non-temporally through buffer descriptors;
-// requests past the end are sent out of the buffer's range, where they return without touching memory.
+// A wave of few_stream has 16 KiB of weights in flight (128 KiB per compute unit); one of few_rows a tile's k steps, K / 256 KiB
+// up to K = 4096 and 7 to 10 KiB above, where the rows leave no registers for more.  They are requested non-temporally
+// through buffer descriptors; requests past the end are sent out of the buffer's range, where they return without touching
+// memory.
 //
-// Bound by HBM, and by launches: a layer of 11 launches has 7.  Kernel trace, one and 16 rows, before (norm + product + rotary
+// Bound by HBM, and by launches: a layer of ten has six.  Kernel trace, one and 16 rows, before (norm + product + rotary
 // step, product + second norm, product, product + epilogue) and now:
 //                    6144 x 4096 q, k, v   4096 x 4096 output + norm   28672 x 4096 gate/up   4096 x 14336 down   layer, wall
 //   1 row     us     18.0 -> 14.7          11.2 -> 8                   40.7 -> 40.5           25.3 -> 21.0        124 -> 110
@@ -67,8 +68,12 @@ template <int MODE, int SRC, int NS, int MB>
 __global__ __launch_bounds__(512, 2) void few_rows_kernel(FewSource src, FewIds arg_ids, int M, const bf16_t* __restrict__ Wp, int NB, int n_tiles,
                                                           void* __restrict__ out, int ldo, FewRope rope) {
   constexpr int K = NS * 256, KB = K / 16;
-  [[maybe_unused]] constexpr int R = NS < FEW_RING ? NS : NS > FEW_RING ? FEW_RING / 2 : FEW_RING;
-  [[maybe_unused]] constexpr int EARLY = SRC == FEW_F32 && R > 12 ? 12 : MB == 2 && NS == 16 ? 3 : R;  // requested ahead of the norm (as registers allow: no spills)
+  static_assert(NS % 2 == 0 && NS <= 32, "pairs of k steps, held in registers");
+  // weight requests in flight: a tile's k steps (R divides NS, so that the next tile's go on in the same registers)
+  [[maybe_unused]] constexpr int R = NS <= FEW_RING ? NS : NS % 8 == 0 ? 8 : NS % 10 == 0 ? 10 : 7;
+  static_assert(NS % R == 0, "the ring goes on from tile to tile");
+  // requested ahead of the norm, as registers allow: the rows take 4 NS of them a block, twice that in fp32, and nothing may spill
+  [[maybe_unused]] constexpr int EARLY = SRC == FEW_F32 ? (R < 12 ? R : 12) : MB == 2 && 35 - 2 * NS < R ? 35 - 2 * NS : R;
   constexpr bool ROPE = MODE == EPI_STORE_BF16;
   __shared__ __align__(16) float red[2][8][MB * 256];
   __shared__ __align__(16) bf16_t turn[8][MB * 16 * 64];
@@ -452,20 +457,43 @@ hipError_t run_rows(const FewSource& given, int M, const PackedWeight& W, int n_
     few_rows_kernel<MODE, SRC, NS, 1><<<grid, block, 0, s>>>(src, ids, M, W.data, W.NB, n_tiles, out, ldo, rope);
     return hipGetLastError();
   };
-  if (W.K == 8 * 256) return run(std::integral_constant<int, 8>{});
-  if (W.K == 16 * 256) return run(std::integral_constant<int, 16>{});
-  if constexpr (MODE == EPI_STORE_BF16 && SRC == FEW_EMBED)
-    if (W.K == 32 * 256) return run(std::integral_constant<int, 32>{});
+  switch (W.K / 256) {
+    case 2: return run(std::integral_constant<int, 2>{});
+    case 4: return run(std::integral_constant<int, 4>{});
+    case 6: return run(std::integral_constant<int, 6>{});
+    case 8: return run(std::integral_constant<int, 8>{});
+    case 10: return run(std::integral_constant<int, 10>{});
+    case 12: return run(std::integral_constant<int, 12>{});
+    case 14: return run(std::integral_constant<int, 14>{});
+    case 16: return run(std::integral_constant<int, 16>{});
+  }
+  if constexpr (MODE == EPI_STORE_BF16 && SRC == FEW_EMBED) switch (W.K / 256) {
+    case 20: return run(std::integral_constant<int, 20>{});
+    case 24: return run(std::integral_constant<int, 24>{});
+    case 28: return run(std::integral_constant<int, 28>{});
+    case 32: return run(std::integral_constant<int, 32>{});
+  }
   return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-// Rows of 8192 leave registers for half a ring of weights only: as good as the kernels it replaces where the rotary step and a
-// norm of Embeds go with it (10240 x 8192: 36.7 us at one row for 2.7 + 29.3 + 4.8, 37.5 at 16 for 3.8 + 30.5 + 5.1).
+// Which rows: a wave's slice is pairs of k steps, so K goes in steps of 512; the rows of a slice stay in registers, fp32 rows
+// twice over while they are normalised, which ends at 4096.  Embeds of q, k, v go on to 8192 in steps of 1024 (with a ring of at
+// least seven).  Every length gains.  Whole layers, us a layer through several with weights from HBM, general path -> this one:
+//   width x mlp       512 x 2048     1024 x 4096    1536 x 8960    2560 x 6912    3072 x 8192    4096 x 14336
+//   1 row             36.5 -> 28.0   42.2 -> 31.6   60.6 -> 46.8   59.7 -> 51.9   72.8 -> 64.0   107.7 -> 95.5
+//   16 rows           41.4 -> 34.3   45.7 -> 37.8   68.4 -> 57.4   67.0 -> 63.2   79.3 -> 73.0   113.1 -> 105.7
+// q, k, v of Embeds alone, a layer at one row: 5120 137.1 -> 134.2, 6144 159.0 -> 156.0, 7168 214.1 -> 211.9, 8192 294.0 -> 291.1; 17 to
+// 32 rows of 512 to 4096: 0 to 5.
+// Logits of up to 16 rows gain 1.5 to 30 us at 512 to 131072 columns.  Of 17 to 32 rows those of up to 3072 gain 0 to 8; at 4096 the
+// norm of two blocks in every workgroup has to be paid by the stream (32000 columns 69.4 -> 63.4, 100000 184.3 -> 163.5, but 2048
+// columns 23.0 -> 24.4 and 16384 40.7 -> 41.9, top-k included), and 3584, 14 requests a wave, loses where it counts (131072 columns 175 -> 182).
 bool few_rows_ok(int M, const PackedWeight& W, int mode, int source) {
   if (M < 1 || M > (source == FEW_F32 || W.K > 16 * 256 ? 16 : FEW_ROWS) || !fits(W)) return false;
-  return W.K == 8 * 256 || W.K == 16 * 256 || (W.K == 32 * 256 && mode == EPI_STORE_BF16 && source == FEW_EMBED);
+  if (W.K < 512 || W.K % 512 != 0) return false;
+  if (mode == EPI_STORE_F32 && M > 16 && W.K > 3072) return W.K == 4096 && W.N > 16384;
+  return W.K <= 4096 || (W.K <= 8192 && W.K % 1024 == 0 && mode == EPI_STORE_BF16 && source == FEW_EMBED);
 }
 
 hipError_t launch_few_qkv(const FewSource& src, int M, const PackedWeight& W, bf16_t* qkv, const FewRope& rope, int n_cus, hipStream_t s) {

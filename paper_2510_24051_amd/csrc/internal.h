@@ -259,7 +259,7 @@ hipError_t launch_gemm(const bf16_t* A, int lda, int M, const PackedWeight& W, c
 // Products of up to FEW_ROWS rows with the small kernels around them taken in (few.hip).  The rows are normalised on the way in
 // (RMSNorm times gain, rounded to bf16 as the norm kernels do): Embeds whose ids are on the device or on the host (which
 // travel as kernel arguments), or fp32 rows.
-#define FEW_ROWS 32  // (16 where the rows are fp32 or 8192 long, and for products that end in the residual)
+#define FEW_ROWS 32  // (16 where the rows are fp32 or longer than 4096, and for products that end in the residual)
 enum FewSourceKind { FEW_EMBED = 0, FEW_EMBED_ARGS = 1, FEW_F32 = 2 };
 struct FewIds { int32_t v[FEW_ROWS]; };
 struct FewSource {

@@ -1,6 +1,6 @@
 """Layers of 1 to 32 tokens, whose products take in the norms, the rotary step and the epilogues: rows around the edges, both
-head sizes, contractions that divide unevenly over the waves, column tiles in one and in several rounds, prompts beside decode
-requests, several layers (wide residual in, wide residual out), pages of 32 tokens."""
+head sizes, every row length, contractions that divide unevenly over the waves, column tiles in one and in several rounds, prompts
+beside decode requests, several layers (wide residual in, wide residual out), pages of 32 tokens."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,7 @@ from test_gpu_parity import compare_layer, small_model
 
 pytestmark = pytest.mark.gpu
 
-# hidden 2048 and 4096: everything is taken in; others: the output and down projections (alone)
+# 2048 and 4096 wide: everything is taken in; 8192: q, k, v of the input Embeds; 96: nothing
 SHAPES = [
     dict(head_dim=64, n_q=8, n_kv=2, hidden=2048, mlp=96),
     dict(head_dim=128, n_q=8, n_kv=2, hidden=4096, mlp=4128),
@@ -33,6 +33,16 @@ def test_layer(shape, T):
     compare_layer(w, what=f"T={T} H{m.hidden} I{m.mlp_dim}")
 
 
+@pytest.mark.parametrize("hidden", [512, 1024, 1536, 2560, 3072, 3584, 5120, 6144, 7168])
+@pytest.mark.parametrize("T", [3, 16, 20])
+def test_row_lengths(hidden, T):
+    """Each length has a kernel of its own (2048, 4096 and 8192: above): ring depths of 2 to 14 requests, and 7, 8 and 10 above 4096."""
+    m = small_model(64, 4, 2, hidden=hidden, mlp=288, vocab=512)
+    w = W.build_workload("few", m, [W.RequestSpec(1, 3 + 9 * i) for i in range(T)], n_kv_pages=T * 14 + 8, seed=1500 + T + hidden, std=0.02,
+                         resid_std=0.005)
+    compare_layer(w, what=f"T={T} H{hidden}")
+
+
 @pytest.mark.parametrize("hidden", [2048, 4096])
 @pytest.mark.parametrize("T", [1, 16])
 def test_layers_in_a_row(hidden, T):
@@ -49,7 +59,8 @@ def test_more_tiles_than_sums_are_kept_for():
     compare_layer(w, what="I33088")
 
 
-@pytest.mark.parametrize("hidden,vocab", [(2048, 96), (2048, 4128), (2048, 131072), (4096, 8224)])
+@pytest.mark.parametrize("hidden,vocab", [(2048, 96), (2048, 4128), (2048, 131072), (4096, 8224), (4096, 16416), (512, 4128), (1536, 96), (3072, 4128),
+                                          (3584, 4128)])
 def test_logits(hidden, vocab):
     m = small_model(64, 4, 2, hidden=hidden, mlp=64, vocab=vocab)
     rng = np.random.default_rng(vocab)

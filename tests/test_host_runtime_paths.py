@@ -250,6 +250,44 @@ def few_rows_with_an_adapter_on_o(c):
         ctx.close()
 
 
+def few_rows_by_width(c):
+    """Which widths have their norms and rotary step inside the products, by the length of a row and the number of rows: every
+    multiple of 512 up to 4096 at up to 16 rows, q, k, v of Embeds at up to 32, those of every multiple of 1024 up to 8192 at up to 16."""
+    for hidden in (256, 480, 512, 768, 1024, 1536, 2048, 2560, 3072, 3584, 4096, 4608, 5120, 7168, 8192):
+        m = SimpleNamespace(**{**vars(MODEL), "hidden": hidden, "n_q_heads": 4, "n_kv_heads": 2, "mlp_dim": 64})
+        ctx = c.loaded(m=m, tokens=40)
+        for tokens in (1, 16, 17, 32, 33):
+            pb = ctx.batch_create(batch_of([(1, 20)] * tokens))
+            c.launches()
+            ctx.forward(0, pb)
+            names = c.launches()
+            fits = hidden % 512 == 0 and hidden <= 4096
+            qkv = tokens <= 32 and fits or tokens <= 16 and hidden > 4096 and hidden % 1024 == 0
+            assert any("few_rows_kernelILi0E" in n for n in names) == qkv != any("rope_append" in n for n in names), (hidden, tokens, names)
+            assert any("few_rows_kernelILi2E" in n for n in names) == (fits and tokens <= 16), (hidden, tokens, names)
+            assert sum("rmsnorm_kernel" in n for n in names) == 2 - qkv - (fits and tokens <= 16), (hidden, tokens, names)
+            pb.destroy()
+        ctx.close()
+
+
+def logits_of_few_rows(c):
+    """Logits with their norm inside: up to 16 rows of every length that has a kernel, 17 to 32 rows of up to 3072, and of 4096 over
+    many columns."""
+    room = np.zeros(40 * 8, np.int32)
+    out = c.C.c_void_p(room.ctypes.data)
+    for hidden, vocab, most in ((512, 96, 32), (1000 // 32 * 32, 4096, 0), (3072, 512, 32), (3584, 32768, 16), (4096, 16384, 16), (4096, 16416, 32),
+                                (5120, 512, 0)):
+        m = SimpleNamespace(**{**vars(MODEL), "hidden": hidden, "mlp_dim": 64, "vocab": vocab})
+        ctx = c.loaded(m=m, tokens=8, dist=(40, 8))
+        for rows in (1, 16, 17, 32, 33):
+            ids = np.arange(rows, dtype=np.int32)
+            c.launches()
+            assert c.lib.pie_get_next_dist(ctx.ctx, ids.ctypes.data_as(c.C.c_void_p), rows, 8, c.C.c_float(1.0), out, out) == 0
+            names = c.launches()
+            assert any("few_rows_kernelILi4E" in n for n in names) == (rows <= most) != any("rmsnorm" in n for n in names), (hidden, vocab, rows, names)
+        ctx.close()
+
+
 def stages_that_do_not_run(c):
     """A stage whose work a product has taken in reports 0, also when the call before it ran that stage."""
     m = SimpleNamespace(**{**vars(MODEL), "hidden": 2048, "n_q_heads": 32, "n_kv_heads": 8, "mlp_dim": 1024, "vocab": 512})
@@ -296,8 +334,8 @@ def attentions_in_one_launch(c):
 
 
 CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy, no_room_for_parts,
-                                 adapter_updates_of_split_products, few_rows_with_an_adapter_on_o, stages_that_do_not_run,
-                                 attentions_in_one_launch)}
+                                 adapter_updates_of_split_products, few_rows_with_an_adapter_on_o, few_rows_by_width,
+                                 logits_of_few_rows, stages_that_do_not_run, attentions_in_one_launch)}
 
 if __name__ == "__main__":
     CASES[sys.argv[2]](Child(sys.argv[1]))

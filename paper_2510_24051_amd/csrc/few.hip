@@ -519,11 +519,39 @@ bool few_resid_ok(int M, int lda, const PackedWeight& W) {
   return M >= 1 && M <= 16 && W.K % 32 == 0 && W.N % 32 == 0 && fits(W) && (int64_t)M * lda * 2 < ((int64_t)1 << 31);
 }
 
+namespace {
+// Workgroups of an output or down product: 16 columns each, or 32 where that is more than one a compute unit.
+int resid_wgs(int N, int n_cus, bool* two) {
+  const int tiles = N / 16;
+  *two = tiles > n_cus;  // (an even number of tiles: two next to each other are a whole 32-column block)
+  return *two ? tiles / 2 : tiles;
+}
+}  // namespace
+
+// Against the product split along K, whose partial sums the kernel behind it adds up at little cost where that is a norm of its own
+// (SUMS_JOIN_NORM); where it is none they take a kernel (SUMS_KERNEL), and where the next product takes its norm in they keep it from
+// doing so, which costs 4 to 5 us more (SUMS_KEEP_NORM).  Whole layers of forms that differ in this product alone, us that
+// few_stream gains (256 compute units, weights from HBM, one and 16 rows):
+//   N x K             1024 x 2048   1024 x 4096   2560 x 8192   3584 x 1024   3584 x 4096   4096 x 4096   5120 x 4096   8192 x 8192
+//   SUMS_JOIN_NORM    -1.7  -1.5    0.0  -0.7     0.6  -2.4     -1.0  -1.1    1.4   0.6     1.5   1.7     2.7   2.8     8.8   5.1
+//   SUMS_KERNEL                     1.1   0.8     2.1  -0.6      0.6   1.8    1.3   1.0     2.6   3.9     5.0   3.8     7.5   6.8
+// So where the sums are free it takes three quarters of the compute units and 2048 of K to gain.  Where they cost something it always
+// gains, but for many long rows in few workgroups: every workgroup reads all rows, and with 9 to 16 of them as many bytes as of 16
+// columns' weights, at what one compute unit takes (sums free: 3072 x 6144 at 16 rows -1.5; a kernel: 2304 x 9216 -1.7, 3328 x 8960
+// -1.4, 2048 x 8192 -0.3; a norm kept: 2048 x 16384 -1.3, 3072 x 24576 -0.7, 5120 x 13824 -2.8, but 2048 x 8192 2.5, 3584 x 18944 2.7,
+// 4096 x 14336 2.5 and, two column tiles to the rows, 6144 x 16384 1.8).
+bool few_resid_pays(int M, const PackedWeight& W, int n_cus, SplitSums sums) {
+  bool two;
+  const int wgs = resid_wgs(W.N, n_cus, &two);
+  const bool busy = wgs * 8 >= n_cus * (two ? 6 : 7);
+  if (M > 8 && !busy && W.K > (sums == SUMS_KEEP_NORM ? 12288 : sums == SUMS_KERNEL || two ? 8192 : 4096)) return false;
+  return sums != SUMS_JOIN_NORM || (W.K >= 2048 && (two || wgs * 4 >= n_cus * 3));
+}
+
 hipError_t launch_few_resid(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, int n_cus, hipStream_t s) {
   if (!few_resid_ok(M, lda, W) || (epi.mode != EPI_RESID_EMBED && epi.mode != EPI_RESID_OUT)) return hipErrorInvalidValue;
-  const int tiles = W.N / 16;
-  const bool two = tiles > n_cus;  // (an even number of tiles: two next to each other are a whole 32-column block)
-  const dim3 grid(two ? tiles / 2 : tiles), block(512);
+  bool two;
+  const dim3 grid(resid_wgs(W.N, n_cus, &two)), block(512);
   if (epi.mode == EPI_RESID_EMBED) {
     if (two) few_stream_kernel<EPI_RESID_EMBED, 2><<<grid, block, 0, s>>>(A, lda, M, W.data, W.NB, W.K, epi);
     else few_stream_kernel<EPI_RESID_EMBED, 1><<<grid, block, 0, s>>>(A, lda, M, W.data, W.NB, W.K, epi);

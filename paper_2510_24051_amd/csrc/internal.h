@@ -280,7 +280,9 @@ bool few_rows_ok(int M, const PackedWeight& W, int mode, int source);  // what t
 hipError_t launch_few_qkv(const FewSource& src, int M, const PackedWeight& W, bf16_t* qkv, const FewRope& rope, int n_cus, hipStream_t s);
 hipError_t launch_few_swiglu(const FewSource& src, int M, const PackedWeight& W, bf16_t* act, int n_cus, hipStream_t s);
 hipError_t launch_few_f32(const FewSource& src, int M, const PackedWeight& W, float* out, int n_cus, hipStream_t s);
-bool few_resid_ok(int M, int lda, const PackedWeight& W);
+bool few_resid_ok(int M, int lda, const PackedWeight& W);  // what launch_few_resid takes
+enum SplitSums { SUMS_JOIN_NORM, SUMS_KERNEL, SUMS_KEEP_NORM };  // what a split product's partial sums would cost behind it
+bool few_resid_pays(int M, const PackedWeight& W, int n_cus, SplitSums sums);
 hipError_t launch_few_resid(const bf16_t* A, int lda, int M, const PackedWeight& W, const EpiArgs& epi, int n_cus, hipStream_t s);
 
 void product_plan(int M, int N, int K, size_t ws_elems, int n_cus, int64_t out[4]);  // see pie_product_plan

@@ -1577,11 +1577,14 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   EpiArgs e{};
 
   // LoRA pairs the batch's adapters carry in this layer, per projection
-  bool lora[PIE_N_PROJ] = {false, false, false, false, false, false, false};
-  if (b->n_lora_tiles > 0)
-    for (int ad : b->used_adapters)
-      for (int pj = 0; pj < PIE_N_PROJ; ++pj)
-        if (c->lora[((size_t)ad * m.n_layers + layer) * PIE_N_PROJ + pj].rank > 0) lora[pj] = true;
+  auto adapted = [&](int l, int pj) {
+    if (b->n_lora_tiles > 0)
+      for (int ad : b->used_adapters)
+        if (c->lora[((size_t)ad * m.n_layers + l) * PIE_N_PROJ + pj].rank > 0) return true;
+    return false;
+  };
+  bool lora[PIE_N_PROJ];
+  for (int pj = 0; pj < PIE_N_PROJ; ++pj) lora[pj] = adapted(layer, pj);
   const int RM = round_up(c->p.max_lora_rank, 16), NL = m.n_layers, LT = b->n_lora_tiles;
   const bool lora_qkv = lora[PIE_PROJ_Q] || lora[PIE_PROJ_K] || lora[PIE_PROJ_V];
   // Small batches split their projections along K.  Where the next kernel reads the projection's output row by
@@ -1597,9 +1600,14 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
   const int n_cus = c->wave_slots / 8;
   const int wide_or_embed = x_in ? FEW_F32 : FEW_EMBED;
   const bool few_qkv = !lora_qkv && carried == 0 && few_rows_ok(T, L.wqkv, EPI_STORE_BF16, wide_or_embed);
-  const bool few_o = !lora[PIE_PROJ_O] && few_resid_ok(T, Hq * D, L.wo);
+  const bool gu_norms = !lora[PIE_PROJ_GATE] && !lora[PIE_PROJ_UP] && few_rows_ok(T, L.wgu, EPI_SWIGLU, FEW_F32);
+  const bool few_o = !lora[PIE_PROJ_O] && few_resid_ok(T, Hq * D, L.wo) && few_resid_pays(T, L.wo, n_cus, gu_norms ? SUMS_KEEP_NORM : SUMS_JOIN_NORM);
   // (reads the rows of c->h, which the general output product may leave as partial sums for the second norm to sum)
-  const bool few_gu = few_o && !lora[PIE_PROJ_GATE] && !lora[PIE_PROJ_UP] && few_rows_ok(T, L.wgu, EPI_SWIGLU, FEW_F32);
+  const bool few_gu = few_o && gu_norms;
+  const bool next_layer = carry && y_out && layer + 1 < m.n_layers;  // its first norm sums what this layer's down product leaves ..
+  const bool next_norms = next_layer && !adapted(layer + 1, PIE_PROJ_Q) && !adapted(layer + 1, PIE_PROJ_K) && !adapted(layer + 1, PIE_PROJ_V) &&
+                          few_rows_ok(T, c->layers[layer + 1].wqkv, EPI_STORE_BF16, FEW_F32);  // .. unless it has none of its own
+  const bool few_down = few_resid_ok(T, I, L.wdown) && few_resid_pays(T, L.wdown, n_cus, next_norms ? SUMS_KEEP_NORM : next_layer ? SUMS_JOIN_NORM : SUMS_KERNEL);
 
   // (a stage that a product takes in is not bracketed: it reports 0)
   if (!few_qkv) {
@@ -1728,7 +1736,7 @@ static pie_status run_layer(pie_ctx* c, int32_t layer, const pie_batch* b, float
 
   tm.begin(PIE_STAGE_DOWN);
   e = EpiArgs{EPI_RESID_OUT, y_out, y_out ? H : 0, c->embeds, b->out_ids, c->h, H};
-  if (few_resid_ok(T, I, L.wdown)) HIP_TRY(c, launch_few_resid(c->act, I, T, L.wdown, e, n_cus, s));
+  if (few_down) HIP_TRY(c, launch_few_resid(c->act, I, T, L.wdown, e, n_cus, s));
   else HIP_TRY(c, launch_gemm(c->act, I, T, L.wdown, e, c->splitk, c->splitk_elems, n_cus, s, (carry && y_out) ? carry : nullptr));
   tm.end(PIE_STAGE_DOWN);
   c->last_T = T;

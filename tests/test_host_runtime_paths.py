@@ -42,11 +42,11 @@ class Child:
         from paper_2510_24051_amd import Pie, binding
         self.Pie, self.binding, self.lib = Pie, binding, binding.load_library()
 
-    def context(self, n_pages=1024, tokens=256, requests=64, m=MODEL, adapters=0, rank=0, dist=(0, 0)):
+    def context(self, n_pages=1024, tokens=256, requests=64, m=MODEL, adapters=0, rank=0, dist=(0, 0), layers=1):
         b, C = self.binding, self.C
         p = self.Pie.__new__(self.Pie)
         p.lib, p.device, p.stream, p.model, h = self.lib, None, None, m, C.c_void_p()
-        md = b.ModelDescC(m.hidden, m.n_q_heads, m.n_kv_heads, m.head_dim, m.mlp_dim, m.vocab, m.page_size, m.rms_eps, m.rope_theta, 1)
+        md = b.ModelDescC(m.hidden, m.n_q_heads, m.n_kv_heads, m.head_dim, m.mlp_dim, m.vocab, m.page_size, m.rms_eps, m.rope_theta, layers)
         pd = b.PoolDescC(n_pages, 1024, tokens, requests, dist[1], dist[0], adapters, rank)
         assert self.lib.pie_create(C.byref(md), C.byref(pd), None, C.byref(h)) == 0
         p.ctx = h
@@ -57,12 +57,14 @@ class Child:
         ctx, C = self.context(m=m, **kw), self.C
         room = np.zeros(2 * max(m.hidden, m.n_q_heads * m.head_dim) * max(m.mlp_dim, m.hidden, m.n_q_heads * m.head_dim), np.int8)
         at = C.c_void_p(room.ctypes.data)  # (kernels do nothing, copies read from here)
-        assert self.lib.pie_load_layer(ctx.ctx, 0, *[at] * 9) == 0
+        for layer in range(kw.get("layers", 1)):
+            assert self.lib.pie_load_layer(ctx.ctx, layer, *[at] * 9) == 0
         if m.vocab:
             head = np.zeros(m.vocab * m.hidden, np.int16)
             assert self.lib.pie_load_head(ctx.ctx, at, C.c_void_p(head.ctypes.data)) == 0
         for adapter, proj, r in pairs:
-            assert self.lib.pie_load_adapter(ctx.ctx, adapter, 0, proj, r, C.c_float(1.0), at, at) == 0
+            for layer in range(kw.get("layers", 1)):
+                assert self.lib.pie_load_adapter(ctx.ctx, adapter, layer, proj, r, C.c_float(1.0), at, at) == 0
         ctx.synchronize()  # (the copies are carried out here)
         return ctx
 
@@ -270,6 +272,33 @@ def few_rows_by_width(c):
         ctx.close()
 
 
+def few_rows_into_the_residual(c):
+    """Output and down products of up to 16 rows: by themselves where the next kernel would not add split sums up for nothing (it takes
+    its norm in, or there is none), else with most compute units at work and a contraction worth it; not for many long rows in few
+    workgroups.  A table of (width, heads, mlp, tokens, adapter on, output product of each of two layers, down product of each)."""
+    for hidden, heads, mlp, tokens, adapter, o, down in (
+            (2048, 16, 1024, 16, None, 2, 2), (2048, 16, 1024, 17, None, 0, 0),       # norms inside: both, however short
+            (1056, 16, 4096, 3, None, 0, 1), (3040, 64, 4096, 3, None, 0, 1),         # norms apart: only the last down product,
+            (3104, 64, 8192, 3, None, 2, 2), (3104, 16, 1024, 3, None, 0, 1),         # long contractions in 194 workgroups,
+            (4128, 32, 2048, 3, None, 2, 2), (4128, 16, 1024, 3, None, 0, 1),         # and in two column tiles a workgroup
+            (3104, 64, 4096, 16, None, 2, 2), (3104, 64, 4128, 16, None, 2, 1), (3104, 64, 8224, 16, None, 2, 0), (1056, 16, 8224, 8, None, 0, 1),
+            (2048, 16, 12288, 16, None, 2, 1), (2048, 16, 12320, 16, None, 2, 0), (2048, 16, 8224, 16, None, 2, 1), (2048, 16, 12320, 8, None, 2, 2),
+            (3584, 16, 12320, 16, None, 2, 2), (5120, 64, 8192, 16, None, 2, 2), (5120, 64, 8224, 16, None, 2, 0), (6144, 64, 12320, 16, None, 2, 2),
+            (2048, 16, 1024, 3, 3, 0, 2), (2048, 16, 1024, 3, 0, 2, 1), (2048, 16, 1024, 3, 4, 0, 2)):  # on o; q (its norm sums); gate
+        m = SimpleNamespace(**{**vars(MODEL), "hidden": hidden, "n_q_heads": heads, "n_kv_heads": 8, "mlp_dim": mlp})
+        ctx = c.loaded([] if adapter is None else [(0, adapter, 16)], m, tokens=32, adapters=1, rank=16, layers=2)
+        b = batch_of([(1, 20)] * tokens)
+        b.adapter_ids = None if adapter is None else np.zeros(tokens, np.int32)
+        pb = ctx.batch_create(b)
+        c.launches()
+        ctx.forward_all(pb)
+        names = c.launches()
+        got = sum("few_stream_kernelILi1E" in n for n in names), sum("few_stream_kernelILi3E" in n for n in names)
+        assert got == (o, down), (hidden, heads, mlp, tokens, adapter, got, names)
+        pb.destroy()
+        ctx.close()
+
+
 def logits_of_few_rows(c):
     """Logits with their norm inside: up to 16 rows of every length that has a kernel, 17 to 32 rows of up to 3072, and of 4096 over
     many columns."""
@@ -334,7 +363,7 @@ def attentions_in_one_launch(c):
 
 
 CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy, no_room_for_parts,
-                                 adapter_updates_of_split_products, few_rows_with_an_adapter_on_o, few_rows_by_width,
+                                 adapter_updates_of_split_products, few_rows_with_an_adapter_on_o, few_rows_by_width, few_rows_into_the_residual,
                                  logits_of_few_rows, stages_that_do_not_run, attentions_in_one_launch)}
 
 if __name__ == "__main__":

@@ -37,7 +37,7 @@ __device__ __forceinline__ const LoraPair& pair_of(const LoraPair* table, int ad
 // left every wave of lora_up 16 copies to read: 9.3 and 6.2 us there for qkv and o, 20.1 and 12.3 at rank 64.  With at most
 // four copies, and with what the update is added to requested ahead of z, it takes 6.8 and 5.3, 12.5 and 9.2.
 // Many tiles gain more, 2048 tokens of four prompts on rank-16 adapters: down 35.6 and 34.8 -> 17.1 and 17.0 us, up (one instance
-// of 248 registers before, two of 150 and 198) 77 and 36 -> 23 and 21.
+// of 248 registers before, two of 108 and 152) 77 and 36 -> 23 and 21.
 __global__ __launch_bounds__(64 * DOWN_WAVES) void lora_down_kernel(
     const bf16_t* __restrict__ x, int ldx, int in, const int32_t* __restrict__ rows, const int32_t* __restrict__ tile_ad,
     const LoraPair* __restrict__ table, int layer, int n_layers, int proj0, float* __restrict__ z, int rmax_p, int ksplits) {
@@ -148,7 +148,6 @@ __global__ __launch_bounds__(256) void lora_up_kernel(void* __restrict__ dst, in
         for (int u = 0; u < N; ++u) { z0 += pa[u]; z1 += pb[u]; }
       }
     };
-    add(std::integral_constant<int, 8>());
     add(std::integral_constant<int, 4>());
     add(std::integral_constant<int, 1>());
     const bf16x8 b = *reinterpret_cast<const bf16x8*>(br + s * 16);

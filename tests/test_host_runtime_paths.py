@@ -340,6 +340,36 @@ def stages_that_do_not_run(c):
     ctx.close()
 
 
+def packed_prefill(c):
+    """Batches without decode waves whose prompts have at most 64 (token, head) columns run them packed into as many waves as they fill,
+    where that is fewer than a wave per head; not four heads or fewer of 128.  With a decode request in the batch the wave-per-head
+    kernels run, once each, for the same blocks.  (The shapes of the device test of the same.)"""
+    for D, G, new, prior, waves in ((128, 8, (3, 4), 1500, 1), (128, 8, (5, 8, 6, 7), 2500, 2), (128, 8, (8, 5), 2048, 2), (128, 8, (5, 8), 100, 2),
+                                    (128, 8, (8, 9), 2500, 0), (64, 8, (5, 3, 4), 2048, 2), (64, 8, (4, 3), 90, 1), (64, 8, (8, 8), 3000, 2),
+                                    (64, 4, (8, 8), 3000, 1), (64, 4, (13, 5, 16), 1777, 2), (64, 4, (16, 9, 5), 1300, 2), (64, 4, (16, 7), 100, 2),
+                                    (64, 4, (8, 17), 2500, 0), (64, 2, (16,), 1200, 1), (64, 2, (9, 15), 110, 1), (64, 2, (9, 17), 2000, 0),
+                                    (128, 4, (5, 8, 6, 7), 2500, 0), (128, 2, (9, 16, 12), 2000, 0)):
+        m = SimpleNamespace(**{**vars(MODEL), "n_q_heads": 2 * G, "n_kv_heads": 2, "head_dim": D})
+        ctx = c.loaded(m=m)
+        prompts = [(n, prior // (1 + i)) for i, n in enumerate(new)]
+        for decode in (False, True):
+            pb = ctx.batch_create(batch_of(prompts + [(new[0], 0)] + ([(1, 700)] if decode else [])))
+            assert (pb.plan_info()["decode_waves"] > 0) == decode
+            c.launches()
+            ctx.forward(0, pb)
+            names = c.launches()
+            packed = [n for n in names if "attn_packed" in n]
+            plain = [n for n in names if "attn_prefill_kernel" in n and f"ELi{G}ELb0E" in n or "attn_both" in n]
+            if waves and not decode:
+                assert len(packed) == 1 and f"attn_packed_kernelILi{D}ELi{waves}E" in packed[0] and not plain, (D, G, new, names)
+            else:
+                assert not packed and len(plain) == 1, (D, G, new, decode, names)
+            assert sum("attn_prefill_merge" in n for n in names) == (pb.plan_parts()["cut_blocks"] > 0), names
+            assert any("attn_prefill_merge" in n for n in names) or prior <= 800, (D, G, new, prior)
+            pb.destroy()
+        ctx.close()
+
+
 def attentions_in_one_launch(c):
     """Prompts of four query heads per kv head, or the tiles of a shared prefix, go with the decode waves in one launch; with stage
     timing on they are launched apart."""
@@ -364,7 +394,7 @@ def attentions_in_one_launch(c):
 
 CASES = {f.__name__: f for f in (failed_wait, late_copies, captured_stream, failed_allocations, failed_allocation_in_destroy, no_room_for_parts,
                                  adapter_updates_of_split_products, few_rows_with_an_adapter_on_o, few_rows_by_width, few_rows_into_the_residual,
-                                 logits_of_few_rows, stages_that_do_not_run, attentions_in_one_launch)}
+                                 logits_of_few_rows, stages_that_do_not_run, packed_prefill, attentions_in_one_launch)}
 
 if __name__ == "__main__":
     CASES[sys.argv[2]](Child(sys.argv[1]))

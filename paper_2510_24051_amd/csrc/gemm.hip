@@ -766,8 +766,9 @@ __global__ __launch_bounds__(512) void gemm_large_async_kernel(const bf16_t* __r
 // SwiGLU epilogue of a tile whose gate and up blocks (and KS slices of K) are in different waves.  CHUNK rows of accumulator
 // blocks at a time go to LDS (`piece(p)`: 4 KiB pieces, room for 8 * CHUNK; block i of wave w is piece 8 i + w, 16 bytes per
 // lane), and then all eight waves take quarters of the results in turn: a column per lane and four rows.  (With the up
-// sums handed to the gate waves, one wave per SIMD waited out every exponential and store by itself: 28672 x 4096 at 84 rows 44.5
-// -> 43.0 us, at 157 60.2 -> 58.3, at 256 76.1 -> 73.7.)
+// sums handed to the gate waves, one wave per SIMD waited out every exponential and store by itself: 28672 x 4096 within a layer at
+// 64 rows 44.4 -> 43.3 us, at 84 44.6 -> 42.8, at 157 60.1 -> 58.7, at 256 the same, 75.7 and 76.3; 16384 x 2048 at 324 rows 32.1 and
+// 32.0.)
 // ------------------------------------------------------------------------------------------------
 template <bool NT, int MB, int KS, int CHUNK, typename Piece>
 __device__ __forceinline__ void swiglu_through_lds(const f32x16 (&acc)[MB], Piece piece, int wave, int lane, int m0, int nb0, int M, int NB,

@@ -5,9 +5,10 @@
 // with no partial sums in memory and nothing left for another kernel to add up, and the work of the small kernels around a
 // product moves into it:
 //   few_rows_kernel    each wave keeps its K slice of the rows in registers as MFMA operands (K = 256 * NS; MB blocks of 16 rows,
-//                      two of them for q, k, v and logits of Embeds) and walks any number of column tiles; the rows may be normalised on the way in (RMSNorm of Embeds or of fp32
-//                      rows: every workgroup does it for itself, 16 rows, while its first weights are in flight); a QKV tile is
-//                      rotated and appended to its page, a gate/up tile becomes eight activations
+//                      two of them for q, k, v and logits of Embeds) and walks any number of column tiles; the rows may be
+//                      normalised on the way in (RMSNorm of Embeds or of fp32 rows: every workgroup does it for itself while its
+//                      first weights are in flight); a QKV tile is rotated and appended to its page, a gate/up tile becomes
+//                      eight activations
 //   few_stream_kernel  rows streamed beside the weights (long contractions; products that end in the residual)
 // A wave of few_stream has 16 KiB of weights in flight (128 KiB per compute unit); one of few_rows a tile's k steps, K / 256 KiB
 // up to K = 4096 and 7 to 10 KiB above, where the rows leave no registers for more.  They are requested non-temporally

@@ -38,7 +38,7 @@ def build(verbose: bool = True, jobs: int = 8) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
-    r = subprocess.run([hipcc, "-O3", "-std=c++17", "--offload-arch=gfx950", os.path.join(CSRC, "probe_ceilings.hip"),
+    r = subprocess.run([hipcc, *FLAGS, os.path.join(CSRC, "probe_ceilings.hip"),
                         "-o", PROBE], capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for probe_ceilings.hip:\n{r.stdout}\n{r.stderr}")
